@@ -69,6 +69,7 @@ struct avq_index {
     int tune_sample = 0; // 0 = batches guess the candidate scan's bounds from a sample where possible, 1 = never, 2 = from a sample scanned with lists
     int tune_prefilter_cap = 0; // candidate keys per (query, chunk) of that scan, 0 = built-in
     DevBuf block_max, lists, refined, lut_fail, fail, cand_keys, groups, kept, fail_rows;
+    DevBuf train_ws; // training: points by coordinate and the sums of an iteration
     // optional per-stage timing with HIP events recorded on the caller's stream
     bool prof_on = false;
     std::vector<hipEvent_t> prof_pool;
@@ -162,7 +163,7 @@ extern "C" void avq_destroy(avq_index *idx)
                      &idx->codes_blocked, &idx->assign, &idx->perm, &idx->leaf_blk, &idx->lut, &idx->lut8,
                      &idx->scale, &idx->bias, &idx->partial, &idx->cand, &idx->leaf_ids, &idx->leaf_ip,
                      &idx->tmp, &idx->block_max, &idx->lists, &idx->thr, &idx->refined, &idx->lut_fail,
-                     &idx->fail, &idx->cand_keys, &idx->groups, &idx->kept, &idx->fail_rows};
+                     &idx->fail, &idx->cand_keys, &idx->groups, &idx->kept, &idx->fail_rows, &idx->train_ws};
     for (DevBuf *b : all) b->release();
     for (hipEvent_t e : idx->prof_pool) (void)hipEventDestroy(e);
     delete idx;
@@ -329,10 +330,8 @@ extern "C" int avq_train(avq_index *idx, const float *x, int64_t n_train, void *
         AVQ_TRY(assign_to_leaves(idx, x, n_train, idx->tmp.as<int32_t>(), st));
         assign = idx->tmp.as<int32_t>();
     }
-    for (int m = 0; m < c.M; ++m)
-        AVQ_TRY(kmeans_device(x, n_train, c.d, m * idx->ds, idx->ds, idx->kc, c.kmeans_iters, c.seed,
-                              (uint32_t)(1 + m), assign ? idx->centers.as<float>() : nullptr, assign,
-                              idx->codebooks.as<float>() + (size_t)m * idx->kc * idx->ds, st));
+    AVQ_TRY(pq_kmeans_device(x, n_train, c.d, c.M, idx->kc, c.kmeans_iters, c.seed, assign ? idx->centers.as<float>() : nullptr,
+                             assign, idx->codebooks.as<float>(), &idx->train_ws, st));
     AVQ_HIP(hipStreamSynchronize(st));
     idx->have_codebooks = true;
     return AVQ_OK;

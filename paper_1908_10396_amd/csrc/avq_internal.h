@@ -365,6 +365,9 @@ int launch_to_blocked(const uint8_t *logical, int64_t n, int NB, const int32_t *
 int kmeans_device(const float *x, int64_t n, int ld, int col0, int dim, int k, int iters,
                   uint64_t seed, uint32_t stream_id, const float *resid_centers,
                   const int32_t *resid_assign, float *centers, hipStream_t st);
+// The M dictionaries of k (16 or 256) codewords, all subspaces in the same launches; ws: grow-only scratch. Asynchronous.
+int pq_kmeans_device(const float *x, int64_t n, int d, int M, int k, int iters, uint64_t seed, const float *resid_centers,
+                     const int32_t *resid_assign, float *codebooks, DevBuf *ws, hipStream_t st);
 int launch_assign_nearest(const float *x, int64_t n, int d, const float *centers, int k,
                           int32_t *assign, hipStream_t st);
 // every row to the center of smallest anisotropic loss (fp64), lowest index on equal loss

@@ -72,6 +72,266 @@ static int64_t init_index(uint64_t seed, uint32_t stream_id, int j, int k, int64
     return lo + (int64_t)(h % (uint64_t)(hi - lo));
 }
 
+// ---- the dictionaries of all subspaces at once --------------------------------------
+//
+// Lloyd's algorithm for every subspace in the same launches: an iteration is one pass of all (point, subspace)
+// pairs (pq_lloyd_kernel) and one small kernel that turns the sums into codewords. The points are laid out by
+// coordinate first ([d][n], residuals formed once, in fp64, where there are leaf centers), so that a wave reads
+// 64 values of a coordinate side by side; from row-major points each lane would touch a line of its own.
+// The kernel is bound by fp64 arithmetic: per codeword and pair 2 ds + 1 operations for the distance and three for
+// the arg-min, the codewords being scalar operands. 262,144 points x 50 subspaces x 16 codewords of 2 dimensions:
+// 67 us an iteration (53 us at the rate of 140 such operations a pair) and 5 us for the codewords; with a launch
+// sequence per subspace, row-major points and one copy of the sums 51 + 5 + 9 us per subspace and iteration
+// (training as a whole 60.8 -> 1.4 ms).
+__device__ __forceinline__ uint64_t mix64_dev(uint64_t z)
+{
+    z += 0x9E3779B97F4A7C15ull; // splitmix64 output function, as mix64
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
+}
+
+// x [n][d] -> xt [cols][n], columns col0 .. col0 + cols - 1; XT double: the residual to centers[assign[i]]
+template <typename XT>
+__global__ void __launch_bounds__(256)
+points_by_coordinate_kernel(const float *__restrict__ x, int64_t n, int d, int col0, int cols,
+                            const float *__restrict__ centers, const int32_t *__restrict__ assign, XT *__restrict__ xt)
+{
+    __shared__ XT tile[32][65]; // [coordinate][point]
+    const int64_t i0 = (int64_t)blockIdx.x * 64;
+    const int c0 = blockIdx.y * 32;
+    for (int e = threadIdx.x; e < 64 * 32; e += 256) {
+        const int p = e >> 5, c = e & 31;
+        if (i0 + p < n && c0 + c < cols) {
+            const size_t at = (size_t)(col0 + c0 + c);
+            XT v = (XT)x[(size_t)(i0 + p) * d + at];
+            if (centers) v -= (XT)centers[(size_t)assign[i0 + p] * d + at];
+            tile[c][p] = v;
+        }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 64 * 32; e += 256) {
+        const int c = e >> 6, p = e & 63;
+        if (i0 + p < n && c0 + c < cols) xt[(size_t)(c0 + c) * n + i0 + p] = tile[c][p];
+    }
+}
+
+// the stratified draw of init_index for codeword j = blockIdx.x * 256 + threadIdx.x of subspace m0 + blockIdx.y
+template <typename XT>
+__global__ void __launch_bounds__(256)
+pq_init_kernel(const XT *__restrict__ xt, int64_t n, int ds, int k, int m0, uint64_t seed, float *__restrict__ cb,
+               double *__restrict__ cb64)
+{
+    const int j = blockIdx.x * 256 + threadIdx.x, m = blockIdx.y;
+    if (j >= k) return;
+    const uint64_t lo = (uint64_t)j * (uint64_t)n / (uint64_t)k, hi = (uint64_t)(j + 1) * (uint64_t)n / (uint64_t)k;
+    const uint64_t h = mix64_dev(seed ^ mix64_dev(((uint64_t)(1 + m0 + m) << 32) | (uint32_t)j));
+    const uint64_t i = lo + h % (hi - lo);
+    for (int l = 0; l < ds; ++l) {
+        const float v = (float)xt[(size_t)(m * ds + l) * n + i];
+        cb[((size_t)m * k + j) * ds + l] = v;
+        cb64[((size_t)m * k + j) * ds + l] = (double)v;
+    }
+}
+
+// One subspace (blockIdx.y) and per_block points per workgroup: the nearest codeword of every point (fp64 squared
+// distance, lowest index on ties), the point added to that codeword's sums in LDS, the workgroup's sums to
+// part_sum[m][entry][blk] and part_cnt[m][codeword][blk]. `copies` of the sums side by side in LDS keep the lanes
+// of a wave, which share a few codewords, from adding to the same word: 32 of them put a wave's additions into
+// separate banks. copies = 0: the sums do not fit LDS and go to part_* (n_slots = 1, cleared before) directly.
+// DS = dimensions per subspace, KC = codewords (0: known at run time only).
+template <int DS, int KC, typename XT>
+__global__ void __launch_bounds__(256)
+pq_lloyd_kernel(const XT *__restrict__ xt, int64_t n, int ds_rt, int k_rt, int per_block, const double *__restrict__ cb64,
+                int copies, int n_slots, double *__restrict__ part_sum, uint32_t *__restrict__ part_cnt)
+{
+    extern __shared__ __align__(16) double lloyd_lds[]; // [k * ds][copies], then uint32 [k][copies]
+    const int ds = DS ? DS : ds_rt, k = KC ? KC : k_rt;
+    const int m = blockIdx.y, tid = threadIdx.x;
+    double *lsum = lloyd_lds;
+    uint32_t *lcnt = (uint32_t *)(lloyd_lds + (size_t)k * ds * copies);
+    for (int e = tid; e < k * ds * copies; e += 256) lsum[e] = 0.0;
+    for (int e = tid; e < k * copies; e += 256) lcnt[e] = 0u;
+    __syncthreads();
+    const double *cb = cb64 + (size_t)m * k * ds;
+    const XT *xm = xt + (size_t)m * ds * n;
+    const int64_t first = (int64_t)blockIdx.x * per_block;
+    const int64_t end = first + per_block < n ? first + per_block : n;
+    double *gsum = part_sum + (size_t)m * k * ds * n_slots;
+    uint32_t *gcnt = part_cnt + (size_t)m * k * n_slots;
+    const int copy = copies > 0 ? (tid & (copies - 1)) : 0;
+    for (int64_t i = first + tid; i < end; i += 256) {
+        int best = 0;
+        double bestd = INFINITY;
+        double xv[DS ? DS : 1];
+        if constexpr (DS != 0) {
+#pragma unroll
+            for (int l = 0; l < DS; ++l) xv[l] = (double)xm[(size_t)l * n + i];
+#pragma unroll 16
+            for (int j = 0; j < k; ++j) {
+                double t = xv[0] - cb[j * DS];
+                double dd = t * t;
+#pragma unroll
+                for (int l = 1; l < DS; ++l) {
+                    t = xv[l] - cb[j * DS + l];
+                    dd += t * t;
+                }
+                best = dd < bestd ? j : best;
+                bestd = fmin(dd, bestd);
+            }
+        } else {
+            for (int j0 = 0; j0 < k; j0 += 8) { // k is a multiple of 16
+                double dd[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) dd[u] = 0.0;
+                for (int l = 0; l < ds; ++l) {
+                    const double v = (double)xm[(size_t)l * n + i];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const double t = v - cb[(size_t)(j0 + u) * ds + l];
+                        dd[u] += t * t;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    best = dd[u] < bestd ? j0 + u : best;
+                    bestd = fmin(dd[u], bestd);
+                }
+            }
+        }
+        if (copies > 0) {
+            if constexpr (DS != 0) {
+#pragma unroll
+                for (int l = 0; l < DS; ++l)
+                    __hip_atomic_fetch_add(&lsum[(best * DS + l) * copies + copy], xv[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            } else {
+                for (int l = 0; l < ds; ++l)
+                    __hip_atomic_fetch_add(&lsum[(size_t)(best * ds + l) * copies + copy], (double)xm[(size_t)l * n + i],
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            __hip_atomic_fetch_add(&lcnt[best * copies + copy], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        } else {
+            for (int l = 0; l < ds; ++l) unsafeAtomicAdd(&gsum[(size_t)best * ds + l], (double)xm[(size_t)l * n + i]);
+            atomicAdd(&gcnt[best], 1u);
+        }
+    }
+    if (copies == 0) return;
+    __syncthreads();
+    for (int e = tid; e < k * ds; e += 256) {
+        double s = 0.0;
+        for (int c = 0; c < copies; ++c) s += lsum[(size_t)e * copies + ((c + e) & (copies - 1))];
+        gsum[(size_t)e * n_slots + blockIdx.x] = s;
+    }
+    for (int j = tid; j < k; j += 256) {
+        uint32_t s = 0u;
+        for (int c = 0; c < copies; ++c) s += lcnt[j * copies + ((c + j) & (copies - 1))];
+        gcnt[(size_t)j * n_slots + blockIdx.x] = s;
+    }
+}
+
+// One wave per codeword: the workgroups' sums added up, the mean rounded to fp32 (an empty cluster keeps its codeword).
+__global__ void __launch_bounds__(64)
+pq_codewords_kernel(const double *__restrict__ part_sum, const uint32_t *__restrict__ part_cnt, int n_slots, int ds, int k,
+                    float *__restrict__ cb, double *__restrict__ cb64)
+{
+    const size_t mj = (size_t)blockIdx.y * k + blockIdx.x;
+    const int lane = threadIdx.x;
+    uint32_t cnt = 0u;
+    for (int b = lane; b < n_slots; b += 64) cnt += part_cnt[mj * n_slots + b];
+    for (int s = 32; s > 0; s >>= 1) cnt += (uint32_t)__shfl_xor((int)cnt, s, 64);
+    if (cnt == 0u) return;
+    for (int l = 0; l < ds; ++l) {
+        double sum = 0.0;
+        for (int b = lane; b < n_slots; b += 64) sum += part_sum[(mj * ds + l) * n_slots + b];
+        for (int s = 32; s > 0; s >>= 1) sum += __shfl_xor(sum, s, 64);
+        if (lane == 0) {
+            const float v = (float)(sum / (double)cnt);
+            cb[mj * ds + l] = v;
+            cb64[mj * ds + l] = (double)v;
+        }
+    }
+}
+
+template <typename XT>
+static int pq_kmeans_group(const float *x, int64_t n, int d, int m0, int Mg, int ds, int k, int iters, uint64_t seed,
+                           const float *centers, const int32_t *assign, float *codebooks, DevBuf *ws, hipStream_t st)
+{
+    // one round of workgroups (eight of 256 threads per compute unit are resident: two more would be a second round of
+    // them), each with at least one step of work
+    const int n_blk = (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 2048 / Mg));
+    const int per_block = (int)(((n + n_blk - 1) / n_blk + 255) / 256 * 256);
+    const size_t copy_bytes = (size_t)k * (ds * sizeof(double) + sizeof(uint32_t));
+    int copies = 32;
+    while (copies > 1 && copies * copy_bytes > 32 * 1024) copies /= 2;
+    if (copy_bytes > 120 * 1024) copies = 0;
+    const int n_slots = copies ? n_blk : 1;
+    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    const size_t b_xt = up(sizeof(XT) * (size_t)n * Mg * ds), b_cb = up(sizeof(double) * (size_t)Mg * k * ds),
+                 b_sum = up(sizeof(double) * (size_t)Mg * k * ds * n_slots), b_cnt = up(sizeof(uint32_t) * (size_t)Mg * k * n_slots);
+    AVQ_TRY(ws->reserve(b_xt + b_cb + b_sum + b_cnt));
+    XT *xt = ws->as<XT>();
+    double *cb64 = (double *)(ws->as<unsigned char>() + b_xt);
+    double *part_sum = (double *)((unsigned char *)cb64 + b_cb);
+    uint32_t *part_cnt = (uint32_t *)((unsigned char *)part_sum + b_sum);
+    hipLaunchKernelGGL(points_by_coordinate_kernel<XT>, dim3((unsigned)((n + 63) / 64), (unsigned)((Mg * ds + 31) / 32)), dim3(256), 0,
+                       st, x, n, d, m0 * ds, Mg * ds, centers, assign, xt);
+    hipLaunchKernelGGL(pq_init_kernel<XT>, dim3((unsigned)((k + 255) / 256), (unsigned)Mg), dim3(256), 0, st, xt, n, ds, k, m0, seed,
+                       codebooks, cb64);
+    const dim3 grid((unsigned)n_blk, (unsigned)Mg);
+    const size_t lds = copies * copy_bytes;
+    for (int it = 0; it < iters; ++it) {
+        if (copies == 0) AVQ_HIP(hipMemsetAsync(part_sum, 0, b_sum + b_cnt, st));
+#define AVQ_LLOYD(DS, KC)                                                                                          \
+    do {                                                                                                           \
+        static LdsLimitOnce attr_done;                                                                             \
+        AVQ_TRY(set_lds_limit((const void *)pq_lloyd_kernel<DS, KC, XT>, kMaxDynLds, &attr_done));                 \
+        hipLaunchKernelGGL((pq_lloyd_kernel<DS, KC, XT>), grid, dim3(256), lds, st, xt, n, ds, k, per_block, cb64, \
+                           copies, n_slots, part_sum, part_cnt);                                                   \
+    } while (0)
+        if (k == 16) {
+            switch (ds) {
+            case 1: AVQ_LLOYD(1, 16); break;
+            case 2: AVQ_LLOYD(2, 16); break;
+            case 3: AVQ_LLOYD(3, 16); break;
+            case 4: AVQ_LLOYD(4, 16); break;
+            default: AVQ_LLOYD(0, 0); break;
+            }
+        } else {
+            switch (ds) {
+            case 2: AVQ_LLOYD(2, 0); break;
+            case 4: AVQ_LLOYD(4, 0); break;
+            case 8: AVQ_LLOYD(8, 0); break;
+            default: AVQ_LLOYD(0, 0); break;
+            }
+        }
+#undef AVQ_LLOYD
+        hipLaunchKernelGGL(pq_codewords_kernel, dim3((unsigned)k, (unsigned)Mg), dim3(64), 0, st, part_sum, part_cnt, n_slots, ds, k,
+                           codebooks, cb64);
+    }
+    AVQ_HIP(hipGetLastError());
+    return AVQ_OK;
+}
+
+// The M dictionaries of [k][d / M] codewords (16 or 256), each as kmeans_device would learn it with stream id 1 + m.
+// Groups of subspaces whose points by coordinate stay under a gigabyte of scratch.
+int pq_kmeans_device(const float *x, int64_t n, int d, int M, int k, int iters, uint64_t seed, const float *resid_centers,
+                     const int32_t *resid_assign, float *codebooks, DevBuf *ws, hipStream_t st)
+{
+    if (n < k) { set_error("k-means: %lld points for %d centers", (long long)n, k); return AVQ_EINVAL; }
+    const int ds = d / M;
+    const size_t per_m = (size_t)n * ds * (resid_centers ? sizeof(double) : sizeof(float));
+    const int group = (int)std::max<size_t>(1, std::min<size_t>((size_t)M, ((size_t)1 << 30) / per_m));
+    for (int m0 = 0; m0 < M; m0 += group) {
+        const int Mg = std::min(group, M - m0);
+        float *cb = codebooks + (size_t)m0 * k * ds;
+        if (resid_centers)
+            AVQ_TRY(pq_kmeans_group<double>(x, n, d, m0, Mg, ds, k, iters, seed, resid_centers, resid_assign, cb, ws, st));
+        else
+            AVQ_TRY(pq_kmeans_group<float>(x, n, d, m0, Mg, ds, k, iters, seed, nullptr, nullptr, cb, ws, st));
+    }
+    return AVQ_OK;
+}
+
 __device__ __forceinline__ double sub_value(const float *__restrict__ x, int64_t i, int ld, int col,
                                             const float *__restrict__ rc, const int32_t *__restrict__ ra)
 {
