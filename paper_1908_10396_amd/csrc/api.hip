@@ -280,7 +280,11 @@ static int assign_to_leaves(avq_index *idx, const float *x, int64_t n, int32_t *
     if (c.leaf_aniso_iters > 0)
         return launch_assign_aniso(x, n, c.d, idx->centers.as<float>(), c.n_leaves, c.eta_mode, (double)c.T,
                                    (double)c.eta_explicit, assign, st);
-    return launch_assign_nearest(x, n, c.d, idx->centers.as<float>(), c.n_leaves, assign, st);
+    if (!nearest_supported(c.d, c.n_leaves))
+        return launch_assign_nearest(x, n, c.d, idx->centers.as<float>(), c.n_leaves, assign, st);
+    AVQ_TRY(idx->train_ws.reserve(nearest_ws_bytes(n, c.d, c.n_leaves, 1)));
+    return launch_nearest(x, n, c.d, idx->centers.as<float>(), idx->centers_t.as<float>(), c.n_leaves, idx->train_ws.p, assign,
+                          nullptr, 1, nullptr, st);
 }
 
 // Theorem 4.2 for every leaf at once: the leaf centers are the codewords of a one-dictionary quantizer whose
@@ -315,9 +319,13 @@ extern "C" int avq_train(avq_index *idx, const float *x, int64_t n_train, void *
     if (c.n_leaves > 0) {
         // leaf centers from at most 256 rows per leaf, then every training row to its leaf
         const int64_t n_leaf_train = std::min<int64_t>(n_train, (int64_t)256 * c.n_leaves);
-        AVQ_TRY(kmeans_device(x, n_leaf_train, c.d, 0, c.d, c.n_leaves, c.leaf_kmeans_iters, c.seed, 0u,
-                              nullptr, nullptr, idx->centers.as<float>(), st));
-        AVQ_TRY(refresh_centers_t(idx, st));
+        if (nearest_supported(c.d, c.n_leaves)) {
+            AVQ_TRY(kmeans_leaves_device(x, n_leaf_train, c.d, c.n_leaves, c.leaf_kmeans_iters, c.seed, idx->centers.as<float>(),
+                                         idx->centers_t.as<float>(), &idx->train_ws, st));
+        } else {
+            AVQ_TRY(kmeans_device(x, n_leaf_train, c.d, c.n_leaves, c.leaf_kmeans_iters, c.seed, idx->centers.as<float>(), st));
+            AVQ_TRY(refresh_centers_t(idx, st));
+        }
         idx->have_centers = true;
         AVQ_TRY(idx->tmp.reserve(sizeof(int32_t) * (size_t)n_train));
         // Section 4 with the leaf centers as codewords: alternate the assignment under the anisotropic loss
@@ -356,52 +364,33 @@ static int install_database(avq_index *idx, const float *x, int64_t n, hipStream
         idx->n_slots = idx->n_blocks * kBlockPoints;
         AVQ_TRY(idx->codes_blocked.reserve((size_t)idx->n_slots * idx->NB));
         AVQ_TRY(launch_to_blocked(idx->codes_logical.as<uint8_t>(), n, idx->NB, nullptr,
-                                  idx->codes_blocked.as<uint8_t>(), idx->n_slots, st));
+                                  idx->codes_blocked.as<uint8_t>(), idx->n_blocks, st));
     } else {
         // group the points by leaf (ascending id inside a leaf), each leaf padded to whole blocks
-        std::vector<int32_t> assign(n);
-        AVQ_HIP(hipMemcpyAsync(assign.data(), idx->assign.p, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, st));
-        AVQ_HIP(hipStreamSynchronize(st));
-        std::vector<int64_t> count(c.n_leaves, 0);
-        for (int64_t i = 0; i < n; ++i) {
-            if (assign[i] < 0 || assign[i] >= c.n_leaves) {
-                set_error("leaf assignment %d of point %lld out of range", assign[i], (long long)i);
-                return AVQ_EINVAL;
-            }
-            count[assign[i]]++;
-        }
-        std::vector<int32_t> leaf_blk(c.n_leaves + 1);
-        int64_t blk = 0;
-        idx->max_leaf_blocks = 0;
-        for (int l = 0; l < c.n_leaves; ++l) {
-            leaf_blk[l] = (int32_t)blk;
-            blk += (count[l] + kBlockPoints - 1) / kBlockPoints;
-            idx->max_leaf_blocks = std::max<int64_t>(idx->max_leaf_blocks, (count[l] + kBlockPoints - 1) / kBlockPoints);
-        }
-        leaf_blk[c.n_leaves] = (int32_t)blk;
-        if (blk * kBlockPoints > 0x7fffffff) { set_error("index too large"); return AVQ_EINVAL; }
-        idx->n_blocks = blk;
-        idx->n_slots = blk * kBlockPoints;
-        std::vector<int32_t> slot_of(n), perm((size_t)idx->n_slots, -1);
-        std::vector<int64_t> next(c.n_leaves);
-        for (int l = 0; l < c.n_leaves; ++l) next[l] = (int64_t)leaf_blk[l] * kBlockPoints;
-        for (int64_t i = 0; i < n; ++i) {
-            const int64_t s = next[assign[i]]++;
-            slot_of[i] = (int32_t)s;
-            perm[s] = (int32_t)i;
-        }
-        AVQ_TRY(idx->tmp.reserve(sizeof(int32_t) * (size_t)n));
-        AVQ_TRY(idx->perm.reserve(sizeof(int32_t) * (size_t)std::max<int64_t>(idx->n_slots, 1)));
+        const size_t b_ws = (leaf_layout_ws_bytes(n, c.n_leaves) + 255) & ~(size_t)255;
+        AVQ_TRY(idx->tmp.reserve(b_ws + sizeof(LeafLayoutInfo)));
         AVQ_TRY(idx->leaf_blk.reserve(sizeof(int32_t) * (size_t)(c.n_leaves + 1)));
-        AVQ_TRY(idx->codes_blocked.reserve((size_t)std::max<int64_t>(idx->n_slots, 1) * idx->NB));
-        AVQ_HIP(hipMemcpyAsync(idx->tmp.p, slot_of.data(), sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, st));
-        AVQ_HIP(hipMemcpyAsync(idx->perm.p, perm.data(), sizeof(int32_t) * (size_t)idx->n_slots,
-                               hipMemcpyHostToDevice, st));
-        AVQ_HIP(hipMemcpyAsync(idx->leaf_blk.p, leaf_blk.data(), sizeof(int32_t) * (size_t)(c.n_leaves + 1),
-                               hipMemcpyHostToDevice, st));
-        AVQ_TRY(launch_to_blocked(idx->codes_logical.as<uint8_t>(), n, idx->NB, idx->tmp.as<int32_t>(),
-                                  idx->codes_blocked.as<uint8_t>(), idx->n_slots, st));
-        AVQ_HIP(hipStreamSynchronize(st)); // host vectors go out of scope
+        LeafLayoutInfo *info_dev = (LeafLayoutInfo *)(idx->tmp.as<unsigned char>() + b_ws), info;
+        const int32_t *assign = idx->assign.as<int32_t>();
+        AVQ_TRY(launch_leaf_counts(assign, n, c.n_leaves, idx->tmp.p, idx->leaf_blk.as<int32_t>(), info_dev, st));
+        AVQ_HIP(hipMemcpyAsync(&info, info_dev, sizeof(info), hipMemcpyDeviceToHost, st));
+        AVQ_HIP(hipStreamSynchronize(st));
+        if (info.first_bad < n) {
+            int32_t leaf = 0;
+            AVQ_HIP(hipMemcpy(&leaf, assign + info.first_bad, sizeof(leaf), hipMemcpyDeviceToHost));
+            set_error("leaf assignment %d of point %lld out of range", leaf, (long long)info.first_bad);
+            return AVQ_EINVAL;
+        }
+        if (info.n_blocks * kBlockPoints > 0x7fffffff) { set_error("index too large"); return AVQ_EINVAL; }
+        idx->max_leaf_blocks = info.max_leaf_blocks;
+        idx->n_blocks = info.n_blocks;
+        idx->n_slots = info.n_blocks * kBlockPoints;
+        AVQ_TRY(idx->perm.reserve(sizeof(int32_t) * (size_t)idx->n_slots));
+        AVQ_TRY(idx->codes_blocked.reserve((size_t)idx->n_slots * idx->NB));
+        AVQ_TRY(launch_leaf_places(assign, n, c.n_leaves, idx->tmp.p, idx->leaf_blk.as<int32_t>(), idx->perm.as<int32_t>(),
+                                   idx->n_slots, st));
+        AVQ_TRY(launch_to_blocked(idx->codes_logical.as<uint8_t>(), n, idx->NB, idx->perm.as<int32_t>(),
+                                  idx->codes_blocked.as<uint8_t>(), idx->n_blocks, st));
     }
     AVQ_HIP(hipStreamSynchronize(st));
     idx->n = n;

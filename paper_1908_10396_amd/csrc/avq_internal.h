@@ -58,6 +58,29 @@ struct DevBuf {
     template <class T> T *as() const { return (T *)p; }
 };
 
+// splitmix64 output function
+__host__ __device__ inline uint64_t mix64(uint64_t z)
+{
+    z += 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
+}
+// Stratified draw of the first codewords: the row of codeword j (of k, among n rows; j n < 2^64).
+__host__ __device__ inline uint64_t init_row(uint64_t seed, uint32_t stream_id, uint64_t j, uint64_t k, uint64_t n)
+{
+    const uint64_t lo = j * n / k, hi = (j + 1) * n / k;
+    return lo + mix64(seed ^ mix64(((uint64_t)stream_id << 32) | (uint32_t)j)) % (hi - lo);
+}
+// Counters that take many atomic additions: additions to words of one cache line wait for one another, so the
+// counters are spread out, one per 128 bytes while that stays under a megabyte. Words between neighbours:
+inline int spread_stride(int n)
+{
+    int stride = 32;
+    while (stride > 1 && (size_t)n * stride > ((size_t)1 << 18)) stride /= 2;
+    return stride;
+}
+
 // ---- lut.hip ---------------------------------------------------------------
 // L[q][m][j] = <q^(m), c_j^(m)> (fp32 fma chain); u8 mode also writes the
 // quantised tables and per-query scale / bias.
@@ -355,16 +378,29 @@ int launch_leaf_select(const float *centers_t, int n_leaves, int d, const float 
 int launch_transpose(const float *in, int rows, int cols, float *out, hipStream_t st);
 
 // ---- layout.hip ------------------------------------------------------------
-// logical [n][NB] -> blocked; slot_of[i] gives the slot of point i (NULL: slot = i).
-int launch_to_blocked(const uint8_t *logical, int64_t n, int NB, const int32_t *slot_of,
-                      uint8_t *blocked, int64_t n_slots, hipStream_t st);
+// logical [n][NB] -> blocked; perm[slot] gives the point of a slot, -1 = padding (NULL: slot i is point i).
+int launch_to_blocked(const uint8_t *logical, int64_t n, int NB, const int32_t *perm, uint8_t *blocked, int64_t n_blocks,
+                      hipStream_t st);
+// Points grouped by leaf: every leaf starts at a whole block, its points in ascending order. ws: leaf_layout_ws_bytes.
+// launch_leaf_counts fills leaf_blk[n_leaves + 1] and *info (device); launch_leaf_places then perm (n_slots entries).
+struct LeafLayoutInfo { int64_t n_blocks; int64_t max_leaf_blocks; int64_t first_bad; }; // first_bad: a row with a leaf out of range, or n
+size_t leaf_layout_ws_bytes(int64_t n, int n_leaves);
+int launch_leaf_counts(const int32_t *assign, int64_t n, int n_leaves, void *ws, int32_t *leaf_blk, LeafLayoutInfo *info, hipStream_t st);
+int launch_leaf_places(const int32_t *assign, int64_t n, int n_leaves, void *ws, const int32_t *leaf_blk, int32_t *perm, int64_t n_slots,
+                       hipStream_t st);
+
+// ---- nearest.hip -----------------------------------------------------------
+bool nearest_supported(int d, int k); // whether the matrix-core kernels take this shape
+size_t nearest_ws_bytes(int64_t n, int d, int k, int cnt_stride);
+int launch_nearest(const float *x, int64_t n, int d, const float *centers, const float *centers_t, int k, void *ws,
+                   int32_t *assign, uint32_t *cnt, int cnt_stride, uint32_t *pos, hipStream_t st);
+// Lloyd on the rows of x; centers [k][d] and centers_t [d][k] are written. Asynchronous.
+int kmeans_leaves_device(const float *x, int64_t n, int d, int k, int iters, uint64_t seed, float *centers, float *centers_t,
+                         DevBuf *ws, hipStream_t st);
 
 // ---- train.hip -------------------------------------------------------------
-// Lloyd on columns [col0, col0+dim) of x (row stride ld), optionally on residuals
-// to resid_centers[resid_assign[i]]. centers: device [k][dim].
-int kmeans_device(const float *x, int64_t n, int ld, int col0, int dim, int k, int iters,
-                  uint64_t seed, uint32_t stream_id, const float *resid_centers,
-                  const int32_t *resid_assign, float *centers, hipStream_t st);
+// Lloyd on the rows of x, every distance in fp64 (dimensions beyond the matrix-core kernels); centers: device [k][d].
+int kmeans_device(const float *x, int64_t n, int d, int k, int iters, uint64_t seed, float *centers, hipStream_t st);
 // The M dictionaries of k (16 or 256) codewords, all subspaces in the same launches; ws: grow-only scratch. Asynchronous.
 int pq_kmeans_device(const float *x, int64_t n, int d, int M, int k, int iters, uint64_t seed, const float *resid_centers,
                      const int32_t *resid_assign, float *codebooks, DevBuf *ws, hipStream_t st);

@@ -391,20 +391,11 @@ group_items_kernel(const uint32_t *__restrict__ leaf_cnt, const uint32_t *__rest
     for (uint32_t t = 0; t < tiles; ++t) item_list[item_off[l] + t] = ((uint32_t)l << 11) | t;
 }
 
-// Counting a batch's pairs is a million atomic additions to a few thousand words, and additions to words of one
-// cache line wait for one another: the counters that take them are spread out, one per 128 bytes while that
-// stays under a megabyte.
-static int leaf_cnt_stride(int n_leaves)
-{
-    int stride = 32;
-    while (stride > 1 && (size_t)n_leaves * stride > ((size_t)1 << 18)) stride /= 2;
-    return stride;
-}
-
+// Counting a batch's pairs is a million atomic additions to a few thousand words: spread counters (spread_stride).
 size_t group_by_leaf_words(int nq, int Lp, int n_leaves)
 {
     return (size_t)4 * n_leaves + 4 + (size_t)2 * nq * Lp + group_by_leaf_max_items(nq, Lp, n_leaves) +
-           (size_t)n_leaves * leaf_cnt_stride(n_leaves);
+           (size_t)n_leaves * spread_stride(n_leaves);
 }
 
 // Lays the scratch out and clears the pair counts; leaf selection then counts (launch_leaf_select's
@@ -422,7 +413,7 @@ int group_by_leaf_prepare(int nq, int Lp, int n_leaves, uint32_t *ws, LeafGroups
     g->item_list = g->pos + (size_t)nq * Lp;
     g->max_items = (int32_t)group_by_leaf_max_items(nq, Lp, n_leaves);
     g->cnt_wide = g->item_list + g->max_items;
-    g->cnt_stride = leaf_cnt_stride(n_leaves);
+    g->cnt_stride = spread_stride(n_leaves);
     AVQ_HIP(hipMemsetAsync(g->cnt_wide, 0, sizeof(uint32_t) * (size_t)n_leaves * g->cnt_stride, st));
     return AVQ_OK;
 }

@@ -1,38 +1,199 @@
 // Logical code layout ([n][NB] bytes, what the C ABI exchanges) -> the blocked
 // layout the scan streams: blocks of 256 points, byte position b of a block is
 // a 256-byte plane (lane l = points 4l..4l+3), planes grouped by four into
-// 1 KiB rows of 16 bytes per lane, left-over planes stored as dword rows.
+// 1 KiB rows of 16 bytes per lane, left-over planes stored as dword rows; and
+// the grouping of a partitioned index's points by leaf.
 #include "avq_internal.h"
 
 namespace avq {
 
-__global__ void to_blocked_kernel(const uint8_t *__restrict__ logical, int64_t n, int NB,
-                                  const int32_t *__restrict__ slot_of, uint8_t *__restrict__ blocked)
+// One workgroup per block: a thread takes its point's NB bytes to LDS, then the block is written in order, a dword (one
+// code byte of four points) per thread and step. (A thread per byte with scattered stores: 79 us for 1,183,514 x 25
+// bytes.)
+__global__ void __launch_bounds__(256)
+to_blocked_kernel(const uint8_t *__restrict__ logical, int64_t n, int NB, const int32_t *__restrict__ perm,
+                  uint8_t *__restrict__ blocked)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * NB) return;
-    const int64_t i = t / NB;
-    const int b = (int)(t % NB);
-    const int64_t slot = slot_of ? (int64_t)slot_of[i] : i;
-    const int64_t blk = slot >> 8;
-    const int within = (int)(slot & 255);
-    const int lane = within >> 2, pt = within & 3;
+    extern __shared__ uint8_t rows[]; // [256][NB + 1 or 2: odd]
+    const int ld = NB | 1;
+    const int64_t base = (int64_t)blockIdx.x * 256;
+    const int tid = threadIdx.x;
+    if (perm == nullptr) { // 256 rows side by side
+        const int64_t bytes = (n - base < 256 ? n - base : 256) * NB;
+        for (int e = tid; e < 256 * NB; e += 256) rows[(e / NB) * ld + e % NB] = e < bytes ? logical[base * NB + e] : (uint8_t)0;
+    } else { // a row of NB bytes per point: 16 rows at a time, 16 threads on a row
+        for (int r = tid >> 4; r < 256; r += 16) {
+            const int32_t i = perm[base + r];
+            for (int b = tid & 15; b < NB; b += 16) rows[r * ld + b] = i >= 0 ? logical[(size_t)i * NB + b] : (uint8_t)0;
+        }
+    }
+    __syncthreads();
+    uint32_t *out = (uint32_t *)(blocked + (size_t)base * NB);
     const int nfull = NB / 4;
-    size_t off = (size_t)blk * 256 * NB;
-    if (b < nfull * 4) off += (size_t)(b / 4) * 1024 + (size_t)lane * 16 + (size_t)(b % 4) * 4 + pt;
-    else off += (size_t)nfull * 1024 + (size_t)(b - nfull * 4) * 256 + (size_t)lane * 4 + pt;
-    blocked[off] = logical[t];
+    for (int w = tid; w < 64 * NB; w += 256) {
+        int lane, b;
+        if (w < nfull * 256) { lane = (w >> 2) & 63; b = 4 * (w >> 8) + (w & 3); }
+        else { lane = w & 63; b = 4 * nfull + ((w - nfull * 256) >> 6); }
+        uint32_t v = 0u;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) v |= (uint32_t)rows[(4 * lane + p) * ld + b] << (8 * p);
+        out[w] = v;
+    }
 }
 
-int launch_to_blocked(const uint8_t *logical, int64_t n, int NB, const int32_t *slot_of,
-                      uint8_t *blocked, int64_t n_slots, hipStream_t st)
+int launch_to_blocked(const uint8_t *logical, int64_t n, int NB, const int32_t *perm, uint8_t *blocked, int64_t n_blocks,
+                      hipStream_t st)
 {
-    AVQ_HIP(hipMemsetAsync(blocked, 0, (size_t)n_slots * NB, st));
-    const int64_t total = n * NB;
-    const int64_t grid = (total + 255) / 256;
-    if (grid > 0x7fffffff) { set_error("layout: too many code bytes for one launch"); return AVQ_EINVAL; }
-    hipLaunchKernelGGL(to_blocked_kernel, dim3((unsigned)grid), dim3(256), 0, st, logical, n, NB,
-                       slot_of, blocked);
+    if (n_blocks < 1) return AVQ_OK;
+    if (n_blocks > 0x7fffffff) { set_error("layout: too many blocks for one launch"); return AVQ_EINVAL; }
+    static LdsLimitOnce attr_done;
+    AVQ_TRY(set_lds_limit((const void *)to_blocked_kernel, kMaxDynLds, &attr_done));
+    hipLaunchKernelGGL(to_blocked_kernel, dim3((unsigned)n_blocks), dim3(256), (size_t)256 * (NB | 1), st, logical, n, NB, perm, blocked);
+    AVQ_HIP(hipGetLastError());
+    return AVQ_OK;
+}
+
+// ---- points grouped by leaf --------------------------------------------------------------
+//
+// A stable counting sort: the points are cut into chunks, hist[chunk][leaf] counts them, sums down the columns turn
+// the counts into the place of a chunk's first point of a leaf, and a wave per chunk then hands out the places 64
+// points at a time, in order. 1,183,514 points, 2,000 leaves: 39 + 62 + 5 + 68 us (on the host, with the copies to and
+// fro: 10 ms).
+
+static int leaf_chunk_points(int64_t n, int n_leaves)
+{
+    int64_t p = 1024; // as many chunks as 256 MB of counts allow
+    while ((n + p - 1) / p * n_leaves > ((int64_t)64 << 20) && p < n) p *= 2;
+    return (int)p;
+}
+
+size_t leaf_layout_ws_bytes(int64_t n, int n_leaves)
+{
+    const int64_t chunks = (n + leaf_chunk_points(n, n_leaves) - 1) / leaf_chunk_points(n, n_leaves);
+    return sizeof(uint32_t) * ((size_t)chunks * n_leaves + (size_t)n_leaves);
+}
+
+__global__ void __launch_bounds__(256)
+leaf_hist_kernel(const int32_t *__restrict__ assign, int64_t n, int n_leaves, int per, uint32_t *__restrict__ hist,
+                 LeafLayoutInfo *__restrict__ info)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const int32_t leaf = assign[i];
+    if (leaf < 0 || leaf >= n_leaves) {
+        atomicMin((unsigned long long *)&info->first_bad, (unsigned long long)i);
+        return;
+    }
+    atomicAdd(&hist[(size_t)(i / per) * n_leaves + leaf], 1u);
+}
+
+// sums down the columns: 32 leaves by 8 ranges of chunks per workgroup; total[leaf] = points of the leaf
+__global__ void __launch_bounds__(256)
+leaf_columns_kernel(uint32_t *__restrict__ hist, int chunks, int n_leaves, uint32_t *__restrict__ total)
+{
+    __shared__ uint32_t part[8][32];
+    const int c = threadIdx.x & 31, g = threadIdx.x >> 5, leaf = blockIdx.x * 32 + c;
+    const int per = (chunks + 7) / 8, lo = g * per, hi = lo + per < chunks ? lo + per : chunks;
+    uint32_t s = 0u;
+    if (leaf < n_leaves)
+        for (int t = lo; t < hi; ++t) s += hist[(size_t)t * n_leaves + leaf];
+    part[g][c] = s;
+    __syncthreads();
+    uint32_t o = 0u;
+    for (int u = 0; u < g; ++u) o += part[u][c];
+    if (leaf >= n_leaves) return;
+    for (int t = lo; t < hi; ++t) {
+        const uint32_t v = hist[(size_t)t * n_leaves + leaf];
+        hist[(size_t)t * n_leaves + leaf] = o;
+        o += v;
+    }
+    if (g == 7) total[leaf] = o;
+}
+
+__global__ void __launch_bounds__(1024)
+leaf_blocks_kernel(const uint32_t *__restrict__ total, int n_leaves, int32_t *__restrict__ leaf_blk, LeafLayoutInfo *__restrict__ info)
+{
+    __shared__ long long part[1024];
+    __shared__ uint32_t most[1024];
+    const int tid = threadIdx.x;
+    const int per = (n_leaves + 1023) / 1024, lo = tid * per, hi = lo + per < n_leaves ? lo + per : n_leaves;
+    long long s = 0;
+    uint32_t mx = 0u;
+    for (int l = lo; l < hi; ++l) {
+        const uint32_t b = (total[l] + 255u) / 256u;
+        s += b;
+        mx = b > mx ? b : mx;
+    }
+    part[tid] = s;
+    most[tid] = mx;
+    __syncthreads();
+    for (int st = 1; st < 1024; st *= 2) {
+        const long long a = tid >= st ? part[tid - st] : 0;
+        const uint32_t m = tid >= st ? most[tid - st] : 0u;
+        __syncthreads();
+        part[tid] += a;
+        most[tid] = m > most[tid] ? m : most[tid];
+        __syncthreads();
+    }
+    long long o = part[tid] - s;
+    for (int l = lo; l < hi; ++l) { leaf_blk[l] = (int32_t)o; o += (total[l] + 255u) / 256u; }
+    if (tid == 1023) {
+        leaf_blk[n_leaves] = (int32_t)part[1023];
+        info->n_blocks = part[1023];
+        info->max_leaf_blocks = most[1023];
+    }
+}
+
+// one wave per chunk, 64 points at a time in order: lanes of the same leaf find one another by comparing the bits of
+// their leaf numbers, the first of them takes their places
+__global__ void __launch_bounds__(64)
+leaf_places_kernel(const int32_t *__restrict__ assign, int64_t n, int n_leaves, int leaf_bits, int per, uint32_t *__restrict__ hist,
+                   const int32_t *__restrict__ leaf_blk, int32_t *__restrict__ perm)
+{
+    const int lane = threadIdx.x;
+    uint32_t *row = hist + (size_t)blockIdx.x * n_leaves;
+    const int64_t first = (int64_t)blockIdx.x * per, end = first + per < n ? first + per : n;
+    for (int64_t i0 = first; i0 < end; i0 += 64) {
+        const int64_t i = i0 + lane;
+        const bool valid = i < end;
+        const int leaf = valid ? assign[i] : 0;
+        u64 same = __builtin_amdgcn_ballot_w64(valid);
+        for (int b = 0; b < leaf_bits; ++b) {
+            const bool bit = (leaf >> b) & 1;
+            const u64 m = __builtin_amdgcn_ballot_w64(bit);
+            same &= bit ? m : ~m;
+        }
+        const int head = __builtin_ctzll(same | (1ull << 63));
+        uint32_t at = 0u;
+        if (valid && lane == head) at = atomicAdd(&row[leaf], (uint32_t)__builtin_popcountll(same));
+        at = (uint32_t)__shfl((int)at, head, 64) + (uint32_t)__builtin_popcountll(same & ((1ull << lane) - 1ull));
+        if (valid) perm[(size_t)leaf_blk[leaf] * 256 + at] = (int32_t)i;
+    }
+}
+
+int launch_leaf_counts(const int32_t *assign, int64_t n, int n_leaves, void *ws, int32_t *leaf_blk, LeafLayoutInfo *info, hipStream_t st)
+{
+    const int per = leaf_chunk_points(n, n_leaves);
+    const int64_t chunks = (n + per - 1) / per;
+    uint32_t *hist = (uint32_t *)ws, *total = hist + (size_t)chunks * n_leaves;
+    AVQ_HIP(hipMemsetAsync(hist, 0, sizeof(uint32_t) * (size_t)chunks * n_leaves, st));
+    AVQ_HIP(hipMemsetAsync(info, 0x7f, sizeof(*info), st));
+    hipLaunchKernelGGL(leaf_hist_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, assign, n, n_leaves, per, hist, info);
+    hipLaunchKernelGGL(leaf_columns_kernel, dim3((unsigned)((n_leaves + 31) / 32)), dim3(256), 0, st, hist, (int)chunks, n_leaves, total);
+    hipLaunchKernelGGL(leaf_blocks_kernel, dim3(1), dim3(1024), 0, st, total, n_leaves, leaf_blk, info);
+    AVQ_HIP(hipGetLastError());
+    return AVQ_OK;
+}
+
+int launch_leaf_places(const int32_t *assign, int64_t n, int n_leaves, void *ws, const int32_t *leaf_blk, int32_t *perm, int64_t n_slots,
+                       hipStream_t st)
+{
+    const int per = leaf_chunk_points(n, n_leaves);
+    int bits = 0;
+    while (bits < 31 && (1 << bits) < n_leaves) ++bits;
+    AVQ_HIP(hipMemsetAsync(perm, 0xff, sizeof(int32_t) * (size_t)n_slots, st));
+    hipLaunchKernelGGL(leaf_places_kernel, dim3((unsigned)((n + per - 1) / per)), dim3(64), 0, st, assign, n, n_leaves, bits, per,
+                       (uint32_t *)ws, leaf_blk, perm);
     AVQ_HIP(hipGetLastError());
     return AVQ_OK;
 }

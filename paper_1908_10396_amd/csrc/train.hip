@@ -54,24 +54,6 @@ double eta_host(int d, double T, double norm, int mode) { return eta_of_norm(d, 
 
 // ---- k-means ----------------------------------------------------------------------
 
-static inline uint64_t mix64(uint64_t z)
-{
-    // splitmix64 output function
-    z += 0x9E3779B97F4A7C15ull;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    return z ^ (z >> 31);
-}
-
-// Stratified draw of the initial codewords: index of codeword j among n rows.
-static int64_t init_index(uint64_t seed, uint32_t stream_id, int j, int k, int64_t n)
-{
-    const int64_t lo = (int64_t)(((__int128)j * n) / k);
-    const int64_t hi = (int64_t)(((__int128)(j + 1) * n) / k);
-    const uint64_t h = mix64(seed ^ mix64(((uint64_t)stream_id << 32) | (uint32_t)j));
-    return lo + (int64_t)(h % (uint64_t)(hi - lo));
-}
-
 // ---- the dictionaries of all subspaces at once --------------------------------------
 //
 // Lloyd's algorithm for every subspace in the same launches: an iteration is one pass of all (point, subspace)
@@ -83,13 +65,6 @@ static int64_t init_index(uint64_t seed, uint32_t stream_id, int j, int k, int64
 // 67 us an iteration (53 us at the rate of 140 such operations a pair) and 5 us for the codewords; with a launch
 // sequence per subspace, row-major points and one copy of the sums 51 + 5 + 9 us per subspace and iteration
 // (training as a whole 60.8 -> 1.4 ms).
-__device__ __forceinline__ uint64_t mix64_dev(uint64_t z)
-{
-    z += 0x9E3779B97F4A7C15ull; // splitmix64 output function, as mix64
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    return z ^ (z >> 31);
-}
 
 // x [n][d] -> xt [cols][n], columns col0 .. col0 + cols - 1; XT double: the residual to centers[assign[i]]
 template <typename XT>
@@ -116,7 +91,7 @@ points_by_coordinate_kernel(const float *__restrict__ x, int64_t n, int d, int c
     }
 }
 
-// the stratified draw of init_index for codeword j = blockIdx.x * 256 + threadIdx.x of subspace m0 + blockIdx.y
+// the first codewords: the row drawn by init_row, for codeword j = blockIdx.x * 256 + threadIdx.x of subspace m0 + blockIdx.y
 template <typename XT>
 __global__ void __launch_bounds__(256)
 pq_init_kernel(const XT *__restrict__ xt, int64_t n, int ds, int k, int m0, uint64_t seed, float *__restrict__ cb,
@@ -124,9 +99,7 @@ pq_init_kernel(const XT *__restrict__ xt, int64_t n, int ds, int k, int m0, uint
 {
     const int j = blockIdx.x * 256 + threadIdx.x, m = blockIdx.y;
     if (j >= k) return;
-    const uint64_t lo = (uint64_t)j * (uint64_t)n / (uint64_t)k, hi = (uint64_t)(j + 1) * (uint64_t)n / (uint64_t)k;
-    const uint64_t h = mix64_dev(seed ^ mix64_dev(((uint64_t)(1 + m0 + m) << 32) | (uint32_t)j));
-    const uint64_t i = lo + h % (hi - lo);
+    const uint64_t i = init_row(seed, (uint32_t)(1 + m0 + m), (uint64_t)j, (uint64_t)k, (uint64_t)n);
     for (int l = 0; l < ds; ++l) {
         const float v = (float)xt[(size_t)(m * ds + l) * n + i];
         cb[((size_t)m * k + j) * ds + l] = v;
@@ -312,7 +285,7 @@ static int pq_kmeans_group(const float *x, int64_t n, int d, int m0, int Mg, int
     return AVQ_OK;
 }
 
-// The M dictionaries of [k][d / M] codewords (16 or 256), each as kmeans_device would learn it with stream id 1 + m.
+// The M dictionaries of [k][d / M] codewords (16 or 256), drawn with stream ids 1 + m.
 // Groups of subspaces whose points by coordinate stay under a gigabyte of scratch.
 int pq_kmeans_device(const float *x, int64_t n, int d, int M, int k, int iters, uint64_t seed, const float *resid_centers,
                      const int32_t *resid_assign, float *codebooks, DevBuf *ws, hipStream_t st)
@@ -332,197 +305,111 @@ int pq_kmeans_device(const float *x, int64_t n, int d, int M, int k, int iters, 
     return AVQ_OK;
 }
 
-__device__ __forceinline__ double sub_value(const float *__restrict__ x, int64_t i, int ld, int col,
-                                            const float *__restrict__ rc, const int32_t *__restrict__ ra)
-{
-    double v = (double)x[(size_t)i * ld + col];
-    if (rc) v -= (double)rc[(size_t)ra[i] * ld + col];
-    return v;
-}
-
-__global__ void init_centers_kernel(const float *__restrict__ x, int ld, int col0, int dim, int k,
-                                    const int64_t *__restrict__ idx, const float *__restrict__ rc,
-                                    const int32_t *__restrict__ ra, float *__restrict__ centers)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= k * dim) return;
-    const int j = t / dim, l = t % dim;
-    centers[t] = (float)sub_value(x, idx[j], ld, col0 + l, rc, ra);
-}
-
-// One thread per point: nearest center in fp64 squared l2 (lowest index on
-// ties); the point's values are staged in LDS, transposed, so the inner loop
-// reads them conflict-free; every lane reads the same center value.
-// ACCUM: add the point into sums/counts; else write the assignment.
-// ACCUM with k*dim <= kLdsAccMax: sums are first added up per workgroup in LDS.
-constexpr int kLdsAccMax = 4096;
-
-// XT: type of the staged values. float (half the LDS, so twice the waves per compute unit at large dim) holds
-// them exactly when no residual is formed (rc == nullptr: the values are the floats of x).
-template <bool ACCUM, typename XT = double>
+// ---- nearest centers of rows beyond the matrix-core kernels (nearest.hip) ----------------
+//
+// One thread per point: nearest center in fp64 squared l2 (lowest index on ties); the point's values are staged in
+// LDS, transposed, so the inner loop reads them conflict-free; every lane reads the same center value. ACCUM: add
+// the point into sums/counts; else write the assignment. For dimensions that nearest_supported() refuses.
+template <bool ACCUM>
 __global__ void __launch_bounds__(256)
-nearest_kernel(const float *__restrict__ x, int64_t n, int ld, int col0, int dim, int k,
-               const float *__restrict__ rc, const int32_t *__restrict__ ra,
-               const float *__restrict__ centers, double *__restrict__ sums,
+nearest_kernel(const float *__restrict__ x, int64_t n, int d, int k, const float *__restrict__ centers, double *__restrict__ sums,
                unsigned long long *__restrict__ counts, int32_t *__restrict__ assign)
 {
-    extern __shared__ double xs_raw[]; // XT [dim][blockDim.x], then (ACCUM, small k*dim) double [k*dim] + [k]
-    XT *xs = (XT *)xs_raw;
+    extern __shared__ float staged[]; // [d][blockDim.x]
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool valid = i < n;
     const int bs = blockDim.x;
-    const bool lds_acc = ACCUM && k * dim <= kLdsAccMax;
-    double *lsum = (double *)(xs + (size_t)dim * bs); // 8-byte aligned: bs is a multiple of 64
-    unsigned long long *lcnt = (unsigned long long *)(lsum + k * dim);
-    if (lds_acc) {
-        for (int t = threadIdx.x; t < k * dim; t += bs) lsum[t] = 0.0;
-        for (int t = threadIdx.x; t < k; t += bs) lcnt[t] = 0ull;
-        __syncthreads();
-    }
-    for (int l = 0; l < dim; ++l) xs[l * bs + threadIdx.x] = valid ? (XT)sub_value(x, i, ld, col0 + l, rc, ra) : (XT)0;
+    if (i >= n) return; // no barriers below: a thread reads its own column only
+    for (int l = 0; l < d; ++l) staged[l * bs + threadIdx.x] = x[(size_t)i * d + l];
     int best = 0;
     double bestd = INFINITY;
     for (int j = 0; j < k; ++j) {
-        const float *c = centers + (size_t)j * dim;
+        const float *c = centers + (size_t)j * d;
         double dd = 0.0;
-        for (int l = 0; l < dim; ++l) {
-            const double t = (double)xs[l * bs + threadIdx.x] - (double)c[l];
+        for (int l = 0; l < d; ++l) {
+            const double t = (double)staged[l * bs + threadIdx.x] - (double)c[l];
             dd += t * t;
         }
         if (dd < bestd) { bestd = dd; best = j; }
     }
-    if (lds_acc) {
-        if (valid) {
-            for (int l = 0; l < dim; ++l) atomicAdd(&lsum[best * dim + l], (double)xs[l * bs + threadIdx.x]);
-            atomicAdd(&lcnt[best], 1ull);
-        }
-        __syncthreads();
-        for (int t = threadIdx.x; t < k; t += bs) {
-            if (lcnt[t] == 0ull) continue;
-            atomicAdd(&counts[t], lcnt[t]);
-            for (int l = 0; l < dim; ++l) atomicAdd(&sums[(size_t)t * dim + l], lsum[t * dim + l]);
-        }
-        return;
-    }
-    if (!valid) return;
     if (ACCUM) {
-        for (int l = 0; l < dim; ++l) atomicAdd(&sums[(size_t)best * dim + l], (double)xs[l * bs + threadIdx.x]);
+        for (int l = 0; l < d; ++l) atomicAdd(&sums[(size_t)best * d + l], (double)staged[l * bs + threadIdx.x]);
         atomicAdd(&counts[best], 1ull);
     } else {
         assign[i] = best;
     }
 }
 
-__global__ void update_centers_kernel(const double *__restrict__ sums,
-                                      const unsigned long long *__restrict__ counts, int k, int dim,
+__global__ void init_centers_kernel(const float *__restrict__ x, int64_t n, int d, int k, uint64_t seed, float *__restrict__ centers)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (int64_t)k * d) return;
+    centers[t] = x[(size_t)init_row(seed, 0u, (uint64_t)(t / d), (uint64_t)k, (uint64_t)n) * d + t % d];
+}
+
+__global__ void update_centers_kernel(const double *__restrict__ sums, const unsigned long long *__restrict__ counts, int k, int d,
                                       float *__restrict__ centers)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= k * dim) return;
-    const unsigned long long c = counts[t / dim];
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (int64_t)k * d) return;
+    const unsigned long long c = counts[t / d];
     if (c > 0) centers[t] = (float)(sums[t] / (double)c); // an empty cluster keeps its center
 }
 
-static int nearest_block_size(int dim)
+// workgroups of at most 64 KB of staged values where that leaves 64 threads, so that several share a compute unit
+static int nearest_block_size(int d)
 {
     int bs = 256;
-    while (bs > 64 && (size_t)bs * dim * sizeof(double) > 120 * 1024) bs /= 2;
+    while (bs > 64 && (size_t)bs * d * sizeof(float) > 64 * 1024) bs /= 2;
     return bs;
 }
 
-// Values staged as floats (no residual, and doubles would leave room for one small workgroup per compute
-// unit only): workgroups of at most 64 KB, so that several share a compute unit.
-static bool nearest_stage_floats(int dim, bool residual)
+static int nearest_stage_bytes(int d, size_t *bytes)
 {
-    return !residual && (size_t)256 * dim * sizeof(double) > 64 * 1024;
-}
-static int nearest_block_size_floats(int dim)
-{
-    int bs = 256;
-    while (bs > 64 && (size_t)bs * dim * sizeof(float) > 64 * 1024) bs /= 2;
-    return bs;
+    *bytes = (size_t)nearest_block_size(d) * d * sizeof(float);
+    if (*bytes > 150 * 1024) { set_error("nearest center: dimension %d too large", d); return AVQ_EINVAL; }
+    return AVQ_OK;
 }
 
-int kmeans_device(const float *x, int64_t n, int ld, int col0, int dim, int k, int iters,
-                  uint64_t seed, uint32_t stream_id, const float *resid_centers,
-                  const int32_t *resid_assign, float *centers, hipStream_t st)
+int kmeans_device(const float *x, int64_t n, int d, int k, int iters, uint64_t seed, float *centers, hipStream_t st)
 {
     if (n < k) { set_error("k-means: %lld points for %d centers", (long long)n, k); return AVQ_EINVAL; }
-    const bool floats = nearest_stage_floats(dim, resid_centers != nullptr);
-    const int bs = floats ? nearest_block_size_floats(dim) : nearest_block_size(dim);
-    const size_t stage = (size_t)bs * dim * (floats ? sizeof(float) : sizeof(double));
-    if (stage > 150 * 1024) {
-        set_error("k-means: dimension %d too large", dim);
-        return AVQ_EINVAL;
-    }
-    std::vector<int64_t> idx(k);
-    for (int j = 0; j < k; ++j) idx[j] = init_index(seed, stream_id, j, k, n);
-    int64_t *idx_dev = nullptr;
-    double *sums = nullptr;
-    unsigned long long *counts = nullptr;
-    AVQ_HIP(hipMalloc(&idx_dev, sizeof(int64_t) * k));
-    AVQ_HIP(hipMalloc(&sums, sizeof(double) * (size_t)k * dim));
-    AVQ_HIP(hipMalloc(&counts, sizeof(unsigned long long) * k));
-    int rc = AVQ_OK;
+    size_t lds = 0;
+    AVQ_TRY(nearest_stage_bytes(d, &lds));
+    const int bs = nearest_block_size(d);
+    const size_t b_sums = sizeof(double) * (size_t)k * d, b_counts = sizeof(unsigned long long) * (size_t)k;
+    DevBuf ws;
+    AVQ_TRY(ws.reserve(b_sums + b_counts));
+    double *sums = ws.as<double>();
+    unsigned long long *counts = (unsigned long long *)(ws.as<unsigned char>() + b_sums);
+    const unsigned eg = (unsigned)(((int64_t)k * d + 255) / 256);
     auto body = [&]() -> int {
-        AVQ_HIP(hipMemcpyAsync(idx_dev, idx.data(), sizeof(int64_t) * k, hipMemcpyHostToDevice, st));
-        hipLaunchKernelGGL(init_centers_kernel, dim3((k * dim + 255) / 256), dim3(256), 0, st, x, ld,
-                           col0, dim, k, idx_dev, resid_centers, resid_assign, centers);
-        AVQ_HIP(hipGetLastError());
-        AVQ_HIP(hipFuncSetAttribute((const void *)nearest_kernel<true>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds));
-        AVQ_HIP(hipFuncSetAttribute((const void *)nearest_kernel<true, float>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds));
-        const unsigned grid = (unsigned)((n + bs - 1) / bs);
+        static LdsLimitOnce attr_done;
+        AVQ_TRY(set_lds_limit((const void *)nearest_kernel<true>, kMaxDynLds, &attr_done));
+        hipLaunchKernelGGL(init_centers_kernel, dim3(eg), dim3(256), 0, st, x, n, d, k, seed, centers);
         for (int it = 0; it < iters; ++it) {
-            AVQ_HIP(hipMemsetAsync(sums, 0, sizeof(double) * (size_t)k * dim, st));
-            AVQ_HIP(hipMemsetAsync(counts, 0, sizeof(unsigned long long) * k, st));
-            const size_t lds = stage + (k * dim <= kLdsAccMax ? (size_t)(k * dim + k) * sizeof(double) : 0);
-            if (floats)
-                hipLaunchKernelGGL((nearest_kernel<true, float>), dim3(grid), dim3(bs), lds, st, x, n, ld, col0, dim,
-                                   k, resid_centers, resid_assign, centers, sums, counts, (int32_t *)nullptr);
-            else
-                hipLaunchKernelGGL(nearest_kernel<true>, dim3(grid), dim3(bs), lds,
-                                   st, x, n, ld, col0, dim, k, resid_centers, resid_assign, centers, sums,
-                                   counts, (int32_t *)nullptr);
-            AVQ_HIP(hipGetLastError());
-            hipLaunchKernelGGL(update_centers_kernel, dim3((k * dim + 255) / 256), dim3(256), 0, st, sums,
-                               counts, k, dim, centers);
-            AVQ_HIP(hipGetLastError());
+            AVQ_HIP(hipMemsetAsync(ws.p, 0, b_sums + b_counts, st));
+            hipLaunchKernelGGL(nearest_kernel<true>, dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), lds, st, x, n, d, k, centers, sums,
+                               counts, (int32_t *)nullptr);
+            hipLaunchKernelGGL(update_centers_kernel, dim3(eg), dim3(256), 0, st, sums, counts, k, d, centers);
         }
+        AVQ_HIP(hipGetLastError());
         AVQ_HIP(hipStreamSynchronize(st));
         return AVQ_OK;
     };
-    rc = body();
-    (void)hipFree(idx_dev);
-    (void)hipFree(sums);
-    (void)hipFree(counts);
+    const int rc = body();
+    ws.release();
     return rc;
 }
 
-int launch_assign_nearest(const float *x, int64_t n, int d, const float *centers, int k,
-                          int32_t *assign, hipStream_t st)
+int launch_assign_nearest(const float *x, int64_t n, int d, const float *centers, int k, int32_t *assign, hipStream_t st)
 {
-    const bool floats = nearest_stage_floats(d, false);
-    const int bs = floats ? nearest_block_size_floats(d) : nearest_block_size(d);
-    const size_t stage = (size_t)bs * d * (floats ? sizeof(float) : sizeof(double));
-    if (stage > 150 * 1024) {
-        set_error("assign: dimension %d too large", d);
-        return AVQ_EINVAL;
-    }
-    if (floats) {
-        AVQ_HIP(hipFuncSetAttribute((const void *)nearest_kernel<false, float>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds));
-        hipLaunchKernelGGL((nearest_kernel<false, float>), dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), stage, st,
-                           x, n, d, 0, d, k, (const float *)nullptr, (const int32_t *)nullptr, centers,
-                           (double *)nullptr, (unsigned long long *)nullptr, assign);
-    } else {
-        AVQ_HIP(hipFuncSetAttribute((const void *)nearest_kernel<false>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds));
-        hipLaunchKernelGGL(nearest_kernel<false>, dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), stage, st, x, n, d,
-                           0, d, k, (const float *)nullptr, (const int32_t *)nullptr, centers, (double *)nullptr,
-                           (unsigned long long *)nullptr, assign);
-    }
+    size_t lds = 0;
+    AVQ_TRY(nearest_stage_bytes(d, &lds));
+    const int bs = nearest_block_size(d);
+    static LdsLimitOnce attr_done;
+    AVQ_TRY(set_lds_limit((const void *)nearest_kernel<false>, kMaxDynLds, &attr_done));
+    hipLaunchKernelGGL(nearest_kernel<false>, dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), lds, st, x, n, d, k, centers,
+                       (double *)nullptr, (unsigned long long *)nullptr, assign);
     AVQ_HIP(hipGetLastError());
     return AVQ_OK;
 }

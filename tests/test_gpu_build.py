@@ -35,3 +35,74 @@ def test_dictionaries_of_all_subspaces_match(n, d, M, bits, residual):
     want = oracle.train_pq(x, M, 1 << bits, 3, 5, **okw)
     # fp64 means in another order, rounded to fp32: one unit in the last place of values below 1
     np.testing.assert_allclose(idx.get_codebooks(), want, rtol=0, atol=1.2e-7)
+
+
+def leaf_index(d, centers, **kw):
+    idx = avq.Index(d, 1, 4, n_leaves=centers.shape[0], **kw)
+    idx.set_leaf_centers(centers)
+    idx.set_codebooks(np.zeros((1, 16, d), np.float32))
+    return idx
+
+
+# steps of 16 coordinates of the matrix-core kernel (with three for the bias: 13 | 14, 29 | 30, 109 | 110, ...), tiles of
+# 32 centers, workgroups of 128 and 256 points; 270 dimensions take the kernel without matrix cores
+@pytest.mark.parametrize("n,d,k", [(1, 2, 1), (129, 13, 31), (255, 14, 32), (256, 29, 33), (257, 30, 64), (1000, 64, 65),
+                                   (3000, 100, 200), (511, 109, 40), (512, 110, 40), (513, 128, 97), (300, 141, 33),
+                                   (640, 192, 50), (700, 205, 129), (385, 256, 300), (260, 269, 31), (260, 270, 31)])
+@pytest.mark.parametrize("law", ["unit", "far", "lattice", "twins", "scales"])
+def test_nearest_leaf_is_that_of_fp64_distances(n, d, k, law):
+    rng = np.random.default_rng(n * 7 + d)
+    x, c = unit_rows(rng, n, d), unit_rows(rng, k, d)
+    if law == "far":            # distances small against the norms: the f16 product leaves every point open
+        off = 50.0 * unit_rows(rng, 1, d)
+        x, c = (off + 0.1 * x).astype(np.float32), (off + 0.1 * c).astype(np.float32)
+    elif law == "lattice":      # many exact ties: the lowest index wins
+        x, c = np.round(x * 3).astype(np.float32), np.round(c * 3).astype(np.float32)
+    elif law == "twins":        # equal centers, and centers that differ in the last bit
+        c[k // 2:] = c[: k - k // 2]
+        c[-1] = np.nextafter(c[-1], 2.0)
+    elif law == "scales":       # tiny and huge coordinates, points far outside the centers, zero rows
+        c *= np.float32(3e-3)
+        x *= (10.0 ** rng.uniform(-6, 4, (n, 1))).astype(np.float32)
+        x[0] = 0.0
+    idx = leaf_index(d, c)
+    idx.encode(dev(x))
+    np.testing.assert_array_equal(idx.get_leaf_assign(), oracle.assign_nearest(x, c))
+
+
+@pytest.mark.parametrize("n,d,k", [(64, 5, 64), (3001, 100, 70), (2000, 36, 300), (1500, 270, 9)])
+def test_leaf_centers_match(n, d, k):
+    rng = np.random.default_rng(3)
+    x = unit_rows(rng, n, d)
+    idx = avq.Index(d, 1, 4, n_leaves=k, leaf_kmeans_iters=4, kmeans_iters=0, seed=8)
+    idx.train(dev(x))
+    # fp64 means in another order, rounded to fp32: one unit in the last place of values below 1
+    np.testing.assert_allclose(idx.get_leaf_centers(), oracle.kmeans(x, k, 4, seed=8), rtol=0, atol=1.2e-7)
+
+
+# leaves of 0, 1, 255, 256, 257 points and one with most of them; fewer and more points than a chunk of 1,024; code sizes
+# with and without left-over planes; what a search of every leaf returns depends on every place
+@pytest.mark.parametrize("n,d,M,bits,leaves", [(1, 8, 4, 4, 3), (1500, 8, 4, 4, 7), (5000, 10, 5, 8, 2), (2049, 12, 6, 4, 1300)])
+def test_points_are_grouped_by_leaf(n, d, M, bits, leaves):
+    rng = np.random.default_rng(17)
+    x, q = unit_rows(rng, n, d), unit_rows(rng, 3, d)
+    cb = oracle.train_pq(np.tile(x, (256 // n + 1, 1)) if n < 256 else x, M, 1 << bits, 1, 3)
+    codes = rng.integers(0, 1 << bits, (n, M)).astype(np.uint8)
+    centers = unit_rows(rng, leaves, d)
+    assign = rng.integers(0, leaves, n).astype(np.int32)
+    if n >= 1500 and leaves >= 7:
+        assign[:] = 6
+        assign[rng.permutation(n)[:769]] = np.repeat([1, 2, 3, 4], [1, 255, 256, 257])
+    idx = avq.Index(d, M, bits, n_leaves=leaves)
+    idx.set_codebooks(cb)
+    idx.set_leaf_centers(centers)
+    idx.set_database(dev(x), oracle.pack_codes(codes, bits), assign)
+    L = min(leaves, 512)
+    k = min(n, 60)
+    ids, sc = idx.search(dev(q), k, min(n, 100), 0, leaves_to_search=L)
+    oi, os_ = oracle.search(x, cb, codes, bits, q, k, min(n, 100), 0, centers=centers, assign=assign, leaves_to_search=L)
+    np.testing.assert_array_equal(ids.cpu().numpy(), oi)
+    np.testing.assert_array_equal(sc.cpu().numpy(), os_)
+    assign[n // 2] = leaves
+    with pytest.raises(avq.AvqError, match="leaf assignment %d of point %d" % (leaves, n // 2)):
+        idx.set_database(dev(x), oracle.pack_codes(codes, bits), assign)
