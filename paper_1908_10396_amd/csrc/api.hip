@@ -347,11 +347,37 @@ extern "C" int avq_train(avq_index *idx, const float *x, int64_t n_train, void *
 
 // ---- database ------------------------------------------------------------------------
 
-// codes_logical (and assign, if partitioned) are on the device; builds the blocked layout.
+// The points of a partitioned index grouped by the leaves in idx->assign: perm, leaf_blk and the number of blocks.
+static int group_by_leaves(avq_index *idx, int64_t n, hipStream_t st)
+{
+    // ascending id inside a leaf, each leaf padded to whole blocks
+    const avq_config &c = idx->cfg;
+    const size_t b_ws = (leaf_layout_ws_bytes(n, c.n_leaves) + 255) & ~(size_t)255;
+    AVQ_TRY(idx->tmp.reserve(b_ws + sizeof(LeafLayoutInfo)));
+    AVQ_TRY(idx->leaf_blk.reserve(sizeof(int32_t) * (size_t)(c.n_leaves + 1)));
+    LeafLayoutInfo *info_dev = (LeafLayoutInfo *)(idx->tmp.as<unsigned char>() + b_ws), info;
+    const int32_t *assign = idx->assign.as<int32_t>();
+    AVQ_TRY(launch_leaf_counts(assign, n, c.n_leaves, idx->tmp.p, idx->leaf_blk.as<int32_t>(), info_dev, st));
+    AVQ_HIP(hipMemcpyAsync(&info, info_dev, sizeof(info), hipMemcpyDeviceToHost, st));
+    AVQ_HIP(hipStreamSynchronize(st));
+    if (info.first_bad < n) {
+        int32_t leaf = 0;
+        AVQ_HIP(hipMemcpy(&leaf, assign + info.first_bad, sizeof(leaf), hipMemcpyDeviceToHost));
+        set_error("leaf assignment %d of point %lld out of range", leaf, (long long)info.first_bad);
+        return AVQ_EINVAL;
+    }
+    if (info.n_blocks * kBlockPoints > 0x7fffffff) { set_error("index too large"); return AVQ_EINVAL; }
+    idx->max_leaf_blocks = info.max_leaf_blocks;
+    idx->n_blocks = info.n_blocks;
+    idx->n_slots = info.n_blocks * kBlockPoints;
+    AVQ_TRY(idx->perm.reserve(sizeof(int32_t) * (size_t)idx->n_slots));
+    return launch_leaf_places(assign, n, c.n_leaves, idx->tmp.p, idx->leaf_blk.as<int32_t>(), idx->perm.as<int32_t>(), idx->n_slots, st);
+}
+
+// codes_logical (and, if partitioned, the points grouped by leaf) are on the device; builds the blocked layout.
 static int install_database(avq_index *idx, const float *x, int64_t n, hipStream_t st)
 {
     const avq_config &c = idx->cfg;
-    idx->n = 0;
     if (x && !c.borrow_x) {
         AVQ_TRY(idx->x_own.reserve(sizeof(float) * (size_t)n * c.d));
         AVQ_HIP(hipMemcpyAsync(idx->x_own.p, x, sizeof(float) * (size_t)n * c.d, hipMemcpyDeviceToDevice, st));
@@ -362,36 +388,10 @@ static int install_database(avq_index *idx, const float *x, int64_t n, hipStream
     if (c.n_leaves <= 0) {
         idx->n_blocks = (n + kBlockPoints - 1) / kBlockPoints;
         idx->n_slots = idx->n_blocks * kBlockPoints;
-        AVQ_TRY(idx->codes_blocked.reserve((size_t)idx->n_slots * idx->NB));
-        AVQ_TRY(launch_to_blocked(idx->codes_logical.as<uint8_t>(), n, idx->NB, nullptr,
-                                  idx->codes_blocked.as<uint8_t>(), idx->n_blocks, st));
-    } else {
-        // group the points by leaf (ascending id inside a leaf), each leaf padded to whole blocks
-        const size_t b_ws = (leaf_layout_ws_bytes(n, c.n_leaves) + 255) & ~(size_t)255;
-        AVQ_TRY(idx->tmp.reserve(b_ws + sizeof(LeafLayoutInfo)));
-        AVQ_TRY(idx->leaf_blk.reserve(sizeof(int32_t) * (size_t)(c.n_leaves + 1)));
-        LeafLayoutInfo *info_dev = (LeafLayoutInfo *)(idx->tmp.as<unsigned char>() + b_ws), info;
-        const int32_t *assign = idx->assign.as<int32_t>();
-        AVQ_TRY(launch_leaf_counts(assign, n, c.n_leaves, idx->tmp.p, idx->leaf_blk.as<int32_t>(), info_dev, st));
-        AVQ_HIP(hipMemcpyAsync(&info, info_dev, sizeof(info), hipMemcpyDeviceToHost, st));
-        AVQ_HIP(hipStreamSynchronize(st));
-        if (info.first_bad < n) {
-            int32_t leaf = 0;
-            AVQ_HIP(hipMemcpy(&leaf, assign + info.first_bad, sizeof(leaf), hipMemcpyDeviceToHost));
-            set_error("leaf assignment %d of point %lld out of range", leaf, (long long)info.first_bad);
-            return AVQ_EINVAL;
-        }
-        if (info.n_blocks * kBlockPoints > 0x7fffffff) { set_error("index too large"); return AVQ_EINVAL; }
-        idx->max_leaf_blocks = info.max_leaf_blocks;
-        idx->n_blocks = info.n_blocks;
-        idx->n_slots = info.n_blocks * kBlockPoints;
-        AVQ_TRY(idx->perm.reserve(sizeof(int32_t) * (size_t)idx->n_slots));
-        AVQ_TRY(idx->codes_blocked.reserve((size_t)idx->n_slots * idx->NB));
-        AVQ_TRY(launch_leaf_places(assign, n, c.n_leaves, idx->tmp.p, idx->leaf_blk.as<int32_t>(), idx->perm.as<int32_t>(),
-                                   idx->n_slots, st));
-        AVQ_TRY(launch_to_blocked(idx->codes_logical.as<uint8_t>(), n, idx->NB, idx->perm.as<int32_t>(),
-                                  idx->codes_blocked.as<uint8_t>(), idx->n_blocks, st));
     }
+    AVQ_TRY(idx->codes_blocked.reserve((size_t)idx->n_slots * idx->NB));
+    AVQ_TRY(launch_to_blocked(idx->codes_logical.as<uint8_t>(), n, idx->NB, c.n_leaves > 0 ? idx->perm.as<int32_t>() : nullptr,
+                              idx->codes_blocked.as<uint8_t>(), idx->n_blocks, st));
     AVQ_HIP(hipStreamSynchronize(st));
     idx->n = n;
     return AVQ_OK;
@@ -423,6 +423,8 @@ extern "C" int avq_set_database(avq_index *idx, const float *x, const uint8_t *p
         AVQ_HIP(hipMemcpyAsync(idx->assign.p, leaf_assign, sizeof(int32_t) * (size_t)n, hipMemcpyDefault, st));
     }
     AVQ_HIP(hipStreamSynchronize(st));
+    idx->n = 0;
+    if (leaf_assign) AVQ_TRY(group_by_leaves(idx, n, st));
     return install_database(idx, x, n, st);
 }
 
@@ -435,16 +437,18 @@ extern "C" int avq_encode(avq_index *idx, const float *x, int64_t n, void *hip_s
     if (!x) { set_error("avq_encode: x is NULL"); return AVQ_EINVAL; }
     if (!idx->have_codebooks) { set_error("avq_encode: no dictionaries yet (avq_train first)"); return AVQ_ESTATE; }
     if (c.n_leaves > 0 && !idx->have_centers) { set_error("avq_encode: no leaf centers yet"); return AVQ_ESTATE; }
+    idx->n = 0;
     AVQ_TRY(idx->codes_logical.reserve((size_t)n * idx->NB));
     const int32_t *assign = nullptr;
     if (c.n_leaves > 0) {
         AVQ_TRY(idx->assign.reserve(sizeof(int32_t) * (size_t)n));
         AVQ_TRY(assign_to_leaves(idx, x, n, idx->assign.as<int32_t>(), st));
         assign = idx->assign.as<int32_t>();
+        AVQ_TRY(group_by_leaves(idx, n, st));
     }
-    AVQ_TRY(launch_encode(x, n, c.d, c.M, idx->kc, c.bits, idx->codebooks.as<float>(),
-                          assign ? idx->centers.as<float>() : nullptr, assign, c.eta_mode, (double)c.T,
-                          (double)c.eta_explicit, c.encode_passes, idx->codes_logical.as<uint8_t>(), st));
+    AVQ_TRY(launch_encode(x, n, c.d, c.M, idx->kc, c.bits, idx->codebooks.as<float>(), assign ? idx->centers.as<float>() : nullptr,
+                          assign, assign ? idx->perm.as<int32_t>() : nullptr, idx->n_slots, c.eta_mode, (double)c.T,
+                          (double)c.eta_explicit, c.encode_passes, idx->codes_logical.as<uint8_t>(), &idx->train_ws, st));
     return install_database(idx, x, n, st);
 }
 

@@ -419,10 +419,10 @@ int pq_joint_update_device(const float *x, int64_t n, int d, int M, int kc, int 
                            const float *centers, const int32_t *assign,
                            int eta_mode, double T, double eta_explicit, float *codebooks, void *scratch,
                            int max_iters, double tol, int *iters_out, double *rel_residual_out, hipStream_t st);
-int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits,
-                  const float *codebooks, const float *leaf_centers, const int32_t *leaf_assign,
-                  int eta_mode, double T, double eta_explicit, int passes, uint8_t *packed,
-                  hipStream_t st);
+// order (or NULL): the points to take, slot by slot (-1: none), n_slots of them: leaf by leaf on a partitioned index.
+int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, const float *codebooks, const float *leaf_centers,
+                  const int32_t *leaf_assign, const int32_t *order, int64_t n_slots, int eta_mode, double T, double eta_explicit,
+                  int passes, uint8_t *packed, DevBuf *ws, hipStream_t st);
 
 double eta_host(int d, double T, double norm, int mode);
 

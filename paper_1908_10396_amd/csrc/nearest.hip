@@ -215,7 +215,7 @@ nearest_mfma_kernel(const float *__restrict__ x, int64_t n, int d, const v8h *__
                 const float a = __uint_as_float((__float_as_uint(acc[c][v]) & 0xfffffff0u) | (uint32_t)v);
                 third[c] = __builtin_amdgcn_fmed3f(second[c], third[c], a);
                 second[c] = __builtin_amdgcn_fmed3f(best[c], second[c], a);
-                best[c] = fmaxf(best[c], a);
+                best[c] = __builtin_amdgcn_fmed3f(INFINITY, best[c], a); // the larger (fmaxf would first quiet both)
             }
             t_second[c] = second[c] == s_old ? t_second[c] : (second[c] == b_old ? t_best[c] : t);
             t_best[c] = best[c] == b_old ? t_best[c] : t;

@@ -9,6 +9,7 @@
 // All arithmetic here is fp64: the results are arg-mins, and they have to agree
 // with a plain reference evaluation except at exact ties.
 #include "avq_internal.h"
+#include "wave_topk.h"
 
 namespace avq {
 
@@ -481,19 +482,343 @@ int launch_assign_aniso(const float *x, int64_t n, int d, const float *centers, 
 
 // ---- encoding under the anisotropic loss ------------------------------------------
 
-constexpr int kMaxM = 256;
+// With r = x - x~, p = <r, x>, e = ||r||^2: ||r_par||^2 = p^2/||x||^2 and ||r_perp||^2 = e - p^2/||x||^2, so the loss
+// is e + w p^2, w = (eta - 1) / ||x||^2. p and e are sums over the subspaces; with the other subspaces' part P of p
+// fixed, codeword j of subspace m gives e_m(j) + w (P + p_m(j))^2 up to a constant.
+//
+// encode_aniso_kernel (2, 4, 8, ... dimensions per subspace): a lane per point. What decides a codeword is, with
+// t = <c, x>, u = <c, x - center>, q = P + <x - center, x>,
+//     f(j) = ||c||^2 - 2 u + w t^2 - 2 w q t,
+// formed in fp32 with the codewords as scalar operands: ds + 2 operations (ds + ds + 3 with leaf centers) and three
+// to keep the best (its index in its low bits) and the second best. f is within eps F of its real value, F a bound of
+// the terms' magnitudes, so a codeword that leads by more than 2 eps F is the arg-min; else the lane evaluates every
+// codeword in fp64 as above (one (point, subspace) in some thousands). q = p + <codeword in use, x> is kept and
+// updated in fp64. The codes are therefore those of an fp64 evaluation.
+//
+// The points of a wave need different numbers of passes: a lane whose point is done takes the wave's next point at the
+// end of the sweep over the subspaces, so that no lane waits for the slowest of 64. (x of the points in LDS, row by
+// row, for 16 codewords; with 256 the rows are read from memory again, 32 bytes for 1,800 operations.) On a
+// partitioned index the points are taken leaf by leaf, and the lanes' leaf centers mostly are one and the same.
+// Bound by vector operations and by the chain from one subspace's choice to the next one's q: 1,183,514 x 100 points,
+// 50 subspaces of 16 codewords: 2.34 ms (1.5 ms of vector operations at five waves per compute unit; 2.91 ms with leaf
+// centers), against 9.3 (11.8) ms for a thread per point with every codeword in fp64 and its state in scratch memory.
+// Windows of points handed out by a counter instead of split evenly: 2.63 -> 2.34 ms, as one SIMD of four holds two waves.
+struct EncodeParams {
+    const float *x;
+    int64_t n_slots;
+    const int32_t *order; // slot -> point (-1: none), NULL: slot i is point i
+    int32_t d, M, NB, passes;
+    const float *codebooks;   // [M][KC][DS]
+    const float *leaf_centers;
+    const int32_t *leaf_assign;
+    int32_t eta_mode;
+    double T, eta_explicit;
+    const double *w_in;       // NULL: w from eta_mode here
+    uint8_t *packed;
+    uint32_t *next_window;    // windows of 64 slots are handed out: waves that share a SIMD get fewer
+    int32_t row_stride, code_stride; // row_stride: floats per staged row (odd); code_stride: bytes (odd dwords)
+};
 
-// One thread per point. With r = x - x~, p = <r, x>, e = ||r||^2:
-// ||r_par||^2 = p^2/||x||^2 and ||r_perp||^2 = e - p^2/||x||^2, so the loss is
-// e + (eta - 1) p^2 / ||x||^2. p and e are sums over subspaces; changing the
-// codeword of subspace m only changes that subspace's terms, so the terms of the
-// current codewords are kept per subspace and only summed again (every pass forms
-// the sums before and after each subspace afresh from the kept terms: no drift).
-// DS = dimensions per subspace known at compile time (0: any): the point's sub-vector of the
-// subspace at hand then stays in registers while its kc codewords (wave-uniform, read through
-// the scalar cache) pass by, instead of being read again for every codeword from a row that
-// no neighbouring lane shares.
-template <int DS>
+__global__ void __launch_bounds__(64)
+encode_tables_kernel(const float *__restrict__ codebooks, int kc, int ds, float *__restrict__ tab, float2 *__restrict__ lim,
+                     uint32_t *__restrict__ next_window)
+{
+    const int m = blockIdx.x, lane = threadIdx.x;
+    if (m == 0 && lane == 0) *next_window = 0u;
+    float cm = 0.0f, ccm = 0.0f;
+    for (int j = lane; j < kc; j += 64) {
+        const float *c = codebooks + ((size_t)m * kc + j) * ds;
+        float *o = tab + ((size_t)m * kc + j) * (ds + 1);
+        double cc = 0.0;
+        for (int l = 0; l < ds; ++l) {
+            o[l] = c[l];
+            cc += (double)c[l] * (double)c[l];
+            cm = fmaxf(cm, fabsf(c[l]));
+        }
+        o[ds] = (float)cc;
+        ccm = fmaxf(ccm, (float)cc);
+    }
+    for (int s = 32; s > 0; s >>= 1) { cm = fmaxf(cm, __shfl_xor(cm, s, 64)); ccm = fmaxf(ccm, __shfl_xor(ccm, s, 64)); }
+    if (lane == 0) lim[m] = make_float2(cm * 1.0001f, ccm * 1.0001f);
+}
+
+// (eta - 1) / ||x||^2 of every point, for the mode whose eta is an integral per point
+__global__ void __launch_bounds__(256)
+encode_weights_kernel(const float *__restrict__ x, int64_t n, int d, int eta_mode, double T, double eta_explicit, double *__restrict__ w)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const float *xi = x + (size_t)i * d;
+    double nx2 = 0.0;
+    for (int l = 0; l < d; ++l) nx2 += (double)xi[l] * (double)xi[l];
+    const double eta = eta_of_norm(d, T, sqrt(nx2), eta_mode, eta_explicit);
+    w[i] = nx2 > 0.0 ? (eta - 1.0) / nx2 : 0.0;
+}
+
+template <int DS, int KC, bool RES>
+__global__ void __launch_bounds__(512)
+encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, const float2 *__restrict__ limits)
+{
+    constexpr bool kStage = KC == 16; // rows of x and the dictionaries in LDS
+    extern __shared__ __align__(16) float enc_lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+    const int M = p.M, d = p.d;
+    constexpr int kTab4 = 4 * (DS + 1); // float4s of a subspace's table of 16 codewords
+    float *tab_lds = enc_lds; // kStage: [M][KC][DS + 1]
+    float2 *lim_lds = (float2 *)(enc_lds + M * KC * (DS + 1)); // kStage: [M]
+    float *rows = enc_lds + (kStage ? M * (KC * (DS + 1) + 2) + wave * 64 * p.row_stride : 0);
+    uint8_t *codes = (uint8_t *)(enc_lds + (kStage ? M * (KC * (DS + 1) + 2) + n_waves * 64 * p.row_stride : 0)) +
+                     (size_t)wave * 64 * p.code_stride;
+    uint8_t *my_codes = codes + (size_t)lane * p.code_stride;
+    const float *my_row = rows + (size_t)lane * p.row_stride; // kStage
+    if (kStage) {
+        for (int e = threadIdx.x; e < M * KC * (DS + 1); e += blockDim.x) tab_lds[e] = tables[e];
+        for (int e = threadIdx.x; e < M; e += blockDim.x) lim_lds[e] = limits[e];
+        __syncthreads();
+    }
+    for (int e = 0; e < p.code_stride; e += 4) *(uint32_t *)(my_codes + e) = 0u;
+
+    int win_id = -1;                // this lane's slot of the window: its point
+    u64 win = 0ull;                 // slots of the window not yet taken
+    bool drained = false;           // no windows left
+    int id = -1, stage = 0;         // this lane's point (-1: none) and pass (-1: nearest codewords first)
+    double P = 0.0, w = 0.0; // P = <x - center - codewords, x>, the codewords chosen so far
+    const float *xi = p.x, *ce_row = nullptr;
+    bool changed = false;
+    constexpr float kEps = (1.9074e-6f + (2 * DS + 8 + (RES ? 4 : 0)) * 6.0e-8f) * 1.05f;
+
+    for (;;) {
+        // lanes without a point take the wave's next ones
+        u64 need = __builtin_amdgcn_ballot_w64(id < 0), taken = 0ull;
+        while (need != 0ull) {
+            if (win == 0ull) {
+                if (drained) break;
+                uint32_t w64 = 0u;
+                if (lane == 0) w64 = atomicAdd(p.next_window, 1u);
+                const int64_t s0 = (int64_t)__builtin_amdgcn_readfirstlane(w64) * 64, s = s0 + lane;
+                if (s0 >= p.n_slots) { drained = true; break; }
+                win_id = s < p.n_slots ? (p.order ? p.order[s] : (int)s) : -1;
+                win = __builtin_amdgcn_ballot_w64(win_id >= 0);
+                continue;
+            }
+            const int t = __builtin_ctzll(need), from = __builtin_ctzll(win);
+            const int who = __builtin_amdgcn_readlane(win_id, from);
+            need &= need - 1;
+            win &= win - 1;
+            taken |= 1ull << t;
+            if (lane == t) id = who;
+            if constexpr (kStage) {
+                const float *src = p.x + (size_t)who * d;
+                for (int c = 0; c < d; c += 64)
+                    if (c + lane < d)
+                        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + c + lane),
+                                                         (__attribute__((address_space(3))) void *)(rows + t * p.row_stride + c), 4, 0, 0);
+            }
+        }
+        if (__builtin_amdgcn_ballot_w64(id >= 0) == 0ull) break;
+        if (taken != 0ull) {
+            __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0): the rows are in LDS
+            wave_lds_fence();
+            if ((taken >> lane) & 1) {
+                stage = -1;
+                if constexpr (!kStage) xi = p.x + (size_t)id * d;
+                if constexpr (RES) ce_row = p.leaf_centers + (size_t)p.leaf_assign[id] * d;
+                double nx2 = 0.0, cx = 0.0;
+#pragma unroll 4
+                for (int l = 0; l < d; ++l) {
+                    const double v = (double)(kStage ? my_row[l] : xi[l]);
+                    nx2 += v * v;
+                    if constexpr (RES) cx = fma((double)ce_row[l], v, cx);
+                }
+                P = nx2 - cx;
+                if (p.w_in) {
+                    w = p.w_in[id];
+                } else {
+                    double eta = p.eta_explicit;
+                    if (p.eta_mode != AVQ_ETA_EXPLICIT) { // the limit of Theorem 3.4, floored at 1 (see eta_of_norm)
+                        eta = 1.0;
+                        if (nx2 > 0.0) {
+                            const double u = clamp_ratio_sq(p.T, sqrt(nx2));
+                            eta = fmax((double)(d - 1) * u / (1.0 - u), 1.0);
+                        }
+                    }
+                    w = nx2 > 0.0 ? (eta - 1.0) / nx2 : 0.0;
+                }
+            }
+        }
+        const bool active = id >= 0;
+        const bool init = stage < 0;
+        const double wl = init ? 0.0 : w, w2 = 2.0 * wl;
+        const float wf = (float)wl;
+        changed = false;
+
+        // One sweep over the subspaces. What a step needs is asked for during the step before it (two sets of registers
+        // that take turns): a compute unit holds five waves at 100 dimensions, too few to hide a load by another wave.
+        struct Step {
+            float xv[DS], ce[RES ? DS : 1], cur[DS];
+            float4 tab[kStage ? kTab4 : 1]; // kStage: the subspace's codewords and ||c||^2
+            float2 lim;
+            int code;
+        };
+        auto read_lds = [](const float *at, float (&v)[DS]) {
+            typedef const __attribute__((address_space(3))) float lds_float;
+            lds_float *src = (lds_float *)at;
+#pragma unroll
+            for (int l = 0; l < DS; ++l) {
+                if (l == 2) asm volatile("" : "+v"(src)); // three words are not read as one (see build.py)
+                v[l] = src[l];
+            }
+        };
+        auto load_codeword = [&](int m, int j, float (&c)[DS]) {
+            if constexpr (kStage) read_lds(tab_lds + (m * KC + j) * (DS + 1), c);
+            else {
+                const float *src = p.codebooks + ((size_t)m * KC + j) * DS;
+#pragma unroll
+                for (int l = 0; l < DS; ++l) c[l] = src[l];
+            }
+        };
+        auto load_step = [&](int m, Step &s) { // all but the codeword in use, which waits for its index
+            if constexpr (kStage) read_lds(my_row + m * DS, s.xv);
+#pragma unroll
+            for (int l = 0; l < DS; ++l) {
+                if constexpr (!kStage) s.xv[l] = xi[m * DS + l];
+                if constexpr (RES) s.ce[l] = active ? ce_row[m * DS + l] : 0.0f;
+            }
+            s.code = my_codes[m];
+            if constexpr (kStage) {
+                const float4 *t = (const float4 *)(tab_lds + m * KC * (DS + 1));
+#pragma unroll
+                for (int e = 0; e < kTab4; ++e) s.tab[e] = t[e];
+                s.lim = lim_lds[m]; // (a scalar load here would make the wave wait for every LDS read in flight)
+            }
+        };
+        auto step = [&](int m, const Step &s, Step &nx) {
+            const int mn = m + 1 < M ? m + 1 : 0;
+            load_step(mn, nx);
+            // q = (p of the other subspaces) + <x - center, x> of this one = P + <codeword in use, x>
+            double t_cur = 0.0;
+            float sx = 0.0f, sr = 0.0f, xrf[RES ? DS : 1];
+#pragma unroll
+            for (int l = 0; l < DS; ++l) {
+                t_cur = fma((double)s.cur[l], (double)s.xv[l], t_cur);
+                sx += fabsf(s.xv[l]);
+                if constexpr (RES) { xrf[l] = (float)((double)s.xv[l] - (double)s.ce[l]); sr += fabsf(xrf[l]); }
+            }
+            if (init) t_cur = 0.0;
+            const double q = P + t_cur;
+            const float Bf = (float)fma(w2, q, RES ? 0.0 : 2.0);
+            const float2 lim = kStage ? s.lim : limits[m];
+            const float T = lim.x * sx;
+            float F = fmaf(T, fmaf(wf, T, fabsf(Bf)), lim.y);
+            if constexpr (RES) F = fmaf(2.0f * lim.x, sr, F);
+            const float lead = fmaf(F, 2.0f * kEps, 2.0e-37f);
+
+            float best = INFINITY, second = INFINITY;
+            int group = 0;
+            const float *tab = tables + (size_t)m * KC * (DS + 1); // wave-uniform: scalar loads and operands
+            constexpr int kGroups = KC / 16;
+#pragma unroll 1
+            for (int g = 0; g < kGroups; ++g) {
+                const float old = best;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    auto c = [&](int l) -> float {
+                        if constexpr (kStage) {
+                            const float4 q = s.tab[(v * (DS + 1) + l) / 4];
+                            const int r = (v * (DS + 1) + l) % 4;
+                            return r == 0 ? q.x : r == 1 ? q.y : r == 2 ? q.z : q.w;
+                        } else {
+                            return tab[(g * 16 + v) * (DS + 1) + l];
+                        }
+                    };
+                    float t = s.xv[0] * c(0);
+#pragma unroll
+                    for (int l = 1; l < DS; ++l) t = fmaf(s.xv[l], c(l), t);
+                    float f = c(DS);
+                    if constexpr (RES) {
+                        float u = xrf[0] * c(0);
+#pragma unroll
+                        for (int l = 1; l < DS; ++l) u = fmaf(xrf[l], c(l), u);
+                        f = fmaf(-2.0f, u, f);
+                    }
+                    f = fmaf(t, fmaf(wf, t, -Bf), f);
+                    f = __uint_as_float((__float_as_uint(f) & 0xfffffff0u) | (uint32_t)v);
+                    second = __builtin_amdgcn_fmed3f(best, second, f);
+                    best = __builtin_amdgcn_fmed3f(-INFINITY, best, f); // the smaller (fminf would first quiet both)
+                }
+                if (kGroups > 1) group = best == old ? group : g;
+            }
+            int pick = group * 16 + (int)(__float_as_uint(best) & 15u);
+            load_codeword(mn, nx.code, nx.cur);
+            const bool open = active && !(second - best > lead);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(open) != 0ull, 0)) {
+                if (open) {
+                    double bestv = INFINITY;
+                    pick = 0;
+#pragma unroll 1
+                    for (int j = 0; j < KC; ++j) {
+                        const float *c = tab + j * (DS + 1);
+                        double pm = 0.0, em = 0.0, xx = 0.0;
+#pragma unroll
+                        for (int l = 0; l < DS; ++l) {
+                            const double r = (double)s.xv[l] - (RES ? (double)s.ce[RES ? l : 0] : 0.0) - (double)c[l];
+                            pm = fma(r, (double)s.xv[l], pm);
+                            em = fma(r, r, em);
+                            xx = fma((double)s.xv[l] - (RES ? (double)s.ce[RES ? l : 0] : 0.0), (double)s.xv[l], xx);
+                        }
+                        const double pp = init ? 0.0 : (q - xx) + pm;
+                        const double v = em + wl * pp * pp;
+                        if (v < bestv) { bestv = v; pick = j; }
+                    }
+                }
+            }
+            const bool other = active && (init || pick != s.code);
+            if (__builtin_amdgcn_ballot_w64(other) != 0ull) {
+                if (other) {
+                    float c[DS];
+                    load_codeword(m, pick, c);
+                    double t_new = 0.0;
+#pragma unroll
+                    for (int l = 0; l < DS; ++l) t_new = fma((double)c[l], (double)s.xv[l], t_new);
+                    my_codes[m] = (uint8_t)pick;
+                    P = q - t_new;
+                    changed = true;
+                }
+            }
+        };
+        Step even, odd;
+        load_step(0, even);
+        load_codeword(0, even.code, even.cur);
+        int m = 0;
+        for (; m + 1 < M; m += 2) {
+            step(m, even, odd);
+            step(m + 1, odd, even);
+        }
+        if (m < M) step(m, even, odd);
+        const bool done = active && (init ? p.passes == 0 : !changed || stage + 1 >= p.passes);
+        stage = init ? 0 : stage + 1;
+        if (done) {
+            uint8_t *out = p.packed + (size_t)id * p.NB;
+            for (int e = 0; e < p.code_stride && (KC == 16 ? e / 2 : e) < p.NB; e += 4) {
+                const uint32_t v = *(const uint32_t *)(my_codes + e);
+                if constexpr (KC == 16) {
+                    out[e / 2] = (uint8_t)((v & 15u) | ((v >> 4) & 0xf0u));
+                    if (e / 2 + 1 < p.NB) out[e / 2 + 1] = (uint8_t)(((v >> 16) & 15u) | ((v >> 20) & 0xf0u));
+                } else {
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+                        if (e + b < p.NB) out[e + b] = (uint8_t)(v >> (8 * b));
+                }
+            }
+            id = -1;
+        }
+    }
+}
+
+// Any other number of dimensions per subspace: a thread per point, all in fp64, the terms of the current codewords kept
+// per subspace.
+constexpr int kMaxM = 256;
 __global__ void __launch_bounds__(128)
 encode_kernel(const float *__restrict__ x, int64_t n, int d, int M, int kc, int bits,
               const float *__restrict__ codebooks, const float *__restrict__ leaf_centers,
@@ -502,11 +827,9 @@ encode_kernel(const float *__restrict__ x, int64_t n, int d, int M, int kc, int 
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const int ds = DS ? DS : d / M;
+    const int ds = d / M;
     const float *xi = x + (size_t)i * d;
     const float *ce = leaf_centers ? leaf_centers + (size_t)leaf_assign[i] * d : nullptr;
-    constexpr int kReg = DS ? DS : 1;
-    double xv_m[kReg], xr_m[kReg]; // DS != 0: x^(m) and x^(m) - center^(m) of the subspace entered last
     uint8_t code[kMaxM];
     double pm_cur[kMaxM], em_cur[kMaxM]; // terms of the current codeword of every subspace
     double pm_after[kMaxM], em_after[kMaxM]; // their sums over the subspaces after m, as of the start of a pass
@@ -516,35 +839,16 @@ encode_kernel(const float *__restrict__ x, int64_t n, int d, int M, int kc, int 
     const double eta = eta_of_norm(d, T, sqrt(nx2), eta_mode, eta_explicit);
     const double w = nx2 > 0.0 ? (eta - 1.0) / nx2 : 0.0;
 
-    // terms of subspace m for codeword j: pm = <r^(m), x^(m)>, em = ||r^(m)||^2 (fused multiply-adds: one
-    // rounding per term instead of two, a third fewer fp64 operations per codeword)
-    auto enter = [&](int m) {
-        if constexpr (DS != 0) {
-#pragma unroll
-            for (int l = 0; l < DS; ++l) {
-                xv_m[l] = (double)xi[m * DS + l];
-                xr_m[l] = xv_m[l] - (ce ? (double)ce[m * DS + l] : 0.0);
-            }
-        }
-    };
+    // terms of subspace m for codeword j: pm = <r^(m), x^(m)>, em = ||r^(m)||^2
     auto terms = [&](int m, int j, double &pm, double &em) {
         const float *c = codebooks + ((size_t)m * kc + j) * ds;
         pm = 0.0;
         em = 0.0;
-        if constexpr (DS != 0) {
-#pragma unroll
-            for (int l = 0; l < DS; ++l) {
-                const double r = xr_m[l] - (double)c[l];
-                pm = fma(r, xv_m[l], pm);
-                em = fma(r, r, em);
-            }
-        } else {
-            for (int l = 0; l < ds; ++l) {
-                const double xv = (double)xi[m * ds + l];
-                const double r = (xv - (ce ? (double)ce[m * ds + l] : 0.0)) - (double)c[l];
-                pm = fma(r, xv, pm);
-                em = fma(r, r, em);
-            }
+        for (int l = 0; l < ds; ++l) {
+            const double xv = (double)xi[m * ds + l];
+            const double r = (xv - (ce ? (double)ce[m * ds + l] : 0.0)) - (double)c[l];
+            pm = fma(r, xv, pm);
+            em = fma(r, r, em);
         }
     };
 
@@ -552,7 +856,6 @@ encode_kernel(const float *__restrict__ x, int64_t n, int d, int M, int kc, int 
     for (int m = 0; m < M; ++m) {
         int best = 0;
         double bestd = INFINITY, bestp = 0.0;
-        enter(m);
         for (int j = 0; j < kc; ++j) {
             double pm, em;
             terms(m, j, pm, em);
@@ -578,7 +881,6 @@ encode_kernel(const float *__restrict__ x, int64_t n, int d, int M, int kc, int 
             const double Pr = before_p + pm_after[m], Er = before_e + em_after[m];
             int best = 0;
             double bestv = INFINITY, bestp = 0.0, beste = 0.0;
-            enter(m);
             for (int j = 0; j < kc; ++j) {
                 double pm, em;
                 terms(m, j, pm, em);
@@ -610,24 +912,81 @@ encode_kernel(const float *__restrict__ x, int64_t n, int d, int M, int kc, int 
     }
 }
 
-int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits,
-                  const float *codebooks, const float *leaf_centers, const int32_t *leaf_assign,
-                  int eta_mode, double T, double eta_explicit, int passes, uint8_t *packed,
-                  hipStream_t st)
+template <int DS, int KC>
+static int launch_encode_one(EncodeParams p, const float *tab, const float2 *lim, hipStream_t st)
+{
+    // waves per workgroup: as many resident per compute unit as the 160 KB of LDS allow, at most 16
+    const size_t shared = KC == 16 ? (size_t)p.M * (KC * (DS + 1) + 2) * 4 : 0;
+    const size_t per_wave = (KC == 16 ? (size_t)64 * p.row_stride * 4 : 0) + (size_t)64 * p.code_stride;
+    int waves = 0, resident = 0;
+    for (int w = 1; w <= 8; ++w) {
+        const size_t need = shared + w * per_wave;
+        if (need > kMaxDynLds) break;
+        const int r = std::min<int>(16, (int)(kMaxDynLds / need) * w);
+        if (r > resident) { resident = r; waves = w; }
+    }
+    if (waves == 0) return 1; // does not fit: the caller takes the plain kernel
+    const int64_t groups = (p.n_slots + 63) / 64;
+    const int64_t total = std::min<int64_t>(groups, (int64_t)256 * resident); // a resident set of waves
+    const dim3 grid((unsigned)((total + waves - 1) / waves));
+    const size_t lds = shared + waves * per_wave;
+    static LdsLimitOnce flat_done, res_done;
+    AVQ_TRY(set_lds_limit((const void *)encode_aniso_kernel<DS, KC, false>, kMaxDynLds, &flat_done));
+    AVQ_TRY(set_lds_limit((const void *)encode_aniso_kernel<DS, KC, true>, kMaxDynLds, &res_done));
+    if (p.leaf_centers) hipLaunchKernelGGL((encode_aniso_kernel<DS, KC, true>), grid, dim3(64 * waves), lds, st, p, tab, lim);
+    else hipLaunchKernelGGL((encode_aniso_kernel<DS, KC, false>), grid, dim3(64 * waves), lds, st, p, tab, lim);
+    AVQ_HIP(hipGetLastError());
+    return AVQ_OK;
+}
+
+int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, const float *codebooks, const float *leaf_centers,
+                  const int32_t *leaf_assign, const int32_t *order, int64_t n_slots, int eta_mode, double T, double eta_explicit,
+                  int passes, uint8_t *packed, DevBuf *ws, hipStream_t st)
 {
     if (M > kMaxM) { set_error("encode: M = %d exceeds %d", M, kMaxM); return AVQ_EINVAL; }
     if (M < 1 || d % M != 0) { set_error("encode: d = %d is not a multiple of M = %d", d, M); return AVQ_EINVAL; }
-    const dim3 grid((unsigned)((n + 127) / 128)), block(128);
-#define AVQ_ENCODE(DS)                                                                                        \
-    hipLaunchKernelGGL(encode_kernel<DS>, grid, block, 0, st, x, n, d, M, kc, bits, codebooks, leaf_centers, \
-                       leaf_assign, eta_mode, T, eta_explicit, passes, packed)
-    switch (d / M) {
-    case 2: AVQ_ENCODE(2); break;
-    case 4: AVQ_ENCODE(4); break;
-    case 8: AVQ_ENCODE(8); break;
-    default: AVQ_ENCODE(0); break;
+    const int ds = d / M;
+    int rc = 1;
+    if (kc == 16 ? ds >= 1 && ds <= 4 : ds == 2 || ds == 4 || ds == 8) {
+        const size_t b_tab = (sizeof(float) * (size_t)M * kc * (ds + 1) + 255) & ~(size_t)255, b_lim = sizeof(float2) * (size_t)kMaxM + 256;
+        const bool weights = eta_mode == AVQ_ETA_EXACT;
+        AVQ_TRY(ws->reserve(b_tab + b_lim + (weights ? sizeof(double) * (size_t)n : 0)));
+        EncodeParams p;
+        p.x = x; p.order = order; p.n_slots = order ? n_slots : n;
+        p.d = d; p.M = M; p.NB = (M * bits + 7) / 8; p.passes = passes;
+        p.codebooks = codebooks;
+        float *tab = ws->as<float>();                                // [M][kc][ds + 1]: codeword, ||c||^2
+        float2 *lim = (float2 *)(ws->as<unsigned char>() + b_tab); // [M]: largest |coordinate|, largest ||c||^2
+        p.leaf_centers = leaf_centers; p.leaf_assign = leaf_assign;
+        p.eta_mode = eta_mode; p.T = T; p.eta_explicit = eta_explicit;
+        p.w_in = weights ? (const double *)(ws->as<unsigned char>() + b_tab + b_lim) : nullptr;
+        p.packed = packed;
+        p.next_window = (uint32_t *)(lim + kMaxM);
+        p.row_stride = d | 1;
+        p.code_stride = 4 * (((M + 3) / 4) | 1);
+        hipLaunchKernelGGL(encode_tables_kernel, dim3((unsigned)M), dim3(64), 0, st, codebooks, kc, ds, tab, lim,
+                           p.next_window);
+        if (weights)
+            hipLaunchKernelGGL(encode_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, n, d, eta_mode, T,
+                               eta_explicit, (double *)p.w_in);
+        if (kc == 16) {
+            switch (ds) {
+            case 1: rc = launch_encode_one<1, 16>(p, tab, lim, st); break;
+            case 2: rc = launch_encode_one<2, 16>(p, tab, lim, st); break;
+            case 3: rc = launch_encode_one<3, 16>(p, tab, lim, st); break;
+            default: rc = launch_encode_one<4, 16>(p, tab, lim, st); break;
+            }
+        } else {
+            switch (ds) {
+            case 2: rc = launch_encode_one<2, 256>(p, tab, lim, st); break;
+            case 4: rc = launch_encode_one<4, 256>(p, tab, lim, st); break;
+            default: rc = launch_encode_one<8, 256>(p, tab, lim, st); break;
+            }
+        }
     }
-#undef AVQ_ENCODE
+    if (rc <= 0) return rc;
+    hipLaunchKernelGGL(encode_kernel, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, st, x, n, d, M, kc, bits, codebooks, leaf_centers,
+                       leaf_assign, eta_mode, T, eta_explicit, passes, packed);
     AVQ_HIP(hipGetLastError());
     return AVQ_OK;
 }

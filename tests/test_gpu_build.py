@@ -106,3 +106,53 @@ def test_points_are_grouped_by_leaf(n, d, M, bits, leaves):
     assign[n // 2] = leaves
     with pytest.raises(avq.AvqError, match="leaf assignment %d of point %d" % (leaves, n // 2)):
         idx.set_database(dev(x), oracle.pack_codes(codes, bits), assign)
+
+
+# every specialised number of dimensions per subspace and one without; waves of 64 points that hold 1, 63, 64, 65 points or
+# take further ones; rows of x that fill LDS, and rows that do not fit it (1,024 dimensions: the plain kernel)
+@pytest.mark.parametrize("n,d,M,bits", [(1, 4, 4, 4), (63, 6, 3, 4), (64, 30, 6, 4), (65, 100, 50, 4), (700, 105, 35, 4),
+                                        (333, 100, 25, 4), (129, 24, 3, 8), (257, 20, 5, 8), (300, 12, 6, 8), (200, 512, 256, 4),
+                                        (70, 1024, 256, 4), (40_000, 8, 4, 4)])
+@pytest.mark.parametrize("law", ["unit", "scales", "huge", "tiny", "eta_exact", "eta_explicit", "lattice", "one_pass", "no_pass", "leaves"])
+def test_codes_are_those_of_fp64_losses(n, d, M, bits, law):
+    if n > 1000 and law not in ("unit", "leaves"):
+        pytest.skip("many points: the common law only")
+    if law == "leaves" and d > 512:
+        pytest.skip("leaf assignment refuses this dimension")
+    rng = np.random.default_rng(n + 31 * d)
+    x = unit_rows(rng, n, d)
+    cb = unit_rows(rng, (1 << bits) * M, d // M).reshape(M, 1 << bits, d // M) * np.float32((M + 0.0) ** -0.5)
+    kw, okw = dict(T=0.2, encode_passes=6), dict(T=0.2, passes=6)
+    if law == "scales":         # norms from 1e-4 to 1e4 of the codewords' scale
+        x *= (10.0 ** rng.uniform(-4, 4, (n, 1))).astype(np.float32)
+        x[0] = 0.0
+    elif law in ("huge", "tiny"):  # single-precision squares run over, or vanish
+        s = np.float32(1e25 if law == "huge" else 1e-25)
+        x, cb = x * s, cb * s
+        kw["T"] = okw["T"] = float(np.float32(0.2) * s)
+    elif law == "eta_exact":
+        if n * d > 4000:
+            pytest.skip("an integral per point on the CPU")
+        kw["eta_mode"], okw["eta_mode"] = avq.ETA_EXACT, 1
+    elif law == "eta_explicit":
+        kw.update(eta_mode=avq.ETA_EXPLICIT, eta_explicit=37.0)
+        okw.update(eta_mode=2, eta_explicit=37.0)
+    elif law == "lattice":      # exact ties between the nearest codewords (later passes: ties that rounding breaks)
+        x, cb = np.round(x * 4).astype(np.float32), np.round(cb * 8).astype(np.float32)
+        kw["encode_passes"] = okw["passes"] = 0
+    elif law == "one_pass":
+        kw["encode_passes"] = okw["passes"] = 1
+    elif law == "no_pass":
+        kw["encode_passes"] = okw["passes"] = 0
+    if law == "leaves":
+        centers = unit_rows(rng, 5, d)
+        assign = oracle.assign_nearest(x, centers)
+        okw.update(leaf_centers=centers, leaf_assign=assign)
+        idx = avq.Index(d, M, bits, n_leaves=5, **kw)
+        idx.set_leaf_centers(centers)
+    else:
+        idx = avq.Index(d, M, bits, **kw)
+    idx.set_codebooks(cb)
+    idx.encode(dev(x))
+    want = oracle.pack_codes(oracle.encode(x, cb, **okw), bits)
+    np.testing.assert_array_equal(idx.get_codes(), want)
