@@ -69,6 +69,7 @@ struct avq_index {
     int tune_sample = 0; // 0 = batches guess the candidate scan's bounds from a sample where possible, 1 = never, 2 = from a sample scanned with lists
     int tune_prefilter_cap = 0; // candidate keys per (query, chunk) of that scan, 0 = built-in
     DevBuf block_max, lists, refined, lut_fail, fail, cand_keys, groups, kept, fail_rows;
+    DevBuf exact_ws; // exact search: operands, norms, block maxima of a launch's queries
     DevBuf train_ws; // training: points by coordinate and the sums of an iteration
     // optional per-stage timing with HIP events recorded on the caller's stream
     bool prof_on = false;
@@ -159,7 +160,7 @@ extern "C" int avq_create(const avq_config *cfg, avq_index **out)
 extern "C" void avq_destroy(avq_index *idx)
 {
     if (!idx) return;
-    DevBuf *all[] = {&idx->codebooks, &idx->centers, &idx->centers_t, &idx->x_own, &idx->codes_logical,
+    DevBuf *all[] = {&idx->exact_ws, &idx->codebooks, &idx->centers, &idx->centers_t, &idx->x_own, &idx->codes_logical,
                      &idx->codes_blocked, &idx->assign, &idx->perm, &idx->leaf_blk, &idx->lut, &idx->lut8,
                      &idx->scale, &idx->bias, &idx->partial, &idx->cand, &idx->leaf_ids, &idx->leaf_ip,
                      &idx->tmp, &idx->block_max, &idx->lists, &idx->thr, &idx->refined, &idx->lut_fail,
@@ -1469,6 +1470,20 @@ extern "C" int avq_brute_force(avq_index *idx, const float *queries, int32_t nq,
     const int chunks = brute_force_chunks(idx->n, nq);
     AVQ_TRY(idx->partial.reserve(sizeof(u64) * (size_t)nq * chunks * 64 * ns));
     AVQ_TRY(idx->cand.reserve(sizeof(u64) * (size_t)nq * 64 * ns));
+    if (exact_supported(idx->n, idx->cfg.d, nq, k)) {
+        const int d = idx->cfg.d, per = exact_queries_per_launch(idx->n, d, nq);
+        AVQ_TRY(idx->exact_ws.reserve(exact_ws_bytes(idx->n, d, per)));
+        for (int q0 = 0; q0 < nq; q0 += per) {
+            const int m = std::min(per, nq - q0);
+            const float *qs = queries + (size_t)q0 * d;
+            const uint32_t *plain = nullptr;
+            AVQ_TRY(launch_exact(idx->x, idx->n, d, qs, m, k, idx->exact_ws.p, ids_out + (size_t)q0 * k,
+                                 scores_out + (size_t)q0 * k, &plain, st));
+            AVQ_TRY(launch_brute_force(idx->x, idx->n, d, qs, m, k, idx->partial.as<u64>(), chunks,
+                                       idx->cand.as<u64>(), ids_out + (size_t)q0 * k, scores_out + (size_t)q0 * k, st, plain));
+        }
+        return AVQ_OK;
+    }
     return launch_brute_force(idx->x, idx->n, idx->cfg.d, queries, nq, k, idx->partial.as<u64>(), chunks,
                               idx->cand.as<u64>(), ids_out, scores_out, st);
 }

@@ -288,11 +288,22 @@ int launch_select_keys(const u64 *keys, int nq, int64_t n, int ns, int R, u64 *o
 // kind 1: integer sum -> fma(acc, scale, bias)).
 int launch_finalize(const u64 *cand, int ns, int nq, int R, int k, int reorder, int key_kind,
                     const float *x, int d, const float *queries, const float *scale,
-                    const float *bias, int32_t *ids_out, float *scores_out, hipStream_t st);
+                    const float *bias, int32_t *ids_out, float *scores_out, hipStream_t st,
+                    const uint32_t *active = nullptr);
+// Every point in fp32. active (may be NULL): device word, 0: nothing to do, else at least nq (exact.hip).
 int launch_brute_force(const float *x, int64_t n, int d, const float *queries, int nq, int k,
                        u64 *partial_ws, int n_chunks, u64 *cand_ws, int32_t *ids_out,
-                       float *scores_out, hipStream_t st);
+                       float *scores_out, hipStream_t st, const uint32_t *active = nullptr);
 int brute_force_chunks(int64_t n, int nq);
+
+// ---- exact.hip -------------------------------------------------------------
+// Exact search that scores in fp32 only the points a bf16 matrix product leaves open; the same results.
+bool exact_supported(int64_t n, int d, int nq, int k);
+int exact_queries_per_launch(int64_t n, int d, int nq);
+size_t exact_ws_bytes(int64_t n, int d, int nq);
+// *plain_out: device word, non-zero where launch_brute_force has to answer instead (norms out of range).
+int launch_exact(const float *x, int64_t n, int d, const float *queries, int nq, int k, void *ws, int32_t *ids_out,
+                 float *scores_out, const uint32_t **plain_out, hipStream_t st);
 
 // ---- refine.hip ------------------------------------------------------------
 // fp32-table search through the 8-bit-table scan (flat index, 4-bit codes). The matrix-core scan

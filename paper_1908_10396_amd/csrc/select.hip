@@ -134,12 +134,13 @@ __global__ void __launch_bounds__(64)
 finalize_kernel(const u64 *__restrict__ cand, int ns, int R, int k, int reorder, int key_kind,
                 const float *__restrict__ x, int d, const float *__restrict__ queries,
                 const float *__restrict__ scale, const float *__restrict__ bias,
-                int32_t *__restrict__ ids_out, float *__restrict__ scores_out)
+                int32_t *__restrict__ ids_out, float *__restrict__ scores_out, const uint32_t *__restrict__ active)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int C = 64 * ns;
     const int lane = threadIdx.x;
     const int q = blockIdx.x;
+    if (active != nullptr && (uint32_t)q >= *active) return;
     const u64 *mine = cand + (size_t)q * C;
     if (!reorder) {
         for (int j = lane; j < k; j += 64) {
@@ -181,11 +182,11 @@ finalize_kernel(const u64 *__restrict__ cand, int ns, int R, int k, int reorder,
 
 int launch_finalize(const u64 *cand, int ns, int nq, int R, int k, int reorder, int key_kind,
                     const float *x, int d, const float *queries, const float *scale,
-                    const float *bias, int32_t *ids_out, float *scores_out, hipStream_t st)
+                    const float *bias, int32_t *ids_out, float *scores_out, hipStream_t st, const uint32_t *active)
 {
     const size_t lds = (size_t)64 * ns * 8 + (size_t)d * 4;
     hipLaunchKernelGGL(finalize_kernel, dim3(nq), dim3(64), lds, st, cand, ns, R, k, reorder,
-                       key_kind, x, d, queries, scale, bias, ids_out, scores_out);
+                       key_kind, x, d, queries, scale, bias, ids_out, scores_out, active);
     AVQ_HIP(hipGetLastError());
     return AVQ_OK;
 }
@@ -198,8 +199,10 @@ int launch_finalize(const u64 *cand, int ns, int nq, int R, int k, int reorder, 
 template <int QB>
 __global__ void __launch_bounds__(256)
 brute_kernel(const float *__restrict__ x, int64_t n, int d, const float *__restrict__ queries,
-             int nq, int ns, int k, int64_t pts_per_chunk, int n_chunks, u64 *__restrict__ partial)
+             int nq, int ns, int k, int64_t pts_per_chunk, int n_chunks, u64 *__restrict__ partial,
+             const uint32_t *__restrict__ active)
 {
+    if (active != nullptr && *active == 0u) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int C = 64 * ns;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
@@ -273,7 +276,7 @@ int brute_force_chunks(int64_t n, int nq)
 
 int launch_brute_force(const float *x, int64_t n, int d, const float *queries, int nq, int k,
                        u64 *partial_ws, int n_chunks, u64 *cand_ws, int32_t *ids_out,
-                       float *scores_out, hipStream_t st)
+                       float *scores_out, hipStream_t st, const uint32_t *active)
 {
     const int ns = (k + 63) / 64;
     const int C = 64 * ns;
@@ -286,20 +289,20 @@ int launch_brute_force(const float *x, int64_t n, int d, const float *queries, i
         AVQ_HIP(hipFuncSetAttribute((const void *)brute_kernel<8>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds));
         hipLaunchKernelGGL(brute_kernel<8>, dim3(n_chunks, (nq + 7) / 8), dim3(waves * 64),
-                           lds_for(8), st, x, n, d, queries, nq, ns, k, ppc, n_chunks, partial_ws);
+                           lds_for(8), st, x, n, d, queries, nq, ns, k, ppc, n_chunks, partial_ws, active);
     } else if (lds_for(1) <= kMaxDynLds) {
         AVQ_HIP(hipFuncSetAttribute((const void *)brute_kernel<1>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds));
         hipLaunchKernelGGL(brute_kernel<1>, dim3(n_chunks, nq), dim3(waves * 64), lds_for(1), st, x,
-                           n, d, queries, nq, ns, k, ppc, n_chunks, partial_ws);
+                           n, d, queries, nq, ns, k, ppc, n_chunks, partial_ws, active);
     } else {
         set_error("brute force: d = %d too large", d);
         return AVQ_EINVAL;
     }
     AVQ_HIP(hipGetLastError());
-    AVQ_TRY(launch_merge_partials(partial_ws, nq, n_chunks, ns, cand_ws, st));
+    AVQ_TRY(launch_merge_partials(partial_ws, nq, n_chunks, ns, cand_ws, st, nullptr, active));
     return launch_finalize(cand_ws, ns, nq, k, k, 0, 0, nullptr, d, queries, nullptr, nullptr,
-                           ids_out, scores_out, st);
+                           ids_out, scores_out, st, active);
 }
 
 } // namespace avq

@@ -1,0 +1,66 @@
+"""Exact search on the GPU against the oracle, at the sizes where the matrix product's tiles and the block selection meet
+their edges, and with values that its operands cannot hold."""
+import numpy as np
+import pytest
+
+import oracle
+from util import unit_rows
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+avq = pytest.importorskip("paper_1908_10396_amd")
+
+
+def exact_index(x, codes=None):
+    n, d = x.shape
+    idx = avq.Index(d, 1, 4)
+    idx.set_codebooks(np.zeros((1, 16, d), np.float32))
+    idx.set_database(torch.from_numpy(x).cuda(), torch.zeros((n, 1), dtype=torch.uint8, device="cuda"))
+    return idx
+
+
+def check(x, q, k):
+    ids, sc = exact_index(x).brute_force(torch.from_numpy(q).cuda(), k)
+    oi, os_ = oracle.brute_force(x, q, k)
+    np.testing.assert_array_equal(ids.cpu().numpy(), oi)
+    np.testing.assert_array_equal(sc.cpu().numpy(), os_)
+
+
+# blocks of 64 and 32 points, workgroups of 512 and 256, query tiles of 32, every number of 16-coordinate steps and
+# odd dimensions (scalar loads), the edge of the rule for small indexes; 257 dimensions take the plain kernel
+@pytest.mark.parametrize("n,d,nq,k", [(1, 2, 1, 1), (256, 32, 31, 1), (2559, 33, 32, 10), (2560, 33, 32, 10), (513, 48, 33, 2),
+                                      (4097, 64, 64, 16), (25_600, 65, 260, 100), (20_011, 100, 7, 64), (5000, 105, 40, 10),
+                                      (2048, 128, 33, 8), (2049, 129, 20, 8), (1000, 192, 3, 1), (1025, 193, 9, 4),
+                                      (70_000, 256, 17, 200), (900, 257, 5, 3)])
+def test_exact_search_matches(n, d, nq, k):
+    rng = np.random.default_rng(n + d)
+    check(unit_rows(rng, n, d), unit_rows(rng, nq, d), k)
+
+
+# ties everywhere (copies of a few rows), norms over many magnitudes, values that vanish in squares, zero rows
+@pytest.mark.parametrize("kind", ["copies", "norms", "tiny", "zero"])
+def test_exact_search_of_unusual_points(kind):
+    rng = np.random.default_rng(11)
+    x, q = unit_rows(rng, 6000, 36), unit_rows(rng, 40, 36)
+    if kind == "copies":
+        x = np.ascontiguousarray(x[rng.integers(0, 7, 6000)])
+    elif kind == "norms":
+        x *= np.exp(rng.uniform(-20, 20, (6000, 1))).astype(np.float32)
+        q *= np.exp(rng.uniform(-20, 20, (40, 1))).astype(np.float32)
+    elif kind == "tiny":
+        x *= np.float32(1e-21)
+    else:
+        x[::2] = 0
+        q[3] = 0
+    check(x, q, 20)
+
+
+# infinities, and norms above what the product takes: every query by the plain kernel
+@pytest.mark.parametrize("value", [np.inf, 3e18])
+def test_exact_search_of_large_values(value):
+    rng = np.random.default_rng(12)
+    x, q = unit_rows(rng, 3000, 20), np.abs(unit_rows(rng, 9, 20))
+    x[1234] = np.abs(x[1234])
+    x[1234, 5] = value
+    check(x, q, 10)
