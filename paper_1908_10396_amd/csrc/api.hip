@@ -1005,6 +1005,20 @@ static int small_ws_from_index(avq_index *idx, int nq, int R, SmallWs *w)
     return AVQ_OK;
 }
 
+// Small flat indexes of 4-bit codes with fp32 tables: one launch answers the query.
+// Measured up to its 64 blocks at every code size, one launch / several (us): 10,000 points, 16 subspaces, R = 100: one
+// query 17 / 38, 250 queries 19 / 71, 1,000 queries 66 / 187; 2,000 points, 50 subspaces, R = 100: 15 / 32; 16,384 points:
+// 16 subspaces 20 / 44, 64 subspaces 36 / 49, 96 subspaces 53 / 53, where its one compute unit has as much to add up as the
+// launches cost. Rows of R x d <= 100,000 floats are also re-scored by that one (500 x 100 at 2,000 points, one query:
+// 25 / 46; 500 x 192: 35 / 53); more are left to the split re-scoring.
+static bool use_search_one(const avq_index *idx, bool fuse_tables, bool tile)
+{
+    if (!fuse_tables || tile || !search_one_supported(idx->n_blocks, idx->NB)) return false;
+    // any tuning of the other kernels' launches asks for those kernels
+    return idx->tune_small_impl == 0 && idx->tune_waves == 0 && idx->tune_target_wgs == 0 && idx->tune_select_split == 0 &&
+           idx->tune_rerank_split == 0 && idx->tune_stream_loads == 0;
+}
+
 // Launches only: no allocation, no synchronisation. timers: per-stage event pairs while profiling is on.
 // tile: the batch form (8-bit codes): the full scan takes the queries sixteen at a time, with 6-bit byte tables.
 static int search_small(avq_index *idx, const float *queries, int nq, int k, int reorder_k, bool u8, bool fuse_tables,
@@ -1051,16 +1065,6 @@ static int search_small(avq_index *idx, const float *queries, int nq, int k, int
         p.bound_shift = 8 - bits_e;
         p.blocks_per_chunk = block_bound_tile_chunk(idx->n_blocks, nq);
     }
-    if (bounds) {
-        StageTimer t(idx, AVQ_STAGE_LUT, st, timers);
-        AVQ_TRY(launch_bound_tables(p, u8, st));
-    }
-    {
-        StageTimer t(idx, AVQ_STAGE_SCAN, st, timers);
-        if (bounds && tile) AVQ_TRY(launch_block_bound_tile(p, st));
-        else if (bounds) AVQ_TRY(launch_block_bound(p, idx->tune_waves, st));
-        else AVQ_TRY(launch_block_max(p, u8, idx->tune_waves > 0 ? idx->tune_waves : 4, st));
-    }
     FinishParams f;
     memset(&f, 0, sizeof(f));
     f.x = idx->x;
@@ -1078,6 +1082,21 @@ static int search_small(avq_index *idx, const float *queries, int nq, int k, int
     f.rerank_rows = small_rerank_rows(idx, nq, R, f.stage_rows, f.reorder != 0);
     f.fin_out = w.fin_out;
     f.fin_n = w.fin_n;
+    if (use_search_one(idx, fuse_tables, tile) && (f.rerank_rows == 0 || (int64_t)R * c.d <= 100000)) {
+        f.rerank_rows = 0;
+        StageTimer t(idx, AVQ_STAGE_SCAN, st, timers);
+        return launch_search_one(p, f, st);
+    }
+    if (bounds) {
+        StageTimer t(idx, AVQ_STAGE_LUT, st, timers);
+        AVQ_TRY(launch_bound_tables(p, u8, st));
+    }
+    {
+        StageTimer t(idx, AVQ_STAGE_SCAN, st, timers);
+        if (bounds && tile) AVQ_TRY(launch_block_bound_tile(p, st));
+        else if (bounds) AVQ_TRY(launch_block_bound(p, idx->tune_waves, st));
+        else AVQ_TRY(launch_block_max(p, u8, idx->tune_waves > 0 ? idx->tune_waves : 4, st));
+    }
     if (bounds) {
         f.block_max = w.block_max;
         f.n_blocks = idx->n_blocks;

@@ -1866,6 +1866,67 @@ __device__ __forceinline__ int rank_by_four(const u64 *keys, int c, u64 mine, in
     return r;
 }
 
+// The last step of a query, by its workgroup: exact scores of the n_fin chosen candidates (where asked for), their
+// ranks, the k best. fin, fin2: [n_fin] keys, stage: f.stage_rows rows of d + 1 floats, all in LDS.
+__device__ __forceinline__ void rescore_and_rank(const FinishParams &f, int q, int n_fin, const u64 *fin, u64 *fin2, const float *qs,
+                                                 float *stage, int key_kind, const float *__restrict__ scale, const float *__restrict__ bias)
+{
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const int k = f.k;
+    const u64 *ranked = fin;
+    if (f.reorder) {
+        // exact re-scoring: the candidates' rows are copied to LDS by the whole workgroup
+        // (eight threads per row, all loads in flight at once), then one thread per candidate
+        // runs the fma chain in index order. Row stride d + 1 keeps the threads on different banks.
+        const int d = f.d, ld = f.d + 1;
+        const bool vec = (d & 3) == 0;
+        for (int r0 = 0; r0 < n_fin; r0 += f.stage_rows) {
+            const int rows = n_fin - r0 < f.stage_rows ? n_fin - r0 : f.stage_rows;
+            __syncthreads();
+            for (int rb = 0; rb < rows; rb += nt / 8) {
+                const int r = rb + (tid >> 3);
+                if (r >= rows) continue;
+                const float *src = f.x + (size_t)key_id(fin[r0 + r]) * d;
+                float *dst = stage + r * ld;
+                if (vec) {
+                    for (int c4 = tid & 7; c4 < d / 4; c4 += 8) {
+                        const float4 v = ((const float4 *)src)[c4];
+                        dst[4 * c4] = v.x; dst[4 * c4 + 1] = v.y; dst[4 * c4 + 2] = v.z; dst[4 * c4 + 3] = v.w;
+                    }
+                } else {
+                    for (int l = tid & 7; l < d; l += 8) dst[l] = src[l];
+                }
+            }
+            __syncthreads();
+            for (int r = tid; r < rows; r += nt) {
+                const float *row = stage + r * ld;
+                float sc = 0.0f;
+#pragma unroll 20
+                for (int l = 0; l < d; ++l) sc = __fmaf_rn(qs[l], row[l], sc);
+                fin2[r0 + r] = make_key(ord_from_f32(sc), key_id(fin[r0 + r]));
+            }
+        }
+        __syncthreads();
+        ranked = fin2;
+    }
+    for (int j0 = 0; j0 < n_fin; j0 += nt / 4) {
+        const int j = j0 + (tid >> 2);
+        const u64 mine = j < n_fin ? ranked[j] : ~0ull;
+        const int rank = rank_by_four(ranked, n_fin, mine, tid & 3);
+        if (j < n_fin && (tid & 3) == 0 && rank < k) {
+            f.ids_out[(size_t)q * k + rank] = key_id(mine);
+            float sc;
+            if (f.reorder || !key_kind) sc = f32_from_ord(key_ord(mine));
+            else sc = __fmaf_rn((float)(int)(key_ord(mine) - 1u), scale[q], bias[q]);
+            f.scores_out[(size_t)q * k + rank] = sc;
+        }
+    }
+    for (int j = n_fin + tid; j < k; j += nt) { // fewer than k candidates exist
+        f.ids_out[(size_t)q * k + j] = -1;
+        f.scores_out[(size_t)q * k + j] = -INFINITY;
+    }
+}
+
 // key_kind 1: the keys carry integer sums of 8-bit table codes (flat index); 0: fp32 scores.
 __global__ void __launch_bounds__(1024)
 small_batch_final_kernel(const FinishParams f, int R, int key_kind, const float *__restrict__ scale,
@@ -1975,65 +2036,76 @@ small_batch_final_kernel(const FinishParams f, int R, int key_kind, const float 
         __syncthreads();
         n_fin = (int)counters[0]; // min(R, n_cand)
     }
-    const int k = f.k;
-    const u64 *ranked = fin;
     if (f.reorder && f.rerank_rows > 0) {
         // the exact re-scoring is spread over several workgroups per query (rerank_split_kernel, next launch)
         for (int i = tid; i < n_fin; i += nt) f.fin_out[(size_t)q * R + i] = fin[i];
         if (tid == 0) { f.fin_n[2 * q] = (uint32_t)n_fin; f.fin_n[2 * q + 1] = 0u; }
         return;
     }
-    if (f.reorder) {
-        // exact re-scoring: the candidates' rows are copied to LDS by the whole workgroup
-        // (eight threads per row, all loads in flight at once), then one thread per candidate
-        // runs the fma chain in index order. Row stride d + 1 keeps the threads on different banks.
-        const int d = f.d, ld = f.d + 1;
-        const bool vec = (d & 3) == 0;
-        for (int r0 = 0; r0 < n_fin; r0 += f.stage_rows) {
-            const int rows = n_fin - r0 < f.stage_rows ? n_fin - r0 : f.stage_rows;
-            __syncthreads();
-            for (int rb = 0; rb < rows; rb += nt / 8) {
-                const int r = rb + (tid >> 3);
-                if (r >= rows) continue;
-                const float *src = f.x + (size_t)key_id(fin[r0 + r]) * d;
-                float *dst = stage + r * ld;
-                if (vec) {
-                    for (int c4 = tid & 7; c4 < d / 4; c4 += 8) {
-                        const float4 v = ((const float4 *)src)[c4];
-                        dst[4 * c4] = v.x; dst[4 * c4 + 1] = v.y; dst[4 * c4 + 2] = v.z; dst[4 * c4 + 3] = v.w;
-                    }
-                } else {
-                    for (int l = tid & 7; l < d; l += 8) dst[l] = src[l];
-                }
+    rescore_and_rank(f, q, n_fin, fin, fin2, qs, stage, key_kind, scale, bias);
+}
+
+// A query on a small flat index of 4-bit codes with fp32 tables, whole: tables, sums of every point, the R best of them,
+// exact scores, ranks, in one workgroup of sixteen waves and one launch. The sums (the additions of the other kernels,
+// in their order) stay in registers, four blocks a wave at most (16 registers), so the selection reads no memory. Such a search is all
+// latency: the five kernels of the block-bound path spend about 7 us each, most of it on launch, first loads and drain.
+// 10,000 x 32 points, 16 subspaces, R = 100, k = 10: 37.5 -> 17.1 us a query (15 us at 2,000 points: the least that launch,
+// tables, three passes of the selection, the rows and the two rankings take one after another).
+constexpr int kOneBlocks = 4; // blocks a wave keeps the sums of
+
+template <int NBT>
+__global__ void __launch_bounds__(1024)
+search_one_kernel(const ScanParams p, const FinishParams f)
+{
+    // LDS: the tables first; from the end of the scan on, as the final kernel lays it out
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int NB = NBT ? NBT : p.NB;
+    const int q = blockIdx.x, R = p.R;
+    u64 *fin = (u64 *)smem;                       // [R] candidates
+    u64 *fin2 = fin + R;                          // [R] re-scored
+    uint32_t *counters = (uint32_t *)(fin2 + R);  // [4]
+    float *qs = (float *)(counters + 4);          // [d]
+    unsigned char *region = smem + ((((size_t)R * 16 + 16 + (size_t)f.d * 4) + 15) & ~(size_t)15);
+
+    BlockRegs<NBT> regs, nxt;
+    if (wave < p.n_blocks) load_block<NBT>(regs, p.codes, wave, lane); // in flight while the tables are filled
+    const float q_mine = tid < f.d ? f.queries[(size_t)q * f.d + tid] : 0.0f;
+    nibble_tables_fill<false>(smem, p, q, NB);
+    __syncthreads();
+    uint32_t ord[kOneBlocks][4];
+#pragma unroll
+    for (int j = 0; j < kOneBlocks; ++j) {
+        const int blk = wave + 16 * j;
+        if (blk >= p.n_blocks) continue;
+        const bool more = j + 1 < kOneBlocks && blk + 16 < p.n_blocks;
+        if (more) load_block<NBT>(nxt, p.codes, blk + 16, lane);
+        float accf[4];
+        uint32_t acci[4];
+        nibble_accumulate<false, NBT>(smem, regs, p.codes + (size_t)blk * 256 * NB, NB, lane, accf, acci);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ord[j][i] = ord_from_f32(accf[i]);
+        if (more) regs = nxt;
+    }
+    __syncthreads(); // the tables are done with
+    if (tid < f.d) qs[tid] = q_mine;
+    for (int l = tid + 1024; l < f.d; l += 1024) qs[l] = f.queries[(size_t)q * f.d + l];
+    if (tid == 0) counters[0] = 0u;
+    auto for_each_key = [&](auto &&fn) {
+#pragma unroll
+        for (int j = 0; j < kOneBlocks; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int64_t slot = (int64_t)(wave + 16 * j) * 256 + 4 * lane + i;
+                if (slot < p.n_valid) fn(make_key(ord[j][i], (int32_t)slot));
             }
-            __syncthreads();
-            for (int r = tid; r < rows; r += nt) {
-                const float *row = stage + r * ld;
-                float sc = 0.0f;
-#pragma unroll 20
-                for (int l = 0; l < d; ++l) sc = __fmaf_rn(qs[l], row[l], sc);
-                fin2[r0 + r] = make_key(ord_from_f32(sc), key_id(fin[r0 + r]));
-            }
-        }
-        __syncthreads();
-        ranked = fin2;
-    }
-    for (int j0 = 0; j0 < n_fin; j0 += nt / 4) {
-        const int j = j0 + (tid >> 2);
-        const u64 mine = j < n_fin ? ranked[j] : ~0ull;
-        const int rank = rank_by_four(ranked, n_fin, mine, tid & 3);
-        if (j < n_fin && (tid & 3) == 0 && rank < k) {
-            f.ids_out[(size_t)q * k + rank] = key_id(mine);
-            float sc;
-            if (f.reorder || !key_kind) sc = f32_from_ord(key_ord(mine));
-            else sc = __fmaf_rn((float)(int)(key_ord(mine) - 1u), scale[q], bias[q]);
-            f.scores_out[(size_t)q * k + rank] = sc;
-        }
-    }
-    for (int j = n_fin + tid; j < k; j += nt) { // fewer than k candidates exist
-        f.ids_out[(size_t)q * k + j] = -1;
-        f.scores_out[(size_t)q * k + j] = -INFINITY;
-    }
+    };
+    const u64 t = wg_select_threshold_of(for_each_key, R, (WgSelectScratch *)region); // barriers inside
+    for_each_key([&](u64 key) {
+        if (key >= t) fin[atomicAdd(&counters[0], 1u)] = key; // min(R, n) of them
+    });
+    __syncthreads();
+    rescore_and_rank(f, q, (int)counters[0], fin, fin2, qs, (float *)region, 0, nullptr, nullptr);
 }
 
 // The exact re-scoring of a query's R candidates over several workgroups, for a few queries with so many or so
@@ -2613,6 +2685,38 @@ int launch_small_final(const ScanParams &p, const FinishParams &f, bool u8, hipS
     }
     AVQ_HIP(hipGetLastError());
     return AVQ_OK;
+}
+
+template <int NBT>
+static int launch_search_one_nb(const ScanParams &p, const FinishParams &f, size_t lds, hipStream_t st)
+{
+    static LdsLimitOnce attr;
+    AVQ_TRY(set_max_lds(search_one_kernel<NBT>, &attr));
+    hipLaunchKernelGGL(search_one_kernel<NBT>, dim3(p.B), dim3(1024), lds, st, p, f);
+    AVQ_HIP(hipGetLastError());
+    return AVQ_OK;
+}
+
+bool search_one_supported(int64_t n_blocks, int NB)
+{
+    return n_blocks <= 16 * kOneBlocks && (size_t)NB * 128 <= sizeof(WgSelectScratch);
+}
+
+int launch_search_one(const ScanParams &p, const FinishParams &f, hipStream_t st)
+{
+    if (!search_one_supported(p.n_blocks, p.NB) || !p.fuse_queries || p.bits != 4 || f.rerank_rows > 0) {
+        set_error("one-launch search: bad arguments");
+        return AVQ_EINVAL;
+    }
+    const size_t stage = (size_t)f.stage_rows * (f.d + 1) * 4;
+    const size_t lds = small_final_fixed_bytes(p.R, f.d) + std::max(stage, sizeof(WgSelectScratch)) + 16;
+    switch (p.NB) {
+    case 8: return launch_search_one_nb<8>(p, f, lds, st);
+    case 13: return launch_search_one_nb<13>(p, f, lds, st);
+    case 25: return launch_search_one_nb<25>(p, f, lds, st);
+    case 32: return launch_search_one_nb<32>(p, f, lds, st);
+    default: return launch_search_one_nb<0>(p, f, lds, st);
+    }
 }
 
 int launch_block_max(const ScanParams &p, bool u8, int waves, hipStream_t st)

@@ -32,36 +32,14 @@ struct WgSelectScratch {
 };
 
 // All threads of the workgroup (a multiple of 64, at most 1024) must call this.
-// Keys equal to 0 are empty slots and never selected. Returns the R-th largest
-// non-empty key, or 1 when there are fewer than R of them (so "key >= result"
-// selects min(R, count) keys; keys are distinct). The keys are read from global
-// memory once when N <= kSelRegs * blockDim.x, else once per pass. R <= 2^21, N < 2^32.
-__device__ inline u64 wg_select_threshold(const u64 *__restrict__ keys, int64_t N, int R, WgSelectScratch *s)
+// for_each_key(fn) calls fn once for each of the thread's keys, the same ones every time; no key is 0.
+// Returns the R-th largest key of the workgroup, or 1 when there are fewer than R of them (so "key >= result"
+// selects min(R, count) keys; keys are distinct). R <= 2^21, fewer than 2^32 keys.
+template <class ForEachKey>
+__device__ __forceinline__ u64 wg_select_threshold_of(ForEachKey for_each_key, int R, WgSelectScratch *s)
 {
     const int tid = threadIdx.x, nt = blockDim.x;
     const int lane = tid & 63, wave = tid >> 6, n_waves = nt >> 6;
-    const bool cached = N <= (int64_t)kSelRegs * nt;
-    u64 kreg[kSelRegs];
-    if (cached) {
-#pragma unroll
-        for (int r = 0; r < kSelRegs; ++r) {
-            const int64_t i = (int64_t)r * nt + tid;
-            kreg[r] = i < N ? keys[i] : 0ull;
-        }
-    }
-    // visits every non-empty key once
-    auto for_each_key = [&](auto &&fn) {
-        if (cached) {
-#pragma unroll
-            for (int r = 0; r < kSelRegs; ++r)
-                if (kreg[r]) fn(kreg[r]);
-        } else {
-            for (int64_t i = tid; i < N; i += nt) {
-                const u64 kkey = keys[i];
-                if (kkey) fn(kkey);
-            }
-        }
-    };
 
     // pass 0: range and population
     u64 mx = 0ull, mn = ~0ull;
@@ -153,6 +131,36 @@ __device__ inline u64 wg_select_threshold(const u64 *__restrict__ keys, int64_t 
         lo = nlo;
         hi = nhi;
     }
+}
+
+// The same over keys in global memory, 0 marking empty slots; they are read once when N <= kSelRegs * blockDim.x,
+// else once per pass.
+__device__ inline u64 wg_select_threshold(const u64 *__restrict__ keys, int64_t N, int R, WgSelectScratch *s)
+{
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const bool cached = N <= (int64_t)kSelRegs * nt;
+    u64 kreg[kSelRegs];
+    if (cached) {
+#pragma unroll
+        for (int r = 0; r < kSelRegs; ++r) {
+            const int64_t i = (int64_t)r * nt + tid;
+            kreg[r] = i < N ? keys[i] : 0ull;
+        }
+    }
+    // visits every non-empty key once
+    auto for_each_key = [&](auto &&fn) {
+        if (cached) {
+#pragma unroll
+            for (int r = 0; r < kSelRegs; ++r)
+                if (kreg[r]) fn(kreg[r]);
+        } else {
+            for (int64_t i = tid; i < N; i += nt) {
+                const u64 kkey = keys[i];
+                if (kkey) fn(kkey);
+            }
+        }
+    };
+    return wg_select_threshold_of(for_each_key, R, s);
 }
 
 } // namespace avq
