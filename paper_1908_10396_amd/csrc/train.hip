@@ -816,9 +816,14 @@ encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, cons
     }
 }
 
-// Any other number of dimensions per subspace: a thread per point, all in fp64, the terms of the current codewords kept
-// per subspace.
+// Every other shape (16 codewords of 8 dimensions; rows of which LDS does not hold 64; other numbers of dimensions per
+// subspace): a thread per point, all in fp64, the terms of the current codewords kept per subspace. DS = dimensions per
+// subspace known at compile time (0: any): the point's sub-vector then stays in registers while its codewords (wave-
+// uniform, read through the scalar cache) pass by, instead of being read again for every codeword from a row that no
+// neighbouring lane shares. 200,000 points, 4-bit codes, DS known against any: 128 = 16 x 8 dimensions 0.72 against 5.98 ms a
+// call, 512 = 128 x 4 6.1 against 35.7, 512 = 256 x 2 21.0 against 77.8.
 constexpr int kMaxM = 256;
+template <int DS>
 __global__ void __launch_bounds__(128)
 encode_kernel(const float *__restrict__ x, int64_t n, int d, int M, int kc, int bits,
               const float *__restrict__ codebooks, const float *__restrict__ leaf_centers,
@@ -827,9 +832,11 @@ encode_kernel(const float *__restrict__ x, int64_t n, int d, int M, int kc, int 
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const int ds = d / M;
+    const int ds = DS ? DS : d / M;
     const float *xi = x + (size_t)i * d;
     const float *ce = leaf_centers ? leaf_centers + (size_t)leaf_assign[i] * d : nullptr;
+    constexpr int kReg = DS ? DS : 1;
+    double xv_m[kReg], xr_m[kReg]; // DS != 0: x^(m) and x^(m) - center^(m) of the subspace entered last
     uint8_t code[kMaxM];
     double pm_cur[kMaxM], em_cur[kMaxM]; // terms of the current codeword of every subspace
     double pm_after[kMaxM], em_after[kMaxM]; // their sums over the subspaces after m, as of the start of a pass
@@ -839,16 +846,34 @@ encode_kernel(const float *__restrict__ x, int64_t n, int d, int M, int kc, int 
     const double eta = eta_of_norm(d, T, sqrt(nx2), eta_mode, eta_explicit);
     const double w = nx2 > 0.0 ? (eta - 1.0) / nx2 : 0.0;
 
+    auto enter = [&](int m) {
+        if constexpr (DS != 0) {
+#pragma unroll
+            for (int l = 0; l < DS; ++l) {
+                xv_m[l] = (double)xi[m * DS + l];
+                xr_m[l] = xv_m[l] - (ce ? (double)ce[m * DS + l] : 0.0);
+            }
+        }
+    };
     // terms of subspace m for codeword j: pm = <r^(m), x^(m)>, em = ||r^(m)||^2
     auto terms = [&](int m, int j, double &pm, double &em) {
         const float *c = codebooks + ((size_t)m * kc + j) * ds;
         pm = 0.0;
         em = 0.0;
-        for (int l = 0; l < ds; ++l) {
-            const double xv = (double)xi[m * ds + l];
-            const double r = (xv - (ce ? (double)ce[m * ds + l] : 0.0)) - (double)c[l];
-            pm = fma(r, xv, pm);
-            em = fma(r, r, em);
+        if constexpr (DS != 0) {
+#pragma unroll
+            for (int l = 0; l < DS; ++l) {
+                const double r = xr_m[l] - (double)c[l];
+                pm = fma(r, xv_m[l], pm);
+                em = fma(r, r, em);
+            }
+        } else {
+            for (int l = 0; l < ds; ++l) {
+                const double xv = (double)xi[m * ds + l];
+                const double r = (xv - (ce ? (double)ce[m * ds + l] : 0.0)) - (double)c[l];
+                pm = fma(r, xv, pm);
+                em = fma(r, r, em);
+            }
         }
     };
 
@@ -856,6 +881,7 @@ encode_kernel(const float *__restrict__ x, int64_t n, int d, int M, int kc, int 
     for (int m = 0; m < M; ++m) {
         int best = 0;
         double bestd = INFINITY, bestp = 0.0;
+        enter(m);
         for (int j = 0; j < kc; ++j) {
             double pm, em;
             terms(m, j, pm, em);
@@ -881,6 +907,7 @@ encode_kernel(const float *__restrict__ x, int64_t n, int d, int M, int kc, int 
             const double Pr = before_p + pm_after[m], Er = before_e + em_after[m];
             int best = 0;
             double bestv = INFINITY, bestp = 0.0, beste = 0.0;
+            enter(m);
             for (int j = 0; j < kc; ++j) {
                 double pm, em;
                 terms(m, j, pm, em);
@@ -985,8 +1012,16 @@ int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, con
         }
     }
     if (rc <= 0) return rc;
-    hipLaunchKernelGGL(encode_kernel, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, st, x, n, d, M, kc, bits, codebooks, leaf_centers,
-                       leaf_assign, eta_mode, T, eta_explicit, passes, packed);
+#define AVQ_ENCODE(DS)                                                                                                              \
+    hipLaunchKernelGGL(encode_kernel<DS>, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, st, x, n, d, M, kc, bits, codebooks,      \
+                       leaf_centers, leaf_assign, eta_mode, T, eta_explicit, passes, packed)
+    switch (ds) {
+    case 2: AVQ_ENCODE(2); break;
+    case 4: AVQ_ENCODE(4); break;
+    case 8: AVQ_ENCODE(8); break;
+    default: AVQ_ENCODE(0); break;
+    }
+#undef AVQ_ENCODE
     AVQ_HIP(hipGetLastError());
     return AVQ_OK;
 }

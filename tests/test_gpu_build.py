@@ -1,5 +1,7 @@
 """Index building on the GPU (dictionaries, leaf centers, encoding, layout) against the oracle, at the sizes where the
 kernels' tiles and variants meet their edges."""
+import time
+
 import numpy as np
 import pytest
 
@@ -156,3 +158,50 @@ def test_codes_are_those_of_fp64_losses(n, d, M, bits, law):
     idx.encode(dev(x))
     want = oracle.pack_codes(oracle.encode(x, cb, **okw), bits)
     np.testing.assert_array_equal(idx.get_codes(), want)
+
+
+def random_dictionaries(rng, M, kc, ds):
+    return (unit_rows(rng, kc * M, ds).reshape(M, kc, ds) * np.float32(M ** -0.5)).astype(np.float32)
+
+
+# shapes that the search in fp32 does not take: 16 codewords of 8 dimensions, rows of which LDS does not hold 64 (2 and 4
+# dimensions per subspace); workgroups of 128 points
+@pytest.mark.parametrize("n,d,M", [(127, 8, 1), (129, 64, 8), (300, 128, 16), (130, 448, 224), (128, 512, 128)])
+@pytest.mark.parametrize("leaves", [0, 5])
+def test_codes_of_shapes_without_fp32_search(n, d, M, leaves):
+    rng = np.random.default_rng(n + d)
+    x, cb = unit_rows(rng, n, d), random_dictionaries(rng, M, 16, d // M)
+    idx = avq.Index(d, M, 4, T=0.2, encode_passes=6, n_leaves=leaves)
+    okw = {}
+    if leaves:
+        okw["leaf_centers"] = unit_rows(rng, leaves, d)
+        okw["leaf_assign"] = oracle.assign_nearest(x, okw["leaf_centers"])
+        idx.set_leaf_centers(okw["leaf_centers"])
+    idx.set_codebooks(cb)
+    idx.encode(dev(x))
+    np.testing.assert_array_equal(idx.get_codes(), oracle.pack_codes(oracle.encode(x, cb, T=0.2, passes=6, **okw), 4))
+
+
+def encode_seconds(n, d, M, bits=4, codewords=None):
+    """The fastest of five calls."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + M)
+    x = torch.nn.functional.normalize(torch.randn((n, d), generator=gen, device="cuda"))
+    cb = x[: 1 << bits].reshape(1 << bits, M, d // M).transpose(0, 1).contiguous()
+    if codewords is not None:
+        cb = codewords(cb).contiguous()
+    idx = avq.Index(d, M, bits, T=0.2)
+    idx.set_codebooks(cb)
+    best = float("inf")
+    for _ in range(6):
+        t = time.perf_counter()
+        idx.encode(x)
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+# A shape without the fp32 search against one with it: 1.4, 4.0 and 3.6 times as long; with nothing known about the
+# dimensions per subspace at compile time 11.9, 23.5 and 13.3 times.
+@pytest.mark.parametrize("shape,other,most", [((128, 16), (128, 32), 4), ((512, 128), (256, 64), 10), ((512, 256), (256, 128), 7)])
+def test_encode_time_of_shapes_without_fp32_search(shape, other, most):
+    assert encode_seconds(200_000, *shape) < most * encode_seconds(200_000, *other)
