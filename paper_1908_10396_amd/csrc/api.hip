@@ -1006,14 +1006,22 @@ static int small_ws_from_index(avq_index *idx, int nq, int R, SmallWs *w)
 }
 
 // Small flat indexes of 4-bit codes with fp32 tables: one launch answers the query.
-// Measured up to its 64 blocks at every code size, one launch / several (us): 10,000 points, 16 subspaces, R = 100: one
-// query 17 / 38, 250 queries 19 / 71, 1,000 queries 66 / 187; 2,000 points, 50 subspaces, R = 100: 15 / 32; 16,384 points:
-// 16 subspaces 20 / 44, 64 subspaces 36 / 49, 96 subspaces 53 / 53, where its one compute unit has as much to add up as the
-// launches cost. Rows of R x d <= 100,000 floats are also re-scored by that one (500 x 100 at 2,000 points, one query:
-// 25 / 46; 500 x 192: 35 / 53); more are left to the split re-scoring.
-static bool use_search_one(const avq_index *idx, bool fuse_tables, bool tile)
+// Its one compute unit adds up every point, so it grows with the blocks and their code bytes (and tables: n_blocks x
+// (NB + 18) fits the times); the several launches cost about 40 us, and 55 to 65 once R reaches the number of blocks, whose
+// points they then all score exactly. One launch / several (us a call), one query: 10,000 points, 16 subspaces, R = 100:
+// 35 / 56, R = 10: 32 / 38; 16,384 points, R = 10: 16 subspaces 35 / 38, 50 subspaces 45 / 41, 64 50 / 43, 96 68 / 47 and
+// R = 100: 39 / 62, 50 / 66, 53 / 67, 72 / 72; 12,288 points, 50 subspaces (the line, 48 x 43 = 2,064): 41 / 41; code sizes
+// without kernels of their own cross earlier (8,192 x 72 subspaces, 32 x 54 = 1,728: 44 / 45). From sixteen queries on the
+// several launches rise sooner (32 queries, 14,000 x 50 subspaces, R = 50: 45 / 55), from 64 on they never won (300
+// queries, 16,384 x 50 subspaces, R = 10: 76 / 86).
+// Rows of R x d <= 100,000 floats are also re-scored by that one (500 x 100 at 2,000 points, one query: 25 / 46; 500 x 192:
+// 35 / 53); more are left to the split re-scoring.
+static bool use_search_one(const avq_index *idx, int nq, int R, bool fuse_tables, bool tile)
 {
     if (!fuse_tables || tile || !search_one_supported(idx->n_blocks, idx->NB)) return false;
+    const int64_t work = idx->n_blocks * (idx->NB + 18);
+    const bool own = idx->NB == 8 || idx->NB == 13 || idx->NB == 25 || idx->NB == 32;
+    if (nq < 64 && R <= idx->n_blocks && work > (own ? 2064 : 1750) && !(nq >= 16 && 2 * R > idx->n_blocks && work <= 2800)) return false;
     // any tuning of the other kernels' launches asks for those kernels
     return idx->tune_small_impl == 0 && idx->tune_waves == 0 && idx->tune_target_wgs == 0 && idx->tune_select_split == 0 &&
            idx->tune_rerank_split == 0 && idx->tune_stream_loads == 0;
@@ -1082,7 +1090,7 @@ static int search_small(avq_index *idx, const float *queries, int nq, int k, int
     f.rerank_rows = small_rerank_rows(idx, nq, R, f.stage_rows, f.reorder != 0);
     f.fin_out = w.fin_out;
     f.fin_n = w.fin_n;
-    if (use_search_one(idx, fuse_tables, tile) && (f.rerank_rows == 0 || (int64_t)R * c.d <= 100000)) {
+    if (use_search_one(idx, nq, R, fuse_tables, tile) && (f.rerank_rows == 0 || (int64_t)R * c.d <= 100000)) {
         f.rerank_rows = 0;
         StageTimer t(idx, AVQ_STAGE_SCAN, st, timers);
         return launch_search_one(p, f, st);

@@ -57,3 +57,26 @@ def test_search_one_equal_sums(distinct):
     codes = rows[rng.integers(0, distinct, 5000)]
     check(x, cb, codes, q, 10, 0)
     check(x, cb, codes, q, 10, 100)
+
+
+# Which searches the one launch answers: all that score every block anyway (as many candidates as blocks), else up to a
+# number of code bytes that its one compute unit adds up as fast as the several launches do. The selection is a launch of its own on
+# the path over several, so its count tells the two apart.
+@pytest.mark.parametrize("n,M,nq,k,R,one", [(16_384, 16, 1, 10, 0, True), (12_288, 50, 1, 10, 0, True), (12_545, 50, 1, 10, 0, False),
+                                            (16_384, 64, 1, 10, 0, False), (16_384, 64, 1, 64, 0, False), (16_384, 64, 1, 65, 0, True),
+                                            (16_384, 64, 1, 10, 100, True), (8192, 72, 1, 10, 0, True), (8193, 72, 2, 10, 10, False),
+                                            (14_000, 50, 15, 30, 0, False), (14_000, 50, 16, 30, 0, True), (16_384, 64, 64, 10, 0, True)])
+def test_rule_of_search_one(n, M, nq, k, R, one):
+    rng = np.random.default_rng(n + M)
+    x, q = unit_rows(rng, n, 2 * M), unit_rows(rng, nq, 2 * M)
+    cb = (rng.standard_normal((M, 16, 2)) * 0.2).astype(np.float32)
+    codes = rng.integers(0, 16, (n, M)).astype(np.uint8)
+    idx = avq.Index(2 * M, M, 4)
+    idx.set_codebooks(cb)
+    idx.set_database(torch.from_numpy(x).cuda(), torch.from_numpy(pack(codes)).cuda())
+    idx.profile_enable()
+    ids, sc = idx.search(torch.from_numpy(q).cuda(), k, R, avq.LUT_F32)
+    assert (idx.profile_read()["merge"][1] == 0) == one
+    oi, os_ = oracle.search(x, cb, codes, 4, q, k, R, avq.LUT_F32)
+    np.testing.assert_array_equal(ids.cpu().numpy(), oi)
+    np.testing.assert_array_equal(sc.cpu().numpy(), os_)
