@@ -1503,11 +1503,11 @@ extern "C" int avq_brute_force(avq_index *idx, const float *queries, int32_t nq,
         for (int q0 = 0; q0 < nq; q0 += per) {
             const int m = std::min(per, nq - q0);
             const float *qs = queries + (size_t)q0 * d;
-            const uint32_t *plain = nullptr;
+            const uint32_t *need = nullptr;
             AVQ_TRY(launch_exact(idx->x, idx->n, d, qs, m, k, idx->exact_ws.p, ids_out + (size_t)q0 * k,
-                                 scores_out + (size_t)q0 * k, &plain, st));
+                                 scores_out + (size_t)q0 * k, &need, st));
             AVQ_TRY(launch_brute_force(idx->x, idx->n, d, qs, m, k, idx->partial.as<u64>(), chunks,
-                                       idx->cand.as<u64>(), ids_out + (size_t)q0 * k, scores_out + (size_t)q0 * k, st, plain));
+                                       idx->cand.as<u64>(), ids_out + (size_t)q0 * k, scores_out + (size_t)q0 * k, st, need));
         }
         return AVQ_OK;
     }

@@ -282,9 +282,10 @@ int launch_small_final(const ScanParams &p, const FinishParams &f, bool u8, hipS
 // row_of / active (both NULL, or both set): query q's list goes to row row_of[q] of cand, only
 // queries below *active are merged, and the lists are those of a scan with active_queries set
 // (tile_queries per tile, at most n_chunks chunks; tile_queries 0: exactly n_chunks chunks).
+// need (or NULL, here and below): device words; query q is done only if need[0] or need[1 + q] is set (exact.hip).
 int launch_merge_partials(const u64 *partial, int nq, int n_chunks, int ns, u64 *cand,
                           hipStream_t st, const int32_t *row_of = nullptr, const uint32_t *active = nullptr,
-                          int tile_queries = 0);
+                          int tile_queries = 0, const uint32_t *need = nullptr);
 // The R largest of n unsorted keys per query: out[q][64*ns] sorted descending.
 int launch_select_keys(const u64 *keys, int nq, int64_t n, int ns, int R, u64 *out, hipStream_t st);
 // Final stage. reorder != 0: exact <q, x_id> for the first R candidates, then top-k.
@@ -293,11 +294,11 @@ int launch_select_keys(const u64 *keys, int nq, int64_t n, int ns, int R, u64 *o
 int launch_finalize(const u64 *cand, int ns, int nq, int R, int k, int reorder, int key_kind,
                     const float *x, int d, const float *queries, const float *scale,
                     const float *bias, int32_t *ids_out, float *scores_out, hipStream_t st,
-                    const uint32_t *active = nullptr);
-// Every point in fp32. active (may be NULL): device word, 0: nothing to do, else at least nq (exact.hip).
+                    const uint32_t *need = nullptr);
+// Every point in fp32.
 int launch_brute_force(const float *x, int64_t n, int d, const float *queries, int nq, int k,
                        u64 *partial_ws, int n_chunks, u64 *cand_ws, int32_t *ids_out,
-                       float *scores_out, hipStream_t st, const uint32_t *active = nullptr);
+                       float *scores_out, hipStream_t st, const uint32_t *need = nullptr);
 int brute_force_chunks(int64_t n, int nq);
 
 // ---- exact.hip -------------------------------------------------------------
@@ -305,9 +306,9 @@ int brute_force_chunks(int64_t n, int nq);
 bool exact_supported(int64_t n, int d, int nq, int k);
 int exact_queries_per_launch(int64_t n, int d, int nq);
 size_t exact_ws_bytes(int64_t n, int d, int nq);
-// *plain_out: device word, non-zero where launch_brute_force has to answer instead (norms out of range).
+// *need_out: which queries launch_brute_force has to answer instead (its need).
 int launch_exact(const float *x, int64_t n, int d, const float *queries, int nq, int k, void *ws, int32_t *ids_out,
-                 float *scores_out, const uint32_t **plain_out, hipStream_t st);
+                 float *scores_out, const uint32_t **need_out, hipStream_t st);
 
 // ---- refine.hip ------------------------------------------------------------
 // fp32-table search through the 8-bit-table scan (flat index, 4-bit codes). The matrix-core scan

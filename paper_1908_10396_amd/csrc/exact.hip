@@ -7,10 +7,14 @@
 // With theta the k-th largest of the a - E, k blocks hold a point at or above theta each, so no point of a block with
 // a + E < theta can be among the k best, ties included; the other blocks (about k of them) are scored in fp32.
 //
+// Where the product decides little (copies of a few rows, rows that differ by less than the bf16 rounding of what they
+// have in common, a query of zeros) a query's list of blocks is long; beyond exact_max_listed the plain kernel takes that
+// query, as it does one whose norm is not finite or above 1e18. need[0] != 0: every query of the launch (a point with such
+// a norm), need[1 + q]: query q.
+//
 // 1,183,514 x 100 points, 1,000 queries, k = 10: every point in fp32 took 20.8 ms (one 4-byte load and eight fmas a
 // step, bound by the issue of the loads); this way 0.65 ms (product 0.45, which reads x once; selection and fp32 scores
-// 0.22). bf16 rather than f16, whose range needs a scale first. Points or queries with
-// a norm that is not finite or above 1e18 go to the plain kernel.
+// 0.22). bf16 rather than f16, whose range needs a scale first.
 #include <algorithm>
 #include "avq_internal.h"
 #include "wave_topk.h"
@@ -21,7 +25,6 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int kExactGroup = 8 * 64;   // points of a workgroup: a wave holds the operands of 64
-constexpr uint32_t kExactPlain = 0x7fffffffu; // every query goes to the plain kernel
 constexpr float kExactMaxNorm = 1e18f; // products and sums of coordinates stay finite
 
 // Norms from fp32 squares: what they lose to underflow is below 1e-18 a coordinate.
@@ -37,12 +40,13 @@ __device__ __forceinline__ float exact_bound(float qn, float qe, float xn, float
 }
 
 // One workgroup per tile of 32 queries: operand order [step][lane][8], lane (row lane % 32, half lane / 32) holding
-// coordinates 16 step + 8 half .. + 7; padding rows are zero. qnorm[q] = (norm, norm of the conversion error).
+// coordinates 16 step + 8 half .. + 7; padding rows are zero. qnorm[q] = (norm, norm of the conversion error). Sets need.
 __global__ void __launch_bounds__(256)
 exact_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, v8bf *__restrict__ packed, float2 *__restrict__ qnorm,
-                  uint32_t *__restrict__ plain)
+                  uint32_t *__restrict__ need)
 {
     const int tid = threadIdx.x, t = blockIdx.x;
+    if (t == 0 && tid == 0) need[0] = 0u;
     const int r = tid >> 3, g = tid & 7, q = t * 32 + r;
     float n2 = 0.0f, e2 = 0.0f;
     if (q < nq)
@@ -55,7 +59,7 @@ exact_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, v
     if (g == 0 && q < nq) {
         const float qn = exact_norm(n2, d);
         qnorm[q] = make_float2(qn, exact_norm(e2, d));
-        if (!(qn < kExactMaxNorm)) atomicOr(plain, kExactPlain);
+        need[1 + q] = qn < kExactMaxNorm ? 0u : 1u;
     }
     for (int f = tid; f < steps * 64; f += 256) {
         const int lane = f & 63, s = f >> 6, qq = t * 32 + (lane & 31);
@@ -75,7 +79,7 @@ exact_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, v
 template <int NS, int CT>
 __global__ void __launch_bounds__(512, 2)
 exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *__restrict__ packed, int n_tiles, int nq,
-                     float *__restrict__ best, int64_t best_stride, float2 *__restrict__ xnorm, uint32_t *__restrict__ plain)
+                     float *__restrict__ best, int64_t best_stride, float2 *__restrict__ xnorm, uint32_t *__restrict__ need)
 {
     __shared__ __align__(16) v8bf tile[2][NS * 64];
     __shared__ __align__(16) float mx[2][32][8];
@@ -114,7 +118,7 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
         n2 += __shfl_xor(n2, 32, 64);
         e2 += __shfl_xor(e2, 32, 64);
         const float cn = exact_norm(n2, d), ce = exact_norm(e2, d);
-        if (live && !(cn < kExactMaxNorm)) atomicOr(plain, kExactPlain);
+        if (live && !(cn < kExactMaxNorm)) atomicOr(need, 1u);
         xn = fmaxf(xn, cn);
         xe = fmaxf(xe, ce);
     }
@@ -168,19 +172,21 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
 }
 
 // One workgroup per query: theta by two histogram passes over the ordering values of a - E (its 22 high bits, rounded
-// down: a lower theta only adds blocks), then the blocks that reach it, a lane per point, fp32 chain, wave lists.
+// down: a lower theta only adds blocks), then the blocks that reach it as a list, a wave per block and a lane per point,
+// fp32 chain, wave lists. There are at least 4 k blocks (exact_supported). More than max_listed (at most kExactBins)
+// blocks: need[1 + q] is set and the plain kernel answers.
 constexpr int kExactBins = 2048;
 template <int kExactThreads>
 __global__ void __launch_bounds__(kExactThreads)
 exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *__restrict__ queries, const float *__restrict__ best,
                     int64_t n_blocks, int64_t best_stride, int block_points, const float2 *__restrict__ qnorm,
-                    const float2 *__restrict__ xnorm, int ns, int k, const uint32_t *__restrict__ plain, int32_t *__restrict__ ids_out,
-                    float *__restrict__ scores_out)
+                    const float2 *__restrict__ xnorm, int ns, int k, uint32_t max_listed, uint32_t *__restrict__ need,
+                    int32_t *__restrict__ ids_out, float *__restrict__ scores_out)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t hist[kExactBins], wave_sum[kExactThreads / 64], found[2];
-    if (*plain) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = blockIdx.x;
+    if ((need[0] | need[1 + q]) != 0u) return;
     constexpr int nw = kExactThreads / 64;
     const int C = 64 * ns;
     u64 *lists = (u64 *)smem, *mine = lists + (size_t)wave * C;
@@ -191,10 +197,9 @@ exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *
     const float *a = best + (size_t)q * best_stride;
     const float2 qe = qnorm[q];
     auto bound = [&](int64_t b) { const float2 e = xnorm[b]; return exact_bound(qe.x, qe.y, e.x, e.y, d); };
-    // the bin of 11 bits that holds the need-th largest value with the given leading bits (all values: shift 21, prefix 0)
-    uint32_t prefix = 0u, need = (uint32_t)k;
-    bool all = n_blocks < k; // fewer blocks than results: every block is scored
-    for (int pass = 0; pass < 2 && !all; ++pass) {
+    // the bin of 11 bits that holds the left-th largest value with the given leading bits (all values: shift 21, prefix 0)
+    uint32_t prefix = 0u, left = (uint32_t)k;
+    for (int pass = 0; pass < 2; ++pass) {
         for (int b = tid; b < kExactBins; b += kExactThreads) hist[b] = 0u;
         __syncthreads();
         for (int64_t b = tid; b < n_blocks; b += kExactThreads) {
@@ -217,7 +222,7 @@ exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *
         for (int w = wave + 1; w < nw; ++w) above += wave_sum[w];
 #pragma unroll
         for (int i = kExactBins / kExactThreads - 1; i >= 0; --i) {
-            if (above < need && need <= above + h[i]) {
+            if (above < left && left <= above + h[i]) {
                 found[0] = (uint32_t)(tid * (kExactBins / kExactThreads) + i);
                 found[1] = above;
             }
@@ -225,47 +230,49 @@ exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *
         }
         __syncthreads();
         prefix = (prefix << 11) | found[0];
-        need -= found[1];
+        left -= found[1];
         __syncthreads();
     }
-    const float theta = all ? -INFINITY : f32_from_ord(prefix << 10); // the values of the bin are at or above it
+    const float theta = f32_from_ord(prefix << 10); // the values of the bin are at or above it
+    uint32_t *list = hist;
+    if (tid == 0) found[0] = 0u;
     __syncthreads();
+    for (int64_t b = tid; b < n_blocks; b += kExactThreads)
+        if (a[b] + bound(b) >= theta) {
+            const uint32_t at = atomicAdd(&found[0], 1u);
+            if (at < kExactBins) list[at] = (uint32_t)b;
+        }
+    __syncthreads();
+    const uint32_t n_list = found[0];
+    if (n_list > max_listed) {
+        if (tid == 0) need[1 + q] = 1u;
+        return;
+    }
     const bool quad = (d & 3) == 0 && ((uintptr_t)x & 15) == 0;
     u64 thr = 0ull;
     int cnt = 0;
-    for (int64_t g = (int64_t)wave * 64; g < n_blocks; g += nw * 64) {
-        const int64_t mb = g + lane;
-        const bool want = mb < n_blocks && (all || a[mb] + bound(mb) >= theta);
-        u64 mask = __builtin_amdgcn_ballot_w64(want);
-        while (mask) {
-            int64_t b = g + __builtin_ctzll(mask);
-            mask &= mask - 1;
-            bool valid = true;
-            if (block_points == 32 && lane >= 32) { // the upper lanes take the next block
-                valid = mask != 0ull;
-                b = valid ? g + __builtin_ctzll(mask) : b;
+    const uint32_t per = block_points == 32 ? 2 : 1; // blocks of a wave at a time
+    for (uint32_t e = wave * per; e < n_list; e += nw * per) {
+        const uint32_t mine_e = e + (per == 2 ? (uint32_t)lane >> 5 : 0u);
+        const int64_t i = (int64_t)list[mine_e < n_list ? mine_e : e] * block_points + (lane & (block_points - 1));
+        const bool valid = mine_e < n_list && i < n;
+        const float *row = x + (size_t)(valid ? i : 0) * d;
+        float s = 0.0f;
+        int l = 0;
+        if (quad)
+#pragma unroll 8
+            for (; l < d; l += 4) {
+                const float4 v = *(const float4 *)(row + l);
+                s = __fmaf_rn(qs[l], v.x, s);
+                s = __fmaf_rn(qs[l + 1], v.y, s);
+                s = __fmaf_rn(qs[l + 2], v.z, s);
+                s = __fmaf_rn(qs[l + 3], v.w, s);
             }
-            if (block_points == 32 && mask) mask &= mask - 1;
-            const int64_t i = b * block_points + (lane & (block_points - 1));
-            valid = valid && i < n;
-            const float *row = x + (size_t)(valid ? i : b * block_points) * d;
-            float s = 0.0f;
-            int l = 0;
-            if (quad)
+        else
 #pragma unroll 8
-                for (; l < d; l += 4) {
-                    const float4 v = *(const float4 *)(row + l);
-                    s = __fmaf_rn(qs[l], v.x, s);
-                    s = __fmaf_rn(qs[l + 1], v.y, s);
-                    s = __fmaf_rn(qs[l + 2], v.z, s);
-                    s = __fmaf_rn(qs[l + 3], v.w, s);
-                }
-            else
-#pragma unroll 8
-                for (; l < d; ++l) s = __fmaf_rn(qs[l], row[l], s);
-            const u64 key = make_key(ord_from_f32(s), (int32_t)i);
-            if (wave_push(mine, ns, pend, cnt, valid && key > thr, key)) thr = mine[k - 1];
-        }
+            for (; l < d; ++l) s = __fmaf_rn(qs[l], row[l], s);
+        const u64 key = make_key(ord_from_f32(s), (int32_t)i);
+        if (wave_push(mine, ns, pend, cnt, valid && key > thr, key)) thr = mine[k - 1];
     }
     if (cnt > 0) wave_list_flush(mine, ns, pend, cnt);
     for (int stride = 1; stride < nw; stride *= 2) {
@@ -299,7 +306,7 @@ struct ExactWs {
     v8bf *packed;
     float2 *qnorm, *xnorm;
     float *best;
-    uint32_t *plain;
+    uint32_t *need;
     int64_t stride;
 };
 size_t exact_ws_layout(int64_t n, int d, int nq, unsigned char *base, ExactWs *w)
@@ -312,7 +319,7 @@ size_t exact_ws_layout(int64_t n, int d, int nq, unsigned char *base, ExactWs *w
     };
     const int64_t group = exact_steps(d) > 8 ? kExactGroup / 2 : kExactGroup;
     w->stride = (n + group - 1) / group * 8;
-    w->plain = (uint32_t *)take(sizeof(uint32_t));
+    w->need = (uint32_t *)take(sizeof(uint32_t) * (1 + (size_t)nq));
     w->packed = (v8bf *)take(sizeof(v8bf) * (size_t)((nq + 31) / 32) * exact_steps(d) * 64);
     w->qnorm = (float2 *)take(sizeof(float2) * (size_t)nq);
     w->xnorm = (float2 *)take(sizeof(float2) * (size_t)w->stride);
@@ -333,7 +340,8 @@ int exact_queries_per_launch(int64_t n, int d, int nq)
 // The plain kernel alone: d beyond the operands that registers hold, lists that do not fit LDS; and where too few blocks
 // can be left out for what the selection costs, or a few queries' blocks keep a few compute units busy for long. Measured,
 // plain / this: 2,000 x 100, 1,000 queries, k = 100: 0.15 / 0.36 ms; 20,000 x 100, one query: k = 10 74 / 44 us, k = 300 126 / 367;
-// 200,000 x 100, one query, k = 300: 0.25 / 0.43 ms, 64 queries, k = 100: 0.58 / 0.20; 1.2 million, one query, k = 100: 0.63 / 0.33.
+// 200,000 x 100, one query, k = 300: 0.25 / 0.43 ms, 64 queries, k = 100: 0.58 / 0.20; 1,000,000 x 100, one query,
+// k = 100: 0.57 / 0.30, 300: 0.74 / 0.60, 512: 1.12 / 0.91, x 32, k = 512: 0.99 / 0.49.
 bool exact_supported(int64_t n, int d, int nq, int k)
 {
     if (nq < 1 || n < 256 * (int64_t)k || (k > 64 && nq < 16 && n < 1000000)) return false;
@@ -346,22 +354,33 @@ size_t exact_ws_bytes(int64_t n, int d, int nq)
     return exact_ws_layout(n, d, nq, nullptr, &w);
 }
 
-__global__ void exact_clear_kernel(uint32_t *plain) { *plain = 0u; }
+// The longest list of blocks that is scored here rather than by the plain kernel: 2 k (what a search takes anyway) and as
+// much as half of that kernel's time pays for. Measured: a list costs 0.12 to 0.2 ns a point and coordinate while the
+// queries have compute units to themselves, 0.55 ps x nq beyond some 364 queries (the caches' rate), the plain kernel
+// about 75 us and n x d x (3.5 + 0.165 nq) ps. Every point a copy of one row, k = 10, the plain kernel alone / this way /
+// the list whatever its length (us a call): 200,000 x 100 points, one query 103 / 142 / 2,530, 1,000 queries
+// 2,830 / 3,025 / 10,940; 1,183,514 x 100, one query 465 / 646 / 24,640, 300 queries 5,790 / 6,330 / 29,500. At worst, lists
+// just short of the line, a call takes 1.7 times the plain kernel's time (200,000 x 100 rows that share a component of
+// ten times their norm, 16 queries: 178 / 294 / 314; with 300 queries 1,100 / 695).
+static uint32_t exact_max_listed(int64_t n, int d, int nq, int k, int block_points)
+{
+    const double points = (190000.0 / d + (double)n * (0.009 + 0.0004 * nq)) / std::max(1.0, nq / 364.0);
+    return (uint32_t)std::min<double>(kExactBins, 2.0 * k + points / block_points);
+}
 
-// nq as exact_queries_per_launch allows. *plain_out: device word that is non-zero where the plain kernel has to answer.
+// nq as exact_queries_per_launch allows. *need_out: which queries the plain kernel has to answer (see the top).
 int launch_exact(const float *x, int64_t n, int d, const float *queries, int nq, int k, void *ws, int32_t *ids_out,
-                 float *scores_out, const uint32_t **plain_out, hipStream_t st)
+                 float *scores_out, const uint32_t **need_out, hipStream_t st)
 {
     ExactWs w;
     exact_ws_layout(n, d, nq, (unsigned char *)ws, &w);
     const int steps = exact_steps(d), tiles = (nq + 31) / 32, ns = (k + 63) / 64;
     const int block_points = steps > 8 ? 32 : 64;
-    *plain_out = w.plain;
-    hipLaunchKernelGGL(exact_clear_kernel, dim3(1), dim3(1), 0, st, w.plain);
-    hipLaunchKernelGGL(exact_pack_kernel, dim3((unsigned)tiles), dim3(256), 0, st, queries, nq, d, steps, w.packed, w.qnorm, w.plain);
+    *need_out = w.need;
+    hipLaunchKernelGGL(exact_pack_kernel, dim3((unsigned)tiles), dim3(256), 0, st, queries, nq, d, steps, w.packed, w.qnorm, w.need);
 #define AVQ_EXACT(NS, CT)                                                                                                \
     hipLaunchKernelGGL((exact_product_kernel<NS, CT>), dim3((unsigned)(w.stride / 8)), dim3(512), 0, st, x, n, d, w.packed, \
-                       tiles, nq, w.best, w.stride, w.xnorm, w.plain)
+                       tiles, nq, w.best, w.stride, w.xnorm, w.need)
     switch (steps) {
     case 2: AVQ_EXACT(2, 2); break;
     case 3: AVQ_EXACT(3, 2); break;
@@ -378,7 +397,7 @@ int launch_exact(const float *x, int64_t n, int d, const float *queries, int nq,
     const int threads = exact_finish_threads(nq);
     hipLaunchKernelGGL(threads == 512 ? exact_finish_kernel<512> : exact_finish_kernel<1024>, dim3((unsigned)nq), dim3((unsigned)threads),
                        exact_finish_lds(d, k, threads), st, x, n, d, queries, w.best, (n + block_points - 1) / block_points, w.stride,
-                       block_points, w.qnorm, w.xnorm, ns, k, w.plain, ids_out, scores_out);
+                       block_points, w.qnorm, w.xnorm, ns, k, exact_max_listed(n, d, nq, k, block_points), w.need, ids_out, scores_out);
     AVQ_HIP(hipGetLastError());
     return AVQ_OK;
 }

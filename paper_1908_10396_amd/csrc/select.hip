@@ -12,8 +12,10 @@ namespace avq {
 // merges the waves' lists. cand[q][C] sorted descending.
 __global__ void __launch_bounds__(1024)
 merge_partials_kernel(const u64 *__restrict__ partial, int n_chunks, int ns, u64 *__restrict__ cand,
-                      const int32_t *__restrict__ row_of, const uint32_t *__restrict__ active, int tile_queries)
+                      const int32_t *__restrict__ row_of, const uint32_t *__restrict__ active, int tile_queries,
+                      const uint32_t *__restrict__ need)
 {
+    if (need != nullptr && (need[0] | need[1 + blockIdx.x]) == 0u) return;
     if (active != nullptr) {
         if (blockIdx.x >= *active) return;
         if (tile_queries > 0) n_chunks = scan_dynamic_chunks(((int)*active + tile_queries - 1) / tile_queries, n_chunks);
@@ -36,13 +38,14 @@ merge_partials_kernel(const u64 *__restrict__ partial, int n_chunks, int ns, u64
 }
 
 int launch_merge_partials(const u64 *partial, int nq, int n_chunks, int ns, u64 *cand,
-                          hipStream_t st, const int32_t *row_of, const uint32_t *active, int tile_queries)
+                          hipStream_t st, const int32_t *row_of, const uint32_t *active, int tile_queries,
+                          const uint32_t *need)
 {
     int waves = 1;
     while (waves < 16 && waves * 4 <= n_chunks) waves *= 2;
     const size_t lds = (size_t)waves * 64 * ns * 8;
     hipLaunchKernelGGL(merge_partials_kernel, dim3(nq), dim3(waves * 64), lds, st, partial,
-                       n_chunks, ns, cand, row_of, active, tile_queries);
+                       n_chunks, ns, cand, row_of, active, tile_queries, need);
     AVQ_HIP(hipGetLastError());
     return AVQ_OK;
 }
@@ -134,13 +137,13 @@ __global__ void __launch_bounds__(64)
 finalize_kernel(const u64 *__restrict__ cand, int ns, int R, int k, int reorder, int key_kind,
                 const float *__restrict__ x, int d, const float *__restrict__ queries,
                 const float *__restrict__ scale, const float *__restrict__ bias,
-                int32_t *__restrict__ ids_out, float *__restrict__ scores_out, const uint32_t *__restrict__ active)
+                int32_t *__restrict__ ids_out, float *__restrict__ scores_out, const uint32_t *__restrict__ need)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int C = 64 * ns;
     const int lane = threadIdx.x;
     const int q = blockIdx.x;
-    if (active != nullptr && (uint32_t)q >= *active) return;
+    if (need != nullptr && (need[0] | need[1 + q]) == 0u) return;
     const u64 *mine = cand + (size_t)q * C;
     if (!reorder) {
         for (int j = lane; j < k; j += 64) {
@@ -182,11 +185,11 @@ finalize_kernel(const u64 *__restrict__ cand, int ns, int R, int k, int reorder,
 
 int launch_finalize(const u64 *cand, int ns, int nq, int R, int k, int reorder, int key_kind,
                     const float *x, int d, const float *queries, const float *scale,
-                    const float *bias, int32_t *ids_out, float *scores_out, hipStream_t st, const uint32_t *active)
+                    const float *bias, int32_t *ids_out, float *scores_out, hipStream_t st, const uint32_t *need)
 {
     const size_t lds = (size_t)64 * ns * 8 + (size_t)d * 4;
     hipLaunchKernelGGL(finalize_kernel, dim3(nq), dim3(64), lds, st, cand, ns, R, k, reorder,
-                       key_kind, x, d, queries, scale, bias, ids_out, scores_out, active);
+                       key_kind, x, d, queries, scale, bias, ids_out, scores_out, need);
     AVQ_HIP(hipGetLastError());
     return AVQ_OK;
 }
@@ -200,9 +203,13 @@ template <int QB>
 __global__ void __launch_bounds__(256)
 brute_kernel(const float *__restrict__ x, int64_t n, int d, const float *__restrict__ queries,
              int nq, int ns, int k, int64_t pts_per_chunk, int n_chunks, u64 *__restrict__ partial,
-             const uint32_t *__restrict__ active)
+             const uint32_t *__restrict__ need)
 {
-    if (active != nullptr && *active == 0u) return;
+    if (need != nullptr) { // a tile none of whose queries is asked for
+        uint32_t any = need[0];
+        for (int q = blockIdx.y * QB; q < nq && q < (int)(blockIdx.y + 1) * QB; ++q) any |= need[1 + q];
+        if (any == 0u) return;
+    }
     extern __shared__ __align__(16) unsigned char smem[];
     const int C = 64 * ns;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
@@ -276,7 +283,7 @@ int brute_force_chunks(int64_t n, int nq)
 
 int launch_brute_force(const float *x, int64_t n, int d, const float *queries, int nq, int k,
                        u64 *partial_ws, int n_chunks, u64 *cand_ws, int32_t *ids_out,
-                       float *scores_out, hipStream_t st, const uint32_t *active)
+                       float *scores_out, hipStream_t st, const uint32_t *need)
 {
     const int ns = (k + 63) / 64;
     const int C = 64 * ns;
@@ -289,20 +296,20 @@ int launch_brute_force(const float *x, int64_t n, int d, const float *queries, i
         AVQ_HIP(hipFuncSetAttribute((const void *)brute_kernel<8>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds));
         hipLaunchKernelGGL(brute_kernel<8>, dim3(n_chunks, (nq + 7) / 8), dim3(waves * 64),
-                           lds_for(8), st, x, n, d, queries, nq, ns, k, ppc, n_chunks, partial_ws, active);
+                           lds_for(8), st, x, n, d, queries, nq, ns, k, ppc, n_chunks, partial_ws, need);
     } else if (lds_for(1) <= kMaxDynLds) {
         AVQ_HIP(hipFuncSetAttribute((const void *)brute_kernel<1>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds));
         hipLaunchKernelGGL(brute_kernel<1>, dim3(n_chunks, nq), dim3(waves * 64), lds_for(1), st, x,
-                           n, d, queries, nq, ns, k, ppc, n_chunks, partial_ws, active);
+                           n, d, queries, nq, ns, k, ppc, n_chunks, partial_ws, need);
     } else {
         set_error("brute force: d = %d too large", d);
         return AVQ_EINVAL;
     }
     AVQ_HIP(hipGetLastError());
-    AVQ_TRY(launch_merge_partials(partial_ws, nq, n_chunks, ns, cand_ws, st, nullptr, active));
+    AVQ_TRY(launch_merge_partials(partial_ws, nq, n_chunks, ns, cand_ws, st, nullptr, nullptr, 0, need));
     return launch_finalize(cand_ws, ns, nq, k, k, 0, 0, nullptr, d, queries, nullptr, nullptr,
-                           ids_out, scores_out, st, active);
+                           ids_out, scores_out, st, need);
 }
 
 } // namespace avq

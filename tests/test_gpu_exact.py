@@ -1,5 +1,7 @@
 """Exact search on the GPU against the oracle, at the sizes where the matrix product's tiles and the block selection meet
 their edges, and with values that its operands cannot hold."""
+import time
+
 import numpy as np
 import pytest
 
@@ -16,7 +18,7 @@ def exact_index(x, codes=None):
     n, d = x.shape
     idx = avq.Index(d, 1, 4)
     idx.set_codebooks(np.zeros((1, 16, d), np.float32))
-    idx.set_database(torch.from_numpy(x).cuda(), torch.zeros((n, 1), dtype=torch.uint8, device="cuda"))
+    idx.set_database(x if isinstance(x, torch.Tensor) else torch.from_numpy(x).cuda(), torch.zeros((n, 1), dtype=torch.uint8, device="cuda"))
     return idx
 
 
@@ -64,3 +66,49 @@ def test_exact_search_of_large_values(value):
     x[1234] = np.abs(x[1234])
     x[1234, 5] = value
     check(x, q, 10)
+
+
+# Queries whose list of blocks is too long for the selection, alone and among others of the same tile of eight: the plain
+# kernel answers those. 64- and 32-point blocks, several tiles of queries, a last tile that is not full.
+@pytest.mark.parametrize("n,d", [(20_000, 24), (20_001, 33), (12_000, 200)])
+@pytest.mark.parametrize("law", ["copies", "common", "some_queries", "large_query"])
+@pytest.mark.parametrize("nq,k", [(1, 5), (45, 10)])
+def test_exact_search_where_the_product_decides_little(n, d, law, nq, k):
+    rng = np.random.default_rng(n + nq)
+    x, q = unit_rows(rng, n, d), unit_rows(rng, nq, d)
+    if law == "copies":
+        x = np.ascontiguousarray(x[rng.integers(0, 3, n)])
+    elif law == "common":
+        x = (x + 300 * unit_rows(rng, 1, d)).astype(np.float32)
+    else:
+        q[[0, 13, 14, 44] if nq > 1 else 0] = 0 if law == "some_queries" else 3e18 * np.float32(d ** -0.5)
+    check(x, q, k)
+
+
+def exact_seconds(x, q, k):
+    """The fastest of eight calls."""
+    idx = exact_index(x)
+    best = float("inf")
+    for _ in range(9):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        idx.brute_force(q, k)
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+# Measured: copies of a row 1.8 times as long as rows that differ (32 times with the list scored whatever its length), a
+# query of zeros among others 2.1 times (28 times)
+@pytest.mark.parametrize("law", ["copies", "zero_query"])
+def test_exact_search_time_where_the_product_decides_little(law):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    x = torch.nn.functional.normalize(torch.randn((200_000, 100), generator=gen, device="cuda"))
+    q = torch.nn.functional.normalize(torch.randn((16, 100), generator=gen, device="cuda"))
+    usual = exact_seconds(x, q, 10)
+    if law == "copies":
+        x = x[:1].expand(x.shape).contiguous()
+    else:
+        q[5] = 0
+    assert exact_seconds(x, q, 10) < 6 * usual
