@@ -40,6 +40,14 @@ def test_exact_search_matches(n, d, nq, k):
     check(unit_rows(rng, n, d), unit_rows(rng, nq, d), k)
 
 
+# the rule for a few queries and many results: 48 | 49 results of one query (64 | 65 dimensions), of up to seven (200 | 201), 64 | 65
+@pytest.mark.parametrize("n,d,nq,k", [(17_000, 65, 1, 48), (17_000, 65, 1, 49), (17_000, 64, 1, 64), (17_000, 201, 7, 49),
+                                      (17_000, 200, 7, 64), (17_000, 201, 8, 64), (17_000, 40, 15, 65), (17_000, 40, 16, 65)])
+def test_exact_search_of_a_few_queries(n, d, nq, k):
+    rng = np.random.default_rng(n + d)
+    check(unit_rows(rng, n, d), unit_rows(rng, nq, d), k)
+
+
 # ties everywhere (copies of a few rows), norms over many magnitudes, values that vanish in squares, zero rows
 @pytest.mark.parametrize("kind", ["copies", "norms", "tiny", "zero"])
 def test_exact_search_of_unusual_points(kind):
