@@ -69,8 +69,9 @@ struct avq_index {
     int tune_sample = 0; // 0 = batches guess the candidate scan's bounds from a sample where possible, 1 = never, 2 = from a sample scanned with lists
     int tune_prefilter_cap = 0; // candidate keys per (query, chunk) of that scan, 0 = built-in
     DevBuf block_max, lists, refined, lut_fail, fail, cand_keys, groups, kept, fail_rows;
-    DevBuf exact_ws; // exact search: operands, norms, block maxima of a launch's queries
-    DevBuf train_ws; // training: points by coordinate and the sums of an iteration
+    DevBuf exact_ws; // exact search: operands, norms, block maxima of a launch's queries (exact_scratch)
+    // training and encoding: points by coordinate and the sums of an iteration, undecided points, tables (ScratchKeeper)
+    DevBuf train_ws;
     // optional per-stage timing with HIP events recorded on the caller's stream
     bool prof_on = false;
     std::vector<hipEvent_t> prof_pool;
@@ -104,6 +105,22 @@ struct StageTimer {
         idx->prof_recs.push_back({stage, a, b});
     }
 };
+
+// Scratch that an index keeps between calls of one kind; what a larger training or encoding needs is given back at its end
+// (both synchronise there anyway).
+constexpr size_t kKeepScratch = (size_t)256 << 20;
+struct ScratchKeeper {
+    DevBuf *ws;
+    ~ScratchKeeper() { if (ws->cap > kKeepScratch) ws->release(); }
+};
+
+// Exact search does not synchronise, so what it takes it keeps: at most as much as the points themselves (kKeepScratch
+// where they are few, 2 GiB where they are many). Fewer queries a launch cost: with 256 MB, 10,000,000 x 128 points and
+// 1,000 queries took 6.8 instead of 4.5 ms, 1,183,514 x 100 and 4,000 queries 2.13 instead of 1.94.
+static size_t exact_scratch(int64_t n, int d)
+{
+    return std::min<size_t>((size_t)2 << 30, std::max(kKeepScratch, sizeof(float) * (size_t)n * d));
+}
 
 static int check_index(const avq_index *idx)
 {
@@ -283,9 +300,14 @@ static int assign_to_leaves(avq_index *idx, const float *x, int64_t n, int32_t *
                                    (double)c.eta_explicit, assign, st);
     if (!nearest_supported(c.d, c.n_leaves))
         return launch_assign_nearest(x, n, c.d, idx->centers.as<float>(), c.n_leaves, assign, st);
-    AVQ_TRY(idx->train_ws.reserve(nearest_ws_bytes(n, c.d, c.n_leaves, 1)));
-    return launch_nearest(x, n, c.d, idx->centers.as<float>(), idx->centers_t.as<float>(), c.n_leaves, idx->train_ws.p, assign,
-                          nullptr, 1, nullptr, st);
+    // The lists of undecided points take 20 bytes a point: 84 MB for 4,194,304 rows at a time (a launch of so many fills the
+    // chip; the centers are packed again for each, some 10 us).
+    const int64_t rows = std::min<int64_t>(n, (int64_t)1 << 22);
+    AVQ_TRY(idx->train_ws.reserve(nearest_ws_bytes(rows, c.d, c.n_leaves, 1)));
+    for (int64_t i = 0; i < n; i += rows)
+        AVQ_TRY(launch_nearest(x + (size_t)i * c.d, std::min(rows, n - i), c.d, idx->centers.as<float>(), idx->centers_t.as<float>(),
+                               c.n_leaves, idx->train_ws.p, assign + i, nullptr, 1, nullptr, st));
+    return AVQ_OK;
 }
 
 // Theorem 4.2 for every leaf at once: the leaf centers are the codewords of a one-dictionary quantizer whose
@@ -316,6 +338,7 @@ extern "C" int avq_train(avq_index *idx, const float *x, int64_t n_train, void *
         set_error("avq_train: need a device pointer and max(k_c, n_leaves) <= n_train < 2^31");
         return AVQ_EINVAL;
     }
+    const ScratchKeeper keep{&idx->train_ws};
     const int32_t *assign = nullptr;
     if (c.n_leaves > 0) {
         // leaf centers from at most 256 rows per leaf, then every training row to its leaf
@@ -439,6 +462,7 @@ extern "C" int avq_encode(avq_index *idx, const float *x, int64_t n, void *hip_s
     if (!idx->have_codebooks) { set_error("avq_encode: no dictionaries yet (avq_train first)"); return AVQ_ESTATE; }
     if (c.n_leaves > 0 && !idx->have_centers) { set_error("avq_encode: no leaf centers yet"); return AVQ_ESTATE; }
     idx->n = 0;
+    const ScratchKeeper keep{&idx->train_ws};
     AVQ_TRY(idx->codes_logical.reserve((size_t)n * idx->NB));
     const int32_t *assign = nullptr;
     if (c.n_leaves > 0) {
@@ -1493,26 +1517,23 @@ extern "C" int avq_brute_force(avq_index *idx, const float *queries, int32_t nq,
         return AVQ_EINVAL;
     }
     hipStream_t st = (hipStream_t)hip_stream;
-    const int ns = (k + 63) / 64;
-    const int chunks = brute_force_chunks(idx->n, nq);
-    AVQ_TRY(idx->partial.reserve(sizeof(u64) * (size_t)nq * chunks * 64 * ns));
-    AVQ_TRY(idx->cand.reserve(sizeof(u64) * (size_t)nq * 64 * ns));
-    if (exact_supported(idx->n, idx->cfg.d, nq, k)) {
-        const int d = idx->cfg.d, per = exact_queries_per_launch(idx->n, d, nq);
-        AVQ_TRY(idx->exact_ws.reserve(exact_ws_bytes(idx->n, d, per)));
-        for (int q0 = 0; q0 < nq; q0 += per) {
-            const int m = std::min(per, nq - q0);
-            const float *qs = queries + (size_t)q0 * d;
-            const uint32_t *need = nullptr;
-            AVQ_TRY(launch_exact(idx->x, idx->n, d, qs, m, k, idx->exact_ws.p, ids_out + (size_t)q0 * k,
-                                 scores_out + (size_t)q0 * k, &need, st));
-            AVQ_TRY(launch_brute_force(idx->x, idx->n, d, qs, m, k, idx->partial.as<u64>(), chunks,
-                                       idx->cand.as<u64>(), ids_out + (size_t)q0 * k, scores_out + (size_t)q0 * k, st, need));
-        }
-        return AVQ_OK;
+    const int d = idx->cfg.d, ns = (k + 63) / 64;
+    const bool product = exact_supported(idx->n, d, nq, k);
+    const int per = product ? exact_queries_per_launch(idx->n, d, nq, exact_scratch(idx->n, d)) : nq;
+    const int chunks = brute_force_chunks(idx->n, per);
+    AVQ_TRY(idx->partial.reserve(sizeof(u64) * (size_t)per * chunks * 64 * ns));
+    AVQ_TRY(idx->cand.reserve(sizeof(u64) * (size_t)per * 64 * ns));
+    if (product) AVQ_TRY(idx->exact_ws.reserve(exact_ws_bytes(idx->n, d, per)));
+    for (int q0 = 0; q0 < nq; q0 += per) {
+        const int m = std::min(per, nq - q0);
+        const float *qs = queries + (size_t)q0 * d;
+        int32_t *ids = ids_out + (size_t)q0 * k;
+        float *scores = scores_out + (size_t)q0 * k;
+        const uint32_t *need = nullptr; // without the product every query is answered by the plain kernel
+        if (product) AVQ_TRY(launch_exact(idx->x, idx->n, d, qs, m, k, idx->exact_ws.p, ids, scores, &need, st));
+        AVQ_TRY(launch_brute_force(idx->x, idx->n, d, qs, m, k, idx->partial.as<u64>(), chunks, idx->cand.as<u64>(), ids, scores, st, need));
     }
-    return launch_brute_force(idx->x, idx->n, idx->cfg.d, queries, nq, k, idx->partial.as<u64>(), chunks,
-                              idx->cand.as<u64>(), ids_out, scores_out, st);
+    return AVQ_OK;
 }
 
 // ---- stage-level inspection -------------------------------------------------------------

@@ -304,7 +304,7 @@ int brute_force_chunks(int64_t n, int nq);
 // ---- exact.hip -------------------------------------------------------------
 // Exact search that scores in fp32 only the points a bf16 matrix product leaves open; the same results.
 bool exact_supported(int64_t n, int d, int nq, int k);
-int exact_queries_per_launch(int64_t n, int d, int nq);
+int exact_queries_per_launch(int64_t n, int d, int nq, size_t most);
 size_t exact_ws_bytes(int64_t n, int d, int nq);
 // *need_out: which queries launch_brute_force has to answer instead (its need).
 int launch_exact(const float *x, int64_t n, int d, const float *queries, int nq, int k, void *ws, int32_t *ids_out,

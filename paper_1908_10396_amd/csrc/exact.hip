@@ -328,12 +328,17 @@ size_t exact_ws_layout(int64_t n, int d, int nq, unsigned char *base, ExactWs *w
 }
 } // namespace
 
-// Queries of one launch: what the maxima of 64-point blocks may take (at most 2 GiB).
-int exact_queries_per_launch(int64_t n, int d, int nq)
+size_t exact_ws_bytes(int64_t n, int d, int nq)
 {
-    const int64_t group = exact_steps(d) > 8 ? kExactGroup / 2 : kExactGroup;
-    const int64_t per = 32 * ((n + group - 1) / group);
-    const int64_t fit = std::max<int64_t>(32, ((int64_t)1 << 31) / per / 32 * 32);
+    ExactWs w;
+    return exact_ws_layout(n, d, nq, nullptr, &w);
+}
+
+// Queries of one launch, whose scratch takes at most `most` bytes: 32, a multiple of it, or all.
+int exact_queries_per_launch(int64_t n, int d, int nq, size_t most)
+{
+    const size_t fixed = exact_ws_bytes(n, d, 32), per_32 = exact_ws_bytes(n, d, 64) - fixed + 1024; // (rounded up per array)
+    const int64_t fit = most > fixed ? 32 + (int64_t)((most - fixed) / per_32) * 32 : 32;
     return (int)std::min<int64_t>(nq, fit);
 }
 
@@ -349,12 +354,6 @@ bool exact_supported(int64_t n, int d, int nq, int k)
     if (nq < 1 || n < 256 * (int64_t)k || (k > 64 && nq < 16 && n < 1000000)) return false;
     if (k > 48 && n < 400000 && ((nq == 1 && d > 64) || (nq < 8 && d > 200))) return false;
     return exact_steps(d) > 0 && exact_finish_lds(d, k, 1024) <= kMaxDynLds - 16 * 1024;
-}
-
-size_t exact_ws_bytes(int64_t n, int d, int nq)
-{
-    ExactWs w;
-    return exact_ws_layout(n, d, nq, nullptr, &w);
 }
 
 // The longest list of blocks that is scored here rather than by the plain kernel: 2 k (what a search takes anyway) and as

@@ -234,3 +234,32 @@ def test_encode_time_with_equal_codewords():
     def twins(cb):
         return torch.cat([cb[:, :8], cb[:, :8]], dim=1)
     assert encode_seconds(200_000, 100, 50, codewords=twins) < 2.2 * encode_seconds(200_000, 100, 50)
+
+
+def device_bytes_taken(call):
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    call()
+    torch.cuda.synchronize()
+    return before - torch.cuda.mem_get_info()[0]
+
+
+# 1,300,000 x 64 points by coordinate are 333 MB of scratch, which go back at the end of the training
+def test_training_gives_its_scratch_back():
+    x = torch.randn((1_300_000, 64), device="cuda")
+    idx = avq.Index(64, 32, 4, kmeans_iters=1)
+    assert device_bytes_taken(lambda: idx.train(x)) < 64 << 20
+
+
+# Leaves of more points than one launch assigns (three launches, the last one short). What stays is bounded: 9,000,000 points
+# take 36 MB each of leaves and places and 18 MB of codes, 84 MB of lists of undecided points for a launch (180 for all).
+def test_leaves_of_more_points_than_a_launch_assigns():
+    rng = np.random.default_rng(4)
+    n, d, k = 9_000_000, 4, 3
+    x = torch.randn((n, d), device="cuda")
+    c = unit_rows(rng, k, d)
+    idx = avq.Index(d, 1, 4, n_leaves=k, encode_passes=0)
+    idx.set_leaf_centers(c)
+    idx.set_codebooks(np.zeros((1, 16, d), np.float32))
+    assert device_bytes_taken(lambda: idx.encode(x)) < 230 << 20
+    np.testing.assert_array_equal(idx.get_leaf_assign(), oracle.assign_nearest(x.cpu().numpy(), c))
