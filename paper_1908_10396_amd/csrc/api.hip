@@ -27,9 +27,11 @@ int DevBuf::reserve(size_t bytes)
 {
     if (bytes <= cap) return AVQ_OK;
     if (p) { (void)hipFree(p); p = nullptr; cap = 0; }
+    if (limit != 0 && bytes > limit) { set_error("%zu bytes of scratch exceed the limit", bytes); return AVQ_ENOMEM; }
     hipError_t e = hipMalloc(&p, bytes);
     if (e != hipSuccess) {
         p = nullptr;
+        (void)hipGetLastError();
         set_error("hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
         return e == hipErrorOutOfMemory ? AVQ_ENOMEM : AVQ_EHIP;
     }
@@ -208,6 +210,11 @@ extern "C" int avq_set_tuning(avq_index *idx, const char *name, int32_t value)
     else if (!strcmp(name, "rerank_split")) idx->tune_rerank_split = value;
     else if (!strcmp(name, "bound_bits")) idx->tune_bound_bits = value;
     else if (!strcmp(name, "stream_loads")) idx->tune_stream_loads = value;
+    else if (!strcmp(name, "scratch_limit_kb")) {
+        idx->train_ws.limit = idx->exact_ws.limit = (size_t)value * 1024;
+        if (value > 0 && idx->train_ws.cap > idx->train_ws.limit) idx->train_ws.release();
+        if (value > 0 && idx->exact_ws.cap > idx->exact_ws.limit) idx->exact_ws.release();
+    }
     else { set_error("avq_set_tuning: unknown name '%s'", name); return AVQ_EINVAL; }
     return AVQ_OK;
 }
@@ -303,7 +310,9 @@ static int assign_to_leaves(avq_index *idx, const float *x, int64_t n, int32_t *
     // The lists of undecided points take 20 bytes a point: 84 MB for 4,194,304 rows at a time (a launch of so many fills the
     // chip; the centers are packed again for each, some 10 us).
     const int64_t rows = std::min<int64_t>(n, (int64_t)1 << 22);
-    AVQ_TRY(idx->train_ws.reserve(nearest_ws_bytes(rows, c.d, c.n_leaves, 1)));
+    const int rc = idx->train_ws.reserve(nearest_ws_bytes(rows, c.d, c.n_leaves, 1));
+    if (rc == AVQ_ENOMEM) return launch_assign_nearest(x, n, c.d, idx->centers.as<float>(), c.n_leaves, assign, st); // needs no scratch
+    AVQ_TRY(rc);
     for (int64_t i = 0; i < n; i += rows)
         AVQ_TRY(launch_nearest(x + (size_t)i * c.d, std::min(rows, n - i), c.d, idx->centers.as<float>(), idx->centers_t.as<float>(),
                                c.n_leaves, idx->train_ws.p, assign + i, nullptr, 1, nullptr, st));
@@ -343,10 +352,13 @@ extern "C" int avq_train(avq_index *idx, const float *x, int64_t n_train, void *
     if (c.n_leaves > 0) {
         // leaf centers from at most 256 rows per leaf, then every training row to its leaf
         const int64_t n_leaf_train = std::min<int64_t>(n_train, (int64_t)256 * c.n_leaves);
-        if (nearest_supported(c.d, c.n_leaves)) {
-            AVQ_TRY(kmeans_leaves_device(x, n_leaf_train, c.d, c.n_leaves, c.leaf_kmeans_iters, c.seed, idx->centers.as<float>(),
-                                         idx->centers_t.as<float>(), &idx->train_ws, st));
-        } else {
+        int rc = AVQ_ENOMEM;
+        if (nearest_supported(c.d, c.n_leaves))
+            rc = kmeans_leaves_device(x, n_leaf_train, c.d, c.n_leaves, c.leaf_kmeans_iters, c.seed, idx->centers.as<float>(),
+                                      idx->centers_t.as<float>(), &idx->train_ws, st);
+        if (rc != AVQ_ENOMEM) {
+            AVQ_TRY(rc);
+        } else { // another dimension, or no room for its scratch (which it asks for before anything else)
             AVQ_TRY(kmeans_device(x, n_leaf_train, c.d, c.n_leaves, c.leaf_kmeans_iters, c.seed, idx->centers.as<float>(), st));
             AVQ_TRY(refresh_centers_t(idx, st));
         }
@@ -1518,12 +1530,18 @@ extern "C" int avq_brute_force(avq_index *idx, const float *queries, int32_t nq,
     }
     hipStream_t st = (hipStream_t)hip_stream;
     const int d = idx->cfg.d, ns = (k + 63) / 64;
-    const bool product = exact_supported(idx->n, d, nq, k);
-    const int per = product ? exact_queries_per_launch(idx->n, d, nq, exact_scratch(idx->n, d)) : nq;
+    bool product = exact_supported(idx->n, d, nq, k);
+    int per = nq;
+    if (product) {
+        const size_t most = exact_scratch(idx->n, d);
+        per = exact_queries_per_launch(idx->n, d, nq, idx->exact_ws.limit ? std::min(most, idx->exact_ws.limit) : most);
+        const int rc = idx->exact_ws.reserve(exact_ws_bytes(idx->n, d, per));
+        if (rc == AVQ_ENOMEM) { product = false; per = nq; } // the plain kernel needs none of it
+        else AVQ_TRY(rc);
+    }
     const int chunks = brute_force_chunks(idx->n, per);
     AVQ_TRY(idx->partial.reserve(sizeof(u64) * (size_t)per * chunks * 64 * ns));
     AVQ_TRY(idx->cand.reserve(sizeof(u64) * (size_t)per * 64 * ns));
-    if (product) AVQ_TRY(idx->exact_ws.reserve(exact_ws_bytes(idx->n, d, per)));
     for (int q0 = 0; q0 < nq; q0 += per) {
         const int m = std::min(per, nq - q0);
         const float *qs = queries + (size_t)q0 * d;

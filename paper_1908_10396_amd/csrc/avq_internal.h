@@ -49,10 +49,11 @@ inline int set_lds_limit(const void *kernel, size_t bytes, LdsLimitOnce *once)
     return AVQ_OK;
 }
 
-// Grow-only device buffer.
+// Grow-only device buffer. reserve: AVQ_ENOMEM where the memory is not there, or beyond the limit (0: none); the buffer is
+// then empty, and a later launch does not find the allocation's error.
 struct DevBuf {
     void *p = nullptr;
-    size_t cap = 0;
+    size_t cap = 0, limit = 0;
     int reserve(size_t bytes);
     void release();
     template <class T> T *as() const { return (T *)p; }

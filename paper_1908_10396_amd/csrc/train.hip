@@ -294,14 +294,18 @@ int pq_kmeans_device(const float *x, int64_t n, int d, int M, int k, int iters, 
     if (n < k) { set_error("k-means: %lld points for %d centers", (long long)n, k); return AVQ_EINVAL; }
     const int ds = d / M;
     const size_t per_m = (size_t)n * ds * (resid_centers ? sizeof(double) : sizeof(float));
-    const int group = (int)std::max<size_t>(1, std::min<size_t>((size_t)M, ((size_t)1 << 30) / per_m));
-    for (int m0 = 0; m0 < M; m0 += group) {
+    int group = (int)std::max<size_t>(1, std::min<size_t>((size_t)M, ((size_t)1 << 30) / per_m));
+    for (int m0 = 0; m0 < M;) {
         const int Mg = std::min(group, M - m0);
         float *cb = codebooks + (size_t)m0 * k * ds;
-        if (resid_centers)
-            AVQ_TRY(pq_kmeans_group<double>(x, n, d, m0, Mg, ds, k, iters, seed, resid_centers, resid_assign, cb, ws, st));
-        else
-            AVQ_TRY(pq_kmeans_group<float>(x, n, d, m0, Mg, ds, k, iters, seed, nullptr, nullptr, cb, ws, st));
+        const int rc = resid_centers ? pq_kmeans_group<double>(x, n, d, m0, Mg, ds, k, iters, seed, resid_centers, resid_assign, cb, ws, st)
+                                     : pq_kmeans_group<float>(x, n, d, m0, Mg, ds, k, iters, seed, nullptr, nullptr, cb, ws, st);
+        if (rc == AVQ_ENOMEM && Mg > 1) { // nothing was launched yet: fewer subspaces at a time
+            group = (Mg + 1) / 2;
+            continue;
+        }
+        AVQ_TRY(rc);
+        m0 += Mg;
     }
     return AVQ_OK;
 }
@@ -987,11 +991,12 @@ int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, con
     if (M > kMaxM) { set_error("encode: M = %d exceeds %d", M, kMaxM); return AVQ_EINVAL; }
     if (M < 1 || d % M != 0) { set_error("encode: d = %d is not a multiple of M = %d", d, M); return AVQ_EINVAL; }
     const int ds = d / M;
-    int rc = 1;
-    if (kc == 16 ? ds >= 1 && ds <= 4 : ds == 2 || ds == 4 || ds == 8) {
-        const size_t b_tab = (sizeof(float) * (size_t)M * kc * (ds + 1) + 255) & ~(size_t)255, b_lim = sizeof(float2) * (size_t)kMaxM + 256;
-        const bool weights = eta_mode == AVQ_ETA_EXACT;
-        AVQ_TRY(ws->reserve(b_tab + b_lim + (weights ? sizeof(double) * (size_t)n : 0)));
+    int rc = AVQ_ENOMEM; // AVQ_ENOMEM or 1: the kernel below, which needs no scratch, takes the points
+    const size_t b_tab = (sizeof(float) * (size_t)M * kc * (ds + 1) + 255) & ~(size_t)255, b_lim = sizeof(float2) * (size_t)kMaxM + 256;
+    const bool weights = eta_mode == AVQ_ETA_EXACT;
+    if (kc == 16 ? ds >= 1 && ds <= 4 : ds == 2 || ds == 4 || ds == 8)
+        rc = ws->reserve(b_tab + b_lim + (weights ? sizeof(double) * (size_t)n : 0));
+    if (rc == AVQ_OK) {
         EncodeParams p;
         p.x = x; p.order = order; p.n_slots = order ? n_slots : n;
         p.d = d; p.M = M; p.NB = (M * bits + 7) / 8; p.passes = passes;
@@ -1025,7 +1030,7 @@ int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, con
             }
         }
     }
-    if (rc <= 0) return rc;
+    if (rc != 1 && rc != AVQ_ENOMEM) return rc;
 #define AVQ_ENCODE(DS)                                                                                                              \
     hipLaunchKernelGGL(encode_kernel<DS>, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, st, x, n, d, M, kc, bits, codebooks,      \
                        leaf_centers, leaf_assign, eta_mode, T, eta_explicit, passes, packed)

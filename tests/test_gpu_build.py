@@ -263,3 +263,32 @@ def test_leaves_of_more_points_than_a_launch_assigns():
     idx.set_codebooks(np.zeros((1, 16, d), np.float32))
     assert device_bytes_taken(lambda: idx.encode(x)) < 230 << 20
     np.testing.assert_array_equal(idx.get_leaf_assign(), oracle.assign_nearest(x.cpu().numpy(), c))
+
+
+# Less scratch than the fast kernels ask for: ten subspaces take 183 KB (340 with leaves) at once, five 91 (170), two 36 (68),
+# one 18 (34); leaf centers, leaves and codes by the kernels that need none
+@pytest.mark.parametrize("limit_kb", [900, 100, 40])
+@pytest.mark.parametrize("leaves,eta", [(0, "limit"), (7, "limit"), (0, "exact")])
+def test_building_within_limited_scratch(limit_kb, leaves, eta):
+    rng = np.random.default_rng(6)
+    n, d, M = 2000, 20, 10
+    x = unit_rows(rng, n, d)
+    kw = dict(eta_mode=avq.ETA_EXACT) if eta == "exact" else {}
+    idx = avq.Index(d, M, 4, T=0.2, encode_passes=4, kmeans_iters=3, seed=5, n_leaves=leaves, leaf_kmeans_iters=2, **kw)
+    idx.set_tuning("scratch_limit_kb", limit_kb)
+    idx.train(dev(x))
+    okw = {}
+    if leaves:
+        okw["leaf_centers"] = idx.get_leaf_centers()
+        # fp64 means in another order, rounded to fp32: one unit in the last place of values below 1
+        np.testing.assert_allclose(okw["leaf_centers"], oracle.kmeans(x[: 256 * leaves], leaves, 2, seed=5), rtol=0, atol=1.2e-7)
+        okw["leaf_assign"] = oracle.assign_nearest(x, okw["leaf_centers"])
+    cb = idx.get_codebooks()
+    np.testing.assert_allclose(cb, oracle.train_pq(x, M, 16, 3, 5, **okw), rtol=0, atol=1.2e-7)
+    m = 120 if eta == "exact" else n # (an integral per point on the CPU)
+    idx.set_tuning("scratch_limit_kb", 4)
+    idx.encode(dev(x[:m]))
+    if leaves:
+        np.testing.assert_array_equal(idx.get_leaf_assign(), okw["leaf_assign"])
+    want = oracle.encode(x[:m], cb, T=0.2, passes=4, **(dict(eta_mode=1) if eta == "exact" else {}), **okw)
+    np.testing.assert_array_equal(idx.get_codes(), oracle.pack_codes(want, 4))

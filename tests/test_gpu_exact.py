@@ -120,3 +120,19 @@ def test_exact_search_time_where_the_product_decides_little(law):
     else:
         q[5] = 0
     assert exact_seconds(x, q, 10) < 6 * usual
+
+
+# Queries in several launches (96, 96 and 38 at 38,000 x 24 points, whose block maxima take 2.4 KB a query), one of them with a
+# query for the plain kernel; a limit below 32 queries' scratch: the plain kernel for all
+@pytest.mark.parametrize("limit_kb,bad", [(300, None), (300, 120), (300, 5), (8, None), (0, 120)])
+def test_exact_search_within_limited_scratch(limit_kb, bad):
+    rng = np.random.default_rng(21)
+    x, q = unit_rows(rng, 38_000, 24), unit_rows(rng, 230, 24)
+    if bad is not None:
+        q[bad] = 3e18
+    idx = exact_index(x)
+    idx.set_tuning("scratch_limit_kb", limit_kb)
+    ids, sc = idx.brute_force(torch.from_numpy(q).cuda(), 7)
+    oi, os_ = oracle.brute_force(x, q, 7)
+    np.testing.assert_array_equal(ids.cpu().numpy(), oi)
+    np.testing.assert_array_equal(sc.cpu().numpy(), os_)
