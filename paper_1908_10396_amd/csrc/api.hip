@@ -473,6 +473,7 @@ extern "C" int avq_encode(avq_index *idx, const float *x, int64_t n, void *hip_s
     if (!x) { set_error("avq_encode: x is NULL"); return AVQ_EINVAL; }
     if (!idx->have_codebooks) { set_error("avq_encode: no dictionaries yet (avq_train first)"); return AVQ_ESTATE; }
     if (c.n_leaves > 0 && !idx->have_centers) { set_error("avq_encode: no leaf centers yet"); return AVQ_ESTATE; }
+    if (c.n_leaves > 0) AVQ_TRY(check_assign(c.d, c.n_leaves, c.leaf_aniso_iters > 0)); // refused: the database stays
     idx->n = 0;
     const ScratchKeeper keep{&idx->train_ws};
     AVQ_TRY(idx->codes_logical.reserve((size_t)n * idx->NB));

@@ -423,6 +423,8 @@ int pq_kmeans_device(const float *x, int64_t n, int d, int M, int k, int iters, 
                      const int32_t *resid_assign, float *codebooks, DevBuf *ws, hipStream_t st);
 int launch_assign_nearest(const float *x, int64_t n, int d, const float *centers, int k,
                           int32_t *assign, hipStream_t st);
+// whether rows of d dimensions can be assigned to k centers, by l2 or by anisotropic loss: AVQ_EINVAL if not
+int check_assign(int d, int k, bool aniso);
 // every row to the center of smallest anisotropic loss (fp64), lowest index on equal loss
 int launch_assign_aniso(const float *x, int64_t n, int d, const float *centers, int k, int eta_mode, double T,
                         double eta_explicit, int32_t *assign, hipStream_t st);

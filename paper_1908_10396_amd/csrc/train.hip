@@ -471,11 +471,22 @@ assign_aniso_kernel(const float *__restrict__ x, int64_t n, int d, const float *
     }
 }
 
+static size_t assign_aniso_lds(int d) { return sizeof(double) * ((size_t)64 * (d + 1) + 256) + sizeof(int) * 256; }
+
+int check_assign(int d, int k, bool aniso)
+{
+    size_t lds = 0;
+    if (aniso ? assign_aniso_lds(d) <= kMaxDynLds : nearest_supported(d, k)) return AVQ_OK;
+    if (!aniso) return nearest_stage_bytes(d, &lds);
+    set_error("assign: dimension %d too large", d);
+    return AVQ_EINVAL;
+}
+
 int launch_assign_aniso(const float *x, int64_t n, int d, const float *centers, int k, int eta_mode, double T,
                         double eta_explicit, int32_t *assign, hipStream_t st)
 {
-    const size_t lds = sizeof(double) * ((size_t)64 * (d + 1) + 256) + sizeof(int) * 256;
-    if (lds > kMaxDynLds) { set_error("assign: dimension %d too large", d); return AVQ_EINVAL; }
+    const size_t lds = assign_aniso_lds(d);
+    AVQ_TRY(check_assign(d, k, true));
     static LdsLimitOnce attr_done;
     AVQ_TRY(set_lds_limit((const void *)assign_aniso_kernel, kMaxDynLds, &attr_done));
     hipLaunchKernelGGL(assign_aniso_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), lds, st, x, n, d, centers, k,

@@ -292,3 +292,22 @@ def test_building_within_limited_scratch(limit_kb, leaves, eta):
         np.testing.assert_array_equal(idx.get_leaf_assign(), okw["leaf_assign"])
     want = oracle.encode(x[:m], cb, T=0.2, passes=4, **(dict(eta_mode=1) if eta == "exact" else {}), **okw)
     np.testing.assert_array_equal(idx.get_codes(), oracle.pack_codes(want, 4))
+
+
+# A dimension whose leaves cannot be assigned (l2, anisotropic): the call is refused and the installed database stays
+@pytest.mark.parametrize("d,aniso", [(640, 0), (320, 1)])
+def test_refused_encode_leaves_the_database(d, aniso):
+    rng = np.random.default_rng(2)
+    n, M, leaves = 700, d // 4, 3
+    x, q, centers = unit_rows(rng, n, d), unit_rows(rng, 2, d), unit_rows(rng, leaves, d)
+    codes = rng.integers(0, 16, (n, M)).astype(np.uint8)
+    idx = avq.Index(d, M, 4, n_leaves=leaves, leaf_aniso_iters=aniso)
+    idx.set_codebooks(random_dictionaries(rng, M, 16, 4))
+    idx.set_leaf_centers(centers)
+    idx.set_database(dev(x), oracle.pack_codes(codes, 4), rng.integers(0, leaves, n).astype(np.int32))
+    before = [t.cpu().numpy() for t in idx.search(dev(q), 10, 50, 0, leaves_to_search=2)]
+    with pytest.raises(avq.AvqError, match="too large"):
+        idx.encode(dev(x))
+    assert idx.n == n
+    for b, a in zip(before, idx.search(dev(q), 10, 50, 0, leaves_to_search=2)):
+        np.testing.assert_array_equal(a.cpu().numpy(), b)
