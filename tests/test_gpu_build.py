@@ -50,7 +50,10 @@ def leaf_index(d, centers, **kw):
 # 32 centers, workgroups of 128 and 256 points; 270 dimensions take the kernel without matrix cores
 @pytest.mark.parametrize("n,d,k", [(1, 2, 1), (129, 13, 31), (255, 14, 32), (256, 29, 33), (257, 30, 64), (1000, 64, 65),
                                    (3000, 100, 200), (511, 109, 40), (512, 110, 40), (513, 128, 97), (300, 141, 33),
-                                   (640, 192, 50), (700, 205, 129), (385, 256, 300), (260, 269, 31), (260, 270, 31)])
+                                   (640, 192, 50), (700, 205, 129), (385, 256, 300), (260, 269, 31), (260, 270, 31),
+                                   # (up to 16,384 points and 1,024 = centers x dimensions take the kernel without matrix cores too)
+                                   (1, 2, 600), (129, 13, 90), (255, 14, 80), (256, 29, 40), (300, 32, 32), (300, 32, 33),
+                                   (16_384, 8, 16), (16_385, 8, 16)])
 @pytest.mark.parametrize("law", ["unit", "far", "lattice", "twins", "scales"])
 def test_nearest_leaf_is_that_of_fp64_distances(n, d, k, law):
     rng = np.random.default_rng(n * 7 + d)
