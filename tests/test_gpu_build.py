@@ -113,11 +113,14 @@ def test_points_are_grouped_by_leaf(n, d, M, bits, leaves):
         idx.set_database(dev(x), oracle.pack_codes(codes, bits), assign)
 
 
-# every specialised number of dimensions per subspace and one without; waves of 64 points that hold 1, 63, 64, 65 points or
-# take further ones; rows of x that fill LDS, and rows that do not fit it (1,024 dimensions: the plain kernel)
+# every specialised number of dimensions per subspace and one without; waves of 64 points that hold 1, 63, 64, 65 points;
+# rows of x in LDS copied 64 coordinates at a time, for four, two waves and one of a compute unit (128, 192, 400 dimensions),
+# and rows that do not fit it (512 and 1,024: the plain kernel); more points than all resident waves have lanes (262,144), so
+# that lanes take further points as theirs finish, in passes of their own
 @pytest.mark.parametrize("n,d,M,bits", [(1, 4, 4, 4), (63, 6, 3, 4), (64, 30, 6, 4), (65, 100, 50, 4), (700, 105, 35, 4),
                                         (333, 100, 25, 4), (129, 24, 3, 8), (257, 20, 5, 8), (300, 12, 6, 8), (200, 512, 256, 4),
-                                        (70, 1024, 256, 4), (40_000, 8, 4, 4)])
+                                        (70, 1024, 256, 4), (40_000, 8, 4, 4), (130, 128, 64, 4),
+                                        (100, 192, 96, 4), (90, 400, 200, 4), (400_000, 4, 2, 4), (300_000, 4, 2, 8)])
 @pytest.mark.parametrize("law", ["unit", "scales", "huge", "tiny", "eta_exact", "eta_explicit", "lattice", "one_pass", "no_pass", "leaves"])
 def test_codes_are_those_of_fp64_losses(n, d, M, bits, law):
     if n > 1000 and law not in ("unit", "leaves"):
