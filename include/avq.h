@@ -195,8 +195,11 @@ int avq_update_leaf_centers(avq_index *idx, const float *x, int64_t n, int32_t m
  *    bound of the R-th best score are ranked. Up to 80 queries on a partitioned
  *    index of 4-bit codes (same code sizes) score the blocks of their probed leaves
  *    exactly, keep every block's best key, and score the R blocks with the largest
- *    of those again for the points at or above the R-th largest. Same results,
- *    whatever the data;
+ *    of those again for the points at or above the R-th largest. Small flat
+ *    indexes of 4-bit codes with fp32 tables (16384 points at most, fewer with
+ *    many subspaces and few candidates) are answered by one launch, a workgroup
+ *    per query that forms every point's sum and ranks them in registers. Same
+ *    results, whatever the data;
  *  re-score those exactly, <q, x_i> as an fp32 fma chain in index order, and
  *    return the k best in the same order.
  * reorder_k == 0: no re-scoring; the k best ADC candidates are returned with
@@ -215,8 +218,9 @@ int avq_search(avq_index *idx, const float *queries, int32_t nq, int32_t k, int3
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc. Same
  * results as avq_search for the same arguments, on a flat index, for a handful
  * of queries per call: it runs the launches avq_search uses for up to 35 queries
- * (block maxima or block bounds of the whole code array, selection of the blocks
- * that matter, exact scores of those, exact re-scoring), and takes every scratch
+ * (one launch on small indexes; else block maxima or block bounds of the whole
+ * code array, selection of the blocks that matter, exact scores of those, exact
+ * re-scoring), and takes every scratch
  * buffer of those kernels (tables, block maxima, listed blocks, candidate keys) from one array of
  * AVQ_NOALLOC_SCRATCH_BYTES that is part of the library's code object: each GPU
  * the library is loaded on holds its own copy from load time until the process
@@ -316,6 +320,9 @@ int avq_debug_unverified_queries(avq_index *idx, int32_t *counts_out /* [4] */);
 double avq_eta(int32_t d, double T, double norm, int32_t eta_mode);
 
 /* Launch-shape overrides for experiments; 0 restores the built-in choice.
+ * Any value but 0 of "small_batch_impl", "scan_waves", "scan_target_wgs",
+ * "select_split", "rerank_split" or "stream_loads" also leaves small indexes to
+ * the launches these names shape, instead of the one that answers a search whole.
  * name: "scan_target_wgs" (workgroups the batch scan aims for; for small batches
  * the most workgroups per query of the block-maxima scan), "scan_waves"
  * (waves per scan workgroup), "scan_qt" (queries per tile), "small_batch_max"
@@ -377,7 +384,8 @@ int avq_set_tuning(avq_index *idx, const char *name, int32_t value);
  * events, then writes the summed milliseconds and the number of launches per
  * stage into ms_out[AVQ_N_STAGES] / launches_out[AVQ_N_STAGES] (host pointers);
  * reset != 0 forgets the records. */
-enum { AVQ_STAGE_LEAF = 0,   /* leaf selection                                           */
+enum { /* a small index's search in one launch, tables to ranking, is all AVQ_STAGE_SCAN */
+       AVQ_STAGE_LEAF = 0,   /* leaf selection                                           */
        AVQ_STAGE_LUT = 1,    /* table build                                              */
        AVQ_STAGE_SCAN = 2,   /* the scan over all codes (batch: with candidate lists;
                                 small batch: block maxima only)                          */

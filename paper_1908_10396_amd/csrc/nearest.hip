@@ -8,8 +8,9 @@
 // are decided between two centers, and a few in a thousand against all of them, by fp64 squared distances, lowest
 // index on ties: the assignment is that of an fp64 evaluation of every distance.
 //
-// 262,144 x 100 points, 2,000 centers: product and bookkeeping 0.20 ms (0.05 ms of matrix instructions, and 70 vector
-// instructions for every 32 x 32 values against seven matrix instructions: the two are balanced), open points 0.05 ms;
+// 262,144 x 100 points, 2,000 centers: product and bookkeeping 0.20 ms (0.05 ms of matrix instructions, and about 90
+// vector instructions for every 32 x 32 values against seven matrix instructions: the vector operations are the longer of
+// the two; 16 of them only quiet the operands of a maximum), open points 0.05 ms;
 // every distance in fp64 took 21 ms. 1,183,514 points: 0.93 + 0.08 ms (73 ms).
 #include <cmath>
 #include "avq_internal.h"
@@ -215,7 +216,7 @@ nearest_mfma_kernel(const float *__restrict__ x, int64_t n, int d, const v8h *__
                 const float a = __uint_as_float((__float_as_uint(acc[c][v]) & 0xfffffff0u) | (uint32_t)v);
                 third[c] = __builtin_amdgcn_fmed3f(second[c], third[c], a);
                 second[c] = __builtin_amdgcn_fmed3f(best[c], second[c], a);
-                best[c] = __builtin_amdgcn_fmed3f(INFINITY, best[c], a); // the larger (fmaxf would first quiet both)
+                best[c] = __builtin_amdgcn_fmed3f(INFINITY, best[c], a); // the larger
             }
             t_second[c] = second[c] == s_old ? t_second[c] : (second[c] == b_old ? t_best[c] : t);
             t_best[c] = best[c] == b_old ? t_best[c] : t;

@@ -6,8 +6,9 @@
 // initialisation). Encoding: the partition-assignment step of Section 4.1 under
 // the loss eta*||r_par||^2 + ||r_perp||^2 of Section 3.2.
 //
-// All arithmetic here is fp64: the results are arg-mins, and they have to agree
-// with a plain reference evaluation except at exact ties.
+// The results are arg-mins, and they have to agree with a plain reference
+// evaluation in fp64 except at exact ties: everything is decided in fp64, but for
+// the encode search, which takes what fp32 decides beyond its error bound.
 #include "avq_internal.h"
 #include "wave_topk.h"
 
@@ -501,7 +502,7 @@ int launch_assign_aniso(const float *x, int64_t n, int d, const float *centers, 
 // is e + w p^2, w = (eta - 1) / ||x||^2. p and e are sums over the subspaces; with the other subspaces' part P of p
 // fixed, codeword j of subspace m gives e_m(j) + w (P + p_m(j))^2 up to a constant.
 //
-// encode_aniso_kernel (2, 4, 8, ... dimensions per subspace): a lane per point. What decides a codeword is, with
+// encode_aniso_kernel (16 codewords of 1 to 4 dimensions, 256 of 2, 4 or 8): a lane per point. What decides a codeword is, with
 // t = <c, x>, u = <c, x - center>, q = P + <x - center, x>,
 //     f(j) = ||c||^2 - 2 u + w t^2 - 2 w q t,
 // formed in fp32 with the codewords as scalar operands: ds + 2 operations (ds + ds + 3 with leaf centers) and three
@@ -512,7 +513,10 @@ int launch_assign_aniso(const float *x, int64_t n, int d, const float *centers, 
 //
 // The points of a wave need different numbers of passes: a lane whose point is done takes the wave's next point at the
 // end of the sweep over the subspaces, so that no lane waits for the slowest of 64. (x of the points in LDS, row by
-// row, for 16 codewords; with 256 the rows are read from memory again, 32 bytes for 1,800 operations.) On a
+// row, for 16 codewords; with 256 the rows are read from memory again, 32 bytes for 1,800 operations.) The rows of 64
+// points leave room for fewer waves a compute unit as d grows: five at 100 dimensions, two at 192, one from 240 on, where
+// this kernel still wins (200,000 x 384 points, 192 subspaces: 10.1 ms a call, 14.7 all in fp64), but not if many codewords
+// of a dictionary are equal (all in pairs: 12.7 against 8.6); beyond about 420 dimensions no wave fits. On a
 // partitioned index the points are taken leaf by leaf, and the lanes' leaf centers mostly are one and the same.
 // Bound by vector operations and by the chain from one subspace's choice to the next one's q: 1,183,514 x 100 points,
 // 50 subspaces of 16 codewords: 2.34 ms (1.5 ms of vector operations at five waves per compute unit; 2.91 ms with leaf
@@ -761,7 +765,8 @@ encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, cons
                     f = fmaf(t, fmaf(wf, t, -Bf), f);
                     f = __uint_as_float((__float_as_uint(f) & 0xfffffff0u) | (uint32_t)v);
                     second = __builtin_amdgcn_fmed3f(best, second, f);
-                    best = __builtin_amdgcn_fmed3f(-INFINITY, best, f); // the smaller (fminf would first quiet both)
+                    // the smaller; the compiler makes it the minimum that drops a NaN (a true median would return -infinity)
+                    best = __builtin_amdgcn_fmed3f(-INFINITY, best, f);
                 }
                 if (kGroups > 1) group = best == old ? group : g;
             }
