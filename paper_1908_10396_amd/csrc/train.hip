@@ -851,7 +851,7 @@ encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, cons
 }
 
 // Every other shape (16 codewords of 8 dimensions; rows of which LDS does not hold 64; other numbers of dimensions per
-// subspace): a thread per point, all in fp64, the terms of the current codewords kept per subspace. DS = dimensions per
+// subspace; few subspaces, see encode_few_steps): a thread per point, all in fp64, the terms of the current codewords kept per subspace. DS = dimensions per
 // subspace known at compile time (0: any): the point's sub-vector then stays in registers while its codewords (wave-
 // uniform, read through the scalar cache) pass by, instead of being read again for every codeword from a row that no
 // neighbouring lane shares. 200,000 points, 4-bit codes, DS known against any: 128 = 16 x 8 dimensions 0.72 against 5.98 ms a
@@ -1000,6 +1000,21 @@ static int launch_encode_one(EncodeParams p, const float *tab, const float2 *lim
     return AVQ_OK;
 }
 
+// Few subspaces: a thread per point in fp64 is done before the fp32 search's waves have handed out their points one by one
+// and staged their rows. One avq_encode of 300,000 points, fp64 / fp32 search (us): 16 codewords of 2 dimensions, ten
+// passes: 4 subspaces 75 / 127, 8 126 / 138, 10 153 / 142; no pass: 8 73 / 130, 16 139 / 139; of 1 dimension, ten passes: 4
+// 96 / 126, 6 135 / 134; of 3: 2 82 / 125, 3 133 / 126; of 4: 4 91 / 129, 6 131 / 137; 256 of 2, no pass, 16,000 points: 2
+// 64 / 81, 4 105 / 112, 6 145 / 145. (1,000,000 points, 2 subspaces of 2 dimensions, ten passes: 92 / 251.) At 500 to 16,000
+// points the lines lie one or two subspaces lower.
+static bool encode_few_steps(int ds, int kc, int M, int passes)
+{
+    if (kc == 16) {
+        const int most[5] = {0, 4, 7, 2, 5}, most_no_pass[5] = {0, 10, 14, 4, 8}; // by ds
+        return M <= (passes > 0 ? most : most_no_pass)[ds];
+    }
+    return M <= (ds == 2 ? (passes > 0 ? 2 : 4) : ds == 4 && passes == 0 ? 2 : 0);
+}
+
 int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, const float *codebooks, const float *leaf_centers,
                   const int32_t *leaf_assign, const int32_t *order, int64_t n_slots, int eta_mode, double T, double eta_explicit,
                   int passes, uint8_t *packed, DevBuf *ws, hipStream_t st)
@@ -1010,7 +1025,7 @@ int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, con
     int rc = AVQ_ENOMEM; // AVQ_ENOMEM or 1: the kernel below, which needs no scratch, takes the points
     const size_t b_tab = (sizeof(float) * (size_t)M * kc * (ds + 1) + 255) & ~(size_t)255, b_lim = sizeof(float2) * (size_t)kMaxM + 256;
     const bool weights = eta_mode == AVQ_ETA_EXACT;
-    if (kc == 16 ? ds >= 1 && ds <= 4 : ds == 2 || ds == 4 || ds == 8)
+    if ((kc == 16 ? ds >= 1 && ds <= 4 : ds == 2 || ds == 4 || ds == 8) && !encode_few_steps(ds, kc, M, passes))
         rc = ws->reserve(b_tab + b_lim + (weights ? sizeof(double) * (size_t)n : 0));
     if (rc == AVQ_OK) {
         EncodeParams p;
