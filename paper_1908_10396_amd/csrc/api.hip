@@ -1053,12 +1053,17 @@ static int small_ws_from_index(avq_index *idx, int nq, int R, SmallWs *w)
 // R = 100: 39 / 62, 50 / 66, 53 / 67, 72 / 72; 12,288 points, 50 subspaces (the line, 48 x 43 = 2,064): 41 / 41; code sizes
 // without kernels of their own cross earlier (8,192 x 72 subspaces, 32 x 54 = 1,728: 44 / 45). From sixteen queries on the
 // several launches rise sooner (32 queries, 14,000 x 50 subspaces, R = 50: 45 / 55), from 64 on they never won (300
-// queries, 16,384 x 50 subspaces, R = 10: 76 / 86).
+// queries, 16,384 x 50 subspaces, R = 10: 76 / 86) but where hundreds of queries want one or two points of a few blocks,
+// for which sixteen waves are too many (16 subspaces, R = 1: 300 points, 1,000 queries 65 / 56, 3,000 152 / 103; 1,000 points,
+// 3,000 queries 129 / 107; R = 10, 300 points, 1,000 queries: 66 / 80). Codes of one byte have so many equal sums that
+// every pass of the selection carries them along (16,384 points, one query, R = 10: 42 / 38).
 // Rows of R x d <= 100,000 floats are also re-scored by that one (500 x 100 at 2,000 points, one query: 25 / 46; 500 x 192:
 // 35 / 53); more are left to the split re-scoring.
 static bool use_search_one(const avq_index *idx, int nq, int R, bool fuse_tables, bool tile)
 {
     if (!fuse_tables || tile || !search_one_supported(idx->n_blocks, idx->NB)) return false;
+    if (R <= 2 && nq >= 256 * idx->n_blocks) return false;
+    if (idx->NB == 1 && R <= idx->n_blocks) return false;
     const int64_t work = idx->n_blocks * (idx->NB + 18);
     const bool own = idx->NB == 8 || idx->NB == 13 || idx->NB == 25 || idx->NB == 32;
     if (nq < 64 && R <= idx->n_blocks && work > (own ? 2064 : 1750) && !(nq >= 16 && 2 * R > idx->n_blocks && work <= 2800)) return false;

@@ -65,7 +65,9 @@ def test_search_one_equal_sums(distinct):
 @pytest.mark.parametrize("n,M,nq,k,R,one", [(16_384, 16, 1, 10, 0, True), (12_288, 50, 1, 10, 0, True), (12_545, 50, 1, 10, 0, False),
                                             (16_384, 64, 1, 10, 0, False), (16_384, 64, 1, 64, 0, False), (16_384, 64, 1, 65, 0, True),
                                             (16_384, 64, 1, 10, 100, True), (8192, 72, 1, 10, 0, True), (8193, 72, 2, 10, 10, False),
-                                            (14_000, 50, 15, 30, 0, False), (14_000, 50, 16, 30, 0, True), (16_384, 64, 64, 10, 0, True)])
+                                            (14_000, 50, 15, 30, 0, False), (14_000, 50, 16, 30, 0, True), (16_384, 64, 64, 10, 0, True),
+                                            (300, 16, 511, 2, 0, True), (300, 16, 512, 2, 0, False), (300, 16, 512, 1, 3, True),
+                                            (9000, 2, 1, 10, 0, False), (9000, 2, 1, 37, 0, True)])
 def test_rule_of_search_one(n, M, nq, k, R, one):
     rng = np.random.default_rng(n + M)
     x, q = unit_rows(rng, n, 2 * M), unit_rows(rng, nq, 2 * M)
