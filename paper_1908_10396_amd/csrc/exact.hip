@@ -350,9 +350,13 @@ int exact_queries_per_launch(int64_t n, int d, int nq, size_t most)
 // k = 100: 0.57 / 0.30, 300: 0.74 / 0.60, 512: 1.12 / 0.91, x 32, k = 512: 0.99 / 0.49. Rounds of sixteen waves over about k
 // blocks: one query, k = 48 / 64: 70,000 x 100: 104 / 104 and 104 / 114 us, 200,000 x 256: 159 / 161 and 158 / 195, four
 // queries, k = 64: 123 / 125 and 178 / 192, eight: 202 / 209 (the latter); 500,000 x 100, one query, k = 64: 186 / 158.
+// Two and three dimensions: as many points within the bf16 rounding of the best as to make a long list (k = 10, one query and
+// 300: 300,000 x 2: 110 / 131 and 370 / 410 us, 20,000 x 2: 75 / 60 and 123 / 77; 1,000,000 x 3: 180 / 221 and 636 / 902,
+// 300,000 x 3: 112 / 83 and 400 / 178; 1,000,000 x 4: 180 / 91 and 495 / 177).
 bool exact_supported(int64_t n, int d, int nq, int k)
 {
     if (nq < 1 || n < 256 * (int64_t)k || (k > 64 && nq < 16 && n < 1000000)) return false;
+    if (d < 4 && n > (d == 2 ? 100000 : 500000)) return false;
     if (k > 48 && n < 400000 && ((nq == 1 && d > 64) || (nq < 8 && d > 200))) return false;
     return exact_steps(d) > 0 && exact_finish_lds(d, k, 1024) <= kMaxDynLds - 16 * 1024;
 }

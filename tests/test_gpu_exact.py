@@ -40,6 +40,13 @@ def test_exact_search_matches(n, d, nq, k):
     check(unit_rows(rng, n, d), unit_rows(rng, nq, d), k)
 
 
+# two and three dimensions, on both sides of the line above which the plain kernel takes them (100,000 and 500,000 points)
+@pytest.mark.parametrize("n,d", [(100_000, 2), (100_001, 2), (500_000, 3), (500_001, 3)])
+def test_exact_search_of_a_few_dimensions(n, d):
+    rng = np.random.default_rng(n)
+    check(unit_rows(rng, n, d), unit_rows(rng, 9, d), 10)
+
+
 # the rule for a few queries and many results: 48 | 49 results of one query (64 | 65 dimensions), of up to seven (200 | 201), 64 | 65
 @pytest.mark.parametrize("n,d,nq,k", [(17_000, 65, 1, 48), (17_000, 65, 1, 49), (17_000, 64, 1, 64), (17_000, 201, 7, 49),
                                       (17_000, 200, 7, 64), (17_000, 201, 8, 64), (17_000, 40, 15, 65), (17_000, 40, 16, 65)])
