@@ -337,8 +337,10 @@ adc_scan_kernel(const ScanParams p)
         if (STRICT && mid_block) relaxed |= 1u << q;
         if (FKEY) {
             const uint32_t own = (STRICT && mid_block && ord_own > 0u) ? ord_own - 1u : ord_own;
-            const uint32_t t = STRICT ? (ord_g > 0u && ord_g - 1u > own ? ord_g - 1u : own)
-                                      : (ord_g > own ? ord_g : own);
+            uint32_t t = STRICT ? (ord_g > 0u && ord_g - 1u > own ? ord_g - 1u : own)
+                                : (ord_g > own ? ord_g : own);
+            // no score has the ordering value below that of zero: as a float it is -0, which zero does not beat
+            if (t == 0x7fffffffu) t = 0x7ffffffeu;
             thr_f[q] = t ? f32_from_ord(t) : -INFINITY;
         } else {
             // integer sums: ordering value = sum + 1
