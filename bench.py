@@ -43,6 +43,7 @@ HBM_PEAK_GBS = 8000.0            # MI355X HBM3E, published
 VALU_PEAK_TOPS = 157.3 / 2
 LDS_PEAK_GBS = 256 * 256 * 2.4   # 256 CUs x 256 B/clk x 2.4 GHz
 MFMA_I8_PEAK_TOPS = 5000.0       # dense int8, published
+MFMA_F16_PEAK_TOPS = 2500.0      # dense f16, published
 SPECIAL_NB = (8, 13, 25, 32)     # code sizes with specialised kernels
 
 
@@ -301,8 +302,44 @@ def main():
         r.update(extra)
         return r
 
+    def product_roofline(ms, kernel, extra):
+        # the product of the queries with the decoded points: 2 d operations a pair, d rounded up to the kernel's steps of 16
+        steps = (d + 15) // 16
+        steps += steps & 1 if steps > 8 else 0
+        executed = 2.0 * 16 * steps * scanned * (-(-B // 64) * 64)
+        r = {"bound": "mfma", "achieved": 2.0 * d * scanned * B / (ms * 1e-3) / 1e12, "peak": MFMA_F16_PEAK_TOPS, "unit": "TOP/s",
+             "kernel": kernel, "avg_launch_ms": ms, "mfma_pipe_util": executed / (ms * 1e-3) / 1e12 / MFMA_F16_PEAK_TOPS,
+             "table_adds_TOPs": method_ops / (ms * 1e-3) / 1e12,
+             "note": "achieved = 2 d operations per query and scanned point, per second, against the dense f16 matrix peak: the kernel "
+                     "decodes the points and forms <query, decoded point> on v_mfma_f32_32x32x16_f16 to find the points that can be "
+                     "among the R best, which are scored again with the tables; table_adds_TOPs = the rate of the M look-ups + M "
+                     "additions that this stands for"}
+        r["frac"] = r["achieved"] / r["peak"]
+        r.update(extra)
+        return r
+
+    def product_kernel():
+        steps = (d + 15) // 16
+        return "product_scan_kernel<%d,%d,false>" % ((steps, 4) if steps <= 8 else (steps + (steps & 1), 2))
+
+    by_product = not n_leaves and not small and stage_ms.get("merge", 0.0) == 0.0 and stage_ms.get("sample", 0.0) > 0.0 \
+        and stage_ms.get("finalize", 0.0) == 0.0
     fp32_direct = None
-    if grouped:
+    if by_product:
+        unverified = idx.debug_unverified_queries(reasons=True)
+        traffic, src = traffic_from_profiles(product_kernel(), "%s_b%d" % (workload, B))
+        batch_roof = product_roofline(scan_ms, product_kernel(), {
+            "traffic": traffic, "traffic_source": src, "sample_stage_ms": stage_ms.get("sample", 0.0),
+            "queries_scanned_again": unverified[0], "of_which_too_many_kept_or_bound_too_high_or_other": unverified[1:],
+            "stages_note": "the launch over all points; before it, timed apart (sample_stage_ms), a launch over a sample of the points "
+                           "and the bounds guessed from it; scores with tables and the exact scores are the rescan stage"})
+        idx.set_tuning("scan_prefilter", 1)   # the same step with every point scored with tables
+        dt_d, stage_d = timed_batch(avq.LUT_F32, max(2, args.steps // 5))
+        idx.set_tuning("scan_prefilter", 0)
+        fp32_direct = {"queries_per_s": B * max(2, args.steps // 5) / dt_d, "stage_ms": stage_d,
+                       "roofline": lds_roofline(stage_d["scan"], B, every_point=True)}
+        log("[bench] fp32 batch %d, every point scored in fp32: %.0f q/s, stages(ms) %s" % (B, fp32_direct["queries_per_s"], stage_d))
+    elif grouped:
         unverified = idx.debug_unverified_queries(reasons=True)
         kern = "adc_mfma_scan_kernel<%d,false,true,true>" % nb
         traffic, src = traffic_from_profiles(kern, workload)
@@ -348,7 +385,9 @@ def main():
     qps8 = B * steps8 / dt8
     log("[bench] u8   batch %d: %.0f q/s, stages(ms) %s" % (B, qps8, stage8_ms))
     u8_roof = None
-    if prefiltered:
+    if by_product and stage8_ms.get("finalize", 0.0) == 0.0:
+        u8_roof = product_roofline(stage8_ms["scan"], product_kernel(), {"traffic": None, "sample_stage_ms": stage8_ms.get("sample", 0.0)})
+    elif prefiltered:
         u8_roof = mfma_roofline(stage8_ms["scan"], "adc_mfma_scan_kernel<%d,false,false,true>" % nb,
                                 {"traffic": None, "sample_stage_ms": stage8_ms.get("sample", 0.0)})
 
@@ -475,7 +514,8 @@ def main():
         oracle.set_num_threads(threads)
         log("[bench] oracle, one thread: %.2f q/s quantized, %.2f q/s exact" % (cpu1["value"], cpu_bf["value"]))
 
-    scan_desc = ("int8 matrix-core candidate scan + fp32 re-scoring of the kept points (results equal a full fp32 scan)"
+    scan_desc = ("f16 product of queries and decoded points for candidates + fp32 table scores of those (results equal a full fp32 scan)"
+                 if by_product else "int8 matrix-core candidate scan + fp32 re-scoring of the kept points (results equal a full fp32 scan)"
                  if (prefiltered or grouped) else
                  ("block bounds from 8-bit table sums, exact scores of the blocks that can reach the R-th best"
                   if ((small and bound_scan) or tiled) else "fp32 table sums of every point"))

@@ -306,9 +306,9 @@ int avq_debug_stream_codes(avq_index *idx, uint32_t *words_out, int64_t *n_block
 int avq_debug_scan_parts(avq_index *idx, const float *queries, int32_t nq, int32_t lut_mode, int32_t part,
                          int32_t reps, void *hip_stream);
 
-/* Measurement aid: after an avq_search with fp32 tables that took its candidates
- * from the 8-bit-table scan (see "scan_prefilter" below): counts_out[0] = the
- * number of queries of that call that were scanned again with fp32 tables
+/* Measurement aid: after an avq_search of a batch that took candidates from a
+ * matrix product or scan (see "scan_product", "scan_prefilter" below):
+ * counts_out[0] = the number of queries of that call that were scanned again plainly
  * (-1 if no such search has happened), of which counts_out[1] because the scan
  * kept more points than the refinement holds, counts_out[2] because the bound
  * guessed from the sample was too high, counts_out[3] for other reasons (no
@@ -338,9 +338,13 @@ double avq_eta(int32_t d, double T, double norm, int32_t eta_mode);
  * workgroup per query whatever the batch size), "scan_mfma"
  * (1: batches with 8-bit tables on 4-bit codes use the LDS-table scan instead
  * of the matrix-core scan; for that scan "scan_target_wgs" counts waves),
- * "scan_prefilter" (1: batches with fp32 tables on a flat index of 4-bit codes
- * are scanned with the fp32 tables directly instead of taking candidates from
- * the matrix-core scan over the 8-bit tables and re-scoring them in fp32;
+ * "scan_product" (batches on a flat index of at most 256 dimensions take their
+ * candidates from a matrix product of the queries with the decoded points where
+ * that is expected to be fastest, and no other tuning of the batch scans is set;
+ * 1: never, 2: wherever it can), "scan_prefilter" (1: batches on a flat index
+ * have every point scored with the tables, instead of taking candidates from that
+ * product or, with fp32 tables on 4-bit codes, from the matrix-core scan over the
+ * 8-bit tables and scoring those;
  * 2: candidates are taken as usual, but every odd query is treated as one
  * whose candidates cannot be used and is scanned again with fp32 tables),
  * "prefilter_cap" (candidate keys that scan may keep per query and chunk of

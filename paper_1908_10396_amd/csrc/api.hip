@@ -68,9 +68,10 @@ struct avq_index {
                             // 2 = as 0 but odd queries always take the plain scan afterwards (exercises that branch)
     int tune_bound_leaves = 0; // leaves per query that supply the bound of the grouped scan over leaves, 0 = built-in
     int tune_group_min = 0; // (query, leaf) pairs from which a batch on a partitioned index is regrouped by leaf; 0 = built in
+    int tune_product = 0; // 0 = flat batches through the product of queries and decoded points where it applies, 1 = never, 2 = wherever it can
     int tune_sample = 0; // 0 = batches guess the candidate scan's bounds from a sample where possible, 1 = never, 2 = from a sample scanned with lists
     int tune_prefilter_cap = 0; // candidate keys per (query, chunk) of that scan, 0 = built-in
-    DevBuf block_max, lists, refined, lut_fail, fail, cand_keys, groups, kept, fail_rows;
+    DevBuf block_max, lists, refined, lut_fail, fail, cand_keys, groups, kept, fail_rows, product;
     DevBuf exact_ws; // exact search: operands, norms, block maxima of a launch's queries (exact_scratch)
     // training and encoding: points by coordinate and the sums of an iteration, undecided points, tables (ScratchKeeper)
     DevBuf train_ws;
@@ -183,7 +184,7 @@ extern "C" void avq_destroy(avq_index *idx)
                      &idx->codes_blocked, &idx->assign, &idx->perm, &idx->leaf_blk, &idx->lut, &idx->lut8,
                      &idx->scale, &idx->bias, &idx->partial, &idx->cand, &idx->leaf_ids, &idx->leaf_ip,
                      &idx->tmp, &idx->block_max, &idx->lists, &idx->thr, &idx->refined, &idx->lut_fail,
-                     &idx->fail, &idx->cand_keys, &idx->groups, &idx->kept, &idx->fail_rows, &idx->train_ws};
+                     &idx->fail, &idx->cand_keys, &idx->groups, &idx->kept, &idx->fail_rows, &idx->product, &idx->train_ws};
     for (DevBuf *b : all) b->release();
     for (hipEvent_t e : idx->prof_pool) (void)hipEventDestroy(e);
     delete idx;
@@ -203,6 +204,7 @@ extern "C" int avq_set_tuning(avq_index *idx, const char *name, int32_t value)
     else if (!strcmp(name, "scan_mfma")) idx->tune_mfma = value;
     else if (!strcmp(name, "scan_prefilter")) idx->tune_prefilter = value;
     else if (!strcmp(name, "prefilter_cap")) idx->tune_prefilter_cap = value;
+    else if (!strcmp(name, "scan_product")) idx->tune_product = value;
     else if (!strcmp(name, "scan_sample")) idx->tune_sample = value;
     else if (!strcmp(name, "group_min_pairs")) idx->tune_group_min = value;
     else if (!strcmp(name, "bound_leaves")) idx->tune_bound_leaves = value;
@@ -455,7 +457,7 @@ extern "C" int avq_set_database(avq_index *idx, const float *x, const uint8_t *p
         return AVQ_EINVAL;
     }
     if (c.n_leaves > 0 && !idx->have_centers) { set_error("avq_set_database: no leaf centers yet"); return AVQ_ESTATE; }
-    AVQ_TRY(idx->codes_logical.reserve((size_t)n * idx->NB));
+    AVQ_TRY(idx->codes_logical.reserve((size_t)n * idx->NB + 16)); // rows are read in whole words
     AVQ_HIP(hipMemcpyAsync(idx->codes_logical.p, packed, (size_t)n * idx->NB, hipMemcpyDefault, st));
     if (leaf_assign) {
         AVQ_TRY(idx->assign.reserve(sizeof(int32_t) * (size_t)n));
@@ -479,7 +481,7 @@ extern "C" int avq_encode(avq_index *idx, const float *x, int64_t n, void *hip_s
     if (c.n_leaves > 0) AVQ_TRY(check_assign(c.d, c.n_leaves, c.leaf_aniso_iters > 0)); // refused: the database stays
     idx->n = 0;
     const ScratchKeeper keep{&idx->train_ws};
-    AVQ_TRY(idx->codes_logical.reserve((size_t)n * idx->NB));
+    AVQ_TRY(idx->codes_logical.reserve((size_t)n * idx->NB + 16)); // rows are read in whole words
     const int32_t *assign = nullptr;
     if (c.n_leaves > 0) {
         AVQ_TRY(idx->assign.reserve(sizeof(int32_t) * (size_t)n));
@@ -790,6 +792,155 @@ static int search_through_candidates(avq_index *idx, const float *queries, int n
     StageTimer t(idx, AVQ_STAGE_FINAL, st);
     return launch_finalize(idx->refined.as<u64>(), ns, nq, R, k, reorder_k != 0, u8 ? 1 : 0, idx->x, c.d, queries,
                            idx->scale.as<float>(), idx->bias.as<float>(), ids_out, scores_out, st);
+}
+
+// Batches on a flat index through the product of the queries with the decoded points (product.hip), where it is expected to
+// be faster than the path that the call takes otherwise, for which few_max is the number of queries answered one by one.
+// What the other paths cost is estimated from below. Measured, other path / product, us a call (100 dimensions, R = 100):
+//  4-bit codes, fp32 tables: 1,000,000 points 93 / 120 (16 queries), 144 / 121 (32), 505 / 297 (1,024), 1,697 / 932 (4,096);
+//    200,000 points 66 / 69 (32), 170 / 87 (256), 581 / 376; 32,000 points 59 / 70 (64), 109 / 77 (256), 287 / 203; up to
+//    16,384 points one launch answers 256 queries in about 20 us: 4,000 points 68 / 109 (1,024), 264 / 212 (4,096), and
+//    R = 500 432 / 567.
+//  4-bit codes, 8-bit tables, whose rounding lets through several times R: 1,000,000 points 168 / 150 (64), 1,560 / 1,089;
+//    64,000 points 131 / 104 (256), 308 / 324 (4,096); R = 500: 200,000 points 790 / 1,078, 1,000,000 1,904 / 1,803.
+//  code sizes without matrix-core kernels (192 dimensions, 96 subspaces): 1,000,000 points 360 / 264 (32), 12,877 / 1,788.
+//  8-bit codes: 4,000 points 70 / 92 (64), 103 / 94 (256), 844 / 249; 1,000,000 points 155 / 126 (32), 203 / 129, 5,369 / 976;
+//    256 dimensions, R = 10: 1,000,000 points 210 / 399 (64, mostly the decoding), 398 / 410 (256), 1,406 / 679.
+//  and where the other batch path cannot guess its bounds (guessed false: 20,000 points, R = 100) 151 / 98 (256), 718 / 196.
+static bool use_product(const avq_index *idx, int nq, int R, bool u8, int few_max, bool guessed)
+{
+    const avq_config &c = idx->cfg;
+    if (idx->tune_product == 1 || c.n_leaves > 0 || !product_supported(c.d, c.M, idx->n, R)) return false;
+    if (idx->tune_product == 2) return true;
+    // any tuning of the other kernels' launches asks for those kernels
+    if (idx->tune_target_wgs || idx->tune_waves || idx->tune_qt || idx->tune_mfma || idx->tune_prefilter == 1 || idx->tune_prefilter_cap ||
+        idx->tune_sample || idx->tune_small_impl || idx->tune_bound_bits || idx->tune_small_batch >= 0) return false;
+    if (nq < 16) return false;
+    const double n = (double)idx->n, q = (double)nq, d = (double)c.d, r = (double)R;
+    const double decode = std::max(0.0, n - 3e5) * d * (c.bits == 8 ? 1.0e-6 : 6e-7) * (d > 128 ? 1.0 : 0.8);
+    double product = 30.0 + 0.35 * d + 0.14 * r + decode + q * (0.02 + 0.00018 * r) + 1.6e-9 * n * q * d;
+    const double few = 20.0 + q * (0.1 + 0.000037 * idx->NB * (double)idx->n_blocks + (guessed ? 0.001 : 0.002) * r);
+    if (c.bits == 8) {
+        if (!block_bound_supported(idx->NB, c.bits)) return true; // plain scans: 400 us and more
+        product += 0.12 * d + (u8 ? 4.0 + 0.12 * d : 0.0);
+        const double tiles = 40.0 + 0.15 * q + idx->NB / 25.0 * (1.1e-4 * n + 6.5e-7 * n * q) + (n < 3e5 ? std::min(100.0, 0.003 * n) : 0.0);
+        return product < (nq > few_max ? (u8 ? 0.93 : 1.0) * tiles : few);
+    }
+    const bool own = scan_mfma_supported(idx->NB, c.bits);
+    if (u8) product += 12.0;
+    if (idx->n <= 16384) {
+        if (u8) return own ? nq >= 2048 && R >= 50 && R <= 100 : nq > few_max && (c.d <= 128 || (nq >= 1024 && n >= 8192.0));
+        return own ? nq >= 2048 && R <= 100 : nq > few_max;
+    }
+    if (u8 && own && guessed && (n < 2000.0 * r || n < 32768.0)) return false;
+    return nq > few_max || product < (own && !guessed ? std::min(560.0, few) : few);
+}
+
+static int search_product(avq_index *idx, const float *queries, int nq, int k, int reorder_k, int R, int ns, bool u8, int32_t *ids_out,
+                          float *scores_out, hipStream_t st)
+{
+    const avq_config &c = idx->cfg;
+    const int C = 64 * ns;
+    const ProductPlan pl = product_plan(nq, idx->n, c.d, R, u8);
+    ProductParams p;
+    memset(&p, 0, sizeof(p));
+    p.codes = idx->codes_blocked.as<uint8_t>();
+    p.n = idx->n;
+    p.nq = nq; p.d = c.d; p.M = c.M; p.bits = c.bits; p.NB = idx->NB;
+    p.n_tiles = pl.n_tiles;
+    p.n_classes = pl.n_classes;
+    p.run = pl.run;
+    p.kept_cap = pl.kept_cap;
+    p.cnt_stride = pl.cnt_stride;
+    // scratch, 256-byte aligned pieces
+    size_t off = 0;
+    auto take = [&](size_t bytes) -> size_t { const size_t at = (off + 255) & ~(size_t)255; off = at + bytes; return at; };
+    const size_t o_cb = take((size_t)c.M * idx->kc * idx->ds * 2), o_packed = take((size_t)pl.n_tiles * pl.steps * 1024),
+                 o_meta = take(kProductInfoBytes), o_q = take(kProductInfoBytes * (size_t)nq),
+                 o_thr = take(sizeof(float) * ((size_t)pl.n_tiles * 32 + 64)), o_margin = take(sizeof(float) * (size_t)nq * 2),
+                 o_classes = take(sizeof(float) * (size_t)nq * pl.n_classes), o_kept = take(sizeof(u64) * (size_t)nq * pl.kept_cap),
+                 o_cnt = take(sizeof(uint32_t) * (size_t)nq * pl.cnt_stride);
+    AVQ_TRY(idx->product.reserve(off));
+    unsigned char *base = (unsigned char *)idx->product.p;
+    p.cb16 = base + o_cb;
+    p.packed = base + o_packed;
+    p.meta = (ProductMeta *)(base + o_meta);
+    p.qinfo = (ProductQuery *)(base + o_q);
+    p.thr = (float *)(base + o_thr);
+    p.classes = (float *)(base + o_classes);
+    p.kept = (u64 *)(base + o_kept);
+    p.kept_cnt = (uint32_t *)(base + o_cnt);
+    float *margin = (float *)(base + o_margin), *guess = margin + nq;
+    // the plain scan for the queries whose candidates cannot be used: its grid is cut on the device to their number
+    ScanParams pf;
+    fill_scan_params(idx, nq, R, ns, &pf);
+    ScanShape shape;
+    if (scan_pick_shape(idx->NB, c.bits, u8, ns, nq, false, c.bits == 4 ? 8 : 0, 0, &shape) != AVQ_OK)
+        AVQ_TRY(scan_pick_shape(idx->NB, c.bits, u8, ns, nq, false, 0, 0, &shape));
+    pf.n_tiles = (nq + shape.qt - 1) / shape.qt;
+    pf.n_chunks = (int32_t)std::max<int64_t>(1, std::min<int64_t>(128, idx->n_blocks / shape.waves)); // at most
+    pf.blocks_per_chunk = 0; // derived on the device
+    const size_t items = (size_t)std::max(kDynamicItems, pf.n_tiles); // (tiles of live queries) x chunks
+    AVQ_TRY(idx->partial.reserve(sizeof(u64) * items * shape.qt * C));
+    if (shape.lists_global) AVQ_TRY(idx->lists.reserve(sizeof(u64) * items * shape.waves * shape.qt * C));
+    const size_t row_floats = u8 ? (size_t)c.M * idx->kc / 4 : (size_t)c.M * idx->kc; // a query's tables, in 4-byte units
+    AVQ_TRY(idx->lut_fail.reserve(sizeof(float) * (size_t)pf.n_tiles * shape.qt * row_floats));
+    AVQ_TRY(idx->fail.reserve(sizeof(int32_t) * (4 + (size_t)nq)));
+    uint32_t *fail_count = idx->fail.as<uint32_t>();
+    int32_t *fail_list = idx->fail.as<int32_t>() + 4;
+    {
+        StageTimer t(idx, AVQ_STAGE_LUT, st);
+        if (u8) AVQ_TRY(build_tables(idx, queries, nq, AVQ_LUT_U8, st));
+        AVQ_TRY(launch_product_pack(p, queries, idx->codebooks.as<float>(), fail_count, st));
+    }
+    {
+        StageTimer t(idx, AVQ_STAGE_SAMPLE, st);
+        p.groups = pl.sample_groups;
+        p.stages_per_chunk = pl.sample_stages_per_chunk;
+        p.chunks = pl.sample_chunks;
+        p.stride = pl.stride;
+        AVQ_TRY(launch_product_scan(p, true, st));
+        AVQ_TRY(launch_product_bound(p, pl.r, u8 ? idx->scale.as<float>() : nullptr, margin, guess, st));
+    }
+    {
+        StageTimer t(idx, AVQ_STAGE_SCAN, st); // the launch over all points, nothing else
+        p.groups = pl.groups;
+        p.stages_per_chunk = pl.stages_per_chunk;
+        p.chunks = pl.chunks;
+        p.stride = 1;
+        AVQ_TRY(launch_product_scan(p, false, st));
+    }
+    StageTimer t(idx, AVQ_STAGE_RESCAN, st);
+    ProductRefineParams r;
+    memset(&r, 0, sizeof(r));
+    r.kept = p.kept;
+    r.kept_cnt = p.kept_cnt;
+    r.margin = margin;
+    r.guess = guess;
+    r.queries = queries;
+    r.codebooks = idx->codebooks.as<float>();
+    r.x = idx->x;
+    r.codes = idx->codes_logical.as<uint8_t>();
+    r.lut8 = u8 ? idx->lut8.as<uint8_t>() : nullptr;
+    r.scale = idx->scale.as<float>();
+    r.bias = idx->bias.as<float>();
+    r.ids_out = ids_out;
+    r.scores_out = scores_out;
+    r.fail_list = fail_list;
+    r.fail_count = fail_count;
+    r.fail_lut = idx->lut_fail.p;
+    r.kept_cap = pl.kept_cap; r.cnt_stride = pl.cnt_stride;
+    r.nq = nq; r.d = c.d; r.M = c.M; r.NB = idx->NB; r.R = R; r.k = k; r.reorder = reorder_k != 0;
+    r.force_fail_odd = idx->tune_prefilter == 2;
+    AVQ_TRY(launch_product_refine(r, u8, c.bits, st));
+    // the other queries, whose tables lie side by side now: the plain scan over them
+    pf.lut = idx->lut_fail.as<float>();
+    pf.lut8 = idx->lut_fail.as<uint8_t>();
+    pf.partial = idx->partial.as<u64>();
+    if (shape.lists_global) pf.lists_ws = idx->lists.as<u64>();
+    pf.active_queries = fail_count;
+    AVQ_TRY(launch_scan(pf, u8, SCAN_CHUNK, shape, st));
+    return launch_product_fallback(r, pf.partial, pf.n_chunks, shape.qt, ns, u8, st);
 }
 
 // Batches on a partitioned index of 4-bit codes: the (query, leaf) pairs are regrouped by leaf and
@@ -1318,13 +1469,14 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
     // crossovers: 36 to 44 queries at 1.2 million points, 20 at 10 million, about 200 at 100,000, thousands at
     // 10,000 points.
     int small_max = c.bits == 4 ? (idx->n_blocks < 12000 ? 35 : 20) : 8; // code sizes without kernels of their own: as measured at first
+    bool guessed = false; // whether the matrix-core scan of this batch would guess its bounds from class maxima
     if (c.bits == 4 && small_uses_bounds(idx)) {
         const double nb = (double)idx->n_blocks;
         double batch_us = 150.0 + 0.017 * nb;
         ScanParams plan, sample;
         fill_scan_params(idx, nq, R, ns, &plan);
         scan_mfma_plan(nq, idx->n_blocks, idx->tune_target_wgs, &plan);
-        const bool guessed = scan_mfma_sample_plan(plan, &sample) && sample.n_chunks * 32 >= 8 * sample.R && sample.n_chunks * 32 <= 8192;
+        guessed = scan_mfma_sample_plan(plan, &sample) && sample.n_chunks * 32 >= 8 * sample.R && sample.n_chunks * 32 <= 8192;
         if (!guessed) batch_us = 600.0;
         small_max = (int)std::min(4096.0, std::max(8.0, (batch_us - 40.0) / (0.1 + 0.00093 * nb)));
     }
@@ -1333,7 +1485,8 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
         // 125 / 165, 229 / 399 and 500 / 716 us for two queries, equal for three
         small_max = (int)std::min<int64_t>(32, std::max<int64_t>(2, 120000 / std::max<int64_t>(1, idx->n_blocks)));
     if (idx->tune_small_batch >= 0) small_max = idx->tune_small_batch;
-    const bool small = !ivf && nq <= small_max;
+    const bool product = use_product(idx, nq, R, u8, small_max, guessed);
+    const bool small = !ivf && !product && nq <= small_max;
     // the single-query kernels compute short fp32 tables themselves (one launch less)
     const bool fuse_tables = small && idx->tune_small_impl != 1 && small_batch_can_fuse_tables(c.bits, c.M, c.d, u8);
     const bool prefilter = !small && use_prefilter(idx, nq, lut_mode, R);
@@ -1344,6 +1497,15 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
         SmallWs w;
         AVQ_TRY(small_ws_from_index(idx, nq, R, &w));
         return search_small(idx, queries, nq, k, reorder_k, u8, fuse_tables, w, true, ids_out, scores_out, st);
+    }
+    if (product) {
+        // at most 16,384 queries at a time: about 100 KB of scratch each, and the points are decoded again for each such part
+        const int parts = (nq + 16383) / 16384, per = (nq + parts - 1) / parts;
+        int rc = AVQ_OK;
+        for (int q0 = 0; q0 < nq && rc == AVQ_OK; q0 += per)
+            rc = search_product(idx, queries + (size_t)q0 * c.d, std::min(per, nq - q0), k, reorder_k, R, ns, u8,
+                                ids_out + (size_t)q0 * k, scores_out + (size_t)q0 * k, st);
+        if (rc != AVQ_ENOMEM) return rc; // no room for its scratch (nothing of that part was launched): the other paths take less
     }
     // Batches of 8-bit codes on a flat index: the same search through block bounds, the full scan taking the queries
     // sixteen at a time (byte tables of six bits); "scan_prefilter" = 1 scores every point instead

@@ -368,6 +368,60 @@ int launch_ivf_refine(const IvfRefineParams &r, hipStream_t st);
 int launch_gather_rows(const float *src, float *dst, const int32_t *row, const uint32_t *count, int max_rows,
                        int row_floats, hipStream_t st);
 
+// ---- product.hip -----------------------------------------------------------
+// Batches on a flat index of at most 256 dimensions: candidates from a matrix product of the queries with the decoded
+// points, scored again the way every scan scores them. launch_product_pack -> launch_product_scan(sample) ->
+// launch_product_bound -> launch_product_scan -> launch_product_refine, which answers every query but those it appends to
+// fail_list (fail_count is cleared by the pack launch); a plain scan of those, and launch_product_fallback.
+struct ProductMeta;
+struct ProductQuery;
+constexpr size_t kProductInfoBytes = 16; // of either
+struct ProductPlan {
+    int64_t groups, sample_groups;  // workgroups that share the points
+    int32_t steps, n_tiles;         // 16 dimensions each; 32 queries each
+    int32_t stages_per_chunk, chunks, sample_stages_per_chunk, sample_chunks;
+    int32_t stride, run, n_classes, r; // the sample: every stride-th 32 points, run products a class, the r-th largest class
+    int32_t kept_cap, cnt_stride;
+};
+bool product_supported(int d, int M, int64_t n, int R);
+ProductPlan product_plan(int nq, int64_t n, int d, int R, bool u8);
+struct ProductParams {
+    const uint8_t *codes;  // blocked layout
+    const void *cb16;      // f16 [M][kc][d / M], scaled
+    const void *packed;    // f16 [n_tiles][steps][64][8], scaled
+    ProductMeta *meta;
+    ProductQuery *qinfo;   // [nq]
+    float *thr;            // [n_tiles * 32 + 64]: the line a kept product reaches
+    float *classes;        // sample: [nq][n_classes]
+    u64 *kept;             // [nq][kept_cap]: ordering value of the product << 32 | point
+    uint32_t *kept_cnt;    // [nq * cnt_stride]
+    int64_t n, groups;
+    int32_t nq, d, M, bits, NB, n_tiles, stages_per_chunk, chunks, stride, run, n_classes, kept_cap, cnt_stride;
+};
+int launch_product_pack(const ProductParams &p, const float *queries, const float *codebooks, uint32_t *fail_count, hipStream_t st);
+int launch_product_scan(const ProductParams &p, bool sample, hipStream_t st);
+// unit: [nq] the 8-bit tables' scale, NULL with fp32 tables
+int launch_product_bound(const ProductParams &p, int r, const float *unit, float *margin, float *guess, hipStream_t st);
+struct ProductRefineParams {
+    const u64 *kept;
+    const uint32_t *kept_cnt;
+    const float *margin;        // [nq], < 0: the product decides nothing
+    const float *guess;         // [nq]: the line was guess - margin
+    const float *queries, *codebooks, *x;
+    const uint8_t *codes;       // logical [n][NB], readable to the next multiple of four bytes
+    const uint8_t *lut8;        // 8-bit tables (with scale and bias), else unused
+    const float *scale, *bias;
+    int32_t *ids_out;           // [nq][k]
+    float *scores_out;
+    int32_t *fail_list;
+    uint32_t *fail_count;
+    void *fail_lut;             // the tables of the queries in fail_list, side by side
+    int32_t kept_cap, cnt_stride, nq, d, M, NB, R, k, reorder, force_fail_odd;
+};
+int launch_product_refine(const ProductRefineParams &r, bool u8, int bits, hipStream_t st);
+// The answers of the queries in fail_list from the lists of a scan with active_queries set, at most max_chunks chunks.
+int launch_product_fallback(const ProductRefineParams &r, const u64 *partial, int max_chunks, int tile_queries, int ns, bool u8, hipStream_t st);
+
 // ---- ivf.hip ---------------------------------------------------------------
 // centers_t: [d][n_leaves] (transposed). Writes the L best leaves per query.
 // The (query, probed leaf) pairs of a batch regrouped by leaf, for the matrix-core scan (see

@@ -1,0 +1,131 @@
+"""Batches through the product of the queries with the decoded points, against the oracle: where tiles of 32 queries, groups of
+32 to 512 points, steps of 16 dimensions, kinds of subspaces and code rows meet their edges; queries that the product decides
+nothing for; the rule that picks this path."""
+import numpy as np
+import pytest
+
+import oracle
+from util import unit_rows
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+avq = pytest.importorskip("paper_1908_10396_amd")
+
+
+def index(x, cb, codes, bits):
+    idx = avq.Index(x.shape[1], codes.shape[1], bits)
+    idx.set_codebooks(cb)
+    idx.set_database(torch.from_numpy(x).cuda(), torch.from_numpy(oracle.pack_codes(codes, bits)).cuda())
+    return idx
+
+
+def check(x, cb, codes, bits, q, k, R, unverified=0):
+    idx = index(x, cb, codes, bits)
+    idx.set_tuning("scan_product", 2)
+    qd = torch.from_numpy(q).cuda()
+    for mode in (avq.LUT_F32, avq.LUT_U8):
+        oi, os_ = oracle.search(x, cb, codes, bits, q, k, R, mode)
+        for prefilter in (0, 2):  # 2: every odd query goes to the plain scan
+            idx.set_tuning("scan_prefilter", prefilter)
+            ids, sc = idx.search(qd, k, R, mode)
+            np.testing.assert_array_equal(ids.cpu().numpy(), oi, err_msg="tables %d prefilter %d" % (mode, prefilter))
+            np.testing.assert_array_equal(sc.cpu().numpy(), os_, err_msg="tables %d prefilter %d" % (mode, prefilter))
+            if prefilter == 2:
+                assert idx.debug_unverified_queries() >= len(q) // 2
+            elif unverified is not None:
+                assert idx.debug_unverified_queries() == unverified
+
+
+def draw(n, d, M, bits, nq, seed=0):
+    rng = np.random.default_rng(n + 7 * d + M + nq + seed)
+    kc = 1 << bits
+    cb = (rng.standard_normal((M, kc, d // M)) * 0.2).astype(np.float32)
+    return unit_rows(rng, n, d), cb, rng.integers(0, kc, (n, M)).astype(np.uint8), unit_rows(rng, nq, d)
+
+
+# one point more than results; the edges of 32 points, of a block, of a workgroup's points; one query, the edges of a tile, of
+# a stage of two tiles and of 128; every kind of subspace (1, 2, 3, 4, 5, 8, 12, 16, 24 dimensions) and number of steps, codes
+# that do not fit the decoder's buffer; rows of 1 to 128 bytes
+@pytest.mark.parametrize("n,d,M,bits,nq,k,R", [
+    (11, 32, 16, 4, 1, 10, 0), (31, 32, 16, 4, 31, 1, 3), (33, 16, 8, 4, 32, 5, 20), (255, 48, 16, 4, 33, 10, 100),
+    (257, 64, 32, 4, 63, 10, 100), (511, 80, 20, 8, 64, 10, 100), (513, 96, 12, 4, 65, 10, 50), (1025, 100, 50, 4, 127, 10, 100),
+    (2049, 105, 35, 4, 129, 10, 100), (5000, 100, 25, 8, 40, 10, 200), (4097, 128, 64, 4, 96, 100, 512), (3000, 144, 6, 4, 20, 10, 100),
+    (3001, 160, 10, 8, 20, 10, 100), (2500, 192, 96, 4, 70, 10, 100), (1500, 224, 224, 4, 18, 10, 60), (1300, 256, 32, 8, 17, 10, 100),
+    (1400, 256, 256, 4, 33, 10, 100), (1100, 60, 60, 8, 16, 10, 100), (1200, 6, 3, 4, 50, 10, 100), (1000, 2, 1, 4, 20, 3, 10),
+    (900, 25, 5, 4, 20, 10, 64), (901, 36, 9, 8, 20, 10, 64), (1800, 128, 128, 4, 20, 10, 100), (700, 15, 15, 8, 20, 10, 0),
+    (40_000, 32, 16, 4, 300, 10, 100), (70_001, 64, 32, 4, 40, 10, 100), (60_000, 100, 25, 8, 33, 10, 10)])
+def test_product_matches(n, d, M, bits, nq, k, R):
+    # few code values against many results: ties, and more than the refinement holds, are in these draws too
+    check(*draw(n, d, M, bits, nq)[:3], bits, draw(n, d, M, bits, nq)[3], k, R, None)
+
+
+# The guess holds, and what it lets through fits, for data without many equal sums.
+@pytest.mark.parametrize("n,d,M,bits,nq", [(30_000, 100, 50, 4, 200), (30_000, 100, 25, 8, 200), (260_000, 64, 32, 4, 64)])
+def test_product_answers_all(n, d, M, bits, nq):
+    x, cb, codes, q = draw(n, d, M, bits, nq)
+    check(x, cb, codes, bits, q, 10, 100, 0)
+
+
+# Queries of zeros and copies of one point (every product the same: the plain scan answers, ties to the lower id), negative
+# scores throughout, values of all magnitudes, a dictionary without a range for its 8-bit tables.
+def test_product_odd_values():
+    x, cb, codes, q = draw(6000, 32, 16, 4, 40)
+    q[3] = 0.0
+    check(x, cb, codes, 4, q, 10, 100, None)
+    check(x, cb, np.repeat(codes[:1], 6000, 0), 4, q, 10, 100, None)
+    check(x, cb, codes[np.random.default_rng(0).integers(0, 3, 6000)], 4, q, 10, 50, None)
+    check(np.abs(x), -np.abs(cb), codes, 4, np.abs(q), 10, 100, None)
+    q2 = q * np.logspace(-20, 17, 40)[:, None].astype(np.float32)
+    check(x, cb, codes, 4, q2.astype(np.float32), 10, 100, None)
+    check(x, (cb * 1e-20).astype(np.float32), codes, 4, q, 10, 100, None)
+    check(x, (cb * 1e15).astype(np.float32), codes, 4, q, 10, 100, None)
+    check(x, np.repeat(cb[:, :1], 16, 1).copy(), codes, 4, q, 10, 100, None)
+
+
+# Which batches take this path: profile stage "sample" counts the sampling launch, "rescan" is one of its launches too, and
+# the path over 8-bit tables or over block bounds records "merge" or "final" instead.
+@pytest.mark.parametrize("n,d,M,bits,nq,k,R,mode,product", [
+    (100_000, 32, 16, 4, 15, 10, 100, 0, False), (100_000, 32, 16, 4, 1000, 10, 100, 0, True), (16_000, 32, 16, 4, 2047, 10, 100, 0, False),
+    (16_000, 32, 16, 4, 2048, 10, 100, 0, True), (16_000, 32, 16, 4, 2048, 10, 200, 0, False), (16_000, 32, 16, 4, 2048, 10, 20, 1, False),
+    (40_000, 32, 16, 4, 1000, 10, 100, 1, False), (40_000, 32, 16, 4, 1000, 10, 10, 1, True), (20_000, 36, 9, 8, 16, 10, 100, 0, True),
+    (20_000, 36, 9, 8, 15, 10, 100, 0, False), (4000, 100, 25, 8, 64, 10, 100, 0, False), (4000, 100, 25, 8, 1000, 10, 100, 1, True),
+    (20_000, 64, 32, 4, 100, 10, 100, 1, True), (3000, 260, 130, 4, 500, 10, 100, 0, False)])
+def test_rule_of_product(n, d, M, bits, nq, k, R, mode, product):
+    x, cb, codes, q = draw(n, d, M, bits, nq)
+    idx = index(x, cb, codes, bits)
+    idx.profile_enable()
+    qd = torch.from_numpy(q).cuda()
+    ids, sc = idx.search(qd, k, R, mode)
+    stages = idx.profile_read()
+    assert (stages["sample"][1] > 0 and stages["finalize"][1] == 0) == product
+    idx.set_tuning("scan_product", 1)
+    ids1, sc1 = idx.search(qd, k, R, mode)
+    assert torch.equal(ids, ids1) and torch.equal(sc, sc1)
+
+
+# More queries than one part of a call takes, and a call that is captured and replayed with other queries in the same place.
+def test_product_parts_and_capture():
+    x, cb, codes, q = draw(20_000, 32, 16, 4, 20_000)
+    idx = index(x, cb, codes, 4)
+    qd = torch.from_numpy(q).cuda()
+    idx.set_tuning("scan_product", 2)
+    ids, sc = idx.search(qd, 10, 50, avq.LUT_F32)
+    for lo in (0, 9_990, 19_900):
+        a, b = idx.search(qd[lo:lo + 100], 10, 50, avq.LUT_F32)
+        assert torch.equal(ids[lo:lo + 100], a) and torch.equal(sc[lo:lo + 100], b)
+    buf = qd[:500].clone()
+    out = (torch.empty((500, 10), dtype=torch.int32, device="cuda"), torch.empty((500, 10), device="cuda"))
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        idx.search(buf, 10, 50, avq.LUT_F32, out=out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        idx.search(buf, 10, 50, avq.LUT_F32, out=out)
+    for lo in (500, 3000, 700):
+        buf.copy_(qd[lo:lo + 500])
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], ids[lo:lo + 500]) and torch.equal(out[1], sc[lo:lo + 500])
