@@ -306,7 +306,7 @@ def main():
         # the product of the queries with the decoded points: 2 d operations a pair, d rounded up to the kernel's steps of 16
         steps = (d + 15) // 16
         steps += steps & 1 if steps > 8 else 0
-        executed = 2.0 * 16 * steps * scanned * (-(-B // 64) * 64)
+        executed = 2.0 * 16 * steps * scanned * (B if n_leaves else -(-B // 64) * 64)   # (leaves: without the padding of their tiles)
         r = {"bound": "mfma", "achieved": 2.0 * d * scanned * B / (ms * 1e-3) / 1e12, "peak": MFMA_F16_PEAK_TOPS, "unit": "TOP/s",
              "kernel": kernel, "avg_launch_ms": ms, "mfma_pipe_util": executed / (ms * 1e-3) / 1e12 / MFMA_F16_PEAK_TOPS,
              "table_adds_TOPs": method_ops / (ms * 1e-3) / 1e12,
@@ -320,9 +320,9 @@ def main():
 
     def product_kernel():
         steps = (d + 15) // 16
-        return "product_scan_kernel<%d,%d,false>" % ((steps, 4) if steps <= 8 else (steps + (steps & 1), 2))
+        return ("product_leaf_kernel<%d,%d,false>" if n_leaves else "product_scan_kernel<%d,%d,false>") % ((steps, 4) if steps <= 8 else (steps + (steps & 1), 2))
 
-    by_product = not n_leaves and not small and stage_ms.get("merge", 0.0) == 0.0 and stage_ms.get("sample", 0.0) > 0.0 \
+    by_product = not small and stage_ms.get("merge", 0.0) == 0.0 and stage_ms.get("sample", 0.0) > 0.0 \
         and stage_ms.get("finalize", 0.0) == 0.0
     fp32_direct = None
     if by_product:
@@ -331,8 +331,10 @@ def main():
         batch_roof = product_roofline(scan_ms, product_kernel(), {
             "traffic": traffic, "traffic_source": src, "sample_stage_ms": stage_ms.get("sample", 0.0),
             "queries_scanned_again": unverified[0], "of_which_too_many_kept_or_bound_too_high_or_other": unverified[1:],
-            "stages_note": "the launch over all points; before it, timed apart (sample_stage_ms), a launch over a sample of the points "
-                           "and the bounds guessed from it; scores with tables and the exact scores are the rescan stage"})
+            "stages_note": ("the second launch over the points of the probed leaves; before it, timed apart (sample_stage_ms), the regrouping, "
+                            "a first such launch that keeps the largest products and the bounds from them" if n_leaves else
+                            "the launch over all points; before it, timed apart (sample_stage_ms), a launch over a sample of the points "
+                            "and the bounds guessed from it") + "; scores with tables and the exact scores are the rescan stage"})
         idx.set_tuning("scan_prefilter", 1)   # the same step with every point scored with tables
         dt_d, stage_d = timed_batch(avq.LUT_F32, max(2, args.steps // 5))
         idx.set_tuning("scan_prefilter", 0)

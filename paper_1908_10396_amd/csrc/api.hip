@@ -891,7 +891,7 @@ static int search_product(avq_index *idx, const float *queries, int nq, int k, i
     {
         StageTimer t(idx, AVQ_STAGE_LUT, st);
         if (u8) AVQ_TRY(build_tables(idx, queries, nq, AVQ_LUT_U8, st));
-        AVQ_TRY(launch_product_pack(p, queries, idx->codebooks.as<float>(), fail_count, st));
+        AVQ_TRY(launch_product_pack(p, queries, idx->codebooks.as<float>(), fail_count, false, st));
     }
     {
         StageTimer t(idx, AVQ_STAGE_SAMPLE, st);
@@ -900,7 +900,7 @@ static int search_product(avq_index *idx, const float *queries, int nq, int k, i
         p.chunks = pl.sample_chunks;
         p.stride = pl.stride;
         AVQ_TRY(launch_product_scan(p, true, st));
-        AVQ_TRY(launch_product_bound(p, pl.r, u8 ? idx->scale.as<float>() : nullptr, margin, guess, st));
+        AVQ_TRY(launch_product_bound(p, pl.r, u8 ? idx->scale.as<float>() : nullptr, margin, guess, nullptr, 0, st));
     }
     {
         StageTimer t(idx, AVQ_STAGE_SCAN, st); // the launch over all points, nothing else
@@ -1094,6 +1094,171 @@ static int search_leaves_grouped(avq_index *idx, const float *queries, int nq, i
     StageTimer t(idx, AVQ_STAGE_FINAL, st);
     return launch_finalize(idx->refined.as<u64>(), ns, nq, R, k, reorder_k != 0, 0, idx->x, c.d, queries,
                            idx->scale.as<float>(), idx->bias.as<float>(), ids_out, scores_out, st);
+}
+
+// Batches on a partitioned index through the product of the queries with the decoded points of the leaves they probe
+// (product_leaf.hip). Measured, other path / product, us a call, by the points scored (queries x probed leaves x points of a leaf), 4-bit
+// codes of 100 dimensions, R = 100: 1e7 137 / 124 (500 queries), 1.5e7 185 / 282 (30 of 1,000 leaves, 15 queries each), 1.8e7 266 / 220,
+// 6e7 536 / 313, 6e8 2,822 / 1,222; R = 500 2,434 / 565 at 1.2e8. Code sizes without kernels of their own are 1.1 to 5.5 times as fast
+// from 2.5e7 on. 8-bit codes of 256 dimensions, 50 queries a leaf: 479 / 508 (the decoding); 8-bit tables, R = 500: 1,216 / 1,344 at 6e7.
+static bool use_product_leaves(const avq_index *idx, int nq, int L, int R, bool u8)
+{
+    const avq_config &c = idx->cfg;
+    if (idx->tune_product == 1 || c.n_leaves <= 0 ||
+        !product_leaf_supported(c.d, c.M, c.n_leaves, idx->n_blocks, idx->max_leaf_blocks, nq, L, R)) return false;
+    if (idx->tune_product == 2) return true;
+    // any tuning of the other kernels' launches asks for those kernels
+    if (idx->tune_target_wgs || idx->tune_waves || idx->tune_qt || idx->tune_mfma || idx->tune_prefilter == 1 || idx->tune_prefilter_cap ||
+        idx->tune_sample || idx->tune_small_impl || idx->tune_small_batch >= 0 || idx->tune_group_min || idx->tune_bound_leaves) return false;
+    const double work = (double)nq * L * ((double)idx->n / c.n_leaves); // points scored
+    if (c.bits == 8 && c.d > 128 && (double)nq * L < 100.0 * c.n_leaves) return false;
+    return nq >= 64 && work >= (u8 && R > 256 ? 1e8 : 2.5e7);
+}
+
+static int search_leaves_product(avq_index *idx, const float *queries, int nq, int k, int reorder_k, int R, int ns, int L, bool u8,
+                                 int32_t *ids_out, float *scores_out, hipStream_t st)
+{
+    const avq_config &c = idx->cfg;
+    const int C = 64 * ns;
+    const ProductLeafPlan pl = product_leaf_plan(nq, L, c.n_leaves, idx->n, idx->n_blocks, idx->max_leaf_blocks, c.d, R, u8);
+    const int64_t pairs = (int64_t)nq * L;
+    ProductLeafParams p;
+    memset(&p, 0, sizeof(p));
+    p.base.codes = idx->codes_blocked.as<uint8_t>();
+    p.base.n = idx->n_blocks * kBlockPoints;
+    p.base.nq = nq; p.base.d = c.d; p.base.M = c.M; p.base.bits = c.bits; p.base.NB = idx->NB;
+    p.base.n_tiles = pl.n_tiles;
+    p.base.n_classes = pl.n_classes;
+    p.base.kept_cap = pl.kept_cap;
+    p.base.cnt_stride = pl.cnt_stride;
+    p.L = L;
+    p.run = pl.run;
+    p.pair_classes = pl.pair_classes;
+    // scratch, 256-byte aligned pieces
+    size_t off = 0;
+    auto take = [&](size_t bytes) -> size_t { const size_t at = (off + 255) & ~(size_t)255; off = at + bytes; return at; };
+    const size_t class_bytes = sizeof(uint32_t) * (size_t)nq * pl.n_classes;
+    const size_t o_cb = take((size_t)c.M * idx->kc * idx->ds * 2), o_packed = take((size_t)pl.n_tiles * pl.steps * 1024),
+                 o_meta = take(kProductInfoBytes), o_q = take(kProductInfoBytes * (size_t)nq), o_thr = take(sizeof(float) * (size_t)pl.n_tiles * 32),
+                 o_margin = take(sizeof(float) * (size_t)nq * 2), o_classes = take(class_bytes), o_kept = take(sizeof(u64) * (size_t)nq * pl.kept_cap),
+                 o_slot = take(sizeof(uint16_t) * (size_t)nq * pl.kept_cap), o_cnt = take(sizeof(uint32_t) * (size_t)nq * pl.cnt_stride),
+                 o_ip = take(sizeof(float) * (size_t)pairs), o_line = take(sizeof(float) * (size_t)pairs),
+                 o_items = take(sizeof(uint2) * (size_t)pl.most_items), o_ni = take(sizeof(uint32_t));
+    AVQ_TRY(idx->product.reserve(off));
+    AVQ_TRY(idx->leaf_ids.reserve(sizeof(int32_t) * (size_t)pairs));
+    AVQ_TRY(idx->leaf_ip.reserve(sizeof(float) * (size_t)pairs));
+    // cleared in pieces of 16 bytes, from a piece's start on: the counters lie last in groups
+    AVQ_TRY(idx->groups.reserve(sizeof(uint32_t) * group_by_leaf_words(nq, L, c.n_leaves) + 32));
+    LeafGroups g;
+    AVQ_TRY(group_by_leaf_lay_out(nq, L, c.n_leaves, idx->groups.as<uint32_t>(), &g));
+    g.cnt_wide = (uint32_t *)(((uintptr_t)g.cnt_wide + 15) & ~(uintptr_t)15);
+    unsigned char *base = (unsigned char *)idx->product.p;
+    p.base.cb16 = base + o_cb;
+    p.base.packed = base + o_packed;
+    p.base.meta = (ProductMeta *)(base + o_meta);
+    p.base.qinfo = (ProductQuery *)(base + o_q);
+    p.base.thr = (float *)(base + o_thr);
+    p.base.classes = (float *)(base + o_classes);
+    p.base.kept = (u64 *)(base + o_kept);
+    p.base.kept_cnt = (uint32_t *)(base + o_cnt);
+    p.kept_slot = (uint16_t *)(base + o_slot);
+    p.classes = (uint32_t *)(base + o_classes);
+    p.pair_ip = (float *)(base + o_ip);
+    p.pair_line = (float *)(base + o_line);
+    p.perm = idx->perm.as<int32_t>();
+    p.leaf_blk = idx->leaf_blk.as<int32_t>();
+    p.leaf_off = g.leaf_off;
+    p.leaf_cnt = g.leaf_cnt;
+    p.qlist = g.qlist;
+    uint2 *items = (uint2 *)(base + o_items);
+    uint32_t *n_items = (uint32_t *)(base + o_ni);
+    p.items = items;
+    p.n_items = n_items;
+    float *margin = (float *)(base + o_margin), *guess = margin + nq;
+    // the plain scan over the leaves of the queries that are handed back
+    ScanShape shape;
+    if (scan_pick_shape(idx->NB, c.bits, u8, ns, nq, true, 0, 16, &shape) != AVQ_OK) AVQ_TRY(scan_pick_shape(idx->NB, c.bits, u8, ns, nq, true, 0, 0, &shape));
+    AVQ_TRY(idx->partial.reserve(sizeof(u64) * (size_t)nq * C));
+    if (shape.lists_global) AVQ_TRY(idx->lists.reserve(sizeof(u64) * (size_t)nq * shape.waves * shape.qt * C));
+    const size_t lut_row = u8 ? (size_t)c.M * idx->kc / 4 : (size_t)c.M * idx->kc; // 4-byte units
+    AVQ_TRY(idx->lut_fail.reserve(sizeof(float) * (size_t)nq * lut_row));
+    AVQ_TRY(idx->fail_rows.reserve(sizeof(float) * (size_t)nq * (2 + (size_t)2 * L)));
+    AVQ_TRY(idx->fail.reserve(sizeof(int32_t) * (4 + (size_t)nq)));
+    uint32_t *fail_count = idx->fail.as<uint32_t>();
+    int32_t *fail_list = idx->fail.as<int32_t>() + 4;
+    if (u8) {
+        StageTimer t(idx, AVQ_STAGE_LUT, st);
+        AVQ_TRY(build_tables(idx, queries, nq, AVQ_LUT_U8, st));
+    }
+    {
+        StageTimer t(idx, AVQ_STAGE_LEAF, st);
+        AVQ_TRY(launch_product_clear(g.cnt_wide, (sizeof(uint32_t) * (size_t)c.n_leaves * g.cnt_stride + 15) / 16 * 16, p.classes, class_bytes, st));
+        AVQ_TRY(launch_leaf_select(idx->centers_t.as<float>(), c.n_leaves, c.d, queries, nq, L, idx->leaf_ids.as<int32_t>(),
+                                   idx->leaf_ip.as<float>(), st, g.cnt_wide, g.pos, g.cnt_stride));
+    }
+    {
+        StageTimer t(idx, AVQ_STAGE_SAMPLE, st); // here: operands, regrouping, bounds
+        AVQ_TRY(launch_product_pack(p.base, queries, idx->codebooks.as<float>(), fail_count, true, st));
+        AVQ_TRY(launch_group_offsets(g, c.n_leaves, st));
+        AVQ_TRY(launch_product_pairs(p, idx->leaf_ids.as<int32_t>(), idx->leaf_ip.as<float>(), g.pos, c.n_leaves, items, pl.most_items, n_items, st));
+        AVQ_TRY(launch_product_leaf(p, true, pl.most_items, st));
+        AVQ_TRY(launch_product_bound(p.base, R, u8 ? idx->scale.as<float>() : nullptr, margin, guess, idx->leaf_ip.as<float>(), L, st));
+        AVQ_TRY(launch_product_lines(p, c.n_leaves, st));
+    }
+    {
+        StageTimer t(idx, AVQ_STAGE_SCAN, st); // the launch over all leaves, nothing else
+        AVQ_TRY(launch_product_leaf(p, false, pl.most_items, st));
+    }
+    StageTimer t(idx, AVQ_STAGE_RESCAN, st);
+    ProductLeafRefineParams r;
+    memset(&r, 0, sizeof(r));
+    r.base.kept = p.base.kept;
+    r.base.kept_cnt = p.base.kept_cnt;
+    r.base.margin = margin;
+    r.base.guess = guess;
+    r.base.queries = queries;
+    r.base.codebooks = idx->codebooks.as<float>();
+    r.base.x = idx->x;
+    r.base.codes = idx->codes_logical.as<uint8_t>();
+    r.base.lut8 = u8 ? idx->lut8.as<uint8_t>() : nullptr;
+    r.base.scale = idx->scale.as<float>();
+    r.base.bias = idx->bias.as<float>();
+    r.base.ids_out = ids_out;
+    r.base.scores_out = scores_out;
+    r.base.fail_list = fail_list;
+    r.base.fail_count = fail_count;
+    r.base.fail_lut = idx->lut_fail.p;
+    r.base.kept_cap = pl.kept_cap; r.base.cnt_stride = pl.cnt_stride;
+    r.base.nq = nq; r.base.d = c.d; r.base.M = c.M; r.base.NB = idx->NB; r.base.R = R; r.base.k = k; r.base.reorder = reorder_k != 0;
+    r.base.force_fail_odd = idx->tune_prefilter == 2;
+    r.kept_slot = p.kept_slot;
+    r.perm = p.perm;
+    r.leaf_ids = idx->leaf_ids.as<int32_t>();
+    r.leaf_ip = idx->leaf_ip.as<float>();
+    r.fail_scale = idx->fail_rows.as<float>();
+    r.fail_bias = r.fail_scale + nq;
+    r.fail_ip = r.fail_bias + nq;
+    r.fail_ids = (int32_t *)(r.fail_ip + pairs);
+    r.L = L;
+    AVQ_TRY(launch_product_leaf_refine(r, u8, c.bits, st));
+    ScanParams pf;
+    fill_scan_params(idx, nq, R, ns, &pf);
+    pf.perm = p.perm;
+    pf.leaf_ids = r.fail_ids;
+    pf.leaf_ip = r.fail_ip;
+    pf.leaf_blk = p.leaf_blk;
+    pf.lut = idx->lut_fail.as<float>();
+    pf.lut8 = idx->lut_fail.as<uint8_t>();
+    pf.scale = r.fail_scale;
+    pf.bias = r.fail_bias;
+    pf.Lp = L;
+    pf.n_tiles = nq;
+    pf.n_chunks = 1;
+    pf.partial = idx->partial.as<u64>();
+    if (shape.lists_global) pf.lists_ws = idx->lists.as<u64>();
+    pf.active_queries = fail_count;
+    AVQ_TRY(launch_scan(pf, u8, SCAN_LEAVES, shape, st));
+    return launch_product_fallback(r.base, pf.partial, 1, 1, ns, false, st);
 }
 
 static int check_query_args(const avq_index *idx, const float *queries, int32_t nq, int32_t lut_mode)
@@ -1490,6 +1655,10 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
     // the single-query kernels compute short fp32 tables themselves (one launch less)
     const bool fuse_tables = small && idx->tune_small_impl != 1 && small_batch_can_fuse_tables(c.bits, c.M, c.d, u8);
     const bool prefilter = !small && use_prefilter(idx, nq, lut_mode, R);
+    if (ivf && use_product_leaves(idx, nq, leaves_to_search, R, u8)) {
+        const int rc = search_leaves_product(idx, queries, nq, k, reorder_k, R, ns, leaves_to_search, u8, ids_out, scores_out, st);
+        if (rc != AVQ_ENOMEM) return rc; // no room for its scratch (nothing was launched): the other paths take less
+    }
     const bool grouped = ivf && use_grouped_leaves(idx, nq, leaves_to_search, R);
     if (ivf && use_leaf_small(idx, nq, leaves_to_search))
         return search_leaves_small(idx, queries, nq, k, reorder_k, R, leaves_to_search, u8, ids_out, scores_out, st);

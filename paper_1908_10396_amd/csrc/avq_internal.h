@@ -398,10 +398,12 @@ struct ProductParams {
     int64_t n, groups;
     int32_t nq, d, M, bits, NB, n_tiles, stages_per_chunk, chunks, stride, run, n_classes, kept_cap, cnt_stride;
 };
-int launch_product_pack(const ProductParams &p, const float *queries, const float *codebooks, uint32_t *fail_count, hipStream_t st);
+// rows: packed as [query][steps][16]
+int launch_product_pack(const ProductParams &p, const float *queries, const float *codebooks, uint32_t *fail_count, bool rows, hipStream_t st);
 int launch_product_scan(const ProductParams &p, bool sample, hipStream_t st);
-// unit: [nq] the 8-bit tables' scale, NULL with fp32 tables
-int launch_product_bound(const ProductParams &p, int r, const float *unit, float *margin, float *guess, hipStream_t st);
+// unit: [nq] the 8-bit tables' scale, NULL with fp32 tables. leaf_ip [nq][L]: classes hold ordering values (0: none) of products plus
+// <q, center>; fewer than r of them: no line (-infinity).
+int launch_product_bound(const ProductParams &p, int r, const float *unit, float *margin, float *guess, const float *leaf_ip, int L, hipStream_t st);
 struct ProductRefineParams {
     const u64 *kept;
     const uint32_t *kept_cnt;
@@ -422,6 +424,44 @@ int launch_product_refine(const ProductRefineParams &r, bool u8, int bits, hipSt
 // The answers of the queries in fail_list from the lists of a scan with active_queries set, at most max_chunks chunks.
 int launch_product_fallback(const ProductRefineParams &r, const u64 *partial, int max_chunks, int tile_queries, int ns, bool u8, hipStream_t st);
 
+// ---- product_leaf.hip ------------------------------------------------------
+// The same on a partitioned index: launch_product_clear (counters, classes) -> launch_leaf_select -> launch_product_pack
+// (rows) -> launch_group_offsets -> launch_product_pairs -> launch_product_leaf(sample) -> launch_product_bound ->
+// launch_product_lines -> launch_product_leaf -> launch_product_leaf_refine -> plain scan and launch_product_fallback.
+struct ProductLeafPlan {
+    int64_t most_items;
+    int32_t steps, n_tiles, run, pair_classes, n_classes, cnt_stride, kept_cap; // run: points of a class; pair_classes: classes of a (query, leaf) pair
+};
+bool product_leaf_supported(int d, int M, int n_leaves, int64_t n_blocks, int64_t max_leaf_blocks, int nq, int L, int R);
+ProductLeafPlan product_leaf_plan(int nq, int L, int n_leaves, int64_t n, int64_t n_blocks, int64_t max_leaf_blocks, int d, int R, bool u8);
+struct ProductLeafParams {
+    ProductParams base;       // packed: rows [nq, rounded up][steps][16]; n: slots; kept: ordering value of the product plus <q, center> << 32 | slot of the index
+    uint16_t *kept_slot;      // [nq][kept_cap]: the leaf's place in the query's list
+    const int32_t *perm, *leaf_blk;
+    const uint32_t *leaf_off, *leaf_cnt; // [n_leaves]: a leaf's pairs
+    uint32_t *qlist;          // [pairs]: query << 9 | slot of the leaf in its list
+    float *pair_ip, *pair_line; // [pairs], scaled
+    uint32_t *classes;        // [nq][L][pair_classes] ordering values, 0: none
+    const uint2 *items;       // leaf, block << 8 | chunk of its queries
+    const uint32_t *n_items;
+    int32_t L, run, pair_classes;
+};
+int launch_product_clear(void *a, size_t a_bytes, void *b, size_t b_bytes, hipStream_t st);
+int launch_product_pairs(const ProductLeafParams &p, const int32_t *leaf_ids, const float *leaf_ip, const uint32_t *pos, int n_leaves,
+                         uint2 *items, int64_t most_items, uint32_t *n_items, hipStream_t st);
+int launch_product_lines(const ProductLeafParams &p, int n_leaves, hipStream_t st);
+int launch_product_leaf(const ProductLeafParams &p, bool sample, int64_t most_items, hipStream_t st);
+struct ProductLeafRefineParams {
+    ProductRefineParams base;
+    const uint16_t *kept_slot;
+    const int32_t *perm, *leaf_ids; // leaf_ids, leaf_ip: [nq][L]
+    const float *leaf_ip;
+    float *fail_scale, *fail_bias, *fail_ip; // rows of the queries in fail_list
+    int32_t *fail_ids;
+    int32_t L;
+};
+int launch_product_leaf_refine(const ProductLeafRefineParams &r, bool u8, int bits, hipStream_t st);
+
 // ---- ivf.hip ---------------------------------------------------------------
 // centers_t: [d][n_leaves] (transposed). Writes the L best leaves per query.
 // The (query, probed leaf) pairs of a batch regrouped by leaf, for the matrix-core scan (see
@@ -435,17 +475,21 @@ struct LeafGroups {
 inline size_t group_by_leaf_max_items(int nq, int Lp, int n_leaves) { return ((size_t)nq * Lp + 31) / 32 + (size_t)n_leaves; }
 size_t group_by_leaf_words(int nq, int Lp, int n_leaves);
 // prepare (lays out ws, clears the counts) -> launch_leaf_select(..., g.cnt_wide, g.pos, g.cnt_stride) -> launch_group_by_leaf
+// (lay_out: the first without the second)
 int group_by_leaf_prepare(int nq, int Lp, int n_leaves, uint32_t *ws, LeafGroups *g, hipStream_t st);
+int group_by_leaf_lay_out(int nq, int Lp, int n_leaves, uint32_t *ws, LeafGroups *g);
 int launch_group_by_leaf(const int32_t *leaf_ids, int nq, int Lp, int n_leaves, const LeafGroups &g, hipStream_t st);
 // The same selection for a handful of queries (L <= 512): scores by many small workgroups into keys[nq][n_leaves]
 // (scratch), then the L best per query.
 int launch_leaf_select_few(const float *centers_t, int n_leaves, int d, const float *queries, int nq, int L, u64 *keys,
                            int32_t *leaf_ids, float *leaf_ip, hipStream_t st);
 // leaf_cnt (optional): leaf_cnt[leaf * cnt_stride] is incremented once per selected (query, leaf) pair; leaf_pos
-// (optional, [nq][L]): the count before the pair's own increment, i.e. its place among the pairs of that leaf
+// (optional, [nq][L]): the count before the pair's own increment, i.e. its place among the pairs of that leaf.
 int launch_leaf_select(const float *centers_t, int n_leaves, int d, const float *queries, int nq,
                        int L, int32_t *leaf_ids, float *leaf_ip, hipStream_t st, uint32_t *leaf_cnt = nullptr,
                        uint32_t *leaf_pos = nullptr, int cnt_stride = 1);
+// running sums of the leaves' counts: leaf_cnt, leaf_off (and item_off, fill)
+int launch_group_offsets(const LeafGroups &g, int n_leaves, hipStream_t st);
 int launch_transpose(const float *in, int rows, int cols, float *out, hipStream_t st);
 
 // ---- layout.hip ------------------------------------------------------------

@@ -400,7 +400,7 @@ size_t group_by_leaf_words(int nq, int Lp, int n_leaves)
 
 // Lays the scratch out and clears the pair counts; leaf selection then counts (launch_leaf_select's
 // leaf_cnt = g.cnt_wide with g.cnt_stride), and launch_group_by_leaf does the rest.
-int group_by_leaf_prepare(int nq, int Lp, int n_leaves, uint32_t *ws, LeafGroups *g, hipStream_t st)
+int group_by_leaf_lay_out(int nq, int Lp, int n_leaves, uint32_t *ws, LeafGroups *g)
 {
     if (Lp > 512 || nq > (1 << 16) || n_leaves > (1 << 21)) { set_error("grouping by leaf: batch or partition too large"); return AVQ_EINVAL; }
     g->leaf_cnt = ws;
@@ -414,7 +414,21 @@ int group_by_leaf_prepare(int nq, int Lp, int n_leaves, uint32_t *ws, LeafGroups
     g->max_items = (int32_t)group_by_leaf_max_items(nq, Lp, n_leaves);
     g->cnt_wide = g->item_list + g->max_items;
     g->cnt_stride = spread_stride(n_leaves);
+    return AVQ_OK;
+}
+
+int group_by_leaf_prepare(int nq, int Lp, int n_leaves, uint32_t *ws, LeafGroups *g, hipStream_t st)
+{
+    AVQ_TRY(group_by_leaf_lay_out(nq, Lp, n_leaves, ws, g));
     AVQ_HIP(hipMemsetAsync(g->cnt_wide, 0, sizeof(uint32_t) * (size_t)n_leaves * g->cnt_stride, st));
+    return AVQ_OK;
+}
+
+int launch_group_offsets(const LeafGroups &g, int n_leaves, hipStream_t st)
+{
+    hipLaunchKernelGGL(group_offsets_kernel, dim3(1), dim3(1024), 0, st, g.cnt_wide, g.cnt_stride, g.leaf_cnt, n_leaves, g.leaf_off,
+                       g.item_off, g.fill, g.n_items);
+    AVQ_HIP(hipGetLastError());
     return AVQ_OK;
 }
 

@@ -129,3 +129,76 @@ def test_product_parts_and_capture():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out[0], ids[lo:lo + 500]) and torch.equal(out[1], sc[lo:lo + 500])
+
+
+# ---- partitioned indexes ----------------------------------------------------------------
+
+def draw_leaves(n, d, M, bits, nq, leaves, seed=0, skew=False):
+    rng = np.random.default_rng(n + 7 * d + M + nq + seed)
+    x, cb, codes, q = draw(n, d, M, bits, nq)
+    centers = (0.5 * unit_rows(rng, leaves, d)).astype(np.float32)
+    assign = rng.integers(0, leaves, n) if not skew else np.minimum(rng.geometric(0.3, n) - 1, leaves - 2)  # one leaf stays empty
+    return x, cb, codes, q, centers, assign.astype(np.int32)
+
+
+def check_leaves(x, cb, codes, bits, q, centers, assign, k, R, L):
+    idx = avq.Index(x.shape[1], codes.shape[1], bits, n_leaves=len(centers))
+    idx.set_codebooks(cb)
+    idx.set_leaf_centers(centers)
+    idx.set_database(torch.from_numpy(x).cuda(), torch.from_numpy(oracle.pack_codes(codes, bits)).cuda(), torch.from_numpy(assign).cuda())
+    idx.set_tuning("scan_product", 2)
+    qd = torch.from_numpy(q).cuda()
+    for mode in (avq.LUT_F32, avq.LUT_U8):
+        oi, os_ = oracle.search(x, cb, codes, bits, q, k, R, mode, centers=centers, assign=assign, leaves_to_search=L)
+        for prefilter in (0, 2):  # 2: every odd query goes to the plain scan
+            idx.set_tuning("scan_prefilter", prefilter)
+            ids, sc = idx.search(qd, k, R, mode, L)
+            np.testing.assert_array_equal(ids.cpu().numpy(), oi, err_msg="tables %d prefilter %d" % (mode, prefilter))
+            np.testing.assert_array_equal(sc.cpu().numpy(), os_, err_msg="tables %d prefilter %d" % (mode, prefilter))
+            assert prefilter == 0 or idx.debug_unverified_queries() >= len(q) // 2
+
+
+# a leaf's last block nearly empty or full, several blocks that share classes, leaves without points; fewer points than results;
+# classes of 64, 16 and 4 points; one query, the edges of a tile and of the 512 queries that a workgroup takes; steps of 16
+# dimensions in waves of two and of four; every kind of subspace
+@pytest.mark.parametrize("n,d,M,bits,nq,leaves,L,k,R,skew", [
+    (500, 32, 16, 4, 1, 20, 3, 10, 100, False), (3000, 100, 50, 4, 33, 11, 5, 10, 100, False), (5120, 64, 32, 4, 64, 20, 20, 10, 20, False),
+    (9000, 32, 16, 4, 40, 6, 4, 10, 50, True), (4000, 100, 25, 8, 31, 8, 8, 10, 100, False), (6000, 105, 35, 4, 32, 12, 6, 100, 0, False),
+    (2500, 192, 96, 4, 20, 5, 3, 10, 100, True), (2000, 256, 32, 8, 18, 7, 2, 10, 64, False), (3000, 160, 10, 8, 20, 9, 9, 10, 500, False),
+    (20_000, 32, 16, 4, 515, 5, 2, 10, 10, True), (1500, 128, 128, 4, 20, 10, 4, 10, 0, False), (30_000, 36, 9, 8, 50, 40, 10, 10, 100, False),
+    (700, 48, 16, 4, 20, 300, 40, 10, 100, False), (4000, 224, 28, 4, 20, 3, 2, 10, 300, False)])
+def test_product_leaves_match(n, d, M, bits, nq, leaves, L, k, R, skew):
+    check_leaves(*reorder_args(draw_leaves(n, d, M, bits, nq, leaves, skew=skew), bits), k, R, L)
+
+
+def reorder_args(drawn, bits):
+    x, cb, codes, q, centers, assign = drawn
+    return x, cb, codes, bits, q, centers, assign
+
+
+# A query of zeros, leaves far from the origin beside tight codes, negative scores, values of all magnitudes.
+def test_product_leaves_odd_values():
+    x, cb, codes, q, centers, assign = draw_leaves(6000, 32, 16, 4, 40, 12)
+    q[3] = 0.0
+    check_leaves(x, cb, codes, 4, q, centers, assign, 10, 100, 3)
+    check_leaves(x, (cb * 1e-3).astype(np.float32), codes, 4, q, centers * 100, assign, 10, 100, 4)
+    check_leaves(np.abs(x), -np.abs(cb), codes, 4, np.abs(q) + 0.01, -np.abs(centers), assign, 10, 100, 5)
+    q2 = (unit_rows(np.random.default_rng(1), 40, 32) * np.logspace(-15, 14, 40)[:, None]).astype(np.float32)
+    check_leaves(x, cb, codes, 4, q2, centers, assign, 10, 100, 5)
+
+
+@pytest.mark.parametrize("n,leaves,nq,L,product", [(20_000, 20, 256, 100 // 10, False), (20_000, 20, 2600, 10, True), (20_000, 20, 2400, 10, False)])
+def test_rule_of_product_leaves(n, leaves, nq, L, product):
+    x, cb, codes, q, centers, assign = draw_leaves(n, 32, 16, 4, nq, leaves)
+    idx = avq.Index(32, 16, 4, n_leaves=leaves)
+    idx.set_codebooks(cb)
+    idx.set_leaf_centers(centers)
+    idx.set_database(torch.from_numpy(x).cuda(), torch.from_numpy(oracle.pack_codes(codes, 4)).cuda(), torch.from_numpy(assign).cuda())
+    idx.profile_enable()
+    qd = torch.from_numpy(q).cuda()
+    ids, sc = idx.search(qd, 10, 100, avq.LUT_F32, L)
+    stages = idx.profile_read()
+    assert (stages["sample"][1] > 0 and stages["finalize"][1] == 0) == product
+    idx.set_tuning("scan_product", 1)
+    ids1, sc1 = idx.search(qd, 10, 100, avq.LUT_F32, L)
+    assert torch.equal(ids, ids1) and torch.equal(sc, sc1)
