@@ -4,15 +4,17 @@
 // points and centers. It is formed on the matrix cores in f16, with fp32 sums, and only has to name the few
 // centers that can be nearest: every s_j computed that way is within a bound E(x) of the real one (nearest_bound
 // below), so a center whose value is more than 2 E under the largest is not the nearest. Per point the kernel
-// keeps the two best centers and the third best value. Mostly the best one stands alone; a few points in a hundred
-// are decided between two centers, and a few in a thousand against all of them, by fp64 squared distances, lowest
+// keeps the two best centers and what bounds the third best value. Mostly the best one stands alone; a few points in a
+// hundred are decided between two centers, and a few in a thousand against all of them, by fp64 squared distances, lowest
 // index on ties: the assignment is that of an fp64 evaluation of every distance.
 //
-// 262,144 x 100 points, 2,000 centers: product and bookkeeping 0.20 ms (0.05 ms of matrix instructions, and about 90
-// vector instructions for every 32 x 32 values against seven matrix instructions: the vector operations are the longer of
-// the two; 16 of them only quiet the operands of a maximum), open points 0.05 ms;
-// every distance in fp64 took 21 ms. 1,183,514 points: 0.93 + 0.08 ms (73 ms).
+// 262,144 x 100 points, 2,000 centers: product and bookkeeping 0.139 ms (0.062 ms of matrix instructions at the 1.9 GHz it
+// runs at, 0.036 ms for the points' operands and the lists; the vector instructions, 65 for every 32 x 32 values against
+// seven matrix instructions, are the longer of the two that overlap), open points 0.05 ms; every distance in fp64 took 21 ms.
+// 1,183,514 points: 0.58 + 0.08 ms (73 ms). With the products and the vector instructions of a tile one after the other, four
+// of those for each value and a tile ahead, it was 0.20 and 1.05 ms.
 #include <cmath>
+#include <type_traits>
 #include "avq_internal.h"
 
 namespace avq {
@@ -124,8 +126,12 @@ __device__ __forceinline__ float nearest_bound(float nx, float ex, int terms, co
     return 1.001f * (ex * cn + (nx + ex) * ce + ((float)terms * 1.2e-7f + 1.91e-6f) * mag + 6.2e-5f * sqrtf((float)terms) * (nx + cn + kOne));
 }
 
-// 64 points per wave as two column tiles of 32 (their operands stay in registers), all centers as row tiles through
-// LDS, one tile ahead. A lane sees 16 centers of a tile for its point (lanes j and j + 32 share point j % 32).
+// 64 points per wave as two column tiles of 32 (their operands stay in registers; one column tile above 141 coordinates), all
+// centers as row tiles through LDS, up to two tiles ahead. A lane sees 16 centers of a tile for its point (lanes j and j + 32
+// share point j % 32). The products of one accumulator are issued between the vector instructions that look through the other
+// one, so that both units work (sched_barrier keeps the order). A group of
+// four values gives its largest to the three best and its second to a bound on what was passed over, 11.5 instructions instead
+// of 16 (0.175 -> 0.160 ms); a single tile to a stage leaves room for three waves per SIMD (0.160 -> 0.150).
 // assign[i] = nearest center; points that need fp64 go to pairs (point, center, center, -) and all_list (point).
 // cnt / pos (optional): as in launch_nearest.
 template <int NS, int CT>
@@ -134,42 +140,82 @@ nearest_mfma_kernel(const float *__restrict__ x, int64_t n, int d, const v8h *__
                     NearMeta *__restrict__ meta, int32_t *__restrict__ assign, int4 *__restrict__ pairs,
                     int32_t *__restrict__ all_list, uint32_t *__restrict__ cnt, int cnt_stride, uint32_t *__restrict__ pos)
 {
-    __shared__ __align__(16) v8h tile[2][NS * 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 31, h = lane >> 5;
+        constexpr int G = CT == 2 ? 4 : 2, Q = 4 * G; // the rows come in parts of G steps: Q quads of coordinates
+    constexpr int kStage = NS * 64, kRows = 4 * 32 * Q;
+    __shared__ __align__(16) v8h tile[2 * kStage + (kStage > kRows ? kStage : kRows)]; // three tiles; the third's place holds rows first
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, h = lane >> 5;
     const float scale = meta->scale;
+    auto to_lds16 = [](const void *src, v8h *dst) __attribute__((always_inline)) {
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+    };
+    auto to_lds4 = [](const void *src, v8h *dst) __attribute__((always_inline)) {
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)dst, 4, 0, 0);
+    };
+    auto stage = [&](int t, int slot) { // a tile is NS KB in operand order: each wave copies a quarter of it
+        for (int s = wave; s < NS; s += 4) to_lds16(packed + (size_t)t * kStage + s * 64 + lane, tile + slot * kStage + s * 64);
+    };
+    stage(0, 0);
+    if (n_tiles > 1) stage(1, 1);
+
+    // The operands of the points. A wave's rows go through LDS, a part of 16 G coordinates of 32 rows at a time, in pieces that
+    // are contiguous in memory (the code for rows read directly, by aligned quads or by single values, took 200 registers and
+    // more, or spilled them). Quad q of row r lies at place q ^ turn(r), so that
+    // lanes of different rows read different banks.
     v8h b[CT][NS];
     float nx[CT], ex[CT];
     bool far_out[CT];
     const int64_t p0 = (int64_t)blockIdx.x * (4 * CT * 32) + wave * (CT * 32);
+    const bool quad = (d & 3) == 0 && ((uintptr_t)x & 15) == 0;
+    v8h *rows = tile + 2 * kStage + wave * (32 * Q);
+    auto turned = [](int r) { return Q == 16 ? r & 15 : (r >> 1) & 7; };
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
-        const int64_t i = p0 + c * 32 + j;
-        const float *row = x + (size_t)(i < n ? i : n - 1) * d;
-        const bool quad = (d & 3) == 0 && ((uintptr_t)x & 15) == 0;
         float n2 = 0.0f, e2 = 0.0f, mx = 0.0f;
+        int own = d - 8 * h; // coordinate 16 s + u of this lane's half is one of the row's below this
+        asm volatile("" : "+v"(own)); // (compared anew for each column tile: kept, the results are a hundred registers)
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int l0 = 16 * s + 8 * h;
-            float v[8];
-            if (quad && l0 + 8 <= d) {
-                const float4 a = *(const float4 *)(row + l0), bb = *(const float4 *)(row + l0 + 4);
-                v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-                v[4] = bb.x; v[5] = bb.y; v[6] = bb.z; v[7] = bb.w;
+        for (int s0 = 0; s0 < NS; s0 += G) {
+            auto from = [&](int r, int l) { // coordinate l of row r; past the last ones: some in range, not used
+                const int64_t i = p0 + c * 32 + r;
+                return x + (size_t)(i < n ? i : n - 1) * d + l;
+            };
+            __builtin_amdgcn_s_waitcnt(0xc07f); // lgkmcnt(0): the part before this has been read
+            __builtin_amdgcn_sched_barrier(0);
+            if (quad) {
+#pragma unroll 4
+                for (int e = lane; e < 32 * Q; e += 64) {
+                    const int r = e / Q, l = 16 * s0 + 4 * ((e % Q) ^ turned(r));
+                    to_lds16(from(r, l < d ? l : d - 4), rows + (e - lane));
+                }
             } else {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = l0 + u < d ? row[l0 + u] : 0.0f;
+#pragma unroll 4
+                for (int e = lane; e < 32 * Q * 4; e += 64) {
+                    const int r = e / (4 * Q), l = 16 * s0 + 4 * ((e % (4 * Q) / 4) ^ turned(r)) + (e & 3);
+                    to_lds4(from(r, l < d ? l : d - 1), rows + (e - lane) / 4);
+                }
             }
+            __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0)
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float sv = v[u] * scale;
-                const _Float16 hv = (_Float16)fminf(fmaxf(sv, -kMaxCoord), kMaxCoord);
-                const float de = sv - (float)hv;
-                mx = fmaxf(mx, fabsf(sv));
-                n2 += sv * sv;
-                e2 += de * de;
-                b[c][s][u] = l0 + u >= d && l0 + u < d + 3 ? (_Float16)kOne : hv;
+            for (int g = 0; g < G && s0 + g < NS; ++g) {
+                const int s = s0 + g;
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const float4 a = *(const float4 *)(rows + j * Q + ((4 * g + 2 * h + u) ^ turned(j)));
+                    v[4 * u] = a.x; v[4 * u + 1] = a.y; v[4 * u + 2] = a.z; v[4 * u + 3] = a.w;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const float sv = 16 * s + u < own ? v[u] * scale : 0.0f;
+                    const _Float16 hv = (_Float16)fminf(fmaxf(sv, -kMaxCoord), kMaxCoord);
+                    const float de = sv - (float)hv;
+                    mx = fmaxf(mx, fabsf(sv));
+                    n2 += sv * sv;
+                    e2 += de * de;
+                    b[c][s][u] = 16 * s + u >= own && 16 * s + u < own + 3 ? (_Float16)kOne : hv;
+                }
             }
-            __builtin_amdgcn_sched_barrier(0); // a step's values at a time: all in flight would not fit the registers
         }
         n2 += __shfl_xor(n2, 32, 64);
         e2 += __shfl_xor(e2, 32, 64);
@@ -178,51 +224,103 @@ nearest_mfma_kernel(const float *__restrict__ x, int64_t n, int d, const v8h *__
         ex[c] = sqrtf(e2) * 1.0001f;
         far_out[c] = !(mx <= kMaxCoord);
     }
-    float best[CT], second[CT], third[CT];
+    float best[CT], second[CT], third[CT], passed[CT];
     int t_best[CT], t_second[CT];
 #pragma unroll
-    for (int c = 0; c < CT; ++c) { best[c] = second[c] = third[c] = -INFINITY; t_best[c] = t_second[c] = 0; }
+    for (int c = 0; c < CT; ++c) { best[c] = second[c] = third[c] = passed[c] = -INFINITY; t_best[c] = t_second[c] = 0; }
 
-    // a tile is NS KB in operand order: each wave copies NS / 4 of it
-    auto stage = [&](int t) {
-        const v8h *src = packed + (size_t)t * NS * 64;
-        v8h *dst = tile[t & 1];
-        for (int s = wave; s < NS; s += 4)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + s * 64 + lane),
-                                             (__attribute__((address_space(3))) void *)(dst + s * 64), 16, 0, 0);
+    // four of a tile's 16 values: their positions in the lowest bits, their largest into the three best, their second into what
+    // stands for a third best that was passed over (the maximum of IEEE 754-2019 quiets no operand first)
+    auto take = [&](int c, const v16f &value, int v) __attribute__((always_inline)) {
+        float a[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] = __uint_as_float((__float_as_uint(value[v + u]) & 0xfffffff0u) | (uint32_t)(v + u));
+        const float m3 = __builtin_elementwise_maximum(__builtin_elementwise_maximum(a[0], a[1]), a[2]);
+        const float s3 = __builtin_amdgcn_fmed3f(a[0], a[1], a[2]);
+        const float m4 = __builtin_elementwise_maximum(m3, a[3]), s4 = __builtin_amdgcn_fmed3f(m3, s3, a[3]);
+        passed[c] = __builtin_elementwise_maximum(passed[c], s4);
+        third[c] = __builtin_amdgcn_fmed3f(second[c], third[c], m4);
+        second[c] = __builtin_amdgcn_fmed3f(best[c], second[c], m4);
+        best[c] = __builtin_elementwise_maximum(best[c], m4);
     };
-    stage(0);
-    for (int t = 0; t < n_tiles; ++t) {
-        __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0): this wave's part of tile t is in LDS
-        __syncthreads();
-        if (t + 1 < n_tiles) stage(t + 1);
-        const v8h *a_tile = tile[t & 1];
-        v16f acc[CT];
+    // (the first values taken are below every real one; an infinity with position bits would be no number)
+    // one tile's products for one column tile (H), while the values before them (of column tile O and its tile t_old) are taken
+    v16f acc[2], zero;
 #pragma unroll
-        for (int c = 0; c < CT; ++c)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[c][v] = 0.0f;
+    for (int v = 0; v < 16; ++v) { zero[v] = 0.0f; acc[0][v] = acc[1][v] = -3e38f; }
+    v8h a[NS];
+    auto half = [&](auto which, const v8h *next, int t_old) __attribute__((always_inline)) {
+        constexpr int H = decltype(which)::value, O = 1 - H, ch = CT == 2 ? H : 0, co = CT == 2 ? O : 0;
+        const float b_old = best[co], s_old = second[co];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const v8h a = a_tile[s * 64 + lane];
+            acc[H] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[s], b[ch][s], s == 0 ? zero : acc[H], 0, 0, 0);
 #pragma unroll
-            for (int c = 0; c < CT; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b[c][s], acc[c], 0, 0, 0);
+            for (int q = 0; q < 4; ++q)
+                if (q * NS / 4 == s) take(co, acc[O], 4 * q);
+            asm volatile("" : "+v"(third[co]), "+v"(passed[co])); // here, not past the products that hide it
+            if (CT == 1 || H == 1) a[s] = next[s * 64 + lane];
+            __builtin_amdgcn_sched_barrier(0);
         }
+        int t_s = second[co] == b_old ? t_best[co] : t_old;
+        asm volatile("" : "+v"(t_s)); // selects, no branches
+        t_second[co] = second[co] == s_old ? t_second[co] : t_s;
+        t_best[co] = best[co] == b_old ? t_best[co] : t_old;
+    };
+    __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0): this wave's part of the first stages is in LDS
+    __syncthreads();
 #pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            const float b_old = best[c], s_old = second[c];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float a = __uint_as_float((__float_as_uint(acc[c][v]) & 0xfffffff0u) | (uint32_t)v);
-                third[c] = __builtin_amdgcn_fmed3f(second[c], third[c], a);
-                second[c] = __builtin_amdgcn_fmed3f(best[c], second[c], a);
-                best[c] = __builtin_amdgcn_fmed3f(INFINITY, best[c], a); // the larger
+    for (int s = 0; s < NS; ++s) a[s] = tile[s * 64 + lane];
+    int slot = 0;
+    auto after = [](int s) { return s == 2 ? 0 : s + 1; };
+    // the tile after t is there; every wave has left the one before t, whose place the one after next takes
+    auto turn = [&](int t) {
+        if (t + 1 < n_tiles) {
+            __builtin_amdgcn_s_waitcnt(0x0f70);
+            __syncthreads();
+            if (t + 2 < n_tiles) stage(t + 2, after(after(slot)));
+        }
+        slot = after(slot);
+    };
+    // (operands read beyond the last tile are not used)
+    if constexpr (CT == 2) {
+#pragma unroll 1
+        for (int t = 0; t < n_tiles; ++t) {
+            half(std::integral_constant<int, 0>{}, tile, t - 1);
+            turn(t);
+            half(std::integral_constant<int, 1>{}, tile + slot * kStage, t);
+        }
+    } else { // the tiles take turns with the accumulators
+#pragma unroll 1
+        for (int t = 0; t < n_tiles; t += 2) {
+            turn(t);
+            half(std::integral_constant<int, 0>{}, tile + slot * kStage, t - 1);
+            if (t + 1 < n_tiles) {
+                turn(t + 1);
+                half(std::integral_constant<int, 1>{}, tile + slot * kStage, t);
             }
-            t_second[c] = second[c] == s_old ? t_second[c] : (second[c] == b_old ? t_best[c] : t);
-            t_best[c] = best[c] == b_old ? t_best[c] : t;
         }
     }
+    // the last values
+    {
+        const bool odd = CT == 1 && (n_tiles & 1);
+        constexpr int c = CT - 1;
+        const float b_old = best[c], s_old = second[c];
+        const int t = n_tiles - 1;
+#pragma unroll
+        for (int v = 0; v < 16; v += 4) take(c, odd ? acc[0] : acc[1], v);
+        t_second[c] = second[c] == s_old ? t_second[c] : (second[c] == b_old ? t_best[c] : t);
+        t_best[c] = best[c] == b_old ? t_best[c] : t;
+    }
     const NearMeta m = *meta;
+    // the two lists' places are asked for once per workgroup (once per wave and column tile, the additions to one line took
+    // 0.015 ms of 0.175)
+    uint32_t *room = (uint32_t *)tile; // [0] pairs, [1] all of this workgroup, [2], [3] their places
+    __syncthreads();
+    if (tid < 2) room[tid] = 0u;
+    __syncthreads();
+    int kind[CT], own_b[CT], own_s[CT];
+    uint32_t at[CT];
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
         // center of accumulator v of half h: row 8 (v / 4) + 4 h + v % 4 of its tile
@@ -249,17 +347,32 @@ nearest_mfma_kernel(const float *__restrict__ x, int64_t n, int d, const v8h *__
             s1 = own ? s1 : b2;
         }
         const int64_t i = p0 + c * 32 + j;
+        r1 = fmaxf(r1, fmaxf(passed[c], __shfl_xor(passed[c], 32, 64)));
+        kind[c] = 0;
+        own_b[c] = ib;
+        own_s[c] = is;
         if (h != 0 || i >= n) continue;
         const float e2 = 2.0f * nearest_bound(nx[c], ex[c], NS * 16, m);
         // (equal best values: one of the two positions may be that of the other, both came from accumulators)
         if (far_out[c] || !(b1 - r1 > e2) || ib >= k || (!(b1 - s1 > e2) && (is >= k || b1 == s1))) {
-            all_list[atomicAdd(&meta->n_all, 1u)] = (int32_t)i;
+            kind[c] = 2;
+            at[c] = atomicAdd(&room[1], 1u);
         } else if (!(b1 - s1 > e2)) {
-            pairs[atomicAdd(&meta->n_pairs, 1u)] = make_int4((int)i, ib, is, 0);
+            kind[c] = 1;
+            at[c] = atomicAdd(&room[0], 1u);
         } else {
             assign[i] = ib;
             if (cnt) pos[i] = atomicAdd(&cnt[(size_t)ib * cnt_stride], 1u);
         }
+    }
+    __syncthreads();
+    if (tid < 2) room[2 + tid] = room[tid] ? atomicAdd(tid ? &meta->n_all : &meta->n_pairs, room[tid]) : 0u;
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        const int i = (int)(p0 + c * 32 + j);
+        if (kind[c] == 1) pairs[room[2] + at[c]] = make_int4(i, own_b[c], own_s[c], 0);
+        else if (kind[c] == 2) all_list[room[3] + at[c]] = i;
     }
 }
 

@@ -75,6 +75,23 @@ def test_nearest_leaf_is_that_of_fp64_distances(n, d, k, law):
     np.testing.assert_array_equal(idx.get_leaf_assign(), oracle.assign_nearest(x, c))
 
 
+# twins a given number of centers apart: in one group of four values (1, 2), in the other half-wave's rows (4), in another group
+# (8), in the next tile (32), with a point on each; one and two column tiles per wave, an odd and an even number of tiles
+@pytest.mark.parametrize("d", [12, 30, 100, 140, 150, 268])
+@pytest.mark.parametrize("k", [96, 128])
+@pytest.mark.parametrize("apart", [1, 2, 4, 8, 32])
+def test_twin_centers_anywhere_in_a_tile(d, k, apart):
+    rng = np.random.default_rng(d * 131 + k + apart)
+    c = unit_rows(rng, k, d)
+    half = (np.arange(k) // apart) % 2 == 1
+    c[half] = c[np.flatnonzero(half) - apart]
+    c[half, 0] = np.nextafter(c[half, 0], np.float32(2.0))
+    x = np.concatenate([c, unit_rows(rng, 900, d)])
+    idx = leaf_index(d, c)
+    idx.encode(dev(x))
+    np.testing.assert_array_equal(idx.get_leaf_assign(), oracle.assign_nearest(x, c))
+
+
 @pytest.mark.parametrize("n,d,k", [(64, 5, 64), (3001, 100, 70), (2000, 36, 300), (1500, 270, 9)])
 def test_leaf_centers_match(n, d, k):
     rng = np.random.default_rng(3)
