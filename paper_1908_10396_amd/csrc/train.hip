@@ -62,11 +62,12 @@ double eta_host(int d, double T, double norm, int mode) { return eta_of_norm(d, 
 // pairs (pq_lloyd_kernel) and one small kernel that turns the sums into codewords. The points are laid out by
 // coordinate first ([d][n], residuals formed once, in fp64, where there are leaf centers), so that a wave reads
 // 64 values of a coordinate side by side; from row-major points each lane would touch a line of its own.
-// The kernel is bound by fp64 arithmetic: per codeword and pair 2 ds + 1 operations for the distance and three for
-// the arg-min, the codewords being scalar operands. 262,144 points x 50 subspaces x 16 codewords of 2 dimensions:
-// 67 us an iteration (53 us at the rate of 140 such operations a pair) and 5 us for the codewords; with a launch
-// sequence per subspace, row-major points and one copy of the sums 51 + 5 + 9 us per subspace and iteration
-// (training as a whole 60.8 -> 1.4 ms).
+// The kernel is bound by vector instructions. For the usual subspace sizes it takes the largest <x, c> - ||c||^2 / 2 in
+// fp32, ds + 3 instructions for a codeword, where it leads the second by more than both can be off by; the others, one
+// pair in tens of thousands, and all pairs of other sizes are decided by fp64 distances, 3 ds + 3 instructions each (the same
+// rate, one by one). 262,144 points x 50 subspaces x 16 codewords of 2 dimensions: 46 us an iteration (67 all in fp64) and
+// 5 us for the codewords; with a launch sequence per subspace, row-major points and one copy of the sums 51 + 5 + 9 us per
+// subspace and iteration. Where codewords are equal, every pair near them takes both: 109 us if all 16 are.
 
 // x [n][d] -> xt [cols][n], columns col0 .. col0 + cols - 1; XT double: the residual to centers[assign[i]]
 template <typename XT>
@@ -109,24 +110,34 @@ pq_init_kernel(const XT *__restrict__ xt, int64_t n, int ds, int k, int m0, uint
     }
 }
 
-// One subspace (blockIdx.y) and per_block points per workgroup: the nearest codeword of every point (fp64 squared
-// distance, lowest index on ties), the point added to that codeword's sums in LDS, the workgroup's sums to
+// One subspace (blockIdx.y) and per_block points per workgroup: the nearest codeword of every point (by fp64
+// squared distances, lowest index on ties), the point added to that codeword's sums in LDS, the workgroup's sums to
 // part_sum[m][entry][blk] and part_cnt[m][codeword][blk]. `copies` of the sums side by side in LDS keep the lanes
 // of a wave, which share a few codewords, from adding to the same word: 32 of them put a wave's additions into
 // separate banks. copies = 0: the sums do not fit LDS and go to part_* (n_slots = 1, cleared before) directly.
 // DS = dimensions per subspace, KC = codewords (0: known at run time only).
 template <int DS, int KC, typename XT>
 __global__ void __launch_bounds__(256)
-pq_lloyd_kernel(const XT *__restrict__ xt, int64_t n, int ds_rt, int k_rt, int per_block, const double *__restrict__ cb64,
-                int copies, int n_slots, double *__restrict__ part_sum, uint32_t *__restrict__ part_cnt)
+pq_lloyd_kernel(const XT *__restrict__ xt, int64_t n, int ds_rt, int k_rt, int per_block, const float *__restrict__ cb32,
+                const double *__restrict__ cb64, int copies, int n_slots, double *__restrict__ part_sum, uint32_t *__restrict__ part_cnt)
 {
-    extern __shared__ __align__(16) double lloyd_lds[]; // [k * ds][copies], then uint32 [k][copies]
+    extern __shared__ __align__(16) double lloyd_lds[]; // [k * ds][copies], then uint32 [k][copies] and float [260]
     const int ds = DS ? DS : ds_rt, k = KC ? KC : k_rt;
     const int m = blockIdx.y, tid = threadIdx.x;
     double *lsum = lloyd_lds;
     uint32_t *lcnt = (uint32_t *)(lloyd_lds + (size_t)k * ds * copies);
     for (int e = tid; e < k * ds * copies; e += 256) lsum[e] = 0.0;
     for (int e = tid; e < k * copies; e += 256) lcnt[e] = 0u;
+    float *bias = (float *)(lcnt + k * copies), *c_max = bias + 256;
+    if constexpr (DS != 0) { // -||c||^2 / 2 of the codewords (at most 256) and their largest norm
+        double n2 = 0.0;
+        if (tid < k)
+            for (int l = 0; l < ds; ++l) { const double c = cb64[((size_t)m * k + tid) * ds + l]; n2 += c * c; }
+        bias[tid] = (float)(-0.5 * n2);
+        float cm = (float)sqrt(n2) * 1.0001f;
+        for (int w = 1; w < 64; w <<= 1) cm = fmaxf(cm, __shfl_xor(cm, w, 64));
+        if ((tid & 63) == 0) c_max[tid >> 6] = cm;
+    }
     __syncthreads();
     const double *cb = cb64 + (size_t)m * k * ds;
     const XT *xm = xt + (size_t)m * ds * n;
@@ -135,26 +146,64 @@ pq_lloyd_kernel(const XT *__restrict__ xt, int64_t n, int ds_rt, int k_rt, int p
     double *gsum = part_sum + (size_t)m * k * ds * n_slots;
     uint32_t *gcnt = part_cnt + (size_t)m * k * n_slots;
     const int copy = copies > 0 ? (tid & (copies - 1)) : 0;
+    const float *cf = cb32 + (size_t)m * k * ds;
+    const float cn = DS ? fmaxf(fmaxf(c_max[0], c_max[1]), fmaxf(c_max[2], c_max[3])) : 0.0f;
+    const float cb_half = 0.5f * cn * cn;
+    float bias16[16];
+    if constexpr (DS != 0 && KC == 16) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) bias16[u] = bias[u];
+    }
     for (int64_t i = first + tid; i < end; i += 256) {
         int best = 0;
-        double bestd = INFINITY;
         double xv[DS ? DS : 1];
         if constexpr (DS != 0) {
+            float xf[DS], xn = 0.0f; // xn: at least the norm
 #pragma unroll
-            for (int l = 0; l < DS; ++l) xv[l] = (double)xm[(size_t)l * n + i];
-#pragma unroll 16
-            for (int j = 0; j < k; ++j) {
-                double t = xv[0] - cb[j * DS];
-                double dd = t * t;
+            for (int l = 0; l < DS; ++l) {
+                xv[l] = (double)xm[(size_t)l * n + i];
+                xf[l] = (float)xv[l];
+                xn += fabsf(xf[l]);
+            }
+            // the two largest <x, c> - ||c||^2 / 2 in fp32, the codeword's place among 16 in the lowest bits
+            float top = -INFINITY, second = -INFINITY;
+            int block = 0;
+            for (int j0 = 0; j0 < k; j0 += 16) {
+                const float old = top;
 #pragma unroll
-                for (int l = 1; l < DS; ++l) {
-                    t = xv[l] - cb[j * DS + l];
-                    dd += t * t;
+                for (int u = 0; u < 16; ++u) {
+                    float v = KC == 16 ? bias16[u] : bias[j0 + u];
+#pragma unroll
+                    for (int l = 0; l < DS; ++l) v = __fmaf_rn(xf[l], cf[(j0 + u) * DS + l], v);
+                    v = __uint_as_float((__float_as_uint(v) & 0xfffffff0u) | (uint32_t)u);
+                    second = __builtin_amdgcn_fmed3f(top, second, v);
+                    top = __builtin_elementwise_maximum(top, v);
                 }
-                best = dd < bestd ? j : best;
-                bestd = fmin(dd, bestd);
+                block = top == old ? block : j0;
+            }
+            best = block + (int)(__float_as_uint(top) & 15u);
+            // what a value can be off by: x rounded to fp32, the bias and DS sums rounded, the place (2^-19 of it); the last
+            // two terms: products under the smallest normal number, and the rounding of the fp64 distances below
+            const float mag = xn * cn + cb_half;
+            const float e = ((float)(DS + 4) * 6.0e-8f + 1.91e-6f) * 1.01f * mag + 1e-36f + 1e-14f * (xn + cn) * (xn + cn);
+            if (!(top - second > 2.0f * e)) { // not by more than both can be off by: by fp64 distances, the lowest index on ties
+                double bestd = INFINITY;
+                best = 0;
+#pragma unroll 4
+                for (int j = 0; j < k; ++j) {
+                    double t = xv[0] - cb[j * DS];
+                    double dd = t * t;
+#pragma unroll
+                    for (int l = 1; l < DS; ++l) {
+                        t = xv[l] - cb[j * DS + l];
+                        dd += t * t;
+                    }
+                    best = dd < bestd ? j : best;
+                    bestd = fmin(dd, bestd);
+                }
             }
         } else {
+            double bestd = INFINITY;
             for (int j0 = 0; j0 < k; j0 += 8) { // k is a multiple of 16
                 double dd[8];
 #pragma unroll
@@ -253,15 +302,15 @@ static int pq_kmeans_group(const float *x, int64_t n, int d, int m0, int Mg, int
     hipLaunchKernelGGL(pq_init_kernel<XT>, dim3((unsigned)((k + 255) / 256), (unsigned)Mg), dim3(256), 0, st, xt, n, ds, k, m0, seed,
                        codebooks, cb64);
     const dim3 grid((unsigned)n_blk, (unsigned)Mg);
-    const size_t lds = copies * copy_bytes;
+    const size_t lds = copies * copy_bytes + 260 * sizeof(float);
     for (int it = 0; it < iters; ++it) {
         if (copies == 0) AVQ_HIP(hipMemsetAsync(part_sum, 0, b_sum + b_cnt, st));
 #define AVQ_LLOYD(DS, KC)                                                                                          \
     do {                                                                                                           \
         static LdsLimitOnce attr_done;                                                                             \
         AVQ_TRY(set_lds_limit((const void *)pq_lloyd_kernel<DS, KC, XT>, kMaxDynLds, &attr_done));                 \
-        hipLaunchKernelGGL((pq_lloyd_kernel<DS, KC, XT>), grid, dim3(256), lds, st, xt, n, ds, k, per_block, cb64, \
-                           copies, n_slots, part_sum, part_cnt);                                                   \
+        hipLaunchKernelGGL((pq_lloyd_kernel<DS, KC, XT>), grid, dim3(256), lds, st, xt, n, ds, k, per_block, codebooks, \
+                           cb64, copies, n_slots, part_sum, part_cnt);                                                   \
     } while (0)
         if (k == 16) {
             switch (ds) {

@@ -39,6 +39,31 @@ def test_dictionaries_of_all_subspaces_match(n, d, M, bits, residual):
     np.testing.assert_allclose(idx.get_codebooks(), want, rtol=0, atol=1.2e-7)
 
 
+# the fp32 search of every specialised size against fp64 distances: exact ties, values whose squares leave fp32, distances small
+# against the norms, a point repeated until codewords are equal
+@pytest.mark.parametrize("d,M,bits", [(3, 3, 4), (6, 3, 4), (6, 2, 4), (8, 2, 4), (4, 2, 8), (8, 2, 8), (16, 2, 8)])
+@pytest.mark.parametrize("law", ["lattice", "tiny", "huge", "far", "equal"])
+def test_dictionaries_of_hard_points(d, M, bits, law):
+    n, rng = 1111, np.random.default_rng(d + M + bits)
+    x = unit_rows(rng, n, d)
+    scale = 1.0
+    if law == "lattice":
+        x = np.round(x * 4).astype(np.float32)
+        scale = 4.0
+    elif law in ("tiny", "huge"):
+        scale = 1e-22 if law == "tiny" else 1e20
+        x = (x * np.float32(scale)).astype(np.float32)
+    elif law == "far":
+        x = (100.0 + 0.01 * x).astype(np.float32)
+        scale = 100.0
+    elif law == "equal":
+        x[: n * 3 // 4] = x[0]
+    idx = avq.Index(d, M, bits, kmeans_iters=3, seed=5)
+    idx.train(dev(x))
+    # fp64 means in another order, rounded to fp32: one unit in the last place of the largest values
+    np.testing.assert_allclose(idx.get_codebooks(), oracle.train_pq(x, M, 1 << bits, 3, 5), rtol=0, atol=1.2e-7 * scale)
+
+
 def leaf_index(d, centers, **kw):
     idx = avq.Index(d, 1, 4, n_leaves=centers.shape[0], **kw)
     idx.set_leaf_centers(centers)
