@@ -165,9 +165,15 @@ int avq_update_leaf_centers(avq_index *idx, const float *x, int64_t n, int32_t m
  *    the two entries of a packed 4-bit byte are added first, then bytes are
  *    accumulated in order; 8-bit tables: exact integer sum). With leaves the
  *    score is s + <q, center> (fp32) or fma(acc, scale, bias + <q, center>);
- *  keep the R = reorder_k best by (score descending, id ascending). Batches
+ *  keep the R = reorder_k best by (score descending, id ascending). Most batches
+ *    (16 queries or more on a flat index large enough, up to 256 dimensions; on
+ *    a partitioned one 64 queries or more that probe 25 million points or more
+ *    in all) do not score every point: an f16 matrix product of the queries with
+ *    the points that the codes stand for names every point that the bound on its
+ *    error does not rule out, and those are scored with the tables, in the order
+ *    of additions given above. Where that does not pay, batches
  *    (36 queries or more) with fp32 tables on a flat index of 4-bit codes do
- *    not score every point in fp32: the 8-bit tables are built as well, the
+ *    not score every point in fp32 either: the 8-bit tables are built as well, the
  *    integer sums of all points are formed on the matrix cores, every point
  *    whose sum is within M + slack units of the R-th best sum is kept (the
  *    rounding of the 8-bit tables moves a sum by at most M/2 units, so no
