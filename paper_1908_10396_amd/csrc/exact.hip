@@ -13,10 +13,11 @@
 // a norm), need[1 + q]: query q.
 //
 // 1,183,514 x 100 points, 1,000 queries, k = 10: every point in fp32 took 20.8 ms (one 4-byte load and eight fmas a
-// step, bound by the issue of the loads); this way 0.65 ms (product 0.45, which reads x once, a quarter of it
-// matrix instructions: one workgroup of eight waves fits a compute unit, and nothing overlaps its row loads and its barrier
-// for every tile of queries; selection and fp32 scores 0.20; the plain kernel's three launches, which leave at once, 0.014). bf16 rather than f16, whose range needs a scale first.
+// step, bound by the issue of the loads); this way 0.51 ms (product 0.33, which reads x once: 0.12 of matrix instructions,
+// 0.09 to read x; selection and fp32 scores 0.20; the plain kernel's three launches, which leave at once, 0.014).
+// bf16 rather than f16, whose range needs a scale first.
 #include <algorithm>
+#include <type_traits>
 #include "avq_internal.h"
 #include "wave_topk.h"
 
@@ -75,18 +76,29 @@ exact_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, v
 }
 
 // Eight waves of 64 points, whose operands stay in registers (x is read once), against all queries, whose tiles of 32
-// go through LDS one ahead (x: 473 MB, queries: 224 KB at the size above). best[q][block of 64]: the workgroup's eight
+// go through LDS up to two ahead (x: 473 MB, queries: 224 KB at the size above). The products of one accumulator are issued
+// between the instructions that take the maximum of the other one (sched_barrier keeps the order): 0.46 -> 0.42 ms at the size
+// above. Up to 14 operands a wave fits 128 registers but for a few outside the loop, so that two workgroups share a compute unit
+// and one's row loads overlap the other's products: 0.33; more operands would spill in the loop. best[q][block of 64]: the workgroup's eight
 // maxima of a query leave as 32 adjacent bytes. xnorm[block] = largest norm and conversion error of its points.
 template <int NS, int CT>
-__global__ void __launch_bounds__(512, 2)
+__global__ void __launch_bounds__(512, NS * CT <= 14 ? 4 : 2)
 exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *__restrict__ packed, int n_tiles, int nq,
                      float *__restrict__ best, int64_t best_stride, float2 *__restrict__ xnorm, uint32_t *__restrict__ need)
 {
-    __shared__ __align__(16) v8bf tile[2][NS * 64];
+    __shared__ __align__(16) v8bf tile[3][NS * 64];
     __shared__ __align__(16) float mx[2][32][8];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 31, h = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, h = lane >> 5;
     const int64_t p0 = (int64_t)blockIdx.x * (8 * CT * 32) + wave * (CT * 32);
     const bool quad = (d & 3) == 0 && ((uintptr_t)x & 15) == 0;
+    auto stage = [&](int t, int slot) {
+        const v8bf *src = packed + (size_t)t * NS * 64;
+        for (int s = wave; s < NS; s += 8)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + s * 64 + lane),
+                                             (__attribute__((address_space(3))) void *)(tile[slot] + s * 64), 16, 0, 0);
+    };
+    stage(0, 0);
+    if (n_tiles > 1) stage(1, 1);
     v8bf a[CT][NS];
     float xn = 0.0f, xe = 0.0f;
 #pragma unroll
@@ -127,13 +139,6 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
     if (lane == 0) xnorm[(size_t)blockIdx.x * 8 + wave] = make_float2(xn, xe);
     const bool any = p0 < n;
 
-    auto stage = [&](int t) {
-        const v8bf *src = packed + (size_t)t * NS * 64;
-        v8bf *dst = tile[t & 1];
-        for (int s = wave; s < NS; s += 8)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + s * 64 + lane),
-                                             (__attribute__((address_space(3))) void *)(dst + s * 64), 16, 0, 0);
-    };
     // wave t % 8 writes tile t's maxima: two lanes per query, 16 bytes each
     auto put = [&](int t) {
         if (wave != (t & 7)) return;
@@ -141,33 +146,80 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
         if (q < nq)
             *(float4 *)(best + (size_t)q * best_stride + (size_t)blockIdx.x * 8 + 4 * (lane & 1)) = *(const float4 *)&mx[t & 1][lane >> 1][4 * (lane & 1)];
     };
-    stage(0);
-    for (int t = 0; t < n_tiles; ++t) {
-        __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0): this wave's part of tile t is in LDS
-        __syncthreads();
-        if (t + 1 < n_tiles) stage(t + 1);
-        if (t > 0) put(t - 1); // read before the next barrier; mx[t & 1] is another row
-        const v8bf *b_tile = tile[t & 1];
-        v16f acc[CT];
+    // the largest of an accumulator, two values an instruction (the maximum of IEEE 754-2019 quiets no operand first)
+    float m = -INFINITY;
+    auto take = [&](const v16f &v, int q) __attribute__((always_inline)) {
+        m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, v[2 * q]), v[2 * q + 1]);
+    };
+    // column j of tile t is query j: this lane's 16 CT points of it, then the other half's
+    auto finish = [&](int t) {
+        const float o = __shfl_xor(m, 32, 64);
+        if (h == 0) mx[t & 1][j][wave] = any ? fmaxf(m, o) : -INFINITY;
+    };
+    // the products of one accumulator (H) with a tile, while the values of the other one, formed before them, are taken
+    v16f acc[2], zero;
 #pragma unroll
-        for (int c = 0; c < CT; ++c)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[c][v] = 0.0f;
+    for (int v = 0; v < 16; ++v) { zero[v] = 0.0f; acc[0][v] = acc[1][v] = -3e38f; }
+    v8bf b[NS];
+    auto half = [&](auto which, const v8bf *next) __attribute__((always_inline)) {
+        constexpr int H = decltype(which)::value, O = 1 - H, ch = CT == 2 ? H : 0;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const v8bf b = b_tile[s * 64 + lane];
+            acc[H] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ch][s], b[s], s == 0 ? zero : acc[H], 0, 0, 0);
 #pragma unroll
-            for (int c = 0; c < CT; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[c][s], b, acc[c], 0, 0, 0);
+            for (int q = 0; q < 8; ++q)
+                if (q * NS / 8 == s) take(acc[O], q);
+            asm volatile("" : "+v"(m)); // here, not past the products that hide it
+            if (CT == 1 || H == 1) b[s] = next[s * 64 + lane];
+            __builtin_amdgcn_sched_barrier(0);
         }
-        // column j of the tile is query j: this lane's 16 CT points of it, then the other half's
-        float m = acc[0][0];
+    };
+    __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0): this wave's part of the first tiles is in LDS
+    __syncthreads();
 #pragma unroll
-        for (int c = 0; c < CT; ++c)
+    for (int s = 0; s < NS; ++s) b[s] = tile[0][s * 64 + lane];
+    int slot = 0;
+    auto after = [](int s) { return s == 2 ? 0 : s + 1; };
+    // the tile after t is there, and the maxima written before; every wave has left the tile before t, whose place the one after
+    // next takes
+    auto turn = [&](int t) {
+        __builtin_amdgcn_s_waitcnt(0x0f70);
+        __syncthreads();
+        if (t + 2 < n_tiles) stage(t + 2, after(after(slot)));
+        slot = after(slot);
+    };
+    // (operands read beyond the last tile are not used)
+    if constexpr (CT == 2) {
+#pragma unroll 1
+        for (int t = 0; t < n_tiles; ++t) {
+            half(std::integral_constant<int, 0>{}, nullptr);
+            if (t > 0) finish(t - 1);
+            m = -INFINITY;
+            turn(t);
+            if (t > 0) put(t - 1); // read before the next barrier; the next maxima go to the other half of mx
+            half(std::integral_constant<int, 1>{}, tile[slot]);
+        }
 #pragma unroll
-            for (int v = 0; v < 16; ++v) m = __builtin_amdgcn_fmed3f(INFINITY, m, acc[c][v]);
-        m = fmaxf(m, __shfl_xor(m, 32, 64));
-        if (h == 0) mx[t & 1][j][wave] = any ? m : -INFINITY;
+        for (int q = 0; q < 8; ++q) take(acc[1], q);
+    } else { // the tiles take turns with the accumulators
+        auto step = [&](auto which, int t) __attribute__((always_inline)) {
+            turn(t);
+            if (t > 1) put(t - 2);
+            half(which, tile[slot]);
+            if (t > 0) finish(t - 1);
+            m = -INFINITY;
+        };
+#pragma unroll 1
+        for (int t = 0; t < n_tiles; t += 2) {
+            step(std::integral_constant<int, 0>{}, t);
+            if (t + 1 < n_tiles) step(std::integral_constant<int, 1>{}, t + 1);
+        }
+        __syncthreads();
+        if (n_tiles > 1) put(n_tiles - 2);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) take((n_tiles & 1) ? acc[0] : acc[1], q);
     }
+    finish(n_tiles - 1);
     __syncthreads();
     put(n_tiles - 1);
 }

@@ -40,6 +40,15 @@ def test_exact_search_matches(n, d, nq, k):
     check(unit_rows(rng, n, d), unit_rows(rng, nq, d), k)
 
 
+# one to four query tiles through three buffers and two accumulators: two column tiles per wave with two workgroups to a compute
+# unit (112 dimensions), with one (113), and one column tile (129, 256); points beyond the last full wave
+@pytest.mark.parametrize("d", [112, 113, 129, 256])
+@pytest.mark.parametrize("nq", [32, 33, 96, 97])
+def test_exact_search_of_every_number_of_query_tiles(d, nq):
+    rng = np.random.default_rng(d + nq)
+    check(unit_rows(rng, 4097, d), unit_rows(rng, nq, d), 10)
+
+
 # two and three dimensions, on both sides of the line above which the plain kernel takes them (100,000 and 500,000 points)
 @pytest.mark.parametrize("n,d", [(100_000, 2), (100_001, 2), (500_000, 3), (500_001, 3)])
 def test_exact_search_of_a_few_dimensions(n, d):
