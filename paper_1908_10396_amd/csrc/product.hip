@@ -675,9 +675,11 @@ product_fallback_kernel(const ProductRefineParams r, const u64 *__restrict__ par
             if (s < slots) wave_list_insert_sorted(mine, ns, wave_sort_desc(nk[s]));
     }
     for (int i = lane; i < r.k; i += 64) {
-        const u64 key = mine[i]; // n > R: there are R
-        r.ids_out[(size_t)q * r.k + i] = key_id(key);
-        r.scores_out[(size_t)q * r.k + i] = u8 && !r.reorder ? __fmaf_rn((float)(int)(key_ord(key) - 1u), r.scale[q], r.bias[q]) : f32_from_ord(key_ord(key));
+        const u64 key = mine[i]; // 0: none, the probed leaves of a partitioned index hold fewer points
+        float s = -INFINITY;
+        if (key) s = u8 && !r.reorder ? __fmaf_rn((float)(int)(key_ord(key) - 1u), r.scale[q], r.bias[q]) : f32_from_ord(key_ord(key));
+        r.ids_out[(size_t)q * r.k + i] = key ? key_id(key) : -1;
+        r.scores_out[(size_t)q * r.k + i] = s;
     }
 }
 

@@ -187,6 +187,15 @@ def test_product_leaves_odd_values():
     check_leaves(x, cb, codes, 4, q2, centers, assign, 10, 100, 5)
 
 
+# Fewer points in a query's leaves than results: id -1 and score -infinity fill up, whoever answers (a query of zeros has no
+# range of 8-bit entries and is always scanned plainly).
+@pytest.mark.parametrize("R", [0, 100])
+def test_product_leaves_fill_up(R):
+    x, cb, codes, q, centers, assign = draw_leaves(700, 48, 16, 4, 20, 300)
+    q[3] = 0.0
+    check_leaves(x, cb, codes, 4, q, centers, assign, 50, R, 6)
+
+
 @pytest.mark.parametrize("n,leaves,nq,L,product", [(20_000, 20, 256, 100 // 10, False), (20_000, 20, 2600, 10, True), (20_000, 20, 2400, 10, False)])
 def test_rule_of_product_leaves(n, leaves, nq, L, product):
     x, cb, codes, q, centers, assign = draw_leaves(n, 32, 16, 4, nq, leaves)
