@@ -900,7 +900,7 @@ static int search_product(avq_index *idx, const float *queries, int nq, int k, i
         p.chunks = pl.sample_chunks;
         p.stride = pl.stride;
         AVQ_TRY(launch_product_scan(p, true, st));
-        AVQ_TRY(launch_product_bound(p, pl.r, u8 ? idx->scale.as<float>() : nullptr, margin, guess, nullptr, 0, st));
+        AVQ_TRY(launch_product_bound(p, pl.r, u8 ? idx->scale.as<float>() : nullptr, margin, guess, nullptr, nullptr, 0, st));
     }
     {
         StageTimer t(idx, AVQ_STAGE_SCAN, st); // the launch over all points, nothing else
@@ -1202,7 +1202,8 @@ static int search_leaves_product(avq_index *idx, const float *queries, int nq, i
         AVQ_TRY(launch_group_offsets(g, c.n_leaves, st));
         AVQ_TRY(launch_product_pairs(p, idx->leaf_ids.as<int32_t>(), idx->leaf_ip.as<float>(), g.pos, c.n_leaves, items, pl.most_items, n_items, st));
         AVQ_TRY(launch_product_leaf(p, true, pl.most_items, st));
-        AVQ_TRY(launch_product_bound(p.base, R, u8 ? idx->scale.as<float>() : nullptr, margin, guess, idx->leaf_ip.as<float>(), L, st));
+        AVQ_TRY(launch_product_bound(p.base, R, u8 ? idx->scale.as<float>() : nullptr, margin, guess, idx->leaf_ids.as<int32_t>(),
+                                     idx->leaf_ip.as<float>(), L, st));
         AVQ_TRY(launch_product_lines(p, c.n_leaves, st));
     }
     {

@@ -401,9 +401,10 @@ struct ProductParams {
 // rows: packed as [query][steps][16]
 int launch_product_pack(const ProductParams &p, const float *queries, const float *codebooks, uint32_t *fail_count, bool rows, hipStream_t st);
 int launch_product_scan(const ProductParams &p, bool sample, hipStream_t st);
-// unit: [nq] the 8-bit tables' scale, NULL with fp32 tables. leaf_ip [nq][L]: classes hold ordering values (0: none) of products plus
-// <q, center>; fewer than r of them: no line (-infinity).
-int launch_product_bound(const ProductParams &p, int r, const float *unit, float *margin, float *guess, const float *leaf_ip, int L, hipStream_t st);
+// unit: [nq] the 8-bit tables' scale, NULL with fp32 tables. leaf_ids, leaf_ip [nq][L] (NULL: flat index): classes hold ordering
+// values (0: none) of products plus <q, center>; fewer than r of them: no line (-infinity).
+int launch_product_bound(const ProductParams &p, int r, const float *unit, float *margin, float *guess, const int32_t *leaf_ids,
+                         const float *leaf_ip, int L, hipStream_t st);
 struct ProductRefineParams {
     const u64 *kept;
     const uint32_t *kept_cnt;

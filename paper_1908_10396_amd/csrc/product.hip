@@ -387,7 +387,8 @@ template <int THREADS, int PER>
 __global__ void __launch_bounds__(THREADS == 64 ? 256 : THREADS)
 product_bound_kernel(const float *__restrict__ classes, int S, int r, int nq, int nq_pad, int d, int M, const float *__restrict__ unit,
                      bool u8, const ProductQuery *__restrict__ qinfo, const ProductMeta *__restrict__ meta, float *__restrict__ thr,
-                     float *__restrict__ margin, float *__restrict__ guess, const float *__restrict__ leaf_ip, int L)
+                     float *__restrict__ margin, float *__restrict__ guess, const int32_t *__restrict__ leaf_ids,
+                     const float *__restrict__ leaf_ip, int L)
 {
     constexpr bool WIDE = THREADS > 64;
     constexpr int NW = THREADS / 64;
@@ -440,12 +441,13 @@ product_bound_kernel(const float *__restrict__ classes, int S, int r, int nq, in
             if (count_ge(mid) >= r) lo = mid; else hi = mid;
         }
     }
-    // leaves: the largest |<q, center>|, and whether all are finite
+    // leaves: the largest |<q, center>|; infinite where one is not finite, which leaves no line to compare with
     float ip = 0.0f;
     if (leaf_ip) {
         for (int l = lane; l < L; l += 64) {
+            if (leaf_ids[(size_t)q * L + l] < 0) continue; // no such leaf
             const float v = fabsf(leaf_ip[(size_t)q * L + l]);
-            ip = v < INFINITY ? fmaxf(ip, v) : ip; // (-infinity: no such leaf)
+            ip = v < INFINITY ? fmaxf(ip, v) : INFINITY;
         }
         for (int s = 32; s > 0; s >>= 1) ip = fmaxf(ip, __shfl_xor(ip, s, 64));
     }
@@ -771,12 +773,14 @@ int launch_product_pack(const ProductParams &p, const float *queries, const floa
     return AVQ_OK;
 }
 
-int launch_product_bound(const ProductParams &p, int r, const float *unit, float *margin, float *guess, const float *leaf_ip, int L, hipStream_t st)
+int launch_product_bound(const ProductParams &p, int r, const float *unit, float *margin, float *guess, const int32_t *leaf_ids,
+                         const float *leaf_ip, int L, hipStream_t st)
 {
     const int S = p.n_classes, nq_pad = p.n_tiles * 32;
     const bool u8 = unit != nullptr;
     auto go = [&](auto kern, int threads, int grid) {
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, p.classes, S, r, p.nq, nq_pad, p.d, p.M, unit, u8, p.qinfo, p.meta, p.thr, margin, guess, leaf_ip, L);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, p.classes, S, r, p.nq, nq_pad, p.d, p.M, unit, u8, p.qinfo, p.meta, p.thr, margin, guess, leaf_ids,
+                           leaf_ip, L);
     };
     if (S <= 512) go(product_bound_kernel<64, 8>, 256, (nq_pad + 3) / 4);
     else if (S <= 1280) go(product_bound_kernel<64, 20>, 256, (nq_pad + 3) / 4);

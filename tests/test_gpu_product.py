@@ -141,11 +141,16 @@ def draw_leaves(n, d, M, bits, nq, leaves, seed=0, skew=False):
     return x, cb, codes, q, centers, assign.astype(np.int32)
 
 
-def check_leaves(x, cb, codes, bits, q, centers, assign, k, R, L):
+def leaf_index(x, cb, codes, bits, centers, assign):
     idx = avq.Index(x.shape[1], codes.shape[1], bits, n_leaves=len(centers))
     idx.set_codebooks(cb)
     idx.set_leaf_centers(centers)
     idx.set_database(torch.from_numpy(x).cuda(), torch.from_numpy(oracle.pack_codes(codes, bits)).cuda(), torch.from_numpy(assign).cuda())
+    return idx
+
+
+def check_leaves(x, cb, codes, bits, q, centers, assign, k, R, L):
+    idx = leaf_index(x, cb, codes, bits, centers, assign)
     idx.set_tuning("scan_product", 2)
     qd = torch.from_numpy(q).cuda()
     for mode in (avq.LUT_F32, avq.LUT_U8):
@@ -194,6 +199,30 @@ def test_product_leaves_fill_up(R):
     x, cb, codes, q, centers, assign = draw_leaves(700, 48, 16, 4, 20, 300)
     q[3] = 0.0
     check_leaves(x, cb, codes, 4, q, centers, assign, 50, R, 6)
+
+
+# A query whose product with the center of a probed leaf is infinite has no line to compare with: it is scanned plainly, the others
+# are not. (A leaf at -infinity is not probed.)
+@pytest.mark.parametrize("k,R", [(50, 0), (50, 512)])
+def test_product_leaves_infinite_center(k, R):
+    x, cb, codes, q, centers, assign = draw_leaves(700, 32, 16, 4, 40, 3)
+    centers[1] = 0.0
+    centers[1, 0] = 1e20
+    q[::2] *= 1e22
+    handed = int((q[::2, 0] > 0).sum())
+    assert 0 < handed < 20
+    idx = leaf_index(x, cb, codes, 4, centers, assign)
+    qd = torch.from_numpy(q).cuda()
+    for mode in (avq.LUT_F32, avq.LUT_U8):
+        idx.set_tuning("scan_product", 2)
+        idx.set_tuning("small_batch_impl", 0)
+        ids, sc = idx.search(qd, k, R, mode, 3)
+        assert idx.debug_unverified_queries() == handed
+        idx.set_tuning("scan_product", 1)
+        idx.set_tuning("small_batch_impl", 1) # every point scored
+        ids1, sc1 = idx.search(qd, k, R, mode, 3)
+        assert torch.equal(ids, ids1)
+        np.testing.assert_array_equal(sc.cpu().numpy(), sc1.cpu().numpy())
 
 
 @pytest.mark.parametrize("n,leaves,nq,L,product", [(20_000, 20, 256, 100 // 10, False), (20_000, 20, 2600, 10, True), (20_000, 20, 2400, 10, False)])
