@@ -1115,6 +1115,22 @@ static bool use_product_leaves(const avq_index *idx, int nq, int L, int R, bool 
     return nq >= 64 && work >= (u8 && R > 256 ? 1e8 : 2.5e7);
 }
 
+// The most scratch that a part of a batch through the product takes; parts cost: the points are decoded again for each. Bytes
+// of a query beside the product's own: its tables twice (8-bit ones with the fp32 ones they are made from), the lists and, on
+// a partitioned index, the leaves of the plain scan.
+constexpr size_t kProductScratch = (size_t)4 << 30;
+static size_t product_query_bytes(const avq_index *idx, int ns, bool u8, const ScanShape &shape, int L)
+{
+    const size_t entries = (size_t)idx->cfg.M * idx->kc, list = sizeof(u64) * 64 * (size_t)ns;
+    return entries * (u8 ? 6 : 4) + list + (shape.lists_global ? list * shape.waves * shape.qt : 0) + (size_t)L * 8;
+}
+
+static int product_leaf_shape(const avq_index *idx, int nq, int ns, bool u8, ScanShape *shape)
+{
+    if (scan_pick_shape(idx->NB, idx->cfg.bits, u8, ns, nq, true, 0, 16, shape) == AVQ_OK) return AVQ_OK;
+    return scan_pick_shape(idx->NB, idx->cfg.bits, u8, ns, nq, true, 0, 0, shape);
+}
+
 static int search_leaves_product(avq_index *idx, const float *queries, int nq, int k, int reorder_k, int R, int ns, int L, bool u8,
                                  int32_t *ids_out, float *scores_out, hipStream_t st)
 {
@@ -1177,7 +1193,7 @@ static int search_leaves_product(avq_index *idx, const float *queries, int nq, i
     float *margin = (float *)(base + o_margin), *guess = margin + nq;
     // the plain scan over the leaves of the queries that are handed back
     ScanShape shape;
-    if (scan_pick_shape(idx->NB, c.bits, u8, ns, nq, true, 0, 16, &shape) != AVQ_OK) AVQ_TRY(scan_pick_shape(idx->NB, c.bits, u8, ns, nq, true, 0, 0, &shape));
+    AVQ_TRY(product_leaf_shape(idx, nq, ns, u8, &shape));
     AVQ_TRY(idx->partial.reserve(sizeof(u64) * (size_t)nq * C));
     if (shape.lists_global) AVQ_TRY(idx->lists.reserve(sizeof(u64) * (size_t)nq * shape.waves * shape.qt * C));
     const size_t lut_row = u8 ? (size_t)c.M * idx->kc / 4 : (size_t)c.M * idx->kc; // 4-byte units
@@ -1657,8 +1673,15 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
     const bool fuse_tables = small && idx->tune_small_impl != 1 && small_batch_can_fuse_tables(c.bits, c.M, c.d, u8);
     const bool prefilter = !small && use_prefilter(idx, nq, lut_mode, R);
     if (ivf && use_product_leaves(idx, nq, leaves_to_search, R, u8)) {
-        const int rc = search_leaves_product(idx, queries, nq, k, reorder_k, R, ns, leaves_to_search, u8, ids_out, scores_out, st);
-        if (rc != AVQ_ENOMEM) return rc; // no room for its scratch (nothing was launched): the other paths take less
+        ScanShape shape;
+        AVQ_TRY(product_leaf_shape(idx, nq, ns, u8, &shape));
+        const int per = product_leaf_part(nq, leaves_to_search, c.n_leaves, idx->n, idx->n_blocks, idx->max_leaf_blocks, c.d, R, u8,
+                                          product_query_bytes(idx, ns, u8, shape, leaves_to_search), kProductScratch);
+        int rc = AVQ_OK;
+        for (int q0 = 0; q0 < nq && rc == AVQ_OK; q0 += per)
+            rc = search_leaves_product(idx, queries + (size_t)q0 * c.d, std::min(per, nq - q0), k, reorder_k, R, ns, leaves_to_search, u8,
+                                       ids_out + (size_t)q0 * k, scores_out + (size_t)q0 * k, st);
+        if (rc != AVQ_ENOMEM) return rc; // no room for its scratch (nothing of that part was launched): the other paths take less
     }
     const bool grouped = ivf && use_grouped_leaves(idx, nq, leaves_to_search, R);
     if (ivf && use_leaf_small(idx, nq, leaves_to_search))

@@ -506,7 +506,13 @@ product_leaf_refine_kernel(const ProductLeafRefineParams r)
 bool product_leaf_supported(int d, int M, int n_leaves, int64_t n_blocks, int64_t max_leaf_blocks, int nq, int L, int R)
 {
     return d <= 256 && M <= 256 && L >= 2 && L <= 512 && nq <= (1 << 16) && n_leaves <= (1 << 20) && n_blocks < (1 << 24) &&
-           max_leaf_blocks <= 1024 && R <= AVQ_MAX_SELECT && n_blocks * (1 + nq / kLeafQueries) < ((int64_t)1 << 30);
+           max_leaf_blocks <= 1024 && R <= AVQ_MAX_SELECT;
+}
+
+// Every leaf's blocks once, and again for every further kLeafQueries of its queries (a query probes a leaf once).
+static int64_t product_leaf_items(int nq, int L, int64_t n_blocks, int64_t max_leaf_blocks)
+{
+    return n_blocks + std::min(max_leaf_blocks * ((int64_t)nq * L / kLeafQueries), n_blocks * (nq / kLeafQueries));
 }
 
 // Scratch for nq queries: words, slots and items of the launches.
@@ -524,11 +530,24 @@ ProductLeafPlan product_leaf_plan(int nq, int L, int n_leaves, int64_t n, int64_
     while ((int64_t)L * pl.pair_classes > kProductMaxClasses && pl.pair_classes > 256 / pl.run) pl.pair_classes -= 256 / pl.run;
     while ((int64_t)L * pl.pair_classes > kProductMaxClasses && pl.run < 16) { pl.run = 16; pl.pair_classes = 16; }
     pl.n_classes = L * pl.pair_classes;
-    // every leaf's blocks once, and again for every further kLeafQueries of its queries (a query probes a leaf once)
-    pl.most_items = n_blocks + std::min(max_leaf_blocks * ((int64_t)nq * L / kLeafQueries), n_blocks * (nq / kLeafQueries));
+    pl.most_items = product_leaf_items(nq, L, n_blocks, max_leaf_blocks);
     pl.cnt_stride = spread_stride(nq);
     pl.kept_cap = u8 ? ProductRoom<true>::kept : ProductRoom<false>::kept;
     return pl;
+}
+
+// Queries of one part of a batch: as many as `most` bytes hold at `other` bytes a query beside the plan's, and no more than a
+// launch of a workgroup per item allows (below 2^32 threads; fewer than kLeafQueries queries always do, as n_blocks is
+// below 2^24).
+int product_leaf_part(int nq, int L, int n_leaves, int64_t n, int64_t n_blocks, int64_t max_leaf_blocks, int d, int R, bool u8, size_t other, size_t most)
+{
+    const ProductLeafPlan pl = product_leaf_plan(nq, L, n_leaves, n, n_blocks, max_leaf_blocks, d, R, u8);
+    const size_t row = (size_t)pl.n_classes * 4 + (size_t)pl.kept_cap * 10 + (size_t)pl.steps * 32 + (size_t)L * 24 + 256 + other;
+    const int64_t threads = 64 * 8 / product_ct(pl.steps);
+    int per = (int)std::min<int64_t>(nq, std::max<int64_t>(1, (int64_t)(most / row)));
+    while (per >= kLeafQueries && product_leaf_items(per, L, n_blocks, max_leaf_blocks) * threads >= ((int64_t)1 << 32)) per -= per / 8;
+    const int parts = (nq + per - 1) / per; // of about the same size
+    return (nq + parts - 1) / parts;
 }
 
 int launch_product_clear(void *a, size_t a_bytes, void *b, size_t b_bytes, hipStream_t st)

@@ -201,6 +201,24 @@ def test_product_leaves_fill_up(R):
     check_leaves(x, cb, codes, 4, q, centers, assign, 50, R, 6)
 
 
+# A leaf of 1,024 blocks among 131,200: as many workgroups as the blocks and 65,536 queries allow for would be 2^32 threads, more
+# than a launch takes, and the scratch several GB; the batch is taken in parts.
+def test_product_leaves_parts():
+    rng = np.random.default_rng(3)
+    d, M, leaves, big, nq, L, k = 130, 10, 131_200, 262_144, 65_536, 128, 5
+    n = big + leaves - 1
+    assign = np.maximum(np.arange(n) - big + 1, 0).astype(np.int32)
+    cb = (rng.standard_normal((M, 16, d // M)) * 0.2).astype(np.float32)
+    idx = leaf_index(unit_rows(rng, n, d), cb, rng.integers(0, 16, (n, M)).astype(np.uint8), 4, 0.5 * unit_rows(rng, leaves, d), assign)
+    qd = torch.nn.functional.normalize(torch.randn((nq, d), device="cuda", generator=torch.Generator("cuda").manual_seed(1)))
+    idx.set_tuning("scan_product", 2)
+    ids, sc = idx.search(qd, k, 0, avq.LUT_F32, L)
+    idx.set_tuning("scan_product", 1)
+    for lo in (0, nq // 2 - 20, nq - 40):
+        a, b = idx.search(qd[lo:lo + 40].contiguous(), k, 0, avq.LUT_F32, L)
+        assert torch.equal(ids[lo:lo + 40], a) and torch.equal(sc[lo:lo + 40], b)
+
+
 # A query whose product with the center of a probed leaf is infinite has no line to compare with: it is scanned plainly, the others
 # are not. (A leaf at -infinity is not probed.)
 @pytest.mark.parametrize("k,R", [(50, 0), (50, 512)])
