@@ -78,11 +78,14 @@ exact_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, v
 // Eight waves of 64 points, whose operands stay in registers (x is read once), against all queries, whose tiles of 32
 // go through LDS up to two ahead (x: 473 MB, queries: 224 KB at the size above). The products of one accumulator are issued
 // between the instructions that take the maximum of the other one (sched_barrier keeps the order): 0.46 -> 0.42 ms at the size
-// above. Up to 14 operands a wave fits 128 registers but for a few outside the loop, so that two workgroups share a compute unit
-// and one's row loads overlap the other's products: 0.33; more operands would spill in the loop. best[q][block of 64]: the workgroup's eight
+// above. Up to 14 operands of two column tiles a wave fits 128 registers but for a few outside the loop, so that two workgroups
+// share a compute unit and one's row loads overlap the other's products: 0.33. The others would spill in the loop (one column tile
+// of 12 operands: 14 loads from scratch every two tiles, each of which also waits for the staged ones; 1,183,514 x 160, 1,000
+// queries, exact search whole: 1,051 us with one workgroup and products and maxima one after the other, 1,090 with two, 971 with
+// one). best[q][block of 64]: the workgroup's eight
 // maxima of a query leave as 32 adjacent bytes. xnorm[block] = largest norm and conversion error of its points.
 template <int NS, int CT>
-__global__ void __launch_bounds__(512, NS * CT <= 14 ? 4 : 2)
+__global__ void __launch_bounds__(512, CT == 2 && NS <= 7 ? 4 : 2)
 exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *__restrict__ packed, int n_tiles, int nq,
                      float *__restrict__ best, int64_t best_stride, float2 *__restrict__ xnorm, uint32_t *__restrict__ need)
 {
