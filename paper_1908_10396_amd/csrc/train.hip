@@ -67,7 +67,10 @@ double eta_host(int d, double T, double norm, int mode) { return eta_of_norm(d, 
 // pair in tens of thousands, and all pairs of other sizes are decided by fp64 distances, 3 ds + 3 instructions each (the same
 // rate, one by one). 262,144 points x 50 subspaces x 16 codewords of 2 dimensions: 46 us an iteration (67 all in fp64) and
 // 5 us for the codewords; with a launch sequence per subspace, row-major points and one copy of the sums 51 + 5 + 9 us per
-// subspace and iteration. Where codewords are equal, every pair near them takes both: 109 us if all 16 are.
+// subspace and iteration. Where fp32 decides little (equal codewords, points close together but far from the origin), a pair
+// takes both searches (109 us): a wave that sees so leaves the fp32 search out, and marks the subspace for the iterations
+// after this one. Training whole, unit vectors / copies of a row, us: 262,144 x 100, 50 subspaces of 16 codewords 1,360 / 1,350
+// all in fp64, 1,000 / 2,040 without that mark, 990 / 1,350 with it; 25 of 256 codewords 14,450 / 14,430, 8,000 / 22,700, 7,990 / 14,540.
 
 // x [n][d] -> xt [cols][n], columns col0 .. col0 + cols - 1; XT double: the residual to centers[assign[i]]
 template <typename XT>
@@ -98,9 +101,10 @@ points_by_coordinate_kernel(const float *__restrict__ x, int64_t n, int d, int c
 template <typename XT>
 __global__ void __launch_bounds__(256)
 pq_init_kernel(const XT *__restrict__ xt, int64_t n, int ds, int k, int m0, uint64_t seed, float *__restrict__ cb,
-               double *__restrict__ cb64)
+               double *__restrict__ cb64, uint32_t *__restrict__ hard)
 {
     const int j = blockIdx.x * 256 + threadIdx.x, m = blockIdx.y;
+    if (j == 0) hard[m] = 0u;
     if (j >= k) return;
     const uint64_t i = init_row(seed, (uint32_t)(1 + m0 + m), (uint64_t)j, (uint64_t)k, (uint64_t)n);
     for (int l = 0; l < ds; ++l) {
@@ -110,16 +114,42 @@ pq_init_kernel(const XT *__restrict__ xt, int64_t n, int ds, int k, int m0, uint
     }
 }
 
+constexpr int kLloydFp32Points = 512; // of a workgroup (two steps), from which on the fp32 search pays
+
+// nearest codeword by fp64 distances, the lowest index on ties
+template <int DS, int KC>
+__device__ __forceinline__ int lloyd_nearest(const double (&xv)[DS], const double *cb, int k_rt)
+{
+    const int k = KC ? KC : k_rt;
+    int best = 0;
+    double bestd = INFINITY;
+#pragma unroll 16
+    for (int j = 0; j < k; ++j) {
+        double t = xv[0] - cb[j * DS];
+        double dd = t * t;
+#pragma unroll
+        for (int l = 1; l < DS; ++l) {
+            t = xv[l] - cb[j * DS + l];
+            dd += t * t;
+        }
+        best = dd < bestd ? j : best;
+        bestd = fmin(dd, bestd);
+    }
+    return best;
+}
+
 // One subspace (blockIdx.y) and per_block points per workgroup: the nearest codeword of every point (by fp64
 // squared distances, lowest index on ties), the point added to that codeword's sums in LDS, the workgroup's sums to
 // part_sum[m][entry][blk] and part_cnt[m][codeword][blk]. `copies` of the sums side by side in LDS keep the lanes
 // of a wave, which share a few codewords, from adding to the same word: 32 of them put a wave's additions into
 // separate banks. copies = 0: the sums do not fit LDS and go to part_* (n_slots = 1, cleared before) directly.
-// DS = dimensions per subspace, KC = codewords (0: known at run time only).
-template <int DS, int KC, typename XT>
-__global__ void __launch_bounds__(256)
+// DS = dimensions per subspace, KC = codewords (0: known at run time only). FAST: with the fp32 search. hard[m]: set where it
+// decided little.
+template <int DS, int KC, bool FAST, typename XT>
+__global__ void __launch_bounds__(256, FAST && KC == 16 && DS < 4 ? 8 : 1) // (eight waves a SIMD: one round of workgroups)
 pq_lloyd_kernel(const XT *__restrict__ xt, int64_t n, int ds_rt, int k_rt, int per_block, const float *__restrict__ cb32,
-                const double *__restrict__ cb64, int copies, int n_slots, double *__restrict__ part_sum, uint32_t *__restrict__ part_cnt)
+                const double *__restrict__ cb64, uint32_t *hard, int copies, int n_slots, double *__restrict__ part_sum,
+                uint32_t *__restrict__ part_cnt)
 {
     extern __shared__ __align__(16) double lloyd_lds[]; // [k * ds][copies], then uint32 [k][copies] and float [260]
     const int ds = DS ? DS : ds_rt, k = KC ? KC : k_rt;
@@ -129,7 +159,8 @@ pq_lloyd_kernel(const XT *__restrict__ xt, int64_t n, int ds_rt, int k_rt, int p
     for (int e = tid; e < k * ds * copies; e += 256) lsum[e] = 0.0;
     for (int e = tid; e < k * copies; e += 256) lcnt[e] = 0u;
     float *bias = (float *)(lcnt + k * copies), *c_max = bias + 256;
-    if constexpr (DS != 0) { // -||c||^2 / 2 of the codewords (at most 256) and their largest norm
+    const bool search = FAST && per_block >= kLloydFp32Points;
+    if (search) { // -||c||^2 / 2 of the codewords (at most 256) and their largest norm
         double n2 = 0.0;
         if (tid < k)
             for (int l = 0; l < ds; ++l) { const double c = cb64[((size_t)m * k + tid) * ds + l]; n2 += c * c; }
@@ -147,62 +178,87 @@ pq_lloyd_kernel(const XT *__restrict__ xt, int64_t n, int ds_rt, int k_rt, int p
     uint32_t *gcnt = part_cnt + (size_t)m * k * n_slots;
     const int copy = copies > 0 ? (tid & (copies - 1)) : 0;
     const float *cf = cb32 + (size_t)m * k * ds;
-    const float cn = DS ? fmaxf(fmaxf(c_max[0], c_max[1]), fmaxf(c_max[2], c_max[3])) : 0.0f;
-    const float cb_half = 0.5f * cn * cn;
-    float bias16[16];
-    if constexpr (DS != 0 && KC == 16) {
+    if constexpr (DS != 0) {
+        auto load = [&](int64_t i, double (&xv)[DS]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < 16; ++u) bias16[u] = bias[u];
-    }
-    for (int64_t i = first + tid; i < end; i += 256) {
-        int best = 0;
-        double xv[DS ? DS : 1];
-        if constexpr (DS != 0) {
-            float xf[DS], xn = 0.0f; // xn: at least the norm
+            for (int l = 0; l < DS; ++l) xv[l] = (double)xm[(size_t)l * n + i];
+        };
+        auto add = [&](int best, const double (&xv)[DS]) __attribute__((always_inline)) {
+            if (copies > 0) {
 #pragma unroll
-            for (int l = 0; l < DS; ++l) {
-                xv[l] = (double)xm[(size_t)l * n + i];
-                xf[l] = (float)xv[l];
-                xn += fabsf(xf[l]);
+                for (int l = 0; l < DS; ++l)
+                    __hip_atomic_fetch_add(&lsum[(best * DS + l) * copies + copy], xv[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add(&lcnt[best * copies + copy], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            } else {
+                for (int l = 0; l < DS; ++l) unsafeAtomicAdd(&gsum[(size_t)best * DS + l], xv[l]);
+                atomicAdd(&gcnt[best], 1u);
             }
-            // the two largest <x, c> - ||c||^2 / 2 in fp32, the codeword's place among 16 in the lowest bits
-            float top = -INFINITY, second = -INFINITY;
-            int block = 0;
-            for (int j0 = 0; j0 < k; j0 += 16) {
-                const float old = top;
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    float v = KC == 16 ? bias16[u] : bias[j0 + u];
-#pragma unroll
-                    for (int l = 0; l < DS; ++l) v = __fmaf_rn(xf[l], cf[(j0 + u) * DS + l], v);
-                    v = __uint_as_float((__float_as_uint(v) & 0xfffffff0u) | (uint32_t)u);
-                    second = __builtin_amdgcn_fmed3f(top, second, v);
-                    top = __builtin_elementwise_maximum(top, v);
-                }
-                block = top == old ? block : j0;
-            }
-            best = block + (int)(__float_as_uint(top) & 15u);
-            // what a value can be off by: x rounded to fp32, the bias and DS sums rounded, the place (2^-19 of it); the last
-            // two terms: products under the smallest normal number, and the rounding of the fp64 distances below
-            const float mag = xn * cn + cb_half;
-            const float e = ((float)(DS + 4) * 6.0e-8f + 1.91e-6f) * 1.01f * mag + 1e-36f + 1e-14f * (xn + cn) * (xn + cn);
-            if (!(top - second > 2.0f * e)) { // not by more than both can be off by: by fp64 distances, the lowest index on ties
-                double bestd = INFINITY;
-                best = 0;
-#pragma unroll 4
-                for (int j = 0; j < k; ++j) {
-                    double t = xv[0] - cb[j * DS];
-                    double dd = t * t;
-#pragma unroll
-                    for (int l = 1; l < DS; ++l) {
-                        t = xv[l] - cb[j * DS + l];
-                        dd += t * t;
-                    }
-                    best = dd < bestd ? j : best;
-                    bestd = fmin(dd, bestd);
-                }
+        };
+        if constexpr (!FAST) {
+            for (int64_t i = first + tid; i < end; i += 256) {
+                double xv[DS];
+                load(i, xv);
+                add(lloyd_nearest<DS, KC>(xv, cb, k), xv);
             }
         } else {
+            bool direct = !search || hard[m] != 0u; // this wave: fp64 distances for every point
+            const float cn = search ? fmaxf(fmaxf(c_max[0], c_max[1]), fmaxf(c_max[2], c_max[3])) : 0.0f;
+            const float cb_half = 0.5f * cn * cn;
+            float bias16[16];
+            if (KC == 16 && search) {
+#pragma unroll
+                for (int u = 0; u < 16; ++u) bias16[u] = bias[u];
+            }
+            int debt = 0; // of this wave: steps with points that take fp64 distances (many: two), less those without
+            for (int64_t i = first + tid; i < end; i += 256) {
+                int best = 0;
+                double xv[DS];
+                load(i, xv);
+                float xf[DS], xn = 0.0f; // xn: at least the norm
+#pragma unroll
+                for (int l = 0; l < DS; ++l) {
+                    xf[l] = (float)xv[l];
+                    xn += fabsf(xf[l]);
+                }
+                bool open = true; // whether it takes the fp64 distances
+                if (!direct) {
+                    // the two largest <x, c> - ||c||^2 / 2 in fp32, the codeword's place among 16 in the lowest bits
+                    float top = -INFINITY, second = -INFINITY;
+                    int block = 0;
+                    for (int j0 = 0; j0 < k; j0 += 16) {
+                        const float old = top;
+#pragma unroll
+                        for (int u = 0; u < 16; ++u) {
+                            float v = KC == 16 ? bias16[u] : bias[j0 + u];
+#pragma unroll
+                            for (int l = 0; l < DS; ++l) v = __fmaf_rn(xf[l], cf[(j0 + u) * DS + l], v);
+                            v = __uint_as_float((__float_as_uint(v) & 0xfffffff0u) | (uint32_t)u);
+                            second = __builtin_amdgcn_fmed3f(top, second, v);
+                            top = __builtin_elementwise_maximum(top, v);
+                        }
+                        block = top == old ? block : j0;
+                    }
+                    best = block + (int)(__float_as_uint(top) & 15u);
+                    // what a value can be off by: x rounded to fp32, the bias and DS sums rounded, the place (2^-19 of it); the last
+                    // two terms: products under the smallest normal number, and the rounding of the fp64 distances
+                    const float mag = xn * cn + cb_half;
+                    const float e = ((float)(DS + 4) * 6.0e-8f + 1.91e-6f) * 1.01f * mag + 1e-36f + 1e-14f * (xn + cn) * (xn + cn);
+                    open = !(top - second > 2.0f * e); // not by more than both can be off by
+                    // a wave that often has such points does the work twice: it, and the launches after this one, leave the fp32 search out
+                    const int n_open = (int)__popcll(__builtin_amdgcn_ballot_w64(open));
+                    debt += n_open >= 16 ? 2 : n_open > 0 ? 1 : debt > 0 ? -1 : 0;
+                    if (__builtin_expect(debt >= 4, 0)) {
+                        direct = true;
+                        hard[m] = 1u;
+                    }
+                }
+                if (open) best = lloyd_nearest<DS, KC>(xv, cb, k);
+                add(best, xv);
+            }
+        }
+    } else {
+        for (int64_t i = first + tid; i < end; i += 256) {
+            int best = 0;
             double bestd = INFINITY;
             for (int j0 = 0; j0 < k; j0 += 8) { // k is a multiple of 16
                 double dd[8];
@@ -222,21 +278,15 @@ pq_lloyd_kernel(const XT *__restrict__ xt, int64_t n, int ds_rt, int k_rt, int p
                     bestd = fmin(dd[u], bestd);
                 }
             }
-        }
-        if (copies > 0) {
-            if constexpr (DS != 0) {
-#pragma unroll
-                for (int l = 0; l < DS; ++l)
-                    __hip_atomic_fetch_add(&lsum[(best * DS + l) * copies + copy], xv[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            } else {
+            if (copies > 0) {
                 for (int l = 0; l < ds; ++l)
                     __hip_atomic_fetch_add(&lsum[(size_t)(best * ds + l) * copies + copy], (double)xm[(size_t)l * n + i],
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add(&lcnt[best * copies + copy], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            } else {
+                for (int l = 0; l < ds; ++l) unsafeAtomicAdd(&gsum[(size_t)best * ds + l], (double)xm[(size_t)l * n + i]);
+                atomicAdd(&gcnt[best], 1u);
             }
-            __hip_atomic_fetch_add(&lcnt[best * copies + copy], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        } else {
-            for (int l = 0; l < ds; ++l) unsafeAtomicAdd(&gsum[(size_t)best * ds + l], (double)xm[(size_t)l * n + i]);
-            atomicAdd(&gcnt[best], 1u);
         }
     }
     if (copies == 0) return;
@@ -292,25 +342,35 @@ static int pq_kmeans_group(const float *x, int64_t n, int d, int m0, int Mg, int
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t b_xt = up(sizeof(XT) * (size_t)n * Mg * ds), b_cb = up(sizeof(double) * (size_t)Mg * k * ds),
                  b_sum = up(sizeof(double) * (size_t)Mg * k * ds * n_slots), b_cnt = up(sizeof(uint32_t) * (size_t)Mg * k * n_slots);
-    AVQ_TRY(ws->reserve(b_xt + b_cb + b_sum + b_cnt));
+    AVQ_TRY(ws->reserve(b_xt + b_cb + b_sum + b_cnt + up(sizeof(uint32_t) * (size_t)Mg)));
     XT *xt = ws->as<XT>();
     double *cb64 = (double *)(ws->as<unsigned char>() + b_xt);
     double *part_sum = (double *)((unsigned char *)cb64 + b_cb);
     uint32_t *part_cnt = (uint32_t *)((unsigned char *)part_sum + b_sum);
+    uint32_t *hard = (uint32_t *)((unsigned char *)part_cnt + b_cnt); // subspaces whose points mostly take fp64 distances
     hipLaunchKernelGGL(points_by_coordinate_kernel<XT>, dim3((unsigned)((n + 63) / 64), (unsigned)((Mg * ds + 31) / 32)), dim3(256), 0,
                        st, x, n, d, m0 * ds, Mg * ds, centers, assign, xt);
     hipLaunchKernelGGL(pq_init_kernel<XT>, dim3((unsigned)((k + 255) / 256), (unsigned)Mg), dim3(256), 0, st, xt, n, ds, k, m0, seed,
-                       codebooks, cb64);
+                       codebooks, cb64, hard);
     const dim3 grid((unsigned)n_blk, (unsigned)Mg);
-    const size_t lds = copies * copy_bytes + 260 * sizeof(float);
+    // The fp32 search from two steps of a workgroup on (training, us, without / with it: 4,000 x 100, 50 subspaces of 16 codewords
+    // 203 / 207, 10,000 254 / 260, 20,000 298 / 282; 25 of 256 codewords 5,000 870 / 1,506, 20,000 1,630 / 2,020, 40,000 2,760 /
+    // 2,460). Eight dimensions: the kernel that has both is the faster one for fp64 distances too (5,000 x 256 2,070 / 1,590).
+    const bool fast = per_block >= kLloydFp32Points || ds == 8;
+    const size_t lds = copies * copy_bytes + (fast ? 260 * sizeof(float) : 0);
     for (int it = 0; it < iters; ++it) {
         if (copies == 0) AVQ_HIP(hipMemsetAsync(part_sum, 0, b_sum + b_cnt, st));
+        auto go = [&](auto kern, LdsLimitOnce *once) -> int {
+            AVQ_TRY(set_lds_limit((const void *)kern, kMaxDynLds, once));
+            hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, xt, n, ds, k, per_block, codebooks, cb64, hard, copies, n_slots, part_sum,
+                               part_cnt);
+            return AVQ_OK;
+        };
 #define AVQ_LLOYD(DS, KC)                                                                                          \
     do {                                                                                                           \
-        static LdsLimitOnce attr_done;                                                                             \
-        AVQ_TRY(set_lds_limit((const void *)pq_lloyd_kernel<DS, KC, XT>, kMaxDynLds, &attr_done));                 \
-        hipLaunchKernelGGL((pq_lloyd_kernel<DS, KC, XT>), grid, dim3(256), lds, st, xt, n, ds, k, per_block, codebooks, \
-                           cb64, copies, n_slots, part_sum, part_cnt);                                                   \
+        static LdsLimitOnce once[2];                                                                               \
+        if (fast && DS != 0) AVQ_TRY(go(pq_lloyd_kernel<DS, KC, DS != 0, XT>, &once[1]));                          \
+        else AVQ_TRY(go(pq_lloyd_kernel<DS, KC, false, XT>, &once[0]));                                            \
     } while (0)
         if (k == 16) {
             switch (ds) {
