@@ -213,9 +213,10 @@ extern "C" int avq_set_tuning(avq_index *idx, const char *name, int32_t value)
     else if (!strcmp(name, "bound_bits")) idx->tune_bound_bits = value;
     else if (!strcmp(name, "stream_loads")) idx->tune_stream_loads = value;
     else if (!strcmp(name, "scratch_limit_kb")) {
-        idx->train_ws.limit = idx->exact_ws.limit = (size_t)value * 1024;
+        idx->train_ws.limit = idx->exact_ws.limit = idx->product.limit = (size_t)value * 1024;
         if (value > 0 && idx->train_ws.cap > idx->train_ws.limit) idx->train_ws.release();
         if (value > 0 && idx->exact_ws.cap > idx->exact_ws.limit) idx->exact_ws.release();
+        if (value > 0 && idx->product.cap > idx->product.limit) idx->product.release();
     }
     else { set_error("avq_set_tuning: unknown name '%s'", name); return AVQ_EINVAL; }
     return AVQ_OK;
@@ -836,6 +837,56 @@ static bool use_product(const avq_index *idx, int nq, int R, bool u8, int few_ma
     return nq > few_max || product < (own && !guessed ? std::min(560.0, few) : few);
 }
 
+// The most scratch that a part of a batch through the product takes ("scratch_limit_kb" where that is less); parts cost: the
+// points are decoded again for each. The flat batches' measured range ends at 16,384 queries a part.
+constexpr size_t kProductScratch = (size_t)4 << 30;
+static size_t product_scratch(const avq_index *idx) { return idx->product.limit ? std::min(idx->product.limit, kProductScratch) : kProductScratch; }
+
+// the plain scan of queries that the product hands back
+static int product_shape(const avq_index *idx, int nq, int ns, bool u8, bool leaves, ScanShape *shape)
+{
+    const int bits = idx->cfg.bits, qt = !leaves && bits == 4 ? 8 : 0, waves = leaves ? 16 : 0;
+    if ((qt || waves) && scan_pick_shape(idx->NB, bits, u8, ns, nq, leaves, qt, waves, shape) == AVQ_OK) return AVQ_OK;
+    return scan_pick_shape(idx->NB, bits, u8, ns, nq, leaves, 0, 0, shape);
+}
+
+// Queries of one part of a batch.
+static int product_part(const avq_index *idx, int nq, int R, int ns, int L, bool u8, int *per)
+{
+    const avq_config &c = idx->cfg;
+    ScanShape shape;
+    AVQ_TRY(product_shape(idx, nq, ns, u8, L > 0, &shape));
+    // bytes of a query beside the product's own: its tables twice (8-bit ones with the fp32 ones they are made from), the lists
+    // and, on a partitioned index, the leaves of the plain scan
+    const size_t entries = (size_t)c.M * idx->kc, list = sizeof(u64) * 64 * (size_t)ns;
+    const size_t other = entries * (u8 ? 6 : 4) + list + (shape.lists_global ? list * shape.waves * shape.qt : 0) + (size_t)L * 8;
+    if (L > 0) {
+        *per = product_leaf_part(nq, L, c.n_leaves, idx->n, idx->n_blocks, idx->max_leaf_blocks, c.d, R, u8, other, product_scratch(idx));
+        return AVQ_OK;
+    }
+    const ProductPlan pl = product_plan(std::min(nq, 16384), idx->n, c.d, R, u8);
+    const size_t row = (size_t)pl.n_classes * 4 + (size_t)pl.kept_cap * 8 + (size_t)pl.steps * 32 + 256 + other;
+    const int64_t most = std::max<int64_t>(64, std::min<int64_t>(16384, (int64_t)(product_scratch(idx) / row)));
+    const int parts = (int)((nq + most - 1) / most); // of about the same size
+    *per = (nq + parts - 1) / parts;
+    return AVQ_OK;
+}
+
+// A batch in parts through go(first query, queries). AVQ_ENOMEM: no room for a part's scratch
+// (nothing of that part was launched); what it had of it is given back, as the other paths, which take less, need it now.
+template <class Go>
+static int product_in_parts(avq_index *idx, int nq, int per, Go go)
+{
+    int rc = AVQ_OK;
+    for (int q0 = 0; q0 < nq && rc == AVQ_OK; q0 += per) rc = go(q0, std::min(per, nq - q0));
+    if (rc == AVQ_ENOMEM) {
+        idx->product.release();
+        idx->lut_fail.release();
+        idx->fail_rows.release();
+    }
+    return rc;
+}
+
 static int search_product(avq_index *idx, const float *queries, int nq, int k, int reorder_k, int R, int ns, bool u8, int32_t *ids_out,
                           float *scores_out, hipStream_t st)
 {
@@ -875,8 +926,7 @@ static int search_product(avq_index *idx, const float *queries, int nq, int k, i
     ScanParams pf;
     fill_scan_params(idx, nq, R, ns, &pf);
     ScanShape shape;
-    if (scan_pick_shape(idx->NB, c.bits, u8, ns, nq, false, c.bits == 4 ? 8 : 0, 0, &shape) != AVQ_OK)
-        AVQ_TRY(scan_pick_shape(idx->NB, c.bits, u8, ns, nq, false, 0, 0, &shape));
+    AVQ_TRY(product_shape(idx, nq, ns, u8, false, &shape));
     pf.n_tiles = (nq + shape.qt - 1) / shape.qt;
     pf.n_chunks = (int32_t)std::max<int64_t>(1, std::min<int64_t>(128, idx->n_blocks / shape.waves)); // at most
     pf.blocks_per_chunk = 0; // derived on the device
@@ -1115,22 +1165,6 @@ static bool use_product_leaves(const avq_index *idx, int nq, int L, int R, bool 
     return nq >= 64 && work >= (u8 && R > 256 ? 1e8 : 2.5e7);
 }
 
-// The most scratch that a part of a batch through the product takes; parts cost: the points are decoded again for each. Bytes
-// of a query beside the product's own: its tables twice (8-bit ones with the fp32 ones they are made from), the lists and, on
-// a partitioned index, the leaves of the plain scan.
-constexpr size_t kProductScratch = (size_t)4 << 30;
-static size_t product_query_bytes(const avq_index *idx, int ns, bool u8, const ScanShape &shape, int L)
-{
-    const size_t entries = (size_t)idx->cfg.M * idx->kc, list = sizeof(u64) * 64 * (size_t)ns;
-    return entries * (u8 ? 6 : 4) + list + (shape.lists_global ? list * shape.waves * shape.qt : 0) + (size_t)L * 8;
-}
-
-static int product_leaf_shape(const avq_index *idx, int nq, int ns, bool u8, ScanShape *shape)
-{
-    if (scan_pick_shape(idx->NB, idx->cfg.bits, u8, ns, nq, true, 0, 16, shape) == AVQ_OK) return AVQ_OK;
-    return scan_pick_shape(idx->NB, idx->cfg.bits, u8, ns, nq, true, 0, 0, shape);
-}
-
 static int search_leaves_product(avq_index *idx, const float *queries, int nq, int k, int reorder_k, int R, int ns, int L, bool u8,
                                  int32_t *ids_out, float *scores_out, hipStream_t st)
 {
@@ -1193,7 +1227,7 @@ static int search_leaves_product(avq_index *idx, const float *queries, int nq, i
     float *margin = (float *)(base + o_margin), *guess = margin + nq;
     // the plain scan over the leaves of the queries that are handed back
     ScanShape shape;
-    AVQ_TRY(product_leaf_shape(idx, nq, ns, u8, &shape));
+    AVQ_TRY(product_shape(idx, nq, ns, u8, true, &shape));
     AVQ_TRY(idx->partial.reserve(sizeof(u64) * (size_t)nq * C));
     if (shape.lists_global) AVQ_TRY(idx->lists.reserve(sizeof(u64) * (size_t)nq * shape.waves * shape.qt * C));
     const size_t lut_row = u8 ? (size_t)c.M * idx->kc / 4 : (size_t)c.M * idx->kc; // 4-byte units
@@ -1673,15 +1707,13 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
     const bool fuse_tables = small && idx->tune_small_impl != 1 && small_batch_can_fuse_tables(c.bits, c.M, c.d, u8);
     const bool prefilter = !small && use_prefilter(idx, nq, lut_mode, R);
     if (ivf && use_product_leaves(idx, nq, leaves_to_search, R, u8)) {
-        ScanShape shape;
-        AVQ_TRY(product_leaf_shape(idx, nq, ns, u8, &shape));
-        const int per = product_leaf_part(nq, leaves_to_search, c.n_leaves, idx->n, idx->n_blocks, idx->max_leaf_blocks, c.d, R, u8,
-                                          product_query_bytes(idx, ns, u8, shape, leaves_to_search), kProductScratch);
-        int rc = AVQ_OK;
-        for (int q0 = 0; q0 < nq && rc == AVQ_OK; q0 += per)
-            rc = search_leaves_product(idx, queries + (size_t)q0 * c.d, std::min(per, nq - q0), k, reorder_k, R, ns, leaves_to_search, u8,
-                                       ids_out + (size_t)q0 * k, scores_out + (size_t)q0 * k, st);
-        if (rc != AVQ_ENOMEM) return rc; // no room for its scratch (nothing of that part was launched): the other paths take less
+        int per = 0;
+        AVQ_TRY(product_part(idx, nq, R, ns, leaves_to_search, u8, &per));
+        const int rc = product_in_parts(idx, nq, per, [&](int q0, int m) {
+            return search_leaves_product(idx, queries + (size_t)q0 * c.d, m, k, reorder_k, R, ns, leaves_to_search, u8,
+                                         ids_out + (size_t)q0 * k, scores_out + (size_t)q0 * k, st);
+        });
+        if (rc != AVQ_ENOMEM) return rc;
     }
     const bool grouped = ivf && use_grouped_leaves(idx, nq, leaves_to_search, R);
     if (ivf && use_leaf_small(idx, nq, leaves_to_search))
@@ -1692,13 +1724,13 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
         return search_small(idx, queries, nq, k, reorder_k, u8, fuse_tables, w, true, ids_out, scores_out, st);
     }
     if (product) {
-        // at most 16,384 queries at a time: about 100 KB of scratch each, and the points are decoded again for each such part
-        const int parts = (nq + 16383) / 16384, per = (nq + parts - 1) / parts;
-        int rc = AVQ_OK;
-        for (int q0 = 0; q0 < nq && rc == AVQ_OK; q0 += per)
-            rc = search_product(idx, queries + (size_t)q0 * c.d, std::min(per, nq - q0), k, reorder_k, R, ns, u8,
-                                ids_out + (size_t)q0 * k, scores_out + (size_t)q0 * k, st);
-        if (rc != AVQ_ENOMEM) return rc; // no room for its scratch (nothing of that part was launched): the other paths take less
+        int per = 0;
+        AVQ_TRY(product_part(idx, nq, R, ns, 0, u8, &per));
+        const int rc = product_in_parts(idx, nq, per, [&](int q0, int m) {
+            return search_product(idx, queries + (size_t)q0 * c.d, m, k, reorder_k, R, ns, u8, ids_out + (size_t)q0 * k,
+                                  scores_out + (size_t)q0 * k, st);
+        });
+        if (rc != AVQ_ENOMEM) return rc;
     }
     // Batches of 8-bit codes on a flat index: the same search through block bounds, the full scan taking the queries
     // sixteen at a time (byte tables of six bits); "scan_prefilter" = 1 scores every point instead

@@ -544,7 +544,7 @@ int product_leaf_part(int nq, int L, int n_leaves, int64_t n, int64_t n_blocks, 
     const ProductLeafPlan pl = product_leaf_plan(nq, L, n_leaves, n, n_blocks, max_leaf_blocks, d, R, u8);
     const size_t row = (size_t)pl.n_classes * 4 + (size_t)pl.kept_cap * 10 + (size_t)pl.steps * 32 + (size_t)L * 24 + 256 + other;
     const int64_t threads = 64 * 8 / product_ct(pl.steps);
-    int per = (int)std::min<int64_t>(nq, std::max<int64_t>(1, (int64_t)(most / row)));
+    int per = (int)std::min<int64_t>(nq, std::max<int64_t>(64, (int64_t)(most / row)));
     while (per >= kLeafQueries && product_leaf_items(per, L, n_blocks, max_leaf_blocks) * threads >= ((int64_t)1 << 32)) per -= per / 8;
     const int parts = (nq + per - 1) / per; // of about the same size
     return (nq + parts - 1) / parts;

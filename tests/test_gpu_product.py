@@ -243,6 +243,29 @@ def test_product_leaves_infinite_center(k, R):
         np.testing.assert_array_equal(sc.cpu().numpy(), sc1.cpu().numpy())
 
 
+# Scratch for some 300 queries: the batch is taken in parts. Scratch for none: the other paths answer.
+@pytest.mark.parametrize("leaves", [0, 12])
+@pytest.mark.parametrize("bits,M", [(4, 16), (8, 8)])
+def test_product_scratch_limit(leaves, bits, M):
+    x, cb, codes, q, centers, assign = draw_leaves(20_000, 32, M, bits, 900, max(leaves, 1))
+    idx = leaf_index(x, cb, codes, bits, centers, assign) if leaves else index(x, cb, codes, bits)
+    idx.set_tuning("scan_product", 2)
+    idx.profile_enable()
+    qd = torch.from_numpy(q).cuda()
+    for mode in (avq.LUT_F32, avq.LUT_U8):
+        ids, sc = idx.search(qd, 10, 50, mode, leaves // 2)
+        assert idx.profile_read()["scan"][1] == 1
+        for limit, parts in ((30_000, True), (100, False)):
+            idx.set_tuning("scratch_limit_kb", limit)
+            idx.set_tuning("scan_prefilter", 2) # every odd query of a part is handed back
+            a, b = idx.search(qd, 10, 50, mode, leaves // 2)
+            stages = idx.profile_read()
+            assert (stages["scan"][1] > 1) == parts and (stages["finalize"][1] == 0 or not parts)
+            assert torch.equal(ids, a) and torch.equal(sc, b)
+            idx.set_tuning("scratch_limit_kb", 0)
+            idx.set_tuning("scan_prefilter", 0)
+
+
 @pytest.mark.parametrize("n,leaves,nq,L,product", [(20_000, 20, 256, 100 // 10, False), (20_000, 20, 2600, 10, True), (20_000, 20, 2400, 10, False)])
 def test_rule_of_product_leaves(n, leaves, nq, L, product):
     x, cb, codes, q, centers, assign = draw_leaves(n, 32, 16, 4, nq, leaves)
