@@ -872,13 +872,13 @@ static int product_part(const avq_index *idx, int nq, int R, int ns, int L, bool
     return AVQ_OK;
 }
 
-// A batch in parts through go(first query, queries). AVQ_ENOMEM: no room for a part's scratch
+// A batch in parts through go(first query, queries, whether it is the first part). AVQ_ENOMEM: no room for a part's scratch
 // (nothing of that part was launched); what it had of it is given back, as the other paths, which take less, need it now.
 template <class Go>
 static int product_in_parts(avq_index *idx, int nq, int per, Go go)
 {
     int rc = AVQ_OK;
-    for (int q0 = 0; q0 < nq && rc == AVQ_OK; q0 += per) rc = go(q0, std::min(per, nq - q0));
+    for (int q0 = 0; q0 < nq && rc == AVQ_OK; q0 += per) rc = go(q0, std::min(per, nq - q0), q0 == 0);
     if (rc == AVQ_ENOMEM) {
         idx->product.release();
         idx->lut_fail.release();
@@ -887,8 +887,8 @@ static int product_in_parts(avq_index *idx, int nq, int per, Go go)
     return rc;
 }
 
-static int search_product(avq_index *idx, const float *queries, int nq, int k, int reorder_k, int R, int ns, bool u8, int32_t *ids_out,
-                          float *scores_out, hipStream_t st)
+static int search_product(avq_index *idx, const float *queries, int nq, int k, int reorder_k, int R, int ns, bool u8, bool first,
+                          int32_t *ids_out, float *scores_out, hipStream_t st)
 {
     const avq_config &c = idx->cfg;
     const int C = 64 * ns;
@@ -935,13 +935,13 @@ static int search_product(avq_index *idx, const float *queries, int nq, int k, i
     if (shape.lists_global) AVQ_TRY(idx->lists.reserve(sizeof(u64) * items * shape.waves * shape.qt * C));
     const size_t row_floats = u8 ? (size_t)c.M * idx->kc / 4 : (size_t)c.M * idx->kc; // a query's tables, in 4-byte units
     AVQ_TRY(idx->lut_fail.reserve(sizeof(float) * (size_t)pf.n_tiles * shape.qt * row_floats));
-    AVQ_TRY(idx->fail.reserve(sizeof(int32_t) * (4 + (size_t)nq)));
-    uint32_t *fail_count = idx->fail.as<uint32_t>();
-    int32_t *fail_list = idx->fail.as<int32_t>() + 4;
+    AVQ_TRY(idx->fail.reserve(sizeof(int32_t) * (8 + (size_t)nq)));
+    uint32_t *fail_total = idx->fail.as<uint32_t>(), *fail_count = fail_total + 4;
+    int32_t *fail_list = idx->fail.as<int32_t>() + 8;
     {
         StageTimer t(idx, AVQ_STAGE_LUT, st);
         if (u8) AVQ_TRY(build_tables(idx, queries, nq, AVQ_LUT_U8, st));
-        AVQ_TRY(launch_product_pack(p, queries, idx->codebooks.as<float>(), fail_count, false, st));
+        AVQ_TRY(launch_product_pack(p, queries, idx->codebooks.as<float>(), first ? fail_total : fail_count, first ? 8 : 4, false, st));
     }
     {
         StageTimer t(idx, AVQ_STAGE_SAMPLE, st);
@@ -978,6 +978,7 @@ static int search_product(avq_index *idx, const float *queries, int nq, int k, i
     r.scores_out = scores_out;
     r.fail_list = fail_list;
     r.fail_count = fail_count;
+    r.fail_total = fail_total;
     r.fail_lut = idx->lut_fail.p;
     r.kept_cap = pl.kept_cap; r.cnt_stride = pl.cnt_stride;
     r.nq = nq; r.d = c.d; r.M = c.M; r.NB = idx->NB; r.R = R; r.k = k; r.reorder = reorder_k != 0;
@@ -1166,7 +1167,7 @@ static bool use_product_leaves(const avq_index *idx, int nq, int L, int R, bool 
 }
 
 static int search_leaves_product(avq_index *idx, const float *queries, int nq, int k, int reorder_k, int R, int ns, int L, bool u8,
-                                 int32_t *ids_out, float *scores_out, hipStream_t st)
+                                 bool first, int32_t *ids_out, float *scores_out, hipStream_t st)
 {
     const avq_config &c = idx->cfg;
     const int C = 64 * ns;
@@ -1233,9 +1234,9 @@ static int search_leaves_product(avq_index *idx, const float *queries, int nq, i
     const size_t lut_row = u8 ? (size_t)c.M * idx->kc / 4 : (size_t)c.M * idx->kc; // 4-byte units
     AVQ_TRY(idx->lut_fail.reserve(sizeof(float) * (size_t)nq * lut_row));
     AVQ_TRY(idx->fail_rows.reserve(sizeof(float) * (size_t)nq * (2 + (size_t)2 * L)));
-    AVQ_TRY(idx->fail.reserve(sizeof(int32_t) * (4 + (size_t)nq)));
-    uint32_t *fail_count = idx->fail.as<uint32_t>();
-    int32_t *fail_list = idx->fail.as<int32_t>() + 4;
+    AVQ_TRY(idx->fail.reserve(sizeof(int32_t) * (8 + (size_t)nq)));
+    uint32_t *fail_total = idx->fail.as<uint32_t>(), *fail_count = fail_total + 4;
+    int32_t *fail_list = idx->fail.as<int32_t>() + 8;
     if (u8) {
         StageTimer t(idx, AVQ_STAGE_LUT, st);
         AVQ_TRY(build_tables(idx, queries, nq, AVQ_LUT_U8, st));
@@ -1248,7 +1249,7 @@ static int search_leaves_product(avq_index *idx, const float *queries, int nq, i
     }
     {
         StageTimer t(idx, AVQ_STAGE_SAMPLE, st); // here: operands, regrouping, bounds
-        AVQ_TRY(launch_product_pack(p.base, queries, idx->codebooks.as<float>(), fail_count, true, st));
+        AVQ_TRY(launch_product_pack(p.base, queries, idx->codebooks.as<float>(), first ? fail_total : fail_count, first ? 8 : 4, true, st));
         AVQ_TRY(launch_group_offsets(g, c.n_leaves, st));
         AVQ_TRY(launch_product_pairs(p, idx->leaf_ids.as<int32_t>(), idx->leaf_ip.as<float>(), g.pos, c.n_leaves, items, pl.most_items, n_items, st));
         AVQ_TRY(launch_product_leaf(p, true, pl.most_items, st));
@@ -1278,6 +1279,7 @@ static int search_leaves_product(avq_index *idx, const float *queries, int nq, i
     r.base.scores_out = scores_out;
     r.base.fail_list = fail_list;
     r.base.fail_count = fail_count;
+    r.base.fail_total = fail_total;
     r.base.fail_lut = idx->lut_fail.p;
     r.base.kept_cap = pl.kept_cap; r.base.cnt_stride = pl.cnt_stride;
     r.base.nq = nq; r.base.d = c.d; r.base.M = c.M; r.base.NB = idx->NB; r.base.R = R; r.base.k = k; r.base.reorder = reorder_k != 0;
@@ -1709,8 +1711,8 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
     if (ivf && use_product_leaves(idx, nq, leaves_to_search, R, u8)) {
         int per = 0;
         AVQ_TRY(product_part(idx, nq, R, ns, leaves_to_search, u8, &per));
-        const int rc = product_in_parts(idx, nq, per, [&](int q0, int m) {
-            return search_leaves_product(idx, queries + (size_t)q0 * c.d, m, k, reorder_k, R, ns, leaves_to_search, u8,
+        const int rc = product_in_parts(idx, nq, per, [&](int q0, int m, bool first) {
+            return search_leaves_product(idx, queries + (size_t)q0 * c.d, m, k, reorder_k, R, ns, leaves_to_search, u8, first,
                                          ids_out + (size_t)q0 * k, scores_out + (size_t)q0 * k, st);
         });
         if (rc != AVQ_ENOMEM) return rc;
@@ -1726,8 +1728,8 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
     if (product) {
         int per = 0;
         AVQ_TRY(product_part(idx, nq, R, ns, 0, u8, &per));
-        const int rc = product_in_parts(idx, nq, per, [&](int q0, int m) {
-            return search_product(idx, queries + (size_t)q0 * c.d, m, k, reorder_k, R, ns, u8, ids_out + (size_t)q0 * k,
+        const int rc = product_in_parts(idx, nq, per, [&](int q0, int m, bool first) {
+            return search_product(idx, queries + (size_t)q0 * c.d, m, k, reorder_k, R, ns, u8, first, ids_out + (size_t)q0 * k,
                                   scores_out + (size_t)q0 * k, st);
         });
         if (rc != AVQ_ENOMEM) return rc;

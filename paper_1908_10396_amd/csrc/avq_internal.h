@@ -372,7 +372,7 @@ int launch_gather_rows(const float *src, float *dst, const int32_t *row, const u
 // Batches on a flat index of at most 256 dimensions: candidates from a matrix product of the queries with the decoded
 // points, scored again the way every scan scores them. launch_product_pack -> launch_product_scan(sample) ->
 // launch_product_bound -> launch_product_scan -> launch_product_refine, which answers every query but those it appends to
-// fail_list (fail_count is cleared by the pack launch); a plain scan of those, and launch_product_fallback.
+// fail_list (its counters are cleared by the pack launch); a plain scan of those, and launch_product_fallback.
 struct ProductMeta;
 struct ProductQuery;
 constexpr size_t kProductInfoBytes = 16; // of either
@@ -398,8 +398,9 @@ struct ProductParams {
     int64_t n, groups;
     int32_t nq, d, M, bits, NB, n_tiles, stages_per_chunk, chunks, stride, run, n_classes, kept_cap, cnt_stride;
 };
-// rows: packed as [query][steps][16]
-int launch_product_pack(const ProductParams &p, const float *queries, const float *codebooks, uint32_t *fail_count, bool rows, hipStream_t st);
+// rows: packed as [query][steps][16]. fail_clear: the n_clear words to clear of the counters.
+int launch_product_pack(const ProductParams &p, const float *queries, const float *codebooks, uint32_t *fail_clear, int n_clear, bool rows,
+                        hipStream_t st);
 int launch_product_scan(const ProductParams &p, bool sample, hipStream_t st);
 // unit: [nq] the 8-bit tables' scale, NULL with fp32 tables. leaf_ids, leaf_ip [nq][L] (NULL: flat index): classes hold ordering
 // values (0: none) of products plus <q, center>; fewer than r of them: no line (-infinity).
@@ -417,7 +418,7 @@ struct ProductRefineParams {
     int32_t *ids_out;           // [nq][k]
     float *scores_out;
     int32_t *fail_list;
-    uint32_t *fail_count;
+    uint32_t *fail_count, *fail_total; // of this part of a call; [4] of the call: all, and by reason
     void *fail_lut;             // the tables of the queries in fail_list, side by side
     int32_t kept_cap, cnt_stride, nq, d, M, NB, R, k, reorder, force_fail_odd;
 };

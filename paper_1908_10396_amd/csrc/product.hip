@@ -49,8 +49,8 @@ __device__ __forceinline__ int scale_exp(float largest) // 2^result * largest is
 __global__ void __launch_bounds__(1024)
 product_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, int n_tiles, const float *__restrict__ codebooks,
                     int M, int kc, _Float16 *__restrict__ cb16, ProductMeta *__restrict__ meta, v8h *__restrict__ packed,
-                    ProductQuery *__restrict__ qinfo, uint32_t *__restrict__ kept_cnt, int cnt_stride, uint32_t *__restrict__ fail_count,
-                    int rows)
+                    ProductQuery *__restrict__ qinfo, uint32_t *__restrict__ kept_cnt, int cnt_stride, uint32_t *__restrict__ fail_clear,
+                    int n_clear, int rows)
 {
     __shared__ float wave_max[16];
     __shared__ uint32_t n2_max[256], e2_max[256];
@@ -69,7 +69,7 @@ product_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps,
         if (__builtin_amdgcn_ballot_w64(odd) != 0ull) big = INFINITY;
         if (lane == 0) wave_max[wave] = big;
         if (tid < 256) { n2_max[tid] = 0u; e2_max[tid] = 0u; }
-        if (tid < 4) fail_count[tid] = 0u;
+        if (tid < n_clear) fail_clear[tid] = 0u;
         __syncthreads();
         for (int w = 0; w < 16; ++w) big = fmaxf(big, wave_max[w]);
         const bool bad = !(big < INFINITY);
@@ -534,7 +534,8 @@ product_refine_kernel(const ProductRefineParams r)
         if (tid == 0) {
             slot_s = (int)atomicAdd(r.fail_count, 1u);
             r.fail_list[slot_s] = q;
-            atomicAdd(r.fail_count + why, 1u); // statistics: 1 = too many kept points, 2 = bound guessed too high, 3 = other
+            atomicAdd(r.fail_total, 1u); // statistics of the call: 1 = too many kept points, 2 = bound guessed too high, 3 = other
+            atomicAdd(r.fail_total + why, 1u);
         }
         __syncthreads();
         const int entries = r.M << BITS;
@@ -764,11 +765,12 @@ int launch_product_scan(const ProductParams &p, bool sample, hipStream_t st)
     }
 }
 
-int launch_product_pack(const ProductParams &p, const float *queries, const float *codebooks, uint32_t *fail_count, bool rows, hipStream_t st)
+int launch_product_pack(const ProductParams &p, const float *queries, const float *codebooks, uint32_t *fail_clear, int n_clear, bool rows,
+                        hipStream_t st)
 {
     hipLaunchKernelGGL(product_pack_kernel, dim3(1 + (p.n_tiles + 3) / 4), dim3(1024), 0, st, queries, p.nq, p.d, product_steps(p.d),
                        p.n_tiles, codebooks, p.M, 1 << p.bits, (_Float16 *)p.cb16, p.meta, (v8h *)p.packed, p.qinfo, p.kept_cnt,
-                       p.cnt_stride, fail_count, rows ? 1 : 0);
+                       p.cnt_stride, fail_clear, n_clear, rows ? 1 : 0);
     AVQ_HIP(hipGetLastError());
     return AVQ_OK;
 }

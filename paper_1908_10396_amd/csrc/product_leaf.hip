@@ -395,7 +395,8 @@ product_leaf_refine_kernel(const ProductLeafRefineParams r)
         if (tid == 0) {
             slot_s = (int)atomicAdd(b.fail_count, 1u);
             b.fail_list[slot_s] = q;
-            atomicAdd(b.fail_count + why, 1u); // statistics: 1 = too many kept points, 2 = bound too high, 3 = other
+            atomicAdd(b.fail_total, 1u); // statistics of the call: 1 = too many kept points, 2 = bound too high, 3 = other
+            atomicAdd(b.fail_total + why, 1u);
             if (U8) { r.fail_scale[slot_s] = scale; r.fail_bias[slot_s] = bias; }
         }
         __syncthreads();

@@ -243,7 +243,8 @@ def test_product_leaves_infinite_center(k, R):
         np.testing.assert_array_equal(sc.cpu().numpy(), sc1.cpu().numpy())
 
 
-# Scratch for some 300 queries: the batch is taken in parts. Scratch for none: the other paths answer.
+# Scratch for some 300 queries: the batch is taken in parts, whose handed back queries are counted together. Scratch for none: the
+# other paths answer.
 @pytest.mark.parametrize("leaves", [0, 12])
 @pytest.mark.parametrize("bits,M", [(4, 16), (8, 8)])
 def test_product_scratch_limit(leaves, bits, M):
@@ -261,6 +262,7 @@ def test_product_scratch_limit(leaves, bits, M):
             a, b = idx.search(qd, 10, 50, mode, leaves // 2)
             stages = idx.profile_read()
             assert (stages["scan"][1] > 1) == parts and (stages["finalize"][1] == 0 or not parts)
+            assert not parts or 440 <= idx.debug_unverified_queries() <= 460
             assert torch.equal(ids, a) and torch.equal(sc, b)
             idx.set_tuning("scratch_limit_kb", 0)
             idx.set_tuning("scan_prefilter", 0)
