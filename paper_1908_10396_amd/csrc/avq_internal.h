@@ -436,6 +436,7 @@ struct ProductLeafPlan {
 };
 bool product_leaf_supported(int d, int M, int n_leaves, int64_t n_blocks, int64_t max_leaf_blocks, int nq, int L, int R);
 ProductLeafPlan product_leaf_plan(int nq, int L, int n_leaves, int64_t n, int64_t n_blocks, int64_t max_leaf_blocks, int d, int R, bool u8);
+bool product_leaf_narrow(int L, int n_leaves, int R); // few of the leaves are probed
 int product_leaf_part(int nq, int L, int n_leaves, int64_t n, int64_t n_blocks, int64_t max_leaf_blocks, int d, int R, bool u8, size_t other, size_t most);
 struct ProductLeafParams {
     ProductParams base;       // packed: rows [nq, rounded up][steps][16]; n: slots; kept: ordering value of the product plus <q, center> << 32 | slot of the index

@@ -516,18 +516,26 @@ static int64_t product_leaf_items(int nq, int L, int64_t n_blocks, int64_t max_l
     return n_blocks + std::min(max_leaf_blocks * ((int64_t)nq * L / kLeafQueries), n_blocks * (nq / kLeafQueries));
 }
 
+bool product_leaf_narrow(int L, int n_leaves, int R) { return (double)L < (R > 256 ? 0.06 : 0.03) * n_leaves; }
+
 // Scratch for nq queries: words, slots and items of the launches.
 ProductLeafPlan product_leaf_plan(int nq, int L, int n_leaves, int64_t n, int64_t n_blocks, int64_t max_leaf_blocks, int d, int R, bool u8)
 {
     ProductLeafPlan pl{};
     pl.steps = product_steps(d);
     pl.n_tiles = (nq + 127) / 128 * 4;
-    // classes as large as leave three of them per result, at most all of a lane's products
+    // Classes as large as leave three of them per result, at most all of a lane's products. Where a query probes a few leaves in
+    // a hundred, its best points lie in a few of those, and large classes would leave a line far below them and more points than
+    // there is room for: smaller ones, and with many results more blocks with classes of their own. (10,000,000 points, 3,000 queries, R =
+    // 500, 20 of 2,000 leaves: 320 classes 18.8 ms, every query scanned plainly, 20,480 of them 3.5; 4,000,000, 40 of 4,000 leaves,
+    // R = 100 1.41 / 1.16, R = 500 4.2 / 1.9. Classes of four points where 100 leaves are probed cost too much otherwise: 2.3 / 14 ms.)
     const double points = (double)L * (double)n / n_leaves;
     const int whole = product_ct(pl.steps) * 16;
-    pl.run = points >= 3.0 * whole * R ? whole : points >= 48.0 * R ? 16 : 4;
+    const bool narrow = product_leaf_narrow(L, n_leaves, R);
+    pl.run = points >= 3.0 * whole * R && !narrow ? whole : points >= 48.0 * R && !(narrow && R > 256 && L <= 128) ? 16 : 4;
     // up to four blocks of a leaf have classes of their own
-    pl.pair_classes = (int)std::min<int64_t>(4, std::max<int64_t>(1, max_leaf_blocks)) * (256 / pl.run);
+    const int64_t own_blocks = narrow && R > 256 ? 16 : 4;
+    pl.pair_classes = (int)std::min<int64_t>(own_blocks, std::max<int64_t>(1, max_leaf_blocks)) * (256 / pl.run);
     while ((int64_t)L * pl.pair_classes > kProductMaxClasses && pl.pair_classes > 256 / pl.run) pl.pair_classes -= 256 / pl.run;
     while ((int64_t)L * pl.pair_classes > kProductMaxClasses && pl.run < 16) { pl.run = 16; pl.pair_classes = 16; }
     pl.n_classes = L * pl.pair_classes;

@@ -268,6 +268,23 @@ def test_product_scratch_limit(leaves, bits, M):
             idx.set_tuning("scan_prefilter", 0)
 
 
+# Few of the leaves probed and many results: classes enough for a line that holds, rather than every query scanned plainly.
+def test_product_leaves_few_of_large_ones():
+    rng = np.random.default_rng(8)
+    n, d, M, leaves, nq = 1_300_000, 16, 8, 100, 64
+    cb = (rng.standard_normal((M, 16, d // M)) * 0.2).astype(np.float32)
+    idx = leaf_index(unit_rows(rng, n, d), cb, rng.integers(0, 16, (n, M)).astype(np.uint8), 4, 0.5 * unit_rows(rng, leaves, d),
+                     rng.integers(0, leaves, n).astype(np.int32))
+    qd = torch.from_numpy(unit_rows(rng, nq, d)).cuda()
+    for mode in (avq.LUT_F32, avq.LUT_U8):
+        idx.set_tuning("scan_product", 2)
+        ids, sc = idx.search(qd, 10, 500, mode, 2)
+        assert idx.debug_unverified_queries() <= nq // 10
+        idx.set_tuning("scan_product", 1)
+        a, b = idx.search(qd, 10, 500, mode, 2)
+        assert torch.equal(ids, a) and torch.equal(sc, b)
+
+
 @pytest.mark.parametrize("n,leaves,nq,L,product", [(20_000, 20, 256, 100 // 10, False), (20_000, 20, 2600, 10, True), (20_000, 20, 2400, 10, False)])
 def test_rule_of_product_leaves(n, leaves, nq, L, product):
     x, cb, codes, q, centers, assign = draw_leaves(n, 32, 16, 4, nq, leaves)
