@@ -1148,10 +1148,18 @@ static int search_leaves_grouped(avq_index *idx, const float *queries, int nq, i
 }
 
 // Batches on a partitioned index through the product of the queries with the decoded points of the leaves they probe
-// (product_leaf.hip). Measured, other path / product, us a call, by the points scored (queries x probed leaves x points of a leaf), 4-bit
-// codes of 100 dimensions, R = 100: 1e7 137 / 124 (500 queries), 1.5e7 185 / 282 (30 of 1,000 leaves, 15 queries each), 1.8e7 266 / 220,
-// 6e7 536 / 313, 6e8 2,822 / 1,222; R = 500 2,434 / 565 at 1.2e8. Code sizes without kernels of their own are 1.1 to 5.5 times as fast
-// from 2.5e7 on. 8-bit codes of 256 dimensions, 50 queries a leaf: 479 / 508 (the decoding); 8-bit tables, R = 500: 1,216 / 1,344 at 6e7.
+// (product_leaf.hip). Both launches decode every block of every probed leaf whatever its queries, and those are rounded up to 32, so
+// what counts beside the points scored (queries x probed leaves x points of a leaf) is the queries of a leaf. Measured, other path /
+// product, us a call, R = 100 and fp32 tables unless said otherwise:
+//  points scored: 100 dimensions, 4-bit codes: 1e7 137 / 124 (500 queries), 1.8e7 266 / 220, 6e7 536 / 313, 6e8 2,822 / 1,222; R = 500
+//   2,434 / 565 at 1.2e8; 8-bit tables, R = 500: 1,216 / 1,344 at 6e7.
+//  queries of a leaf, where the other path is one workgroup a query: 10,000,000 points: 3 (64 queries) 226 / 1,536, 16 665 / 1,747,
+//   25 1,449 / 1,800; 5,000,000 x 105 points: 24 785 / 1,236, 30 1,050 / 910; 1,183,514 x 128: 25 330 / 451, 50 647 / 524; 8-bit codes of 256
+//   dimensions 50 479 / 508; R = 500: 24 689 / 500.
+//  where it is regrouped by leaf: leaves of 1,000 points 10 3,029 / 2,228, 75 6,085 / 3,012; of 3,300 to 5,000 points 75 2,034 / 2,041,
+//   80 760 / 1,098, 90 1,499 / 1,248, 250 3,660 / 2,949; R = 500 50 10,194 / 5,023.
+//  few of the leaves probed (many small classes of points): 1,183,514 points, 30 of 2,000 leaves, 45 queries a leaf 452 / 605, 10,000,000,
+//   100 of 10,000, 100 a leaf, 8-bit codes 4,297 / 4,921; 1,183,514, 5 of 500 leaves, 100 a leaf 1,093 / 704: the two estimates below.
 static bool use_product_leaves(const avq_index *idx, int nq, int L, int R, bool u8)
 {
     const avq_config &c = idx->cfg;
@@ -1161,9 +1169,16 @@ static bool use_product_leaves(const avq_index *idx, int nq, int L, int R, bool 
     // any tuning of the other kernels' launches asks for those kernels
     if (idx->tune_target_wgs || idx->tune_waves || idx->tune_qt || idx->tune_mfma || idx->tune_prefilter == 1 || idx->tune_prefilter_cap ||
         idx->tune_sample || idx->tune_small_impl || idx->tune_small_batch >= 0 || idx->tune_group_min || idx->tune_bound_leaves) return false;
-    const double work = (double)nq * L * ((double)idx->n / c.n_leaves); // points scored
-    if (c.bits == 8 && c.d > 128 && (double)nq * L < 100.0 * c.n_leaves) return false;
-    return nq >= 64 && work >= (u8 && R > 256 ? 1e8 : 2.5e7);
+    const double n = (double)idx->n, q = (double)nq, leaf = n / c.n_leaves, work = q * L * leaf, per_leaf = q * L / c.n_leaves;
+    if (nq < 64 || work < (u8 && R > 256 ? 1e8 : 2.5e7)) return false;
+    if (use_grouped_leaves(idx, nq, L, R)) return per_leaf >= (leaf <= 1500.0 ? 8.0 : R <= 256 ? 100.0 : 50.0);
+    if (per_leaf < (c.bits == 8 && c.d > 128 ? 100.0 : R <= 256 ? 30.0 : 28.0)) return false;
+    if (!product_leaf_narrow(L, c.n_leaves, R)) return true;
+    const ProductLeafPlan pl = product_leaf_plan(nq, L, c.n_leaves, idx->n, idx->n_blocks, idx->max_leaf_blocks, c.d, R, u8);
+    const double slots = 256.0 * (double)idx->n_blocks;
+    const double product = 125.0 + slots * pl.steps * (2e-5 + 8e-8 * (per_leaf + 16.0)) + q * (0.0001 * L + (u8 ? 0.00055 : 0.00025) * R + 8e-6 * pl.n_classes);
+    const double plain = 130.0 + work * (idx->NB * (c.bits == 8 ? 1.4e-7 : idx->NB <= 32 ? 1.5e-7 : 2.8e-7) + 0.0007 / q) + q * (0.0002 * L + (u8 ? 0.0 : 0.0003) * R);
+    return product < 1.15 * plain;
 }
 
 static int search_leaves_product(avq_index *idx, const float *queries, int nq, int k, int reorder_k, int R, int ns, int L, bool u8,

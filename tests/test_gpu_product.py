@@ -285,7 +285,9 @@ def test_product_leaves_few_of_large_ones():
         assert torch.equal(ids, a) and torch.equal(sc, b)
 
 
-@pytest.mark.parametrize("n,leaves,nq,L,product", [(20_000, 20, 256, 100 // 10, False), (20_000, 20, 2600, 10, True), (20_000, 20, 2400, 10, False)])
+# too little work; enough; just too few and enough queries of a leaf
+@pytest.mark.parametrize("n,leaves,nq,L,product", [(20_000, 20, 256, 100 // 10, False), (20_000, 20, 2600, 10, True), (20_000, 20, 2400, 10, False),
+                                                   (1_000_000, 1000, 100, 290, False), (1_000_000, 1000, 100, 310, True)])
 def test_rule_of_product_leaves(n, leaves, nq, L, product):
     x, cb, codes, q, centers, assign = draw_leaves(n, 32, 16, 4, nq, leaves)
     idx = avq.Index(32, 16, 4, n_leaves=leaves)
