@@ -61,7 +61,8 @@ def test_product_matches(n, d, M, bits, nq, k, R):
 
 
 # The guess holds, and what it lets through fits, for data without many equal sums.
-@pytest.mark.parametrize("n,d,M,bits,nq", [(30_000, 100, 50, 4, 200), (30_000, 100, 25, 8, 200), (260_000, 64, 32, 4, 64)])
+@pytest.mark.parametrize("n,d,M,bits,nq", [(30_000, 100, 50, 4, 200), (30_000, 100, 25, 8, 200), (260_000, 64, 32, 4, 64),
+                                           (20_000, 160, 20, 8, 100), (20_000, 192, 96, 4, 70), (12_000, 256, 64, 4, 50)])
 def test_product_answers_all(n, d, M, bits, nq):
     x, cb, codes, q = draw(n, d, M, bits, nq)
     check(x, cb, codes, bits, q, 10, 100, 0)
@@ -149,7 +150,7 @@ def leaf_index(x, cb, codes, bits, centers, assign):
     return idx
 
 
-def check_leaves(x, cb, codes, bits, q, centers, assign, k, R, L):
+def check_leaves(x, cb, codes, bits, q, centers, assign, k, R, L, unverified=None):
     idx = leaf_index(x, cb, codes, bits, centers, assign)
     idx.set_tuning("scan_product", 2)
     qd = torch.from_numpy(q).cuda()
@@ -160,7 +161,10 @@ def check_leaves(x, cb, codes, bits, q, centers, assign, k, R, L):
             ids, sc = idx.search(qd, k, R, mode, L)
             np.testing.assert_array_equal(ids.cpu().numpy(), oi, err_msg="tables %d prefilter %d" % (mode, prefilter))
             np.testing.assert_array_equal(sc.cpu().numpy(), os_, err_msg="tables %d prefilter %d" % (mode, prefilter))
-            assert prefilter == 0 or idx.debug_unverified_queries() >= len(q) // 2
+            if prefilter == 2:
+                assert idx.debug_unverified_queries() >= len(q) // 2
+            elif unverified is not None:
+                assert idx.debug_unverified_queries() == unverified
 
 
 # a leaf's last block nearly empty or full, several blocks that share classes, leaves without points; fewer points than results;
@@ -174,6 +178,16 @@ def check_leaves(x, cb, codes, bits, q, centers, assign, k, R, L):
     (700, 48, 16, 4, 20, 300, 40, 10, 100, False), (4000, 224, 28, 4, 20, 3, 2, 10, 300, False)])
 def test_product_leaves_match(n, d, M, bits, nq, leaves, L, k, R, skew):
     check_leaves(*reorder_args(draw_leaves(n, d, M, bits, nq, leaves, skew=skew), bits), k, R, L)
+
+
+# Data without many equal sums: no query is handed back. Classes of 64, 16 and 4 points in waves of two column tiles, of 32, 16 and 4 in
+# waves of one; blocks that share classes; few of the leaves probed.
+@pytest.mark.parametrize("n,d,M,bits,nq,leaves,L,R", [
+    (6000, 100, 50, 4, 64, 12, 4, 10), (6000, 100, 50, 4, 64, 12, 4, 20), (6000, 100, 25, 8, 64, 12, 4, 100), (6000, 192, 96, 4, 40, 12, 4, 10),
+    (6000, 192, 96, 4, 40, 12, 4, 40), (6000, 256, 32, 8, 40, 12, 4, 100), (20_000, 64, 32, 4, 40, 6, 4, 50), (20_000, 160, 80, 4, 40, 6, 4, 50),
+    (40_000, 32, 16, 4, 40, 70, 2, 10), (40_000, 32, 16, 4, 40, 70, 4, 300)])
+def test_product_leaves_answers_all(n, d, M, bits, nq, leaves, L, R):
+    check_leaves(*reorder_args(draw_leaves(n, d, M, bits, nq, leaves), bits), min(R, 10), R, L, 0)
 
 
 def reorder_args(drawn, bits):
