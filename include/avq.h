@@ -168,10 +168,10 @@ int avq_update_leaf_centers(avq_index *idx, const float *x, int64_t n, int32_t m
  *  keep the R = reorder_k best by (score descending, id ascending). Most batches
  *    (16 queries or more on a flat index large enough, up to 256 dimensions; on
  *    a partitioned one 64 queries or more that probe 25 million points or more
- *    in all) do not score every point: an f16 matrix product of the queries with
- *    the points that the codes stand for names every point that the bound on its
- *    error does not rule out, and those are scored with the tables, in the order
- *    of additions given above. Where that does not pay, batches
+ *    in all, some tens of queries a leaf) do not score every point: an f16 matrix
+ *    product of the queries with the points that the codes stand for names every
+ *    point that the bound on its error does not rule out, and those are scored with
+ *    the tables, in the order of additions given above. Where that does not pay, batches
  *    (36 queries or more) with fp32 tables on a flat index of 4-bit codes do
  *    not score every point in fp32 either: the 8-bit tables are built as well, the
  *    integer sums of all points are formed on the matrix cores, every point

@@ -458,7 +458,7 @@ extern "C" int avq_set_database(avq_index *idx, const float *x, const uint8_t *p
         return AVQ_EINVAL;
     }
     if (c.n_leaves > 0 && !idx->have_centers) { set_error("avq_set_database: no leaf centers yet"); return AVQ_ESTATE; }
-    AVQ_TRY(idx->codes_logical.reserve((size_t)n * idx->NB + 16)); // rows are read in whole words
+    AVQ_TRY(idx->codes_logical.reserve((size_t)n * idx->NB + 16)); // rows are read in whole words, and a word ahead
     AVQ_HIP(hipMemcpyAsync(idx->codes_logical.p, packed, (size_t)n * idx->NB, hipMemcpyDefault, st));
     if (leaf_assign) {
         AVQ_TRY(idx->assign.reserve(sizeof(int32_t) * (size_t)n));
@@ -482,7 +482,7 @@ extern "C" int avq_encode(avq_index *idx, const float *x, int64_t n, void *hip_s
     if (c.n_leaves > 0) AVQ_TRY(check_assign(c.d, c.n_leaves, c.leaf_aniso_iters > 0)); // refused: the database stays
     idx->n = 0;
     const ScratchKeeper keep{&idx->train_ws};
-    AVQ_TRY(idx->codes_logical.reserve((size_t)n * idx->NB + 16)); // rows are read in whole words
+    AVQ_TRY(idx->codes_logical.reserve((size_t)n * idx->NB + 16)); // rows are read in whole words, and a word ahead
     const int32_t *assign = nullptr;
     if (c.n_leaves > 0) {
         AVQ_TRY(idx->assign.reserve(sizeof(int32_t) * (size_t)n));

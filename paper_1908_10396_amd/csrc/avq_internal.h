@@ -412,7 +412,7 @@ struct ProductRefineParams {
     const float *margin;        // [nq], < 0: the product decides nothing
     const float *guess;         // [nq]: the line was guess - margin
     const float *queries, *codebooks, *x;
-    const uint8_t *codes;       // logical [n][NB], readable to the next multiple of four bytes
+    const uint8_t *codes;       // logical [n][NB], readable for eight bytes beyond the last row (words are read ahead)
     const uint8_t *lut8;        // 8-bit tables (with scale and bias), else unused
     const float *scale, *bias;
     int32_t *ids_out;           // [nq][k]
