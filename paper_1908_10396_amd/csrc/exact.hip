@@ -78,14 +78,16 @@ exact_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, v
 // Eight waves of 64 points, whose operands stay in registers (x is read once), against all queries, whose tiles of 32
 // go through LDS up to two ahead (x: 473 MB, queries: 224 KB at the size above). The products of one accumulator are issued
 // between the instructions that take the maximum of the other one (sched_barrier keeps the order): 0.46 -> 0.42 ms at the size
-// above. Up to 14 operands of two column tiles a wave fits 128 registers but for a few outside the loop, so that two workgroups
-// share a compute unit and one's row loads overlap the other's products: 0.33. The others would spill in the loop (one column tile
-// of 12 operands: 14 loads from scratch every two tiles, each of which also waits for the staged ones; 1,183,514 x 160, 1,000
-// queries, exact search whole: 1,051 us with one workgroup and products and maxima one after the other, 1,090 with two, 971 with
-// one). best[q][block of 64]: the workgroup's eight
+// above. 14 operands of two column tiles fit 128 registers but for a few outside the loop, so that two workgroups share a compute
+// unit and one's row loads overlap the other's products: 0.33 (PAIR; fewer operands fit without being told). With one workgroup
+// for a compute unit, or a few queries and hence nothing to overlap, those few registers are a loss (launch_exact has the line). More
+// operands would spill in the loop (one column tile of 12: 14 loads from scratch every two tiles, each of which also waits for
+// the staged ones; 1,183,514 x 160, 1,000 queries, exact search whole: 1,051 us with one workgroup and products and maxima one after
+// the other, 1,090 with two, 971 with one). best[q][block of 64]: the workgroup's eight
 // maxima of a query leave as 32 adjacent bytes. xnorm[block] = largest norm and conversion error of its points.
-template <int NS, int CT>
-__global__ void __launch_bounds__(512, CT == 2 && NS <= 7 ? 4 : 2)
+// PAIR: as many registers as let two share a compute unit.
+template <int NS, int CT, bool PAIR>
+__global__ void __launch_bounds__(512, PAIR ? 4 : 2)
 exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *__restrict__ packed, int n_tiles, int nq,
                      float *__restrict__ best, int64_t best_stride, float2 *__restrict__ xnorm, uint32_t *__restrict__ need)
 {
@@ -440,17 +442,25 @@ int launch_exact(const float *x, int64_t n, int d, const float *queries, int nq,
     const int block_points = steps > 8 ? 32 : 64;
     *need_out = w.need;
     hipLaunchKernelGGL(exact_pack_kernel, dim3((unsigned)tiles), dim3(256), 0, st, queries, nq, d, steps, w.packed, w.qnorm, w.need);
-#define AVQ_EXACT(NS, CT)                                                                                                \
-    hipLaunchKernelGGL((exact_product_kernel<NS, CT>), dim3((unsigned)(w.stride / 8)), dim3(512), 0, st, x, n, d, w.packed, \
+    // Two workgroups a compute unit: from 257 of them and three tiles of queries on, or 513 and two. 100 dimensions, one / two, us a
+    // call: 77,000 points, 2 queries 42.8 / 45.1, 1,000 133.6 / 135.5; 200,000, 64 queries 65.4 / 66.3, 130 74.2 / 73.2, 1,000 182.6 / 170.7;
+    // 400,000, 64 89.6 / 87.6; 1,183,514, 16 queries 191.9 / 197.4, 64 202.1 / 200.4, 130 226.4 / 212.6, 1,000 605 / 520.
+    const int64_t groups = w.stride / 8;
+    const bool pair = groups > 256 && tiles > (groups > 512 ? 1 : 2);
+#define AVQ_EXACT(NS, CT, PAIR)                                                                                          \
+    hipLaunchKernelGGL((exact_product_kernel<NS, CT, PAIR>), dim3((unsigned)(w.stride / 8)), dim3(512), 0, st, x, n, d, w.packed, \
                        tiles, nq, w.best, w.stride, w.xnorm, w.need)
     switch (steps) {
-    case 2: AVQ_EXACT(2, 2); break;
-    case 3: AVQ_EXACT(3, 2); break;
-    case 4: AVQ_EXACT(4, 2); break;
-    case 7: AVQ_EXACT(7, 2); break;
-    case 8: AVQ_EXACT(8, 2); break;
-    case 12: AVQ_EXACT(12, 1); break;
-    default: AVQ_EXACT(16, 1); break;
+    case 2: AVQ_EXACT(2, 2, false); break;
+    case 3: AVQ_EXACT(3, 2, false); break;
+    case 4: AVQ_EXACT(4, 2, false); break;
+    case 7:
+        if (pair) AVQ_EXACT(7, 2, true);
+        else AVQ_EXACT(7, 2, false);
+        break;
+    case 8: AVQ_EXACT(8, 2, false); break;
+    case 12: AVQ_EXACT(12, 1, false); break;
+    default: AVQ_EXACT(16, 1, false); break;
     }
 #undef AVQ_EXACT
     static LdsLimitOnce once[2];

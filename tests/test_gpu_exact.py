@@ -40,8 +40,15 @@ def test_exact_search_matches(n, d, nq, k):
     check(unit_rows(rng, n, d), unit_rows(rng, nq, d), k)
 
 
-# one to four query tiles through three buffers and two accumulators: two column tiles per wave with two workgroups to a compute
-# unit (112 dimensions), with one (113), and one column tile (129, 256); points beyond the last full wave
+# 256 and 257, 512 and 513 workgroups, two and three query tiles: one and two workgroups to a compute unit
+@pytest.mark.parametrize("n,nq", [(131_072, 65), (131_073, 64), (131_073, 65), (262_144, 33), (262_145, 33), (262_145, 32)])
+def test_exact_search_of_one_and_two_workgroups_to_a_compute_unit(n, nq):
+    rng = np.random.default_rng(n + nq)
+    check(unit_rows(rng, n, 100), unit_rows(rng, nq, 100), 10)
+
+
+# one to four query tiles through three buffers and two accumulators: two column tiles per wave of 14 (112 dimensions) and 16 (113)
+# operands, and one column tile (129, 256); points beyond the last full wave
 @pytest.mark.parametrize("d", [112, 113, 129, 256])
 @pytest.mark.parametrize("nq", [32, 33, 96, 97])
 def test_exact_search_of_every_number_of_query_tiles(d, nq):
