@@ -131,16 +131,18 @@ __device__ __forceinline__ float nearest_bound(float nx, float ex, int terms, co
 // share point j % 32). The products of one accumulator are issued between the vector instructions that look through the other
 // one, so that both units work (sched_barrier keeps the order). A group of
 // four values gives its largest to the three best and its second to a bound on what was passed over, 11.5 instructions instead
-// of 16 (0.175 -> 0.160 ms); a single tile to a stage leaves room for three waves per SIMD (0.160 -> 0.150).
+// of 16 (0.175 -> 0.160 ms); a single tile to a stage leaves room for three waves per SIMD (0.160 -> 0.150). FEW: one column tile, and
+// every value goes to the three best: among few centers the second is often in the best one's group, whose point would then
+// be decided against all.
 // assign[i] = nearest center; points that need fp64 go to pairs (point, center, center, -) and all_list (point).
 // cnt / pos (optional): as in launch_nearest.
-template <int NS, int CT>
+template <int NS, int CT, bool FEW>
 __global__ void __launch_bounds__(256, 2)
 nearest_mfma_kernel(const float *__restrict__ x, int64_t n, int d, const v8h *__restrict__ packed, int n_tiles, int k,
                     NearMeta *__restrict__ meta, int32_t *__restrict__ assign, int4 *__restrict__ pairs,
                     int32_t *__restrict__ all_list, uint32_t *__restrict__ cnt, int cnt_stride, uint32_t *__restrict__ pos)
 {
-        constexpr int G = CT == 2 ? 4 : 2, Q = 4 * G; // the rows come in parts of G steps: Q quads of coordinates
+    constexpr int G = CT == 2 || (FEW && NS <= 9) ? 4 : 2, Q = 4 * G; // the rows come in parts of G steps: Q quads of coordinates
     constexpr int kStage = NS * 64, kRows = 4 * 32 * Q;
     __shared__ __align__(16) v8h tile[2 * kStage + (kStage > kRows ? kStage : kRows)]; // three tiles; the third's place holds rows first
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, h = lane >> 5;
@@ -154,8 +156,6 @@ nearest_mfma_kernel(const float *__restrict__ x, int64_t n, int d, const v8h *__
     auto stage = [&](int t, int slot) { // a tile is NS KB in operand order: each wave copies a quarter of it
         for (int s = wave; s < NS; s += 4) to_lds16(packed + (size_t)t * kStage + s * 64 + lane, tile + slot * kStage + s * 64);
     };
-    stage(0, 0);
-    if (n_tiles > 1) stage(1, 1);
 
     // The operands of the points. A wave's rows go through LDS, a part of 16 G coordinates of 32 rows at a time, in pieces that
     // are contiguous in memory (the code for rows read directly, by aligned quads or by single values, took 200 registers and
@@ -168,6 +168,28 @@ nearest_mfma_kernel(const float *__restrict__ x, int64_t n, int d, const v8h *__
     const bool quad = (d & 3) == 0 && ((uintptr_t)x & 15) == 0;
     v8h *rows = tile + 2 * kStage + wave * (32 * Q);
     auto turned = [](int r) { return Q == 16 ? r & 15 : (r >> 1) & 7; };
+    auto fetch = [&](int c, int s0) __attribute__((always_inline)) {
+        auto from = [&](int r, int l) { // coordinate l of row r; past the last ones: some in range, not used
+            const int64_t i = p0 + c * 32 + r;
+            return x + (size_t)(i < n ? i : n - 1) * d + l;
+        };
+        if (quad) {
+#pragma unroll 4
+            for (int e = lane; e < 32 * Q; e += 64) {
+                const int r = e / Q, l = 16 * s0 + 4 * ((e % Q) ^ turned(r));
+                to_lds16(from(r, l < d ? l : d - 4), rows + (e - lane));
+            }
+        } else {
+#pragma unroll 4
+            for (int e = lane; e < 32 * Q * 4; e += 64) {
+                const int r = e / (4 * Q), l = 16 * s0 + 4 * ((e % (4 * Q) / 4) ^ turned(r)) + (e & 3);
+                to_lds4(from(r, l < d ? l : d - 1), rows + (e - lane) / 4);
+            }
+        }
+    };
+    fetch(0, 0);
+    stage(0, 0);
+    if (n_tiles > 1) stage(1, 1);
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
         float n2 = 0.0f, e2 = 0.0f, mx = 0.0f;
@@ -175,36 +197,23 @@ nearest_mfma_kernel(const float *__restrict__ x, int64_t n, int d, const v8h *__
         asm volatile("" : "+v"(own)); // (compared anew for each column tile: kept, the results are a hundred registers)
 #pragma unroll
         for (int s0 = 0; s0 < NS; s0 += G) {
-            auto from = [&](int r, int l) { // coordinate l of row r; past the last ones: some in range, not used
-                const int64_t i = p0 + c * 32 + r;
-                return x + (size_t)(i < n ? i : n - 1) * d + l;
-            };
-            __builtin_amdgcn_s_waitcnt(0xc07f); // lgkmcnt(0): the part before this has been read
-            __builtin_amdgcn_sched_barrier(0);
-            if (quad) {
-#pragma unroll 4
-                for (int e = lane; e < 32 * Q; e += 64) {
-                    const int r = e / Q, l = 16 * s0 + 4 * ((e % Q) ^ turned(r));
-                    to_lds16(from(r, l < d ? l : d - 4), rows + (e - lane));
-                }
-            } else {
-#pragma unroll 4
-                for (int e = lane; e < 32 * Q * 4; e += 64) {
-                    const int r = e / (4 * Q), l = 16 * s0 + 4 * ((e % (4 * Q) / 4) ^ turned(r)) + (e & 3);
-                    to_lds4(from(r, l < d ? l : d - 1), rows + (e - lane) / 4);
-                }
-            }
+            // a part goes to registers, the next one is asked for, then it is converted
             __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0)
+            __builtin_amdgcn_sched_barrier(0);
+            float4 part[2 * G];
+#pragma unroll
+            for (int u = 0; u < 2 * G; ++u) part[u] = *(const float4 *)(rows + j * Q + ((4 * (u / 2) + 2 * h + u % 2) ^ turned(j)));
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xc07f); // lgkmcnt(0)
+            __builtin_amdgcn_sched_barrier(0);
+            if (s0 + G < NS) fetch(c, s0 + G);
+            else if (c + 1 < CT) fetch(c + 1, 0);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int g = 0; g < G && s0 + g < NS; ++g) {
                 const int s = s0 + g;
-                float v[8];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const float4 a = *(const float4 *)(rows + j * Q + ((4 * g + 2 * h + u) ^ turned(j)));
-                    v[4 * u] = a.x; v[4 * u + 1] = a.y; v[4 * u + 2] = a.z; v[4 * u + 3] = a.w;
-                }
+                const float v[8] = {part[2 * g].x, part[2 * g].y, part[2 * g].z, part[2 * g].w,
+                                    part[2 * g + 1].x, part[2 * g + 1].y, part[2 * g + 1].z, part[2 * g + 1].w};
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const float sv = 16 * s + u < own ? v[u] * scale : 0.0f;
@@ -235,6 +244,15 @@ nearest_mfma_kernel(const float *__restrict__ x, int64_t n, int d, const v8h *__
         float a[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) a[u] = __uint_as_float((__float_as_uint(value[v + u]) & 0xfffffff0u) | (uint32_t)(v + u));
+        if constexpr (FEW) { // every value into the three best
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                third[c] = __builtin_amdgcn_fmed3f(second[c], third[c], a[u]);
+                second[c] = __builtin_amdgcn_fmed3f(best[c], second[c], a[u]);
+                best[c] = __builtin_elementwise_maximum(best[c], a[u]);
+            }
+            return;
+        }
         const float m3 = __builtin_elementwise_maximum(__builtin_elementwise_maximum(a[0], a[1]), a[2]);
         const float s3 = __builtin_amdgcn_fmed3f(a[0], a[1], a[2]);
         const float m4 = __builtin_elementwise_maximum(m3, a[3]), s4 = __builtin_amdgcn_fmed3f(m3, s3, a[3]);
@@ -507,9 +525,20 @@ int launch_nearest(const float *x, int64_t n, int d, const float *centers, const
     hipLaunchKernelGGL(near_absmax_kernel, dim3(kAbsmaxBlocks), dim3(256), 0, st, centers, (int64_t)k * d, w.absmax, w.meta);
     hipLaunchKernelGGL(near_pack_kernel, dim3((unsigned)tiles), dim3(256), 0, st, centers, k, d, steps, w.absmax, w.packed, w.meta,
                        cnt_any, cnt ? cnt_stride : 1);
-#define AVQ_NEAR(NS, CT)                                                                                              \
-    hipLaunchKernelGGL((nearest_mfma_kernel<NS, CT>), dim3((unsigned)((n + 4 * CT * 32 - 1) / (4 * CT * 32))), dim3(256), 0, st, x, n, d, \
-                       w.packed, tiles, k, w.meta, assign, w.pairs, w.all_list, cnt, cnt_stride, pos)
+    // Few points or centers: the kernel's way in and out and the points left to nearest_decide_kernel count, not the products. Leaf
+    // training (10 iterations) whole, us, all in turns / as FEW: 4,000 x 100 points, 64 centers 522 / 451 (466 with the kernel before that),
+    // 50,000, 64 744 / 694, 256 841 / 828, 120,000, 64 757 / 733, 512 1,184 / 1,270; x 36 points: 4,000, 64 400 / 370 (362), 50,000, 128
+    // 568 / 551, 256 571 / 587, 250,000, 20 562 / 547, 64 594 / 604.
+    const bool few = n * tiles <= (int64_t)1 << 18;
+    auto go = [&](auto kern, int points) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)((n + points - 1) / points)), dim3(256), 0, st, x, n, d, w.packed, tiles, k, w.meta, assign,
+                           w.pairs, w.all_list, cnt, cnt_stride, pos);
+    };
+#define AVQ_NEAR(NS, CT)                                                    \
+    do {                                                                    \
+        if (few) go(nearest_mfma_kernel<NS, 1, true>, 4 * 32);              \
+        else go(nearest_mfma_kernel<NS, CT, false>, 4 * CT * 32);           \
+    } while (0)
     switch (steps) {
     case 2: AVQ_NEAR(2, 2); break;
     case 3: AVQ_NEAR(3, 2); break;

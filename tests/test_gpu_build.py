@@ -151,6 +151,23 @@ def test_twin_centers_anywhere_in_a_tile(d, k, apart):
     np.testing.assert_array_equal(idx.get_leaf_assign(), oracle.assign_nearest(x, c))
 
 
+# The same with points enough for the kernel of many points and centers (n x tiles of 32 centers above 2^18; the line itself).
+@pytest.mark.parametrize("d,k", [(12, 96), (30, 128), (60, 96), (100, 128), (140, 96), (150, 96), (268, 96)])
+@pytest.mark.parametrize("apart", [1, 2, 4, 8, 32])
+def test_twin_centers_among_many_points(d, k, apart):
+    rng = np.random.default_rng(d * 131 + k + apart)
+    c = unit_rows(rng, k, d)
+    half = (np.arange(k) // apart) % 2 == 1
+    c[half] = c[np.flatnonzero(half) - apart]
+    c[half, 0] = np.nextafter(c[half, 0], np.float32(2.0))
+    few = np.concatenate([c, unit_rows(rng, 900, d)])
+    want = oracle.assign_nearest(few, c)
+    for n in ((1 << 18) // ((k + 31) // 32), (1 << 18) // ((k + 31) // 32) + 1, 100_000):
+        idx = leaf_index(d, c)
+        idx.encode(dev(np.resize(few, (n, d))))
+        np.testing.assert_array_equal(idx.get_leaf_assign(), np.resize(want, n))
+
+
 @pytest.mark.parametrize("n,d,k", [(64, 5, 64), (3001, 100, 70), (2000, 36, 300), (1500, 270, 9)])
 def test_leaf_centers_match(n, d, k):
     rng = np.random.default_rng(3)
