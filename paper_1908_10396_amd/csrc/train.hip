@@ -611,40 +611,41 @@ int launch_assign_aniso(const float *x, int64_t n, int d, const float *centers, 
 // is e + w p^2, w = (eta - 1) / ||x||^2. p and e are sums over the subspaces; with the other subspaces' part P of p
 // fixed, codeword j of subspace m gives e_m(j) + w (P + p_m(j))^2 up to a constant.
 //
-// encode_aniso_kernel (16 codewords of 1 to 4 dimensions, 256 of 2, 4 or 8): a lane per point. What decides a codeword is, with
+// encode_aniso_kernel (16 codewords of 1 to 4 dimensions): a lane per point. What decides a codeword is, with
 // t = <c, x>, u = <c, x - center>, q = P + <x - center, x>,
 //     f(j) = ||c||^2 - 2 u + w t^2 - 2 w q t,
-// formed in fp32 with the codewords as scalar operands: ds + 2 operations (ds + ds + 3 with leaf centers) and three
-// to keep the best (its index in its low bits) and the second best. f is within eps F of its real value, F a bound of
-// the terms' magnitudes, so a codeword that leads by more than 2 eps F is the arg-min; else the lane evaluates every
-// codeword in fp64 as above (one (point, subspace) in some thousands). q = p + <codeword in use, x> is kept and
-// updated in fp64. The codes are therefore those of an fp64 evaluation.
+// formed in fp32: ds + 2 operations (ds + ds + 3 with leaf centers) and two and a half to keep the best (its index in its
+// low bits) and the second best. f is within eps F of its real value, F a bound of the terms' magnitudes, so a codeword that
+// leads by more than 2 eps F is the arg-min; else the lane evaluates those that do not trail by as much in fp64 as above (one
+// (point, subspace) in some thousands). q = p + <codeword in use, x> is kept and updated in fp64. The codes are therefore
+// those of an fp64 evaluation.
 //
 // The points of a wave need different numbers of passes: a lane whose point is done takes the wave's next point at the
-// end of the sweep over the subspaces, so that no lane waits for the slowest of 64. (x of the points in LDS, row by
-// row, for 16 codewords; with 256 the rows are read from memory again, 32 bytes for 1,800 operations.) The rows of 64
-// points leave room for fewer waves a compute unit as d grows: five at 100 dimensions, two at 192, one from 240 on, where
-// this kernel still wins (200,000 x 384 points, 192 subspaces: 10.1 ms a call, 14.7 all in fp64), but not if many codewords
-// of a dictionary are equal (all in pairs: 12.7 against 8.6); beyond about 420 dimensions no wave fits. On a
-// partitioned index the points are taken leaf by leaf, and the lanes' leaf centers mostly are one and the same.
-// Bound by vector operations and by the chain from one subspace's choice to the next one's q: 1,183,514 x 100 points,
-// 50 subspaces of 16 codewords: 2.34 ms (1.5 ms of vector operations at five waves per compute unit; 2.91 ms with leaf
-// centers), against 9.3 (11.8) ms for a thread per point with every codeword in fp64 and its state in scratch memory.
-// Windows of points handed out by a counter instead of split evenly: 2.63 -> 2.34 ms, as one SIMD of four holds two waves.
+// end of the sweep over the subspaces, so that no lane waits for the slowest of 64 (4.4 sweeps on average at the Glove
+// shape, eight at most). A lane asks for its point's coordinates four subspaces ahead, 32 bytes at 2 dimensions; the
+// dictionaries are in LDS. On a partitioned index the points are taken leaf by leaf, and the lanes' leaf centers mostly
+// are one and the same.
+//
+// Bound by vector operations: some 160 a step, 0.27 a clock and SIMD at 1.98 GHz by the counters, more waves a compute unit
+// than twelve change nothing. A fifth of them are of waves that have no points left but their last ones. avq_encode of
+// 1,183,514 x 100 points, 50 subspaces, 2.18 ms with the rows of a wave's points in LDS, which left room for five waves a
+// compute unit, 1.43 this way (2,000 leaves: 3.96 / 2.83); 10^6 x 128, 64 subspaces 2.97 / 1.69; 500,000 x 192, 96 of them
+// 5.25 / 1.86; 200,000 x 384, 192: 12.6 / 2.5; a thread per point with every codeword in fp64: 9.3 (11.8) ms at the first.
+// Windows of points handed out by a counter instead of split evenly: 2.63 -> 2.34 ms, as one SIMD of four held two waves.
 struct EncodeParams {
     const float *x;
     int64_t n_slots;
     const int32_t *order; // slot -> point (-1: none), NULL: slot i is point i
     int32_t d, M, NB, passes;
-    const float *codebooks;   // [M][KC][DS]
+    const float *codebooks;   // [M][codewords][dimensions]
     const float *leaf_centers;
     const int32_t *leaf_assign;
     int32_t eta_mode;
     double T, eta_explicit;
     const double *w_in;       // NULL: w from eta_mode here
     uint8_t *packed;
-    uint32_t *next_window;    // windows of 64 slots are handed out: waves that share a SIMD get fewer
-    int32_t row_stride, code_stride; // row_stride: floats per staged row (odd); code_stride: bytes (odd dwords)
+    uint32_t *next_window;    // windows of slots, one a lane, are handed out: waves that share a SIMD get fewer
+    int32_t code_stride;      // bytes (odd dwords)
 };
 
 __global__ void __launch_bounds__(64)
@@ -670,6 +671,36 @@ encode_tables_kernel(const float *__restrict__ codebooks, int kc, int ds, float 
     if (lane == 0) lim[m] = make_float2(cm * 1.0001f, ccm * 1.0001f);
 }
 
+// The same for 256 codewords (encode_wide_kernel): operands [m][(32 codewords g, two dimensions s) / 4][64][4], the lane's
+// word of (g, s) being coordinate 2 s + lane / 32 of codeword 32 g + lane % 32; cc [m][256].
+__global__ void __launch_bounds__(256)
+encode_operands_kernel(const float *__restrict__ codebooks, int ds, float *__restrict__ operands, float *__restrict__ cc_out,
+                       float2 *__restrict__ lim, uint32_t *__restrict__ next_window)
+{
+    __shared__ float wave_cm[4], wave_ccm[4];
+    const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    if (m == 0 && tid == 0) *next_window = 0u;
+    const float *c = codebooks + ((size_t)m * 256 + tid) * ds;
+    float cm = 0.0f;
+    double cc = 0.0;
+    for (int l = 0; l < ds; ++l) {
+        const float v = c[l];
+        const int at = (tid >> 5) * (ds / 2) + (l >> 1);
+        operands[((size_t)m * ds + at / 4) * 256 + ((l & 1) * 32 + (tid & 31)) * 4 + at % 4] = v;
+        cc += (double)v * (double)v;
+        cm = fmaxf(cm, fabsf(v));
+    }
+    cc_out[m * 256 + tid] = (float)cc;
+    float ccm = (float)cc;
+    for (int s = 32; s > 0; s >>= 1) { cm = fmaxf(cm, __shfl_xor(cm, s, 64)); ccm = fmaxf(ccm, __shfl_xor(ccm, s, 64)); }
+    if (lane == 0) { wave_cm[tid >> 6] = cm; wave_ccm[tid >> 6] = ccm; }
+    __syncthreads();
+    if (tid == 0) {
+        for (int v = 1; v < 4; ++v) { cm = fmaxf(cm, wave_cm[v]); ccm = fmaxf(ccm, wave_ccm[v]); }
+        lim[m] = make_float2(cm * 1.0001f, ccm * 1.0001f);
+    }
+}
+
 // (eta - 1) / ||x||^2 of every point, for the mode whose eta is an integral per point
 __global__ void __launch_bounds__(256)
 encode_weights_kernel(const float *__restrict__ x, int64_t n, int d, int eta_mode, double T, double eta_explicit, double *__restrict__ w)
@@ -683,97 +714,110 @@ encode_weights_kernel(const float *__restrict__ x, int64_t n, int d, int eta_mod
     w[i] = nx2 > 0.0 ? (eta - 1.0) / nx2 : 0.0;
 }
 
-template <int DS, int KC, bool RES>
-__global__ void __launch_bounds__(512)
+// (eta - 1) / ||x||^2 of a point
+__device__ __forceinline__ double encode_weight(const EncodeParams &p, int id, double nx2)
+{
+    if (p.w_in) return p.w_in[id];
+    double eta = p.eta_explicit;
+    if (p.eta_mode != AVQ_ETA_EXPLICIT) { // the limit of Theorem 3.4, floored at 1 (see eta_of_norm)
+        eta = 1.0;
+        if (nx2 > 0.0) {
+            const double u = clamp_ratio_sq(p.T, sqrt(nx2));
+            eta = fmax((double)(p.d - 1) * u / (1.0 - u), 1.0);
+        }
+    }
+    return nx2 > 0.0 ? (eta - 1.0) / nx2 : 0.0;
+}
+
+// floats at a float's alignment; one load of several words takes that on this machine
+template <int N>
+__device__ __forceinline__ void load_floats(const float *__restrict__ at, float (&v)[N])
+{
+    __builtin_memcpy(v, at, sizeof(v));
+}
+
+template <int DS, bool RES>
+__global__ void __launch_bounds__(512, 4)
 encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, const float2 *__restrict__ limits)
 {
-    constexpr bool kStage = KC == 16; // rows of x and the dictionaries in LDS
+    constexpr int KC = 16, kAhead = RES && DS > 2 ? 2 : 4; // subspaces whose coordinates are asked for while the ones before are at work
     extern __shared__ __align__(16) float enc_lds[];
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int M = p.M, d = p.d;
-    constexpr int kTab4 = 4 * (DS + 1); // float4s of a subspace's table of 16 codewords
-    float *tab_lds = enc_lds; // kStage: [M][KC][DS + 1]
-    float2 *lim_lds = (float2 *)(enc_lds + M * KC * (DS + 1)); // kStage: [M]
-    float *rows = enc_lds + (kStage ? M * (KC * (DS + 1) + 2) + wave * 64 * p.row_stride : 0);
-    uint8_t *codes = (uint8_t *)(enc_lds + (kStage ? M * (KC * (DS + 1) + 2) + n_waves * 64 * p.row_stride : 0)) +
-                     (size_t)wave * 64 * p.code_stride;
+    float *tab_lds = enc_lds; // [M][KC][DS + 1]
+    float2 *lim_lds = (float2 *)(enc_lds + M * KC * (DS + 1)); // [M]
+    uint8_t *codes = (uint8_t *)(enc_lds + M * (KC * (DS + 1) + 2)) + (size_t)wave * 64 * p.code_stride;
     uint8_t *my_codes = codes + (size_t)lane * p.code_stride;
-    const float *my_row = rows + (size_t)lane * p.row_stride; // kStage
-    if (kStage) {
-        for (int e = threadIdx.x; e < M * KC * (DS + 1); e += blockDim.x) tab_lds[e] = tables[e];
-        for (int e = threadIdx.x; e < M; e += blockDim.x) lim_lds[e] = limits[e];
-        __syncthreads();
-    }
+    for (int e = threadIdx.x; e < M * KC * (DS + 1); e += blockDim.x) tab_lds[e] = tables[e];
+    for (int e = threadIdx.x; e < M; e += blockDim.x) lim_lds[e] = limits[e];
+    __syncthreads();
     for (int e = 0; e < p.code_stride; e += 4) *(uint32_t *)(my_codes + e) = 0u;
 
-    int win_id = -1;                // this lane's slot of the window: its point
-    u64 win = 0ull;                 // slots of the window not yet taken
+    int win_id = -1, win_left = 0;  // the window's points not yet taken: those of lanes 0 .. win_left - 1
     bool drained = false;           // no windows left
     int id = -1, stage = 0;         // this lane's point (-1: none) and pass (-1: nearest codewords first)
     double P = 0.0, w = 0.0; // P = <x - center - codewords, x>, the codewords chosen so far
-    const float *xi = p.x, *ce_row = nullptr;
+    const float *xi = p.x, *ce_row = RES ? p.leaf_centers : nullptr;
     bool changed = false;
     constexpr float kEps = (1.9074e-6f + (2 * DS + 8 + (RES ? 4 : 0)) * 6.0e-8f) * 1.05f;
 
+    auto lanes_below = [](u64 mask) -> int { return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u)); };
     for (;;) {
         // lanes without a point take the wave's next ones
-        u64 need = __builtin_amdgcn_ballot_w64(id < 0), taken = 0ull;
+        u64 need = __builtin_amdgcn_ballot_w64(id < 0);
+        bool taken = false;
         while (need != 0ull) {
-            if (win == 0ull) {
+            if (win_left == 0) {
                 if (drained) break;
                 uint32_t w64 = 0u;
                 if (lane == 0) w64 = atomicAdd(p.next_window, 1u);
                 const int64_t s0 = (int64_t)__builtin_amdgcn_readfirstlane(w64) * 64, s = s0 + lane;
                 if (s0 >= p.n_slots) { drained = true; break; }
-                win_id = s < p.n_slots ? (p.order ? p.order[s] : (int)s) : -1;
-                win = __builtin_amdgcn_ballot_w64(win_id >= 0);
+                const int slot = s < p.n_slots ? (p.order ? p.order[s] : (int)s) : -1;
+                const u64 there = __builtin_amdgcn_ballot_w64(slot >= 0);
+                win_left = (int)__popcll(there);
+                // the points move to lanes 0 .. win_left - 1
+                const int to = slot >= 0 ? lanes_below(there) : win_left + lanes_below(~there);
+                win_id = __builtin_amdgcn_ds_permute(to << 2, slot);
                 continue;
             }
-            const int t = __builtin_ctzll(need), from = __builtin_ctzll(win);
-            const int who = __builtin_amdgcn_readlane(win_id, from);
-            need &= need - 1;
-            win &= win - 1;
-            taken |= 1ull << t;
-            if (lane == t) id = who;
-            if constexpr (kStage) {
-                const float *src = p.x + (size_t)who * d;
-                for (int c = 0; c < d; c += 64)
-                    if (c + lane < d)
-                        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + c + lane),
-                                                         (__attribute__((address_space(3))) void *)(rows + t * p.row_stride + c), 4, 0, 0);
-            }
+            const int rank = lanes_below(need), n_need = (int)__popcll(need);
+            const int who = __builtin_amdgcn_ds_bpermute((win_left - 1 - rank) << 2, win_id);
+            if (id < 0 && rank < win_left) { id = who; taken = true; }
+            win_left = win_left > n_need ? win_left - n_need : 0;
+            need = __builtin_amdgcn_ballot_w64(id < 0);
         }
         if (__builtin_amdgcn_ballot_w64(id >= 0) == 0ull) break;
-        if (taken != 0ull) {
-            __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0): the rows are in LDS
-            wave_lds_fence();
-            if ((taken >> lane) & 1) {
-                stage = -1;
-                if constexpr (!kStage) xi = p.x + (size_t)id * d;
-                if constexpr (RES) ce_row = p.leaf_centers + (size_t)p.leaf_assign[id] * d;
-                double nx2 = 0.0, cx = 0.0;
-#pragma unroll 4
-                for (int l = 0; l < d; ++l) {
-                    const double v = (double)(kStage ? my_row[l] : xi[l]);
-                    nx2 += v * v;
-                    if constexpr (RES) cx = fma((double)ce_row[l], v, cx);
-                }
-                P = nx2 - cx;
-                if (p.w_in) {
-                    w = p.w_in[id];
-                } else {
-                    double eta = p.eta_explicit;
-                    if (p.eta_mode != AVQ_ETA_EXPLICIT) { // the limit of Theorem 3.4, floored at 1 (see eta_of_norm)
-                        eta = 1.0;
-                        if (nx2 > 0.0) {
-                            const double u = clamp_ratio_sq(p.T, sqrt(nx2));
-                            eta = fmax((double)(d - 1) * u / (1.0 - u), 1.0);
-                        }
-                    }
-                    w = nx2 > 0.0 ? (eta - 1.0) / nx2 : 0.0;
-                }
+        if (taken) {
+            stage = -1;
+            xi = p.x + (size_t)id * d;
+            if constexpr (RES) ce_row = p.leaf_centers + (size_t)p.leaf_assign[id] * d;
+            double nx2 = 0.0, cx = 0.0;
+            auto term = [&](float xl, float cl) {
+                const double v = (double)xl;
+                nx2 += v * v;
+                if constexpr (RES) cx = fma((double)cl, v, cx);
+            };
+            int l = 0;
+            constexpr int kSome = RES ? 16 : 32;
+            for (; l + kSome <= d; l += kSome) {
+                float v[kSome], c[RES ? kSome : 1];
+                load_floats(xi + l, v);
+                if constexpr (RES) load_floats(ce_row + l, c);
+#pragma unroll
+                for (int e = 0; e < kSome; ++e) term(v[e], c[RES ? e : 0]);
             }
+            for (; l + 4 <= d; l += 4) {
+                float v[4], c[RES ? 4 : 1];
+                load_floats(xi + l, v);
+                if constexpr (RES) load_floats(ce_row + l, c);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) term(v[e], c[RES ? e : 0]);
+            }
+            for (; l < d; ++l) term(xi[l], RES ? ce_row[l] : 0.0f);
+            P = nx2 - cx;
+            w = encode_weight(p, id, nx2);
         }
         const bool active = id >= 0;
         const bool init = stage < 0;
@@ -781,186 +825,450 @@ encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, cons
         const float wf = (float)wl;
         changed = false;
 
-        // One sweep over the subspaces. What a step needs is asked for during the step before it (two sets of registers
-        // that take turns): a compute unit holds five waves at 100 dimensions, too few to hide a load by another wave.
-        struct Step {
-            float xv[DS], ce[RES ? DS : 1], cur[DS];
-            float4 tab[kStage ? kTab4 : 1]; // kStage: the subspace's codewords and ||c||^2
-            float2 lim;
-            int code;
-        };
-        auto read_lds = [](const float *at, float (&v)[DS]) {
+        auto load_codeword = [&](int m, int j, float (&c)[DS]) {
             typedef const __attribute__((address_space(3))) float lds_float;
-            lds_float *src = (lds_float *)at;
+            lds_float *src = (lds_float *)(tab_lds + (m * KC + j) * (DS + 1));
 #pragma unroll
             for (int l = 0; l < DS; ++l) {
                 if (l == 2) asm volatile("" : "+v"(src)); // three words are not read as one (see build.py)
-                v[l] = src[l];
+                c[l] = src[l];
             }
         };
-        auto load_codeword = [&](int m, int j, float (&c)[DS]) {
-            if constexpr (kStage) read_lds(tab_lds + (m * KC + j) * (DS + 1), c);
-            else {
-                const float *src = p.codebooks + ((size_t)m * KC + j) * DS;
+        // this point's (and its center's) coordinates of subspaces m .. m + kAhead - 1; nothing beyond the row
+        auto load_rows = [&](int m, float (&xs)[kAhead * DS], float (&ces)[RES ? kAhead * DS : 1]) {
+            const int l0 = m * DS;
+            if (l0 + kAhead * DS <= d) {
+                load_floats(xi + l0, xs);
+                if constexpr (RES) load_floats(ce_row + l0, ces);
+            } else {
 #pragma unroll
-                for (int l = 0; l < DS; ++l) c[l] = src[l];
+                for (int l = 0; l < kAhead * DS; ++l) {
+                    xs[l] = l0 + l < d ? xi[l0 + l] : 0.0f;
+                    if constexpr (RES) ces[l] = l0 + l < d ? ce_row[l0 + l] : 0.0f;
+                }
             }
         };
-        auto load_step = [&](int m, Step &s) { // all but the codeword in use, which waits for its index
-            if constexpr (kStage) read_lds(my_row + m * DS, s.xv);
-#pragma unroll
-            for (int l = 0; l < DS; ++l) {
-                if constexpr (!kStage) s.xv[l] = xi[m * DS + l];
-                if constexpr (RES) s.ce[l] = active ? ce_row[m * DS + l] : 0.0f;
-            }
-            s.code = my_codes[m];
-            if constexpr (kStage) {
-                const float4 *t = (const float4 *)(tab_lds + m * KC * (DS + 1));
-#pragma unroll
-                for (int e = 0; e < kTab4; ++e) s.tab[e] = t[e];
-                s.lim = lim_lds[m]; // (a scalar load here would make the wave wait for every LDS read in flight)
-            }
-        };
-        auto step = [&](int m, const Step &s, Step &nx) {
-            const int mn = m + 1 < M ? m + 1 : 0;
-            load_step(mn, nx);
+        // One subspace: xv, ce its coordinates, cur the codeword in use, `code` its index.
+        auto step = [&](int m, const float (&xv)[DS], const float (&ce)[RES ? DS : 1], const float (&cur)[DS], int code) {
             // q = (p of the other subspaces) + <x - center, x> of this one = P + <codeword in use, x>
             double t_cur = 0.0;
             float sx = 0.0f, sr = 0.0f, xrf[RES ? DS : 1];
 #pragma unroll
             for (int l = 0; l < DS; ++l) {
-                t_cur = fma((double)s.cur[l], (double)s.xv[l], t_cur);
-                sx += fabsf(s.xv[l]);
-                if constexpr (RES) { xrf[l] = (float)((double)s.xv[l] - (double)s.ce[l]); sr += fabsf(xrf[l]); }
+                t_cur = fma((double)cur[l], (double)xv[l], t_cur);
+                sx += fabsf(xv[l]);
+                if constexpr (RES) { xrf[l] = (float)((double)xv[l] - (double)ce[l]); sr += fabsf(xrf[l]); }
             }
             if (init) t_cur = 0.0;
             const double q = P + t_cur;
             const float Bf = (float)fma(w2, q, RES ? 0.0 : 2.0);
-            const float2 lim = kStage ? s.lim : limits[m];
+            const float2 lim = lim_lds[m];
             const float T = lim.x * sx;
             float F = fmaf(T, fmaf(wf, T, fabsf(Bf)), lim.y);
             if constexpr (RES) F = fmaf(2.0f * lim.x, sr, F);
             const float lead = fmaf(F, 2.0f * kEps, 2.0e-37f);
 
-            float best = INFINITY, second = INFINITY;
-            int group = 0;
-            const float *tab = tables + (size_t)m * KC * (DS + 1); // wave-uniform: scalar loads and operands
-            constexpr int kGroups = KC / 16;
-            auto entry = [&](int j, int l) -> float { // coordinate l of codeword j (kStage: j a constant), l = DS: ||c||^2
-                if constexpr (kStage) {
-                    const float4 e = s.tab[(j * (DS + 1) + l) / 4];
-                    const int r = (j * (DS + 1) + l) % 4;
-                    return r == 0 ? e.x : r == 1 ? e.y : r == 2 ? e.z : e.w;
-                } else {
-                    return tab[j * (DS + 1) + l];
-                }
+            // a half of the codewords at a time (more at once, or kept for the decisions in fp64, spill)
+            constexpr int kPart = 8, kPart4 = kPart * (DS + 1) / 4;
+            typedef float four_floats __attribute__((ext_vector_type(4)));
+            typedef const __attribute__((address_space(3))) four_floats lds_float4;
+            four_floats part[kPart4];
+            auto load_part = [&](int j0) { // of the codewords j0 .. j0 + kPart - 1
+                lds_float4 *src = (lds_float4 *)(tab_lds + (m * KC + j0) * (DS + 1));
+                asm volatile("" : "+v"(src));
+#pragma unroll
+                for (int e = 0; e < kPart4; ++e) part[e] = src[e];
             };
-#pragma unroll 1
-            for (int g = 0; g < kGroups; ++g) {
-                const float old = best;
+            float best = INFINITY, second = INFINITY;
+            auto entry = [&](int j, int l) -> float { // coordinate l of codeword j of the part (a constant), l = DS: ||c||^2
+                const int at = (j % kPart) * (DS + 1) + l;
+                return part[at / 4][at % 4];
+            };
+            auto value = [&](int v) -> float { // f of codeword v of the part, its index in the low bits
+                auto c = [&](int l) -> float { return entry(v, l); };
+                float t = xv[0] * c(0);
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    auto c = [&](int l) -> float { return entry(g * 16 + v, l); };
-                    float t = s.xv[0] * c(0);
+                for (int l = 1; l < DS; ++l) t = fmaf(xv[l], c(l), t);
+                float f = c(DS);
+                if constexpr (RES) {
+                    float u = xrf[0] * c(0);
 #pragma unroll
-                    for (int l = 1; l < DS; ++l) t = fmaf(s.xv[l], c(l), t);
-                    float f = c(DS);
-                    if constexpr (RES) {
-                        float u = xrf[0] * c(0);
-#pragma unroll
-                        for (int l = 1; l < DS; ++l) u = fmaf(xrf[l], c(l), u);
-                        f = fmaf(-2.0f, u, f);
-                    }
-                    f = fmaf(t, fmaf(wf, t, -Bf), f);
-                    f = __uint_as_float((__float_as_uint(f) & 0xfffffff0u) | (uint32_t)v);
-                    second = __builtin_amdgcn_fmed3f(best, second, f);
-                    // the smaller; the compiler makes it the minimum that drops a NaN (a true median would return -infinity)
-                    best = __builtin_amdgcn_fmed3f(-INFINITY, best, f);
+                    for (int l = 1; l < DS; ++l) u = fmaf(xrf[l], c(l), u);
+                    f = fmaf(-2.0f, u, f);
                 }
-                if (kGroups > 1) group = best == old ? group : g;
+                f = fmaf(t, fmaf(wf, t, -Bf), f);
+                return __uint_as_float((__float_as_uint(f) & 0xfffffff0u) | (uint32_t)v);
+            };
+#pragma unroll
+            for (int v = 0; v < 16; v += 2) {
+                if (v % kPart == 0) load_part(v);
+                const float f0 = value(v), f1 = value(v + 1);
+                // Two at a time: the second smallest of (best, f0, f1) is their median. (Instructions by name: as fminf,
+                // each would be preceded by one that quiets its operands; a NaN is dropped either way.)
+                const float mid = __builtin_amdgcn_fmed3f(best, f0, f1);
+                asm("v_min_f32 %0, %1, %2" : "=v"(second) : "v"(second), "v"(mid));
+                asm("v_min3_f32 %0, %1, %2, %3" : "=v"(best) : "v"(best), "v"(f0), "v"(f1));
             }
-            int pick = group * 16 + (int)(__float_as_uint(best) & 15u);
-            load_codeword(mn, nx.code, nx.cur);
+            int pick = (int)(__float_as_uint(best) & 15u);
             const bool open = active && !(second - best > lead);
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(open) != 0ull, 0)) {
                 if (open) {
-                    // Equal codewords leave this open at every step. The codewords come from registers, or several at a time
-                    // (one at a time by scalar loads, each waited for: 1.50 ms where 200,000 x 100 points meet 50 dictionaries
-                    // of 8 pairs of equal codewords, 0.95 this way; 0.56 without the pairs).
+                    // Equal codewords leave this open at every step, mostly between two: those that f does not rule out are
+                    // found once more, and up to four taken one by one (200,000 x 100 points, 50 dictionaries of 8 pairs of
+                    // equal codewords: 1.06 ms with all sixteen,
+                    // 0.75 this way; 0.43 without the pairs).
                     double bestv = INFINITY, xr[DS], xx = 0.0;
+                    uint32_t left = 0u;
+#pragma unroll
+                    for (int v = 0; v < KC; ++v) {
+                        if (v % kPart == 0) load_part(v);
+                        left |= value(v) - best > lead ? 0u : 1u << v;
+                    }
                     pick = 0;
 #pragma unroll
                     for (int l = 0; l < DS; ++l) {
-                        xr[l] = (double)s.xv[l] - (RES ? (double)s.ce[RES ? l : 0] : 0.0);
-                        xx = fma(xr[l], (double)s.xv[l], xx);
+                        xr[l] = (double)xv[l] - (RES ? (double)ce[RES ? l : 0] : 0.0);
+                        xx = fma(xr[l], (double)xv[l], xx);
                     }
-                    auto try_codeword = [&](int j) {
+                    auto try_codeword = [&](int j, auto coordinate) {
                         double pm = 0.0, em = 0.0;
 #pragma unroll
                         for (int l = 0; l < DS; ++l) {
-                            const double r = xr[l] - (double)entry(j, l);
-                            pm = fma(r, (double)s.xv[l], pm);
+                            const double r = xr[l] - (double)coordinate(l);
+                            pm = fma(r, (double)xv[l], pm);
                             em = fma(r, r, em);
                         }
                         const double pp = init ? 0.0 : (q - xx) + pm;
                         const double v = em + wl * pp * pp;
                         if (v < bestv) { bestv = v; pick = j; }
                     };
-                    if constexpr (kStage) {
+                    if (__builtin_amdgcn_ballot_w64(__popc(left) > 4) != 0ull) {
 #pragma unroll
-                        for (int j = 0; j < KC; ++j) try_codeword(j);
+                        for (int j = 0; j < KC; ++j) {
+                            if (j % kPart == 0) load_part(j);
+                            try_codeword(j, [&](int l) { return entry(j, l); });
+                        }
                     } else {
-                        constexpr int kAtOnce = DS == 8 ? 2 : 8; // eight of 8 dimensions take 218 registers instead of 110
-#pragma unroll kAtOnce
-                        for (int j = 0; j < KC; ++j) try_codeword(j);
+                        while (left != 0u) {
+                            const int j = __builtin_ctz(left);
+                            left &= left - 1u;
+                            float c[DS];
+                            load_codeword(m, j, c);
+                            try_codeword(j, [&](int l) { return c[l]; });
+                        }
                     }
                 }
             }
-            const bool other = active && (init || pick != s.code);
+            const bool other = active && (init || pick != code);
             if (__builtin_amdgcn_ballot_w64(other) != 0ull) {
                 if (other) {
                     float c[DS];
                     load_codeword(m, pick, c);
                     double t_new = 0.0;
 #pragma unroll
-                    for (int l = 0; l < DS; ++l) t_new = fma((double)c[l], (double)s.xv[l], t_new);
+                    for (int l = 0; l < DS; ++l) t_new = fma((double)c[l], (double)xv[l], t_new);
                     my_codes[m] = (uint8_t)pick;
                     P = q - t_new;
                     changed = true;
                 }
             }
         };
-        Step even, odd;
-        load_step(0, even);
-        load_codeword(0, even.code, even.cur);
-        int m = 0;
-        for (; m + 1 < M; m += 2) {
-            step(m, even, odd);
-            step(m + 1, odd, even);
+        // One sweep over the subspaces.
+        float xs[kAhead * DS], ces[RES ? kAhead * DS : 1];
+        load_rows(0, xs, ces);
+#pragma unroll 1
+        for (int m = 0; m < M; m += kAhead) {
+            float xn[kAhead * DS], cen[RES ? kAhead * DS : 1], cur[kAhead][DS];
+            const uint32_t four = *(const uint32_t *)(my_codes + (m & ~3)); // codes of a row start at a word, and end in one
+            int code[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                code[u] = (int)(four >> (8 * ((m + u) & 3))) & 255;
+                if (m + u < M) load_codeword(m + u, code[u], cur[u]);
+            }
+            load_rows(m + kAhead < M ? m + kAhead : 0, xn, cen);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                if (m + u >= M) break;
+                float xv[DS], ce[RES ? DS : 1];
+#pragma unroll
+                for (int l = 0; l < DS; ++l) {
+                    xv[l] = xs[u * DS + l];
+                    if constexpr (RES) ce[l] = ces[u * DS + l];
+                }
+                step(m + u, xv, ce, cur[u], code[u]);
+            }
+#pragma unroll
+            for (int l = 0; l < kAhead * DS; ++l) {
+                xs[l] = xn[l];
+                if constexpr (RES) ces[l] = cen[l];
+            }
         }
-        if (m < M) step(m, even, odd);
         const bool done = active && (init ? p.passes == 0 : !changed || stage + 1 >= p.passes);
         stage = init ? 0 : stage + 1;
         if (done) {
             uint8_t *out = p.packed + (size_t)id * p.NB;
-            for (int e = 0; e < p.code_stride && (KC == 16 ? e / 2 : e) < p.NB; e += 4) {
+            for (int e = 0; e < p.code_stride && e / 2 < p.NB; e += 4) {
                 const uint32_t v = *(const uint32_t *)(my_codes + e);
-                if constexpr (KC == 16) {
-                    out[e / 2] = (uint8_t)((v & 15u) | ((v >> 4) & 0xf0u));
-                    if (e / 2 + 1 < p.NB) out[e / 2 + 1] = (uint8_t)(((v >> 16) & 15u) | ((v >> 20) & 0xf0u));
-                } else {
-#pragma unroll
-                    for (int b = 0; b < 4; ++b)
-                        if (e + b < p.NB) out[e + b] = (uint8_t)(v >> (8 * b));
-                }
+                out[e / 2] = (uint8_t)((v & 15u) | ((v >> 4) & 0xf0u));
+                if (e / 2 + 1 < p.NB) out[e / 2 + 1] = (uint8_t)(((v >> 16) & 15u) | ((v >> 20) & 0xf0u));
             }
             id = -1;
         }
     }
 }
 
-// Every other shape (16 codewords of 8 dimensions; rows of which LDS does not hold 64; other numbers of dimensions per
-// subspace; few subspaces, see encode_few_steps): a thread per point, all in fp64, the terms of the current codewords kept per subspace. DS = dimensions per
+// 256 codewords of 2, 4 or 8 dimensions, as above: a wave takes 32 points, lanes j and j + 32 the same one. <c, x> for 32
+// codewords at a time comes from the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: two dimensions of 32 codewords against
+// 32 points), which leaves a lane 16 of them; with leaf centers a second product has the terms linear in c, <c, y>, y = 2 (x -
+// center) + 2 w q x. The operands are asked for a subspace ahead, in the order the instruction takes them; ||c||^2 is in LDS
+// where it fits. Bound by the vector operations on the products (72 for 16 of a lane's) beside the matrix instruction.
+// A lane per point with the codewords as scalar operands waited for each sixteen of them, as the scalar cache does not hold
+// the dictionaries, and left a small call's few waves alone with 1,800 operations a step. avq_encode, that way / this way:
+// 100,000 x 100, 25 subspaces 4.25 / 1.28 ms; 21,382 of them 2.73 / 0.60; 40,000 x 256, 32 subspaces 2.56 / 0.83, with 200
+// leaves 4.44 / 1.70; 300,000 x 36, 9 subspaces 1.35 / 0.62; 2,000 of them 0.53 / 0.13.
+typedef float v16f __attribute__((ext_vector_type(16)));
+template <int DS, bool RES, bool CC_LDS>
+__global__ void __launch_bounds__(512, 2)
+encode_wide_kernel(const EncodeParams p, const float *__restrict__ operands, const float *__restrict__ cc_all,
+                   const float2 *__restrict__ limits)
+{
+    constexpr int KC = 256, G = 8, S = DS / 2; // groups of 32 codewords, steps of two dimensions
+    extern __shared__ __align__(16) float enc_lds[];
+    const int lane = threadIdx.x & 63, j = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int M = p.M, d = p.d;
+    typedef float four_floats __attribute__((ext_vector_type(4)));
+    typedef const __attribute__((address_space(3))) four_floats lds_float4;
+    float *cc_lds = enc_lds; // [M][256]
+    uint8_t *my_codes = (uint8_t *)(enc_lds + (CC_LDS ? M * KC : 0)) + (size_t)(wave * 32 + j) * p.code_stride;
+    if (CC_LDS) {
+        for (int e = threadIdx.x; e < M * KC; e += blockDim.x) cc_lds[e] = cc_all[e];
+        __syncthreads();
+    }
+    if (h == 0)
+        for (int e = 0; e < p.code_stride; e += 4) *(uint32_t *)(my_codes + e) = 0u;
+
+    int win_id = -1, win_left = 0;  // the window's points not yet taken: those of lanes 0 .. win_left - 1 of either half
+    bool drained = false;           // no windows left
+    int id = -1, stage = 0;
+    double P = 0.0, w = 0.0;
+    const float *xi = p.x, *ce_row = RES ? p.leaf_centers : nullptr;
+    // the error of f, in units of F: that of the instructions, and of the index in the low bits
+    constexpr float kEps = (1.9074e-6f + (2 * DS + 8 + (RES ? 6 : 0)) * 6.0e-8f) * 1.05f;
+    auto below = [&](uint32_t mask) -> int { return (int)__popc(mask & ((1u << j) - 1u)); };
+
+    for (;;) {
+        // points for those who have none (both halves alike)
+        uint32_t need = (uint32_t)__builtin_amdgcn_ballot_w64(id < 0);
+        bool taken = false;
+        while (need != 0u) {
+            if (win_left == 0) {
+                if (drained) break;
+                uint32_t w32 = 0u;
+                if (lane == 0) w32 = atomicAdd(p.next_window, 1u);
+                const int64_t s0 = (int64_t)__builtin_amdgcn_readfirstlane(w32) * 32, s = s0 + j;
+                if (s0 >= p.n_slots) { drained = true; break; }
+                const int slot = s < p.n_slots ? (p.order ? p.order[s] : (int)s) : -1;
+                const uint32_t there = (uint32_t)__builtin_amdgcn_ballot_w64(slot >= 0);
+                win_left = (int)__popc(there);
+                const int to = slot >= 0 ? below(there) : win_left + below(~there); // the points move to the front
+                win_id = __builtin_amdgcn_ds_permute((to + 32 * h) << 2, slot);
+                continue;
+            }
+            const int rank = below(need), n_need = (int)__popc(need);
+            const int who = __builtin_amdgcn_ds_bpermute(((win_left - 1 - rank) & 31) << 2, win_id);
+            if (id < 0 && rank < win_left) { id = who; taken = true; }
+            win_left = win_left > n_need ? win_left - n_need : 0;
+            need = (uint32_t)__builtin_amdgcn_ballot_w64(id < 0);
+        }
+        if (__builtin_amdgcn_ballot_w64(id >= 0) == 0ull) break;
+        if (taken) {
+            stage = -1;
+            xi = p.x + (size_t)id * d;
+            if constexpr (RES) ce_row = p.leaf_centers + (size_t)p.leaf_assign[id] * d;
+            double nx2 = 0.0, cx = 0.0;
+            auto term = [&](float xl, float cl) {
+                const double v = (double)xl;
+                nx2 += v * v;
+                if constexpr (RES) cx = fma((double)cl, v, cx);
+            };
+            constexpr int kSome = 16;
+            int l = 0;
+            for (; l + kSome <= d; l += kSome) {
+                float v[kSome], c[RES ? kSome : 1];
+                load_floats(xi + l, v);
+                if constexpr (RES) load_floats(ce_row + l, c);
+#pragma unroll
+                for (int e = 0; e < kSome; ++e) term(v[e], c[RES ? e : 0]);
+            }
+            for (; l < d; ++l) term(xi[l], RES ? ce_row[l] : 0.0f);
+            P = nx2 - cx;
+            w = encode_weight(p, id, nx2);
+        }
+        const bool active = id >= 0;
+        const bool init = stage < 0;
+        const double wl = init ? 0.0 : w, w2 = 2.0 * wl;
+        const float wf = (float)wl;
+        bool changed = false;
+
+        struct Step { // what a step needs and does not depend on the steps before it
+            float xv[DS], ce[RES ? DS : 1], cur[DS];
+            float a[G * S];
+            float2 lim;
+            int code;
+        };
+        auto load_step = [&](int m, Step &s) {
+            s.code = my_codes[m];
+            load_floats(xi + m * DS, s.xv);
+            if constexpr (RES) load_floats(ce_row + m * DS, s.ce);
+            s.lim = limits[m];
+            // [m][G * S / 4][64][4]
+#pragma unroll
+            for (int e = 0; e < G * S / 4; ++e) {
+                const four_floats v = *(const four_floats *)(operands + (((size_t)m * (G * S / 4) + e) * 64 + lane) * 4);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s.a[e * 4 + i] = v[i];
+            }
+            load_floats(p.codebooks + ((size_t)m * KC + s.code) * DS, s.cur);
+        };
+        Step now;
+        load_step(0, now);
+#pragma unroll 1
+        for (int m = 0; m < M; ++m) {
+            Step next;
+            load_step(m + 1 < M ? m + 1 : 0, next);
+            // q = (p of the other subspaces) + <x - center, x> of this one = P + <codeword in use, x>
+            double t_cur = 0.0;
+            float sx = 0.0f, sr = 0.0f, xrf[RES ? DS : 1];
+#pragma unroll
+            for (int l = 0; l < DS; ++l) {
+                t_cur = fma((double)now.cur[l], (double)now.xv[l], t_cur);
+                sx += fabsf(now.xv[l]);
+                if constexpr (RES) { xrf[l] = (float)((double)now.xv[l] - (double)now.ce[l]); sr += fabsf(xrf[l]); }
+            }
+            if (init) t_cur = 0.0;
+            const double q = P + t_cur;
+            const float Bf = (float)fma(w2, q, RES ? 0.0 : 2.0);
+            const float T = now.lim.x * sx;
+            float F = fmaf(T, fmaf(wf, T, fabsf(Bf)), now.lim.y);
+            if constexpr (RES) F = fmaf(2.0f * now.lim.x, sr, F);
+            // (the instruction may drop products below 2^-126)
+            const float lead = fmaf(F, 2.0f * kEps, fmaf(2.0f * DS * 2.4e-38f, fmaf(wf, T, fabsf(Bf)), 2.0e-37f));
+
+            float b[S], y[RES ? S : 1];
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                b[s] = h ? now.xv[2 * s + 1] : now.xv[2 * s];
+                if constexpr (RES) y[s] = fmaf(Bf, b[s], 2.0f * (h ? xrf[2 * s + 1] : xrf[2 * s]));
+            }
+            float best = INFINITY, second = INFINITY;
+            int group = 0;
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                v16f t, u, zero;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) zero[v] = 0.0f;
+                t = __builtin_amdgcn_mfma_f32_32x32x2f32(now.a[g * S], b[0], zero, 0, 0, 0);
+#pragma unroll
+                for (int s = 1; s < S; ++s) t = __builtin_amdgcn_mfma_f32_32x32x2f32(now.a[g * S + s], b[s], t, 0, 0, 0);
+                if constexpr (RES) {
+                    u = __builtin_amdgcn_mfma_f32_32x32x2f32(now.a[g * S], y[0], zero, 0, 0, 0);
+#pragma unroll
+                    for (int s = 1; s < S; ++s) u = __builtin_amdgcn_mfma_f32_32x32x2f32(now.a[g * S + s], y[s], u, 0, 0, 0);
+                }
+                const float old = best;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    four_floats cc;
+                    if constexpr (CC_LDS) cc = *(lds_float4 *)(cc_lds + m * KC + g * 32 + 8 * r + 4 * h);
+                    else cc = *(const four_floats *)(cc_all + (size_t)m * KC + g * 32 + 8 * r + 4 * h);
+                    float f[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float tv = t[4 * r + e];
+                        if constexpr (RES) f[e] = fmaf(wf * tv, tv, cc[e]) - u[4 * r + e];
+                        else f[e] = fmaf(tv, fmaf(wf, tv, -Bf), cc[e]);
+                        f[e] = __uint_as_float((__float_as_uint(f[e]) & 0xfffffff0u) | (uint32_t)(4 * r + e));
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; e += 2) { // as in encode_aniso_kernel
+                        const float mid = __builtin_amdgcn_fmed3f(best, f[e], f[e + 1]);
+                        asm("v_min_f32 %0, %1, %2" : "=v"(second) : "v"(second), "v"(mid));
+                        asm("v_min3_f32 %0, %1, %2, %3" : "=v"(best) : "v"(best), "v"(f[e]), "v"(f[e + 1]));
+                    }
+                }
+                group = best == old ? group : g;
+            }
+            const int v = (int)(__float_as_uint(best) & 15u);
+            int pick = group * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+            { // the other half's codewords
+                const float ob = __shfl_xor(best, 32, 64), os = __shfl_xor(second, 32, 64);
+                const int op = __shfl_xor(pick, 32, 64);
+                second = fminf(fmaxf(best, ob), fminf(second, os));
+                pick = ob < best ? op : pick;
+                best = fminf(best, ob);
+            }
+            const bool open = active && !(second - best > lead);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(open) != 0ull, 0)) {
+                if (open) { // in fp64, each half of the codewords by one of the point's lanes
+                    double bestv = INFINITY, xr[DS], xx = 0.0;
+                    pick = 128 * h;
+#pragma unroll
+                    for (int l = 0; l < DS; ++l) {
+                        xr[l] = (double)now.xv[l] - (RES ? (double)now.ce[RES ? l : 0] : 0.0);
+                        xx = fma(xr[l], (double)now.xv[l], xx);
+                    }
+                    const float *cb = p.codebooks + ((size_t)m * KC + 128 * h) * DS;
+#pragma unroll 4
+                    for (int c = 0; c < 128; ++c) {
+                        float cv[DS];
+                        load_floats(cb + c * DS, cv);
+                        double pm = 0.0, em = 0.0;
+#pragma unroll
+                        for (int l = 0; l < DS; ++l) {
+                            const double r = xr[l] - (double)cv[l];
+                            pm = fma(r, (double)now.xv[l], pm);
+                            em = fma(r, r, em);
+                        }
+                        const double pp = init ? 0.0 : (q - xx) + pm;
+                        const double val = em + wl * pp * pp;
+                        if (val < bestv) { bestv = val; pick = 128 * h + c; }
+                    }
+                    const double ov = __shfl_xor(bestv, 32, 64);
+                    const int op = __shfl_xor(pick, 32, 64);
+                    if (ov < bestv || (ov == bestv && op < pick)) pick = op;
+                }
+            }
+            const bool other = active && (init || pick != now.code);
+            if (__builtin_amdgcn_ballot_w64(other) != 0ull) {
+                if (other) {
+                    float c[DS];
+                    load_floats(p.codebooks + ((size_t)m * KC + pick) * DS, c);
+                    double t_new = 0.0;
+#pragma unroll
+                    for (int l = 0; l < DS; ++l) t_new = fma((double)c[l], (double)now.xv[l], t_new);
+                    if (h == 0) my_codes[m] = (uint8_t)pick;
+                    P = q - t_new;
+                    changed = true;
+                }
+            }
+            now = next;
+        }
+        const bool done = active && (init ? p.passes == 0 : !changed || stage + 1 >= p.passes);
+        stage = init ? 0 : stage + 1;
+        if (done) {
+            if (h == 0) {
+                uint8_t *out = p.packed + (size_t)id * p.NB;
+                for (int e = 0; e < p.NB; ++e) out[e] = my_codes[e];
+            }
+            id = -1;
+        }
+    }
+}
+
+// Every other shape (16 codewords of 8 dimensions; other numbers of dimensions per subspace; few subspaces, see
+// encode_few_steps): a thread per point, all in fp64, the terms of the current codewords kept per subspace. DS = dimensions per
 // subspace known at compile time (0: any): the point's sub-vector then stays in registers while its codewords (wave-
 // uniform, read through the scalar cache) pass by, instead of being read again for every codeword from a row that no
 // neighbouring lane shares. 200,000 points, 4-bit codes, DS known against any: 128 = 16 x 8 dimensions 0.72 against 5.98 ms a
@@ -1082,29 +1390,69 @@ encode_kernel(const float *__restrict__ x, int64_t n, int d, int M, int kc, int 
     }
 }
 
-template <int DS, int KC>
+template <int DS>
 static int launch_encode_one(EncodeParams p, const float *tab, const float2 *lim, hipStream_t st)
 {
-    // waves per workgroup: as many resident per compute unit as the 160 KB of LDS allow, at most 16
-    const size_t shared = KC == 16 ? (size_t)p.M * (KC * (DS + 1) + 2) * 4 : 0;
-    const size_t per_wave = (KC == 16 ? (size_t)64 * p.row_stride * 4 : 0) + (size_t)64 * p.code_stride;
+    // waves per workgroup: as many resident per compute unit as the 160 KB of LDS and the registers allow; few points are
+    // spread over the compute units first
+    const int most = DS <= 2 && p.leaf_centers == nullptr ? 20 : 16;
+    const size_t shared = (size_t)p.M * (16 * (DS + 1) + 2) * 4, per_wave = (size_t)64 * p.code_stride;
+    const int64_t groups = (p.n_slots + 63) / 64;
+    const int wanted = (int)std::min<int64_t>(8, std::max<int64_t>(1, (groups + 255) / 256));
     int waves = 0, resident = 0;
-    for (int w = 1; w <= 8; ++w) {
+    for (int w = 1; w <= wanted; ++w) {
         const size_t need = shared + w * per_wave;
         if (need > kMaxDynLds) break;
-        const int r = std::min<int>(16, (int)(kMaxDynLds / need) * w);
+        const int r = std::min<int>(most, (int)(kMaxDynLds / need) * w);
         if (r > resident) { resident = r; waves = w; }
     }
     if (waves == 0) return 1; // does not fit: the caller takes the plain kernel
-    const int64_t groups = (p.n_slots + 63) / 64;
     const int64_t total = std::min<int64_t>(groups, (int64_t)256 * resident); // a resident set of waves
     const dim3 grid((unsigned)((total + waves - 1) / waves));
     const size_t lds = shared + waves * per_wave;
     static LdsLimitOnce flat_done, res_done;
-    AVQ_TRY(set_lds_limit((const void *)encode_aniso_kernel<DS, KC, false>, kMaxDynLds, &flat_done));
-    AVQ_TRY(set_lds_limit((const void *)encode_aniso_kernel<DS, KC, true>, kMaxDynLds, &res_done));
-    if (p.leaf_centers) hipLaunchKernelGGL((encode_aniso_kernel<DS, KC, true>), grid, dim3(64 * waves), lds, st, p, tab, lim);
-    else hipLaunchKernelGGL((encode_aniso_kernel<DS, KC, false>), grid, dim3(64 * waves), lds, st, p, tab, lim);
+    AVQ_TRY(set_lds_limit((const void *)encode_aniso_kernel<DS, false>, kMaxDynLds, &flat_done));
+    AVQ_TRY(set_lds_limit((const void *)encode_aniso_kernel<DS, true>, kMaxDynLds, &res_done));
+    if (p.leaf_centers) hipLaunchKernelGGL((encode_aniso_kernel<DS, true>), grid, dim3(64 * waves), lds, st, p, tab, lim);
+    else hipLaunchKernelGGL((encode_aniso_kernel<DS, false>), grid, dim3(64 * waves), lds, st, p, tab, lim);
+    AVQ_HIP(hipGetLastError());
+    return AVQ_OK;
+}
+
+template <int DS>
+static int launch_encode_wide(EncodeParams p, const float *operands, const float *cc, const float2 *lim, hipStream_t st)
+{
+    const size_t shared = (size_t)p.M * 1024, per_wave = (size_t)32 * p.code_stride;
+    const bool cc_lds = shared + 4 * per_wave <= kMaxDynLds;
+    const size_t fixed = cc_lds ? shared : 0;
+    const int64_t groups = (p.n_slots + 31) / 32;
+    // waves per workgroup: few points are spread over the compute units first
+    const int wanted = (int)std::min<int64_t>(8, std::max<int64_t>(1, (groups + 255) / 256));
+    int waves = 0, resident = 0;
+    for (int w = 1; w <= wanted; ++w) {
+        const size_t need = fixed + w * per_wave;
+        if (need > kMaxDynLds) break;
+        const int r = std::min<int>(8, (int)(kMaxDynLds / need) * w);
+        if (r >= resident) { resident = r; waves = w; }
+    }
+    if (waves == 0) return 1;
+    const int64_t total = std::min<int64_t>(groups, (int64_t)256 * resident);
+    const dim3 grid((unsigned)((total + waves - 1) / waves)), block(64 * waves);
+    const size_t lds = fixed + waves * per_wave;
+    static LdsLimitOnce done[4];
+#define AVQ_WIDE(RES, CC, I)                                                                                          \
+    do {                                                                                                              \
+        AVQ_TRY(set_lds_limit((const void *)encode_wide_kernel<DS, RES, CC>, kMaxDynLds, &done[I]));                  \
+        hipLaunchKernelGGL((encode_wide_kernel<DS, RES, CC>), grid, block, lds, st, p, operands, cc, lim);            \
+    } while (0)
+    if (p.leaf_centers) {
+        if (cc_lds) AVQ_WIDE(true, true, 0);
+        else AVQ_WIDE(true, false, 1);
+    } else {
+        if (cc_lds) AVQ_WIDE(false, true, 2);
+        else AVQ_WIDE(false, false, 3);
+    }
+#undef AVQ_WIDE
     AVQ_HIP(hipGetLastError());
     return AVQ_OK;
 }
@@ -1148,25 +1496,27 @@ int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, con
         p.w_in = weights ? (const double *)(ws->as<unsigned char>() + b_tab + b_lim) : nullptr;
         p.packed = packed;
         p.next_window = (uint32_t *)(lim + kMaxM);
-        p.row_stride = d | 1;
         p.code_stride = 4 * (((M + 3) / 4) | 1);
-        hipLaunchKernelGGL(encode_tables_kernel, dim3((unsigned)M), dim3(64), 0, st, codebooks, kc, ds, tab, lim,
-                           p.next_window);
+        float *cc = tab + (size_t)M * kc * ds; // 256 codewords: after their operands
+        if (kc == 16)
+            hipLaunchKernelGGL(encode_tables_kernel, dim3((unsigned)M), dim3(64), 0, st, codebooks, kc, ds, tab, lim, p.next_window);
+        else
+            hipLaunchKernelGGL(encode_operands_kernel, dim3((unsigned)M), dim3(256), 0, st, codebooks, ds, tab, cc, lim, p.next_window);
         if (weights)
             hipLaunchKernelGGL(encode_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, n, d, eta_mode, T,
                                eta_explicit, (double *)p.w_in);
         if (kc == 16) {
             switch (ds) {
-            case 1: rc = launch_encode_one<1, 16>(p, tab, lim, st); break;
-            case 2: rc = launch_encode_one<2, 16>(p, tab, lim, st); break;
-            case 3: rc = launch_encode_one<3, 16>(p, tab, lim, st); break;
-            default: rc = launch_encode_one<4, 16>(p, tab, lim, st); break;
+            case 1: rc = launch_encode_one<1>(p, tab, lim, st); break;
+            case 2: rc = launch_encode_one<2>(p, tab, lim, st); break;
+            case 3: rc = launch_encode_one<3>(p, tab, lim, st); break;
+            default: rc = launch_encode_one<4>(p, tab, lim, st); break;
             }
         } else {
             switch (ds) {
-            case 2: rc = launch_encode_one<2, 256>(p, tab, lim, st); break;
-            case 4: rc = launch_encode_one<4, 256>(p, tab, lim, st); break;
-            default: rc = launch_encode_one<8, 256>(p, tab, lim, st); break;
+            case 2: rc = launch_encode_wide<2>(p, tab, cc, lim, st); break;
+            case 4: rc = launch_encode_wide<4>(p, tab, cc, lim, st); break;
+            default: rc = launch_encode_wide<8>(p, tab, cc, lim, st); break;
             }
         }
     }

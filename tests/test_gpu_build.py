@@ -285,6 +285,25 @@ def test_codes_of_shapes_without_fp32_search(n, d, M, leaves):
     np.testing.assert_array_equal(idx.get_codes(), oracle.pack_codes(oracle.encode(x, cb, T=0.2, passes=6, **okw), 4))
 
 
+@pytest.mark.parametrize("n,d,M,bits", [(1, 6, 3, 8), (31, 12, 6, 8), (33, 24, 6, 8), (65, 64, 8, 8), (40, 264, 132, 8),
+                                        (40, 512, 256, 8), (1, 10, 10, 4), (63, 27, 9, 4), (65, 52, 13, 4), (40, 510, 255, 4)])
+@pytest.mark.parametrize("leaves", [0, 3])
+def test_codes_at_the_edges_of_a_wave(n, d, M, bits, leaves):
+    """Windows of points that are not full, subspaces that are no multiple of four, dictionaries beyond LDS."""
+    rng = np.random.default_rng([n, d, M, leaves])
+    x = unit_rows(rng, n, d)
+    cb = (rng.standard_normal((M, 1 << bits, d // M)) / np.sqrt(d)).astype(np.float32)
+    idx = avq.Index(d, M, bits, T=0.2, encode_passes=5, n_leaves=leaves)
+    okw = {}
+    if leaves:
+        cen = unit_rows(rng, leaves, d)
+        idx.set_leaf_centers(dev(cen))
+        okw = dict(leaf_centers=cen, leaf_assign=oracle.assign_nearest(x, cen))
+    idx.set_codebooks(dev(cb))
+    idx.encode(dev(x))
+    np.testing.assert_array_equal(idx.get_codes(), oracle.pack_codes(oracle.encode(x, cb, T=0.2, passes=5, **okw), bits))
+
+
 def encode_seconds(n, d, M, bits=4, codewords=None):
     """The fastest of five calls."""
     gen = torch.Generator(device="cuda")
