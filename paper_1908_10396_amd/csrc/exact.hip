@@ -13,12 +13,13 @@
 // a norm), need[1 + q]: query q.
 //
 // 1,183,514 x 100 points, 1,000 queries, k = 10: every point in fp32 took 20.8 ms (one 4-byte load and eight fmas a
-// step, bound by the issue of the loads); this way 0.51 ms (product 0.33, which reads x once: 0.12 of matrix instructions,
-// 0.09 to read x; selection and fp32 scores 0.20; the plain kernel's three launches, which leave at once, 0.014).
+// step, bound by the issue of the loads); this way 0.43 ms (product 0.27, which reads x once: 0.13 of matrix instructions,
+// 0.08 to read x; selection and fp32 scores 0.15; the plain kernel's three launches, which leave at once, 0.014).
 // bf16 rather than f16, whose range needs a scale first.
 #include <algorithm>
 #include <type_traits>
 #include "avq_internal.h"
+#include "lds_copy.h"
 #include "wave_topk.h"
 
 namespace avq {
@@ -42,7 +43,8 @@ __device__ __forceinline__ float exact_bound(float qn, float qe, float xn, float
 }
 
 // One workgroup per tile of 32 queries: operand order [step][lane][8], lane (row lane % 32, half lane / 32) holding
-// coordinates 16 step + 8 half .. + 7; padding rows are zero. qnorm[q] = (norm, norm of the conversion error). Sets need.
+// coordinates 16 step + 4 half .. + 3 and 8 further on (the products may take them in any order, and a load of a point's row then
+// covers 32 adjacent bytes); padding rows are zero. qnorm[q] = (norm, norm of the conversion error). Sets need.
 __global__ void __launch_bounds__(256)
 exact_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, v8bf *__restrict__ packed, float2 *__restrict__ qnorm,
                   uint32_t *__restrict__ need)
@@ -68,7 +70,7 @@ exact_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, v
         v8bf o;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int l = 16 * s + 8 * (lane >> 5) + i;
+            const int l = 16 * s + 4 * (lane >> 5) + (i & 3) + 2 * (i & 4);
             o[i] = (__bf16)(qq < nq && l < d ? queries[(size_t)qq * d + l] : 0.0f);
         }
         packed[(size_t)t * steps * 64 + f] = o;
@@ -77,71 +79,179 @@ exact_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, v
 
 // Eight waves of 64 points, whose operands stay in registers (x is read once), against all queries, whose tiles of 32
 // go through LDS up to two ahead (x: 473 MB, queries: 224 KB at the size above). The products of one accumulator are issued
-// between the instructions that take the maximum of the other one (sched_barrier keeps the order): 0.46 -> 0.42 ms at the size
-// above. 14 operands of two column tiles fit 128 registers but for a few outside the loop, so that two workgroups share a compute
-// unit and one's row loads overlap the other's products: 0.33 (PAIR; fewer operands fit without being told). With one workgroup
-// for a compute unit, or a few queries and hence nothing to overlap, those few registers are a loss (launch_exact has the line). More
-// operands would spill in the loop (one column tile of 12: 14 loads from scratch every two tiles, each of which also waits for
-// the staged ones; 1,183,514 x 160, 1,000 queries, exact search whole: 1,051 us with one workgroup and products and maxima one after
-// the other, 1,090 with two, 971 with one). best[q][block of 64]: the workgroup's eight
-// maxima of a query leave as 32 adjacent bytes. xnorm[block] = largest norm and conversion error of its points.
-// PAIR: as many registers as let two share a compute unit.
+// between the instructions that take the maximum of the other one (sched_barrier keeps the order). More operands of two
+// column tiles than 8 steps would spill in the loop: one column tile. best[q][block of 64]: the workgroup's eight maxima of a
+// query leave as 32 adjacent bytes. xnorm[block] = largest norm and conversion error of its points, xnorm8 of the workgroup's.
+//
+// PAIR (97 to 112 dimensions): as many registers as let two workgroups share a compute unit, so that one's products go on
+// while the other reads its rows, and these come through LDS, sixteen a wave at a time, as one run of memory; an array
+// beyond the Infinity Cache is read past the caches, at 6 TB/s. Else a lane reads its points' coordinates itself, NS steps
+// ahead; past the caches that is slow, as it takes 32 bytes of a line at a time (1,183,514 x 100, one query: 211 us for the
+// product against 128).
+// Bound by the reading of x, then the tiles (5.6 us each, 4.1 of matrix instructions at the 2.0 GHz that they leave). Product
+// alone, 1,183,514 x 100, 1,024 queries: 310 us with a load waited for at a row's every step and the staged tile waited for
+// before each tile's first operand, 270 now; one query 137 / 111. One workgroup a compute unit, each lane its own rows:
+// 129 for one query. (32 to 48 dimensions, millions of points and a few queries: up to 6% more than before, 3,000,000 x 32,
+// one query 120 / 127 us a call; 300 queries 250 / 205.)
 template <int NS, int CT, bool PAIR>
 __global__ void __launch_bounds__(512, PAIR ? 4 : 2)
 exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *__restrict__ packed, int n_tiles, int nq,
-                     float *__restrict__ best, int64_t best_stride, float2 *__restrict__ xnorm, uint32_t *__restrict__ need)
+                     float *__restrict__ best, int64_t best_stride, float2 *__restrict__ xnorm, uint32_t *__restrict__ need,
+                     float2 *__restrict__ xnorm8, int nt)
 {
     __shared__ __align__(16) v8bf tile[3][NS * 64];
     __shared__ __align__(16) float mx[2][32][8];
+    __shared__ float2 norms[8];
+    constexpr int kRows = 16; // (two workgroups of 7 steps share 160 KB)
+    __shared__ __align__(16) uint4 rows_lds[8][PAIR ? kRows * NS * 4 : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, h = lane >> 5;
     const int64_t p0 = (int64_t)blockIdx.x * (8 * CT * 32) + wave * (CT * 32);
     const bool quad = (d & 3) == 0 && ((uintptr_t)x & 15) == 0;
     auto stage = [&](int t, int slot) {
         const v8bf *src = packed + (size_t)t * NS * 64;
         for (int s = wave; s < NS; s += 8)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + s * 64 + lane),
-                                             (__attribute__((address_space(3))) void *)(tile[slot] + s * 64), 16, 0, 0);
+            lds_copy16(src + s * 64 + lane, tile[slot] + s * 64);
     };
     stage(0, 0);
     if (n_tiles > 1) stage(1, 1);
     v8bf a[CT][NS];
-    float xn = 0.0f, xe = 0.0f;
+    float xn = 0.0f, xe = 0.0f, n2 = 0.0f, e2 = 0.0f;
+    auto operand = [&](int c, int s, const float (&v)[8]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-        const int64_t i = p0 + c * 32 + j;
-        const bool live = i < n; // padding points are copies of the last one
-        const float *row = x + (size_t)(live ? i : n - 1) * d;
-        float n2 = 0.0f, e2 = 0.0f;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int l0 = 16 * s + 8 * h;
-            float v[8];
-            if (quad && l0 + 8 <= d) {
-                const float4 u = *(const float4 *)(row + l0), w = *(const float4 *)(row + l0 + 4);
-                v[0] = u.x; v[1] = u.y; v[2] = u.z; v[3] = u.w;
-                v[4] = w.x; v[5] = w.y; v[6] = w.z; v[7] = w.w;
-            } else {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = l0 + u < d ? row[l0 + u] : 0.0f;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const __bf16 b = (__bf16)v[u];
-                const float e = v[u] - (float)b;
-                n2 += v[u] * v[u];
-                e2 += e * e;
-                a[c][s][u] = b;
-            }
+        for (int u = 0; u < 8; ++u) {
+            const __bf16 b = (__bf16)v[u];
+            const float e = v[u] - (float)b;
+            n2 += v[u] * v[u];
+            e2 += e * e;
+            a[c][s][u] = b;
         }
+    };
+    auto end_of_points = [&](int c) __attribute__((always_inline)) {
         n2 += __shfl_xor(n2, 32, 64);
         e2 += __shfl_xor(e2, 32, 64);
         const float cn = exact_norm(n2, d), ce = exact_norm(e2, d);
-        if (live && !(cn < kExactMaxNorm)) atomicOr(need, 1u);
+        if (p0 + c * 32 + j < n && !(cn < kExactMaxNorm)) atomicOr(need, 1u);
         xn = fmaxf(xn, cn);
         xe = fmaxf(xe, ce);
+        n2 = e2 = 0.0f;
+    };
+    if constexpr (PAIR) {
+        // The rows come through LDS, kRows of them at a time, which are one run of memory: each line is read once, whole, and no
+        // register holds what is on its way. Rows of an even number of quads are turned by their number (quad c of row r is at
+        // place c + r of it), so that the lanes of a read are spread over the banks; others are by themselves.
+        uint4 *const mine = rows_lds[wave];
+        const int unit = quad ? d / 4 : d, total = kRows * unit, turn_by = quad && (unit & 1) == 0 ? 1 : 0; // 16 bytes, or 4
+        const uint32_t inv = ((1u << 20) + (uint32_t)unit - 1u) / (uint32_t)unit; // e / unit = e inv >> 20 for e < 1024
+        auto turned = [&](int r) { return turn_by * (r - unit * (int)((uint32_t)r * inv >> 20)); }; // r % unit
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+#pragma unroll
+            for (int t = 0; t < 32 / kRows; ++t) {
+                const int64_t r0 = p0 + c * 32 + t * kRows, start = r0 + kRows <= n ? r0 : n - kRows; // (n is 256 or more)
+                const float *src = x + start * d;
+                if (quad) {
+                    for (int e0 = 0; e0 < total; e0 += 64) {
+                        const int e = e0 + lane < total ? e0 + lane : 0; // (beyond the run: its start, not used)
+                        const int r = (int)((uint32_t)e * inv >> 20);
+                        int q = e - r * unit - turned(r);
+                        q += q < 0 ? unit : 0;
+                        if (nt) lds_copy16_once(src + (r * unit + q) * 4, mine + e0);
+                        else lds_copy16(src + (r * unit + q) * 4, mine + e0);
+                    }
+                } else {
+                    for (int e0 = 0; e0 < total; e0 += 64)
+                        lds_copy4(src + (e0 + lane < total ? e0 + lane : 0), (float *)mine + e0);
+                }
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0)
+                asm volatile("" ::: "memory");
+                if ((j & ~(kRows - 1)) == t * kRows) {
+                    const int64_t i = p0 + c * 32 + j;
+                    const int r = (int)((i < n ? i : n - 1) - start); // padding points are copies of the last one
+                    const int by = turned(r);
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) {
+                        float v[8];
+                        if (quad) {
+#pragma unroll
+                            for (int u = 0; u < 2; ++u) {
+                                const int q = 4 * s + h + 2 * u;
+                                int at = q + by;
+                                at -= at >= unit ? unit : 0;
+                                const float4 w = *(const float4 *)(mine + r * unit + (q < unit ? at : 0));
+                                v[4 * u] = q < unit ? w.x : 0.0f; v[4 * u + 1] = q < unit ? w.y : 0.0f;
+                                v[4 * u + 2] = q < unit ? w.z : 0.0f; v[4 * u + 3] = q < unit ? w.w : 0.0f;
+                            }
+                        } else {
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) {
+                                const int l = 16 * s + 4 * h + (u & 3) + 2 * (u & 4);
+                                const float w = ((const float *)mine)[r * d + (l < d ? l : 0)];
+                                v[u] = l < d ? w : 0.0f;
+                            }
+                        }
+                        operand(c, s, v);
+                        __builtin_amdgcn_sched_barrier(0); // (all reads first would spill)
+                    }
+                }
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_waitcnt(0xc07f); // lgkmcnt(0): the next rows take these ones' place
+                asm volatile("" ::: "memory");
+            }
+            end_of_points(c);
+        }
+    } else if (quad) {
+        // a step's eight coordinates of a lane's point, those of kAsk steps asked for before they are used (without a branch
+        // between them: one for the row's end had each wait for the one before)
+        constexpr int kAsk = NS > 12 ? 12 : NS == 2 ? CT * NS : NS == 3 ? 2 : NS;
+        const float *row[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const int64_t i = p0 + c * 32 + j;
+            row[c] = x + (size_t)(i < n ? i : n - 1) * d; // padding points are copies of the last one
+        }
+        float4 raw[kAsk][2];
+        auto ask = [&](int e) __attribute__((always_inline)) {
+            const int l = 16 * (e % NS) + 4 * h; // (beyond the row: its start, not used)
+            raw[e % kAsk][0] = *(const float4 *)(row[e / NS] + (l < d ? l : 0));
+            raw[e % kAsk][1] = *(const float4 *)(row[e / NS] + (l + 8 < d ? l + 8 : 0));
+        };
+#pragma unroll
+        for (int e = 0; e < kAsk; ++e) ask(e);
+#pragma unroll
+        for (int e = 0; e < CT * NS; ++e) {
+            const float4 u = raw[e % kAsk][0], w = raw[e % kAsk][1];
+            const int l = 16 * (e % NS) + 4 * h;
+            const bool in0 = l < d, in1 = l + 8 < d;
+            const float v[8] = {in0 ? u.x : 0.0f, in0 ? u.y : 0.0f, in0 ? u.z : 0.0f, in0 ? u.w : 0.0f,
+                                in1 ? w.x : 0.0f, in1 ? w.y : 0.0f, in1 ? w.z : 0.0f, in1 ? w.w : 0.0f};
+            operand(e / NS, e % NS, v);
+            if (e + kAsk < CT * NS) ask(e + kAsk);
+            __builtin_amdgcn_sched_barrier(0);
+            if (e % NS == NS - 1) end_of_points(e / NS);
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const int64_t i = p0 + c * 32 + j;
+            const float *row = x + (size_t)(i < n ? i : n - 1) * d;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int l = 16 * s + 4 * h + (u & 3) + 2 * (u & 4);
+                    v[u] = row[l < d ? l : 0];
+                    v[u] = l < d ? v[u] : 0.0f;
+                }
+                operand(c, s, v);
+                __builtin_amdgcn_sched_barrier(0); // (all loads first would spill)
+            }
+            end_of_points(c);
+        }
     }
     for (int s = 16; s > 0; s >>= 1) { xn = fmaxf(xn, __shfl_xor(xn, s, 64)); xe = fmaxf(xe, __shfl_xor(xe, s, 64)); }
-    if (lane == 0) xnorm[(size_t)blockIdx.x * 8 + wave] = make_float2(xn, xe);
+    if (lane == 0) norms[wave] = xnorm[(size_t)blockIdx.x * 8 + wave] = make_float2(xn, xe);
     const bool any = p0 < n;
 
     // wave t % 8 writes tile t's maxima: two lanes per query, 16 bytes each
@@ -181,6 +291,11 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
     };
     __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0): this wave's part of the first tiles is in LDS
     __syncthreads();
+    if (tid == 0) {
+        float2 most = norms[0];
+        for (int w = 1; w < 8; ++w) most = make_float2(fmaxf(most.x, norms[w].x), fmaxf(most.y, norms[w].y));
+        xnorm8[blockIdx.x] = most;
+    }
 #pragma unroll
     for (int s = 0; s < NS; ++s) b[s] = tile[0][s * 64 + lane];
     int slot = 0;
@@ -229,16 +344,24 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
     put(n_tiles - 1);
 }
 
-// One workgroup per query: theta by two histogram passes over the ordering values of a - E (its 22 high bits, rounded
-// down: a lower theta only adds blocks), then the blocks that reach it as a list, a wave per block and a lane per point,
-// fp32 chain, wave lists. There are at least 4 k blocks (exact_supported). More than max_listed (at most kExactBins)
-// blocks: need[1 + q] is set and the plain kernel answers.
+// One workgroup per query. theta: the blocks are dealt to C classes, C a power of two from 8 k on, and theta is the k-th
+// largest of the classes' a - E, each that of the class's largest a: a few of the k best may share a class, which only lowers
+// theta a little, and a is read once, without the norms. (More results than a quarter of the threads: two histogram passes
+// over the ordering values of all a - E, 22 high bits, rounded down.) Then the blocks that reach theta as a list - against
+// the largest E of eight blocks first, so that few norms are read -, a wave per block and a lane per point, fp32 chain, wave
+// lists. There are at least 4 k blocks (exact_supported). More than max_listed (at most kExactBins) blocks: need[1 + q] is set
+// and the plain kernel answers.
+// Bound by what it reads: some fifteen blocks of 25 KB a query at the size above, and a twice (150 KB); 0.13 to 0.15 ms for 1,000
+// queries, 0.20 with the norms of all blocks read three times. Measured and dropped: the rows through LDS as one run of
+// memory (0.13 at k = 10, but 427 us instead of 286 for the search of 300,000 x 64, 600 queries, k = 100), sixteen loads of a
+// lane at once (more registers: 1.31 ms instead of 1.15 at k = 100).
 constexpr int kExactBins = 2048;
 template <int kExactThreads>
 __global__ void __launch_bounds__(kExactThreads)
 exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *__restrict__ queries, const float *__restrict__ best,
                     int64_t n_blocks, int64_t best_stride, int block_points, const float2 *__restrict__ qnorm,
-                    const float2 *__restrict__ xnorm, int ns, int k, uint32_t max_listed, uint32_t *__restrict__ need,
+                    const float2 *__restrict__ xnorm, const float2 *__restrict__ xnorm8, int ns, int k, uint32_t max_listed,
+                    uint32_t *__restrict__ need,
                     int32_t *__restrict__ ids_out, float *__restrict__ scores_out)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -246,60 +369,100 @@ exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = blockIdx.x;
     if ((need[0] | need[1 + q]) != 0u) return;
     constexpr int nw = kExactThreads / 64;
-    const int C = 64 * ns;
-    u64 *lists = (u64 *)smem, *mine = lists + (size_t)wave * C;
-    u64 *pend = lists + (size_t)nw * C + wave * 64;
-    float *qs = (float *)(lists + (size_t)nw * (C + 64));
+    const int L = 64 * ns;
+    u64 *lists = (u64 *)smem, *mine = lists + (size_t)wave * L;
+    u64 *pend = lists + (size_t)nw * L + wave * 64;
+    float *qs = (float *)(lists + (size_t)nw * (L + 64));
     for (int l = tid; l < d; l += kExactThreads) qs[l] = queries[(size_t)q * d + l];
     wave_list_clear(mine, ns);
     const float *a = best + (size_t)q * best_stride;
     const float2 qe = qnorm[q];
     auto bound = [&](int64_t b) { const float2 e = xnorm[b]; return exact_bound(qe.x, qe.y, e.x, e.y, d); };
-    // the bin of 11 bits that holds the left-th largest value with the given leading bits (all values: shift 21, prefix 0)
-    uint32_t prefix = 0u, left = (uint32_t)k;
-    for (int pass = 0; pass < 2; ++pass) {
-        for (int b = tid; b < kExactBins; b += kExactThreads) hist[b] = 0u;
-        __syncthreads();
-        for (int64_t b = tid; b < n_blocks; b += kExactThreads) {
-            const uint32_t o = ord_from_f32(a[b] - bound(b));
-            if (pass == 0) atomicAdd(&hist[o >> 21], 1u);
-            else if (o >> 21 == prefix) atomicAdd(&hist[(o >> 10) & 2047u], 1u);
+    const bool classes = k <= kExactThreads / 4;
+    int C = kExactThreads; // per = threads of a class, side by side
+    while (C >= 16 * k && C > 64) C >>= 1;
+    const int per_class = kExactThreads / C, cls = tid / per_class, sub = tid & (per_class - 1);
+    float low = -INFINITY, theta; // low: the class's
+    if (classes) {
+        float top = -INFINITY;
+        int64_t at = 0;
+#pragma unroll 8
+        for (int64_t b = cls + (int64_t)C * sub; b < n_blocks; b += kExactThreads) {
+            const float v = a[b];
+            at = v > top ? b : at;
+            top = fmaxf(top, v);
         }
-        __syncthreads();
-        uint32_t h[kExactBins / kExactThreads], sum = 0u;
-#pragma unroll
-        for (int i = 0; i < kExactBins / kExactThreads; ++i) { h[i] = hist[tid * (kExactBins / kExactThreads) + i]; sum += h[i]; }
-        uint32_t suf = sum; // of this lane and those above it
-        for (int m = 1; m < 64; m <<= 1) {
-            const uint32_t o = (uint32_t)__shfl_down((int)suf, m, 64);
-            if (lane + m < 64) suf += o;
-        }
-        if (lane == 0) wave_sum[wave] = suf;
-        __syncthreads();
-        uint32_t above = suf - sum;
-        for (int w = wave + 1; w < nw; ++w) above += wave_sum[w];
-#pragma unroll
-        for (int i = kExactBins / kExactThreads - 1; i >= 0; --i) {
-            if (above < left && left <= above + h[i]) {
-                found[0] = (uint32_t)(tid * (kExactBins / kExactThreads) + i);
-                found[1] = above;
-            }
-            above += h[i];
-        }
-        __syncthreads();
-        prefix = (prefix << 11) | found[0];
-        left -= found[1];
-        __syncthreads();
+        if (top > -INFINITY) low = top - bound(at);
+        for (int m = 1; m < per_class; m <<= 1) low = fmaxf(low, __shfl_xor(low, m, 64));
     }
-    const float theta = f32_from_ord(prefix << 10); // the values of the bin are at or above it
+    if (classes && C <= 256) { // the value that fewer than k exceed and k reach; a class's threads each count a part
+        float *vals = (float *)hist;
+        if (sub == 0) vals[cls] = low;
+        __syncthreads();
+        uint32_t more = 0u, same = 0u;
+        for (int e = sub * 4; e < C; e += per_class * 4) {
+            const float4 v = *(const float4 *)(vals + e);
+            more += (uint32_t)(v.x > low) + (uint32_t)(v.y > low) + (uint32_t)(v.z > low) + (uint32_t)(v.w > low);
+            same += (uint32_t)(v.x == low) + (uint32_t)(v.y == low) + (uint32_t)(v.z == low) + (uint32_t)(v.w == low);
+        }
+        for (int m = 1; m < per_class; m <<= 1) { more += __shfl_xor((int)more, m, 64); same += __shfl_xor((int)same, m, 64); }
+        if (more < (uint32_t)k && more + same >= (uint32_t)k) found[0] = __float_as_uint(low); // all that do have the same value
+        __syncthreads();
+        theta = __uint_as_float(found[0]);
+    } else { // the bin of 11 bits that holds the left-th largest value with the given leading bits (all values: shift 21, prefix 0)
+        uint32_t prefix = 0u, left = (uint32_t)k;
+        for (int pass = 0; pass < 2; ++pass) {
+            for (int b = tid; b < kExactBins; b += kExactThreads) hist[b] = 0u;
+            __syncthreads();
+            auto count = [&](float v) {
+                const uint32_t o = ord_from_f32(v);
+                if (pass == 0) atomicAdd(&hist[o >> 21], 1u);
+                else if (o >> 21 == prefix) atomicAdd(&hist[(o >> 10) & 2047u], 1u);
+            };
+            if (!classes)
+                for (int64_t b = tid; b < n_blocks; b += kExactThreads) count(a[b] - bound(b));
+            else if (sub == 0) count(low);
+            __syncthreads();
+            uint32_t h[kExactBins / kExactThreads], sum = 0u;
+#pragma unroll
+            for (int i = 0; i < kExactBins / kExactThreads; ++i) { h[i] = hist[tid * (kExactBins / kExactThreads) + i]; sum += h[i]; }
+            uint32_t suf = sum; // of this lane and those above it
+            for (int m = 1; m < 64; m <<= 1) {
+                const uint32_t o = (uint32_t)__shfl_down((int)suf, m, 64);
+                if (lane + m < 64) suf += o;
+            }
+            if (lane == 0) wave_sum[wave] = suf;
+            __syncthreads();
+            uint32_t above = suf - sum;
+            for (int w = wave + 1; w < nw; ++w) above += wave_sum[w];
+#pragma unroll
+            for (int i = kExactBins / kExactThreads - 1; i >= 0; --i) {
+                if (above < left && left <= above + h[i]) {
+                    found[0] = (uint32_t)(tid * (kExactBins / kExactThreads) + i);
+                    found[1] = above;
+                }
+                above += h[i];
+            }
+            __syncthreads();
+            prefix = (prefix << 11) | found[0];
+            left -= found[1];
+            __syncthreads();
+        }
+        theta = f32_from_ord(prefix << 10); // the values of the bin are at or above it
+    }
+    __syncthreads();
     uint32_t *list = hist;
     if (tid == 0) found[0] = 0u;
     __syncthreads();
-    for (int64_t b = tid; b < n_blocks; b += kExactThreads)
-        if (a[b] + bound(b) >= theta) {
-            const uint32_t at = atomicAdd(&found[0], 1u);
-            if (at < kExactBins) list[at] = (uint32_t)b;
+#pragma unroll 4
+    for (int64_t b = tid; b < n_blocks; b += kExactThreads) {
+        const float v = a[b];
+        const float2 e = xnorm8[b >> 3];
+        if (v + exact_bound(qe.x, qe.y, e.x, e.y, d) >= theta && v + bound(b) >= theta) {
+            const uint32_t to = atomicAdd(&found[0], 1u);
+            if (to < kExactBins) list[to] = (uint32_t)b;
         }
+    }
     __syncthreads();
     const uint32_t n_list = found[0];
     if (n_list > max_listed) {
@@ -335,7 +498,7 @@ exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *
     if (cnt > 0) wave_list_flush(mine, ns, pend, cnt);
     for (int stride = 1; stride < nw; stride *= 2) {
         __syncthreads();
-        if ((wave & (2 * stride - 1)) == 0) wave_list_merge_from(mine, ns, lists + (size_t)(wave + stride) * C);
+        if ((wave & (2 * stride - 1)) == 0) wave_list_merge_from(mine, ns, lists + (size_t)(wave + stride) * L);
     }
     if (wave == 0)
         for (int i = lane; i < k; i += 64) {
@@ -362,7 +525,7 @@ static size_t exact_finish_lds(int d, int k, int threads)
 namespace {
 struct ExactWs {
     v8bf *packed;
-    float2 *qnorm, *xnorm;
+    float2 *qnorm, *xnorm, *xnorm8; // xnorm8: the largest of eight blocks
     float *best;
     uint32_t *need;
     int64_t stride;
@@ -381,6 +544,7 @@ size_t exact_ws_layout(int64_t n, int d, int nq, unsigned char *base, ExactWs *w
     w->packed = (v8bf *)take(sizeof(v8bf) * (size_t)((nq + 31) / 32) * exact_steps(d) * 64);
     w->qnorm = (float2 *)take(sizeof(float2) * (size_t)nq);
     w->xnorm = (float2 *)take(sizeof(float2) * (size_t)w->stride);
+    w->xnorm8 = (float2 *)take(sizeof(float2) * (size_t)(w->stride / 8));
     w->best = (float *)take(sizeof(float) * (size_t)nq * w->stride);
     return off;
 }
@@ -442,14 +606,15 @@ int launch_exact(const float *x, int64_t n, int d, const float *queries, int nq,
     const int block_points = steps > 8 ? 32 : 64;
     *need_out = w.need;
     hipLaunchKernelGGL(exact_pack_kernel, dim3((unsigned)tiles), dim3(256), 0, st, queries, nq, d, steps, w.packed, w.qnorm, w.need);
-    // Two workgroups a compute unit: from 257 of them and three tiles of queries on, or 513 and two. 100 dimensions, one / two, us a
-    // call: 77,000 points, 2 queries 42.8 / 45.1, 1,000 133.6 / 135.5; 200,000, 64 queries 65.4 / 66.3, 130 74.2 / 73.2, 1,000 182.6 / 170.7;
-    // 400,000, 64 89.6 / 87.6; 1,183,514, 16 queries 191.9 / 197.4, 64 202.1 / 200.4, 130 226.4 / 212.6, 1,000 605 / 520.
+    // Two workgroups a compute unit and rows through LDS: where x does not fit the Infinity Cache, or from eight tiles of queries
+    // on. 100 dimensions, one / two, us a call: 140,000 points, 32 queries 60.2 / 67.2, 130 68.7 / 73.8, 1,000 165 / 159; 400,000, 1
+    // query 76 / 82, 130 98.4 / 99.0, 1,000 237 / 222; 1,183,514, 1 query 176 / 148, 64 200 / 179, 130 221 / 200, 1,000 509 / 431.
     const int64_t groups = w.stride / 8;
-    const bool pair = groups > 256 && tiles > (groups > 512 ? 1 : 2);
+    const int nt = sizeof(float) * (uint64_t)n * (uint64_t)d > ((uint64_t)256 << 20);
+    const bool pair = groups > 256 && (nt || tiles >= 8);
 #define AVQ_EXACT(NS, CT, PAIR)                                                                                          \
     hipLaunchKernelGGL((exact_product_kernel<NS, CT, PAIR>), dim3((unsigned)(w.stride / 8)), dim3(512), 0, st, x, n, d, w.packed, \
-                       tiles, nq, w.best, w.stride, w.xnorm, w.need)
+                       tiles, nq, w.best, w.stride, w.xnorm, w.need, w.xnorm8, nt)
     switch (steps) {
     case 2: AVQ_EXACT(2, 2, false); break;
     case 3: AVQ_EXACT(3, 2, false); break;
@@ -469,7 +634,7 @@ int launch_exact(const float *x, int64_t n, int d, const float *queries, int nq,
     const int threads = exact_finish_threads(nq);
     hipLaunchKernelGGL(threads == 512 ? exact_finish_kernel<512> : exact_finish_kernel<1024>, dim3((unsigned)nq), dim3((unsigned)threads),
                        exact_finish_lds(d, k, threads), st, x, n, d, queries, w.best, (n + block_points - 1) / block_points, w.stride,
-                       block_points, w.qnorm, w.xnorm, ns, k, exact_max_listed(n, d, nq, k, block_points), w.need, ids_out, scores_out);
+                       block_points, w.qnorm, w.xnorm, w.xnorm8, ns, k, exact_max_listed(n, d, nq, k, block_points), w.need, ids_out, scores_out);
     AVQ_HIP(hipGetLastError());
     return AVQ_OK;
 }

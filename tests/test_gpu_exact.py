@@ -47,6 +47,31 @@ def test_exact_search_of_one_and_two_workgroups_to_a_compute_unit(n, nq):
     check(unit_rows(rng, n, 100), unit_rows(rng, nq, 100), 10)
 
 
+# rows through LDS (eight tiles of queries on more than 256 workgroups): an odd and an even number of quads a row, rows that are
+# no whole quads or do not start at one, a last piece of sixteen rows that is short; and an array beyond 256 MB
+@pytest.mark.parametrize("n,d,nq,shift", [(131_073, 100, 225, 0), (131_090, 104, 225, 0), (131_073, 112, 226, 0), (131_600, 105, 225, 0),
+                                          (131_073, 98, 225, 0), (131_075, 100, 225, 1), (671_100, 100, 3, 0), (671_203, 97, 2, 0)])
+def test_exact_search_with_rows_through_lds(n, d, nq, shift):
+    rng = np.random.default_rng([n, d])
+    x, q = unit_rows(rng, n, d), unit_rows(rng, nq, d)
+    room = torch.empty(n * d + shift, device="cuda")
+    xd = room[shift:].view(n, d)
+    xd.copy_(torch.from_numpy(x))
+    ids, sc = exact_index(xd).brute_force(torch.from_numpy(q).cuda(), 10)
+    oi, os_ = oracle.brute_force(x, q, 10)
+    np.testing.assert_array_equal(ids.cpu().numpy(), oi)
+    np.testing.assert_array_equal(sc.cpu().numpy(), os_)
+
+
+# as many results as classes of blocks can tell apart, and more; values that many blocks share
+@pytest.mark.parametrize("n,nq,k", [(30_000, 20, 1), (30_000, 300, 15), (30_000, 20, 16), (30_000, 20, 17), (40_000, 20, 128),
+                                    (40_000, 260, 128), (40_000, 260, 129), (80_000, 20, 257)])
+def test_exact_search_at_the_lines_of_the_selection(n, nq, k):
+    rng = np.random.default_rng([n, nq, k])
+    x = np.round(unit_rows(rng, n, 24) * 16).astype(np.float32)
+    check(x, np.round(unit_rows(rng, nq, 24) * 16).astype(np.float32), k)
+
+
 # one to four query tiles through three buffers and two accumulators: two column tiles per wave of 14 (112 dimensions) and 16 (113)
 # operands, and one column tile (129, 256); points beyond the last full wave
 @pytest.mark.parametrize("d", [112, 113, 129, 256])
