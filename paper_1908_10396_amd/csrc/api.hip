@@ -795,6 +795,24 @@ static int search_through_candidates(avq_index *idx, const float *queries, int n
                            idx->scale.as<float>(), idx->bias.as<float>(), ids_out, scores_out, st);
 }
 
+// Queries on 8-bit codes one by one, or sixteen to a scan (us a call). Measured, one by one / sixteen to a scan, 25 bytes,
+// R = 100, fp32 tables: 200,000 points, 16 queries 59 / 63, 32 82 / 75; 500,000, 8 54 / 56, 16 72 / 63, 32 109 / 78; 1,183,514, 4
+// 55 / 60, 6 71 / 62, 16 110 / 71, 32 177 / 100; 5,000,000, 2 79 / 102, 4 110 / 110, 16 289 / 127, 64 1,016 / 341; 32 bytes,
+// 2,000,000, 4 80 / 85, 8 112 / 88, 64 580 / 256.
+static double per_query_us(const avq_index *idx, int R) // blocks listed, scored and ranked
+{
+    const double listed = (double)std::min<int64_t>(R, 2 * idx->n_blocks);
+    return 0.25 + 0.005 * std::min(100.0, listed) + 0.009 * std::max(0.0, listed - 100.0);
+}
+static double single_us(const avq_index *idx, int nq, int R)
+{
+    return 35.0 + nq * (0.1 + per_query_us(idx, R) + 3.3e-5 * idx->NB * (double)idx->n_blocks);
+}
+static double tile_us(const avq_index *idx, int nq, int R)
+{
+    return 45.0 + 1.28e-4 * idx->NB * (double)idx->n_blocks * ((nq + 15) / 16) + nq * (per_query_us(idx, R) + (idx->n_blocks < 4000 ? 0.1 : 0.0));
+}
+
 // Batches on a flat index through the product of the queries with the decoded points (product.hip), where it is expected to
 // be faster than the path that the call takes otherwise, for which few_max is the number of queries answered one by one.
 // What the other paths cost is estimated from below. Measured, other path / product, us a call (100 dimensions, R = 100):
@@ -818,14 +836,13 @@ static bool use_product(const avq_index *idx, int nq, int R, bool u8, int few_ma
         idx->tune_sample || idx->tune_small_impl || idx->tune_bound_bits || idx->tune_small_batch >= 0) return false;
     if (nq < 16) return false;
     const double n = (double)idx->n, q = (double)nq, d = (double)c.d, r = (double)R;
-    const double decode = std::max(0.0, n - 3e5) * d * (c.bits == 8 ? 1.0e-6 : 6e-7) * (d > 128 ? 1.0 : 0.8);
+    const double decode = std::max(0.0, n - 3e5) * d * (c.bits == 8 ? (d > 128 ? 5.0e-7 : 5.6e-7) : (d > 128 ? 6e-7 : 4.8e-7));
     double product = 30.0 + 0.35 * d + 0.14 * r + decode + q * (0.02 + 0.00018 * r) + 1.6e-9 * n * q * d;
     const double few = 20.0 + q * (0.1 + 0.000037 * idx->NB * (double)idx->n_blocks + (guessed ? 0.001 : 0.002) * r);
     if (c.bits == 8) {
         if (!block_bound_supported(idx->NB, c.bits)) return true; // plain scans: 400 us and more
-        product += 0.12 * d + (u8 ? 4.0 + 0.12 * d : 0.0);
-        const double tiles = 40.0 + 0.15 * q + idx->NB / 25.0 * (1.1e-4 * n + 6.5e-7 * n * q) + (n < 3e5 ? std::min(100.0, 0.003 * n) : 0.0);
-        return product < (nq > few_max ? (u8 ? 0.93 : 1.0) * tiles : few);
+        product += 0.12 * d + (u8 ? 4.0 + 0.12 * d + 0.1 * std::max(0.0, r - 100.0) : 0.0);
+        return product < (nq > few_max ? (u8 ? 0.93 : 1.0) * tile_us(idx, nq, R) : few);
     }
     const bool own = scan_mfma_supported(idx->NB, c.bits);
     if (u8) product += 12.0;
@@ -1496,8 +1513,11 @@ static int search_small(avq_index *idx, const float *queries, int nq, int k, int
         p.bound_tile = 16;
         // Entries of 6, 7 or 8 bits (tuning "bound_bits"): each bit more halves the width of the bounds, so fewer
         // blocks are scored exactly, and halves how many entries the full scan adds as packed bytes before it must
-        // spread them into 16-bit sums. Seven is the best of the three at 1.2 and at 50 million points.
-        const int bits_e = idx->tune_bound_bits >= 6 && idx->tune_bound_bits <= 8 ? idx->tune_bound_bits : 7;
+        // spread them into 16-bit sums. Seven is the best of the three at 1.2 and at 50 million points for batches; eight
+        // for up to 64 queries on less than 40 MB of codes (1,183,514 x 25 bytes, fp32 tables, 7 / 8: 16 queries 78 / 71 us, 64
+        // 175 / 160; 2,500,000: 90 / 88 and 230 / 232; 2,000,000 x 32 bytes, 8-bit tables, 64 queries 239 / 251).
+        const int own_bits = nq <= 64 && R <= 200 && idx->n_blocks * idx->NB <= 150000 ? 8 : 7;
+        const int bits_e = idx->tune_bound_bits >= 6 && idx->tune_bound_bits <= 8 ? idx->tune_bound_bits : own_bits;
         p.bound_levels = (1 << bits_e) - 1;
         p.bound_shift = 8 - bits_e;
         p.blocks_per_chunk = block_bound_tile_chunk(idx->n_blocks, nq);
@@ -1693,9 +1713,8 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
 
     // 4-bit codes: the block-maxima path costs about 4.5 us per query and million points, the batch scans a fixed
     // 0.2 ms per million points up to a few hundred queries: measured crossover near 36 queries
-    // 8-bit codes: a query by itself costs a scan of its own, sixteen together about one scan and a half (byte
-    // tables side by side): the tile of sixteen wins from about 120,000 query-blocks on (24 queries at 1.2 million
-    // points, 4 at 8 million), where the code size has the kernels for it; else up to 8 queries
+    // 8-bit codes: a query by itself costs a scan of its own, sixteen share one (byte tables side by side), which takes four
+    // times as long (single_us, tile_us)
     // 4-bit codes: the per-query path costs about 40 us + (0.1 + 0.00093 x blocks) us per query, the batch path
     // 150 us + 0.017 us per block up to a few hundred queries -- or 600 us on an index so small that its bounds
     // cannot be guessed from the class maxima of a sample and sorted lists take nearly every point. Measured
@@ -1714,9 +1733,9 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
         small_max = (int)std::min(4096.0, std::max(8.0, (batch_us - 40.0) / (0.1 + 0.00093 * nb)));
     }
     if (c.bits == 8 && block_bound_supported(idx->NB, c.bits) && idx->tune_small_impl == 0)
-        // two queries at least: measured per call, per-query path / batch path, at 8, 20 and 50 million points:
-        // 125 / 165, 229 / 399 and 500 / 716 us for two queries, equal for three
-        small_max = (int)std::min<int64_t>(32, std::max<int64_t>(2, 120000 / std::max<int64_t>(1, idx->n_blocks)));
+        // (more than 200 results: as measured at first, 24 queries at 1.2 million points, two in any case)
+        small_max = R > 200 ? (int)std::min<int64_t>(32, std::max<int64_t>(2, 120000 / std::max<int64_t>(1, idx->n_blocks)))
+                            : nq <= 2 || (nq <= 32 && single_us(idx, nq, R) <= tile_us(idx, nq, R)) ? nq : 0;
     if (idx->tune_small_batch >= 0) small_max = idx->tune_small_batch;
     const bool product = use_product(idx, nq, R, u8, small_max, guessed);
     const bool small = !ivf && !product && nq <= small_max;

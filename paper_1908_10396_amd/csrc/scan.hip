@@ -34,6 +34,7 @@
 //    block's maximum, hence below t), so only those R blocks are scanned again
 //    with the list machinery above.
 #include "avq_internal.h"
+#include "lds_copy.h"
 #include "wave_topk.h"
 #include "wg_select.h"
 
@@ -1451,17 +1452,18 @@ block_bound_tile_kernel(const ScanParams p)
     static_assert(NBT != 0 && NBT <= 32, "specialised code sizes only");
     extern __shared__ __align__(16) unsigned char dyn_smem[];
     const uint4 *tbl = (const uint4 *)dyn_smem; // [NBT][256] entries of 16 queries
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int lane = tid & 63, wave = tid >> 6, n_waves = nt >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = blockDim.x >> 6;
     const int tile = blockIdx.x, q0 = tile * 16;
     const int64_t c0 = (int64_t)blockIdx.y * p.blocks_per_chunk;
     const int64_t c1 = c0 + p.blocks_per_chunk < p.n_blocks ? c0 + p.blocks_per_chunk : p.n_blocks;
     int64_t blk = c0 + wave;
     BlockRegs<NBT> regs, nxt;
     if (blk < c1) load_block<NBT>(regs, p.codes, blk, lane);
-    {
+    { // all of a wave's copies on their way at once (one load after the other took 7 us)
         const uint4 *src = (const uint4 *)(p.bound_tbl + (size_t)tile * NBT * 256 * 16);
-        for (int it = tid; it < NBT * 256; it += nt) ((uint4 *)dyn_smem)[it] = src[it];
+        for (int it = wave * 64; it < NBT * 256; it += n_waves * 64) lds_copy16(src + it + lane, (uint4 *)dyn_smem + it);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0)
     }
     __syncthreads();
     for (; blk < c1; blk += n_waves) {
@@ -1813,8 +1815,26 @@ rescan_listed_blocks_kernel(const ScanParams p, const FinishParams f)
     BlockRegs<NBT> regs;
     int64_t blk = j < n_sel ? sel[j] : 0;
     if (j < n_sel) load_block<NBT>(regs, p.codes, blk, lane);
-    if (NIB) nibble_tables_fill<U8>(smem, p, q, NB);
-    else build_tables<1, U8>((entry_t *)smem, p, q, NB);
+    if constexpr (NIB) {
+        nibble_tables_fill<U8>(smem, p, q, NB);
+    } else { // 256 entries a byte position, four a thread and step, all loads on their way first
+        constexpr int kSteps = (NBT * 64 + 255) / 256;
+        uint4 four[kSteps];
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) {
+            const int e = threadIdx.x + i * 256;
+            if (e >= NBT * 64) continue;
+            if constexpr (U8) four[i].x = ((const uint32_t *)(p.lut8 + (size_t)q * NBT * 256))[e];
+            else four[i] = ((const uint4 *)(p.lut + (size_t)q * NBT * 256))[e];
+        }
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) {
+            const int e = threadIdx.x + i * 256;
+            if (e >= NBT * 64) continue;
+            if constexpr (U8) { const uint32_t w = four[i].x; four[i] = make_uint4(w & 255u, (w >> 8) & 255u, (w >> 16) & 255u, w >> 24); }
+            ((uint4 *)smem)[e] = four[i];
+        }
+    }
     __syncthreads();
     const u64 t1 = f.meta[q].t1;
     u64 *cand = f.cand + (size_t)q * f.cand_stride;
@@ -2494,10 +2514,13 @@ static int launch_block_bound_tile_one(const ScanParams &p, hipStream_t st)
 
 int block_bound_tile_chunk(int64_t n_blocks, int B)
 {
-    // about four rounds of one workgroup per compute unit, chunks of at least 128 blocks (eight per wave)
-    const int tiles = (B + 15) / 16;
-    int64_t chunks = std::max<int64_t>(1, 1024 / tiles);
-    chunks = std::min<int64_t>(chunks, std::max<int64_t>(1, n_blocks / 128));
+    // Whole rounds of one workgroup per compute unit: up to four, of at least 128 blocks a workgroup (eight a wave); one, and
+    // as little as a block a wave, where there are not as many. 5,000,000 points of 25 bytes, 32 queries (two tiles): 152 chunks
+    // each, 304 workgroups, 262 us a search; 128 each: 195.
+    const int64_t tiles = (B + 15) / 16;
+    const int64_t rounds = std::max<int64_t>(1, std::min<int64_t>(4, n_blocks * tiles / (256 * 128)));
+    int64_t chunks = std::max<int64_t>(1, 256 * rounds / tiles);
+    chunks = std::min<int64_t>(chunks, std::max<int64_t>(1, (n_blocks + 15) / 16));
     return (int)((n_blocks + chunks - 1) / chunks);
 }
 

@@ -1,0 +1,36 @@
+"""Some queries on 8-bit codes: one by one and sixteen to a scan, against the oracle, where tiles of sixteen queries, chunks of
+a block a wave and byte tables of seven and eight bits meet their edges."""
+import numpy as np
+import pytest
+
+import oracle
+from util import unit_rows
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+avq = pytest.importorskip("paper_1908_10396_amd")
+
+
+# one block, sixteen and seventeen (a block a wave and one more), as many chunks as compute units; a tile that is not full, two
+# tiles, and more queries than eight-bit tables are taken for
+@pytest.mark.parametrize("n,d,M,nq,k,R", [(200, 32, 8, 3, 10, 20), (256 * 16, 26, 13, 16, 10, 0), (256 * 16 + 1, 50, 25, 17, 5, 100),
+                                          (66_000, 50, 25, 5, 10, 100), (66_000, 64, 32, 33, 10, 201), (70_001, 26, 13, 65, 1, 1)])
+@pytest.mark.parametrize("mode", [avq.LUT_F32, avq.LUT_U8])
+def test_queries_sixteen_to_a_scan(n, d, M, nq, k, R, mode):
+    rng = np.random.default_rng([n, d, nq])
+    x, q = unit_rows(rng, n, d), unit_rows(rng, nq, d)
+    cb = (rng.standard_normal((M, 256, d // M)) / np.sqrt(d)).astype(np.float32)
+    codes = rng.integers(0, 256, (n, M), dtype=np.uint8)
+    idx = avq.Index(d, M, 8)
+    idx.set_codebooks(cb)
+    idx.set_database(torch.from_numpy(x).cuda(), torch.from_numpy(codes).cuda())
+    oi, os_ = oracle.search(x, cb, codes, 8, q, k, R, mode)
+    qd = torch.from_numpy(q).cuda()
+    for most_by_themselves, bits in ((0, 0), (1, 0), (1, 7), (1, 8), (1001, 0)):  # 0: as built in; 1: sixteen to a scan; 1001: one by one
+        idx.set_tuning("small_batch_max", most_by_themselves)
+        idx.set_tuning("bound_bits", bits)
+        ids, sc = idx.search(qd, k, R, mode)
+        what = "small_batch_max %d, bound_bits %d" % (most_by_themselves, bits)
+        np.testing.assert_array_equal(ids.cpu().numpy(), oi, err_msg=what)
+        np.testing.assert_array_equal(sc.cpu().numpy(), os_, err_msg=what)
