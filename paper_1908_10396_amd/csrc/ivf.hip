@@ -242,36 +242,124 @@ leaf_scores_kernel(const float *__restrict__ centers_t, int n_leaves, int d, con
     keys[(size_t)q * n_leaves + leaf] = make_key(ord_from_f32(s), leaf);
 }
 
+// The L best of a query's leaves, in order; one workgroup a query, bound by its chain of exchanges and barriers. The scores
+// are counted in bins of equal width between the smallest and the largest; what reaches the bin of the L-th best - L leaves and
+// the few that share the bin - is ranked by counting, several threads a leaf. Up to 8,192 leaves whose scores are finite and
+// spread over the bins; the others by wg_select_threshold, which narrows the range pass by pass (2,000 leaves, L = 100: 11.2 us
+// that way, 6.0 this).
+constexpr int kLeafBins = 1024, kLeafTop = 1024;
 __global__ void __launch_bounds__(1024)
 leaf_top_kernel(const u64 *__restrict__ keys, int n_leaves, int L, int32_t *__restrict__ leaf_ids, float *__restrict__ leaf_ip)
 {
-    __shared__ WgSelectScratch sel;
-    __shared__ u64 top[512];
-    __shared__ uint32_t n_top;
-    const int tid = threadIdx.x, q = blockIdx.x;
+    __shared__ union { WgSelectScratch sel; uint32_t hist[kLeafBins]; } u;
+    __shared__ __align__(16) u64 top[kLeafTop + 64];
+    __shared__ float wave_hi[16], wave_lo[16];
+    __shared__ uint32_t wave_sum[16], n_top, edge;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = blockIdx.x;
     const u64 *row = keys + (size_t)q * n_leaves;
-    if (tid == 0) n_top = 0u;
-    const u64 t = wg_select_threshold(row, n_leaves, L, &sel);
-    __syncthreads();
-    for (int i = tid; i < n_leaves; i += 1024) {
-        const u64 key = row[i];
-        if (key >= t && key) {
-            const uint32_t at = atomicAdd(&n_top, 1u);
-            if (at < 512u) top[at] = key;
+    constexpr int kPer = 8;
+    float sc[kPer]; // this thread's leaves tid, tid + 1024, ..
+    const int want = L < n_leaves ? L : n_leaves;
+    bool fast = n_leaves <= kPer * 1024;
+    if (fast) {
+        float hi = -INFINITY, lo = INFINITY;
+        bool odd = false; // not finite
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int l = tid + i * 1024;
+            if (l >= n_leaves) continue;
+            sc[i] = f32_from_ord(key_ord(row[l]));
+            odd = odd || !(fabsf(sc[i]) < INFINITY);
+            hi = fmaxf(hi, sc[i]);
+            lo = fminf(lo, sc[i]);
         }
+        u.hist[tid] = 0u;
+        if (tid == 0) { n_top = 0u; edge = 0u; }
+        if (odd) hi = INFINITY;
+#pragma unroll
+        for (int m = 32; m > 0; m >>= 1) {
+            hi = fmaxf(hi, __shfl_xor(hi, m, 64));
+            lo = fminf(lo, __shfl_xor(lo, m, 64));
+        }
+        if (lane == 0) { wave_hi[wave] = hi; wave_lo[wave] = lo; }
+        __syncthreads();
+        hi = wave_hi[lane & 15];
+        lo = wave_lo[lane & 15];
+#pragma unroll
+        for (int m = 8; m > 0; m >>= 1) {
+            hi = fmaxf(hi, __shfl_xor(hi, m, 64));
+            lo = fminf(lo, __shfl_xor(lo, m, 64));
+        }
+        // a bin's number does not fall where the score rises: each of the three roundings keeps order
+        const float per_bin = (float)(kLeafBins - 1) / (hi - lo);
+        fast = hi - lo > 0.0f && hi - lo < INFINITY && per_bin < INFINITY;
+        if (fast) { // (the same for the whole workgroup)
+            uint32_t bin[kPer];
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                if (tid + i * 1024 >= n_leaves) continue;
+                const uint32_t b = (uint32_t)((sc[i] - lo) * per_bin);
+                bin[i] = b < kLeafBins ? b : kLeafBins - 1;
+                atomicAdd(&u.hist[bin[i]], 1u);
+            }
+            __syncthreads();
+            const uint32_t own = u.hist[tid];
+            uint32_t suf = own; // of this bin and those above it
+#pragma unroll
+            for (int m = 1; m < 64; m <<= 1) {
+                const uint32_t o = (uint32_t)__shfl_down((int)suf, m, 64);
+                if (lane + m < 64) suf += o;
+            }
+            if (lane == 0) wave_sum[wave] = suf;
+            __syncthreads();
+            uint32_t above = lane < 16 && lane > wave ? wave_sum[lane] : 0u;
+#pragma unroll
+            for (int m = 8; m > 0; m >>= 1) above += (uint32_t)__shfl_xor((int)above, m, 64);
+            suf += (uint32_t)__builtin_amdgcn_readfirstlane((int)above);
+            // bin (its number) and what reaches it (at most 8,192), in one word: one of them only
+            if (suf >= (uint32_t)want && suf - own < (uint32_t)want) edge = (uint32_t)tid << 16 | suf;
+            __syncthreads();
+            const uint32_t from = edge >> 16;
+            fast = (edge & 0xffffu) <= kLeafTop;
+            if (fast) {
+#pragma unroll
+                for (int i = 0; i < kPer; ++i) {
+                    const int l = tid + i * 1024;
+                    if (l < n_leaves && bin[i] >= from) top[atomicAdd(&n_top, 1u)] = make_key(ord_from_f32(sc[i]), l);
+                }
+            }
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    const int n = (int)(n_top < 512u ? n_top : 512u); // min(L, leaves)
-    for (int i = tid; i < n; i += 1024) {
-        const u64 mine = top[i];
+    if (!fast) {
+        if (tid == 0) n_top = 0u;
+        const u64 t = wg_select_threshold(row, n_leaves, L, &u.sel);
+        __syncthreads();
+        for (int i = tid; i < n_leaves; i += 1024) {
+            const u64 key = row[i];
+            if (key >= t && key) {
+                const uint32_t at = atomicAdd(&n_top, 1u);
+                if (at < kLeafTop) top[at] = key;
+            }
+        }
+        __syncthreads();
+    }
+    const int n = (int)(n_top < kLeafTop ? n_top : kLeafTop);
+    int per = 16; // threads that count for a key, side by side
+    while (per > 1 && per * n > 1024) per >>= 1;
+    const int at = tid / per, part = tid & (per - 1);
+    if (at < n) {
+        const u64 mine = top[at];
         int rank = 0;
-        for (int j = 0; j < n; ++j) rank += top[j] > mine;
-        if (rank < L) {
+#pragma unroll 4
+        for (int j = part; j < n; j += per) rank += top[j] > mine;
+        for (int m = 1; m < per; m <<= 1) rank += __shfl_xor(rank, m, 64);
+        if (part == 0 && rank < L) {
             leaf_ids[(size_t)q * L + rank] = key_id(mine);
             leaf_ip[(size_t)q * L + rank] = f32_from_ord(key_ord(mine));
         }
     }
-    for (int i = n + tid; i < L; i += 1024) { // fewer leaves than asked for
+    for (int i = want + tid; i < L; i += 1024) { // fewer leaves than asked for
         leaf_ids[(size_t)q * L + i] = -1;
         leaf_ip[(size_t)q * L + i] = -INFINITY;
     }
