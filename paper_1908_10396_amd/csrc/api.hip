@@ -1608,11 +1608,21 @@ static int check_search_args(const avq_index *idx, const float *queries, int32_t
 // with the one-query-per-workgroup scan over leaves, which keeps sorted lists per wave: between 64 and 96 queries at
 // 100 of 2,000 leaves).
 constexpr int kLeafSmallMaxQueries = 80;
-static bool use_leaf_small(const avq_index *idx, int nq, int L)
+// 8-bit codes and code sizes without kernels of their own take it too, but for a few results from a few blocks, where the four
+// launches of the list scan are done before the six here. Many results from many blocks for many queries, all of which are
+// scored twice here, are left to the list scan. List scan / this, us a call, fp32 tables: 5,000 points, 5 of 70 leaves, 16 code
+// bytes, one query: R = 1 27 / 30, 100 39 / 36, 500 76 / 40; 900,000, 120 of 1,500: 1 query R = 100 106 / 42, 80 queries 146 / 132,
+// R = 500 384 / 128, 532 / 508 (40 queries), 616 / 734 (60), 387 / 939 (80); 25 bytes of 8-bit codes 113 / 42, 168 / 144, 416 / 127,
+// 717 / 509 (60), 446 / 610 (80); 48 bytes of 4-bit codes 159 / 62, 293 / 218, 550 / 148, 938 / 774, 575 / 973.
+static bool use_leaf_small(const avq_index *idx, int nq, int L, int R)
 {
     const int max_q = idx->tune_small_batch >= 0 ? std::min(idx->tune_small_batch, 4096) : kLeafSmallMaxQueries;
-    return idx->cfg.n_leaves > 0 && idx->tune_small_impl != 1 && nq <= max_q && L <= 512 &&
-           leaf_small_supported(idx->NB, idx->cfg.bits);
+    if (idx->cfg.n_leaves == 0 || idx->tune_small_impl == 1 || nq > max_q || L > 512 || !leaf_small_supported(idx->NB, idx->cfg.bits)) return false;
+    if (idx->tune_small_batch >= 0) return true;
+    const bool own = idx->cfg.bits == 4 && block_bound_supported(idx->NB, 4);
+    const double listed = (double)L * (double)idx->n_blocks / idx->cfg.n_leaves; // blocks of a query's leaves
+    if (!own && R < 32 && listed < 12.0) return false;
+    return R <= 200 || nq * listed <= 20000.0 || (nq <= 64 && (own || idx->cfg.bits == 8 || idx->NB >= 24));
 }
 
 static int search_leaves_small(avq_index *idx, const float *queries, int nq, int k, int reorder_k, int R, int L, bool u8,
@@ -1752,7 +1762,7 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
         if (rc != AVQ_ENOMEM) return rc;
     }
     const bool grouped = ivf && use_grouped_leaves(idx, nq, leaves_to_search, R);
-    if (ivf && use_leaf_small(idx, nq, leaves_to_search))
+    if (ivf && use_leaf_small(idx, nq, leaves_to_search, R))
         return search_leaves_small(idx, queries, nq, k, reorder_k, R, leaves_to_search, u8, ids_out, scores_out, st);
     if (small && idx->tune_small_impl != 1) {
         SmallWs w;

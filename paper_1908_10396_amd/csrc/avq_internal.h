@@ -261,7 +261,7 @@ int launch_small_rescan(const ScanParams &p, const FinishParams &f, bool u8, hip
 // (p.fuse_queries), a small flat index, f.rerank_rows 0. No scratch.
 bool search_one_supported(int64_t n_blocks, int NB);
 int launch_search_one(const ScanParams &p, const FinishParams &f, hipStream_t st);
-// A handful of queries on a partitioned index (4-bit codes, specialised code sizes): exact block maxima over the
+// A handful of queries on a partitioned index: exact block maxima over the
 // blocks of the probed leaves (p.leaf_ids / leaf_ip / leaf_blk / perm, p.Lp leaves per query), listed per query in
 // probe order; selection of the R blocks with the largest maxima (positions in the list to f.sel_blk[q][R], f.meta);
 // the points of those at or above t1 to f.cand. launch_small_final finishes (keys carry fp32 scores and point ids).

@@ -1009,6 +1009,53 @@ struct LeafBlockList {
     int64_t stride;
 };
 
+// The 256-entry tables of 8-bit codes, four bytes an entry: four entries a thread and step, eight steps' loads on their way at
+// once. 256 threads.
+template <bool U8>
+__device__ __forceinline__ void wide_tables_fill(unsigned char *tbl, const ScanParams &p, int q, int NB)
+{
+    const int total = NB * 64;
+    for (int e0 = 0; e0 < total; e0 += 2048) {
+        u32x4 four[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int at = e0 + (int)threadIdx.x + i * 256, e = at < total ? at : 0;
+            if constexpr (U8) {
+                const uint32_t w = ((const uint32_t *)(p.lut8 + (size_t)q * NB * 256))[e];
+                four[i] = u32x4{w & 255u, (w >> 8) & 255u, (w >> 16) & 255u, w >> 24};
+            } else {
+                four[i] = ((const u32x4 *)(p.lut + (size_t)q * NB * 256))[e];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int e = e0 + (int)threadIdx.x + i * 256;
+            if (e < total) ((u32x4 *)tbl)[e] = four[i];
+        }
+    }
+}
+
+// A block's sums for the two leaf kernels: WIDE: 8-bit codes, else 4-bit ones; NBT = 0: any number of code bytes.
+template <bool U8, int NBT, bool WIDE>
+__device__ __forceinline__ void leaf_block_sums(const unsigned char *tables, const BlockRegs<NBT> &regs, const ScanParams &p, int64_t blk,
+                                                int NB, int lane, float (&accf)[4], uint32_t (&acci)[4])
+{
+    if constexpr (WIDE) {
+        uint32_t acc[4];
+        accumulate_block<1, U8, NBT>((const uint32_t *)tables, regs, p.codes, blk, NB, lane, acc);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { acci[i] = acc[i]; accf[i] = __uint_as_float(acc[i]); }
+    } else {
+        nibble_accumulate<U8, NBT>(tables, regs, p.codes + (size_t)blk * 256 * NB, NB, lane, accf, acci);
+    }
+}
+template <bool U8, bool WIDE>
+__device__ __forceinline__ void leaf_tables_fill(unsigned char *tables, const ScanParams &p, int q, int NB)
+{
+    if constexpr (WIDE) wide_tables_fill<U8>(tables, p, q, NB);
+    else nibble_tables_fill<U8>(tables, p, q, NB);
+}
+
 template <bool U8>
 __device__ __forceinline__ float leaf_point_score(float accf, uint32_t acci, float ip, float scale, float bias)
 {
@@ -1016,12 +1063,12 @@ __device__ __forceinline__ float leaf_point_score(float accf, uint32_t acci, flo
     return __fadd_rn(accf, ip);
 }
 
-template <bool U8, int NBT>
+template <bool U8, int NBT, bool WIDE>
 __global__ void __launch_bounds__(256)
 leaf_block_max_kernel(const ScanParams p, const LeafBlockList list)
 {
-    static_assert(NBT != 0, "specialised code sizes only");
-    __shared__ __align__(16) unsigned char tables[2 * NBT * 16 * (U8 ? 1 : 4)];
+    extern __shared__ __align__(16) unsigned char tables[];
+    const int NB = NBT ? NBT : p.NB;
     __shared__ int red_before[4], red_total[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j = blockIdx.x, q = blockIdx.y;
@@ -1043,7 +1090,7 @@ leaf_block_max_kernel(const ScanParams p, const LeafBlockList list)
     BlockRegs<NBT> regs;
     int64_t blk = b0 + wave;
     if (blk < b1) load_block<NBT>(regs, p.codes, blk, lane); // in flight while the tables are filled
-    nibble_tables_fill<U8>(tables, p, q, NBT);
+    leaf_tables_fill<U8, WIDE>(tables, p, q, NB);
     __syncthreads();
     before = red_before[0] + red_before[1] + red_before[2] + red_before[3];
     total = red_total[0] + red_total[1] + red_total[2] + red_total[3];
@@ -1053,7 +1100,7 @@ leaf_block_max_kernel(const ScanParams p, const LeafBlockList list)
     for (; blk < b1; blk += 4) {
         float accf[4];
         uint32_t acci[4];
-        nibble_accumulate<U8, NBT>(tables, regs, p.codes + (size_t)blk * 256 * NBT, NBT, lane, accf, acci);
+        leaf_block_sums<U8, NBT, WIDE>(tables, regs, p, blk, NB, lane, accf, acci);
         const int64_t next = blk + 4;
         if (next < b1) load_block<NBT>(regs, p.codes, next, lane);
         u64 best = 0ull;
@@ -1122,12 +1169,12 @@ select_listed_blocks_kernel(const LeafBlockList list, int R, int32_t *__restrict
 }
 
 // E. one wave per selected block: its points at or above t1 go to the query's candidates.
-template <bool U8, int NBT>
+template <bool U8, int NBT, bool WIDE>
 __global__ void __launch_bounds__(256)
 rescan_leaf_blocks_kernel(const ScanParams p, const FinishParams f, const LeafBlockList list)
 {
-    static_assert(NBT != 0, "specialised code sizes only");
-    __shared__ __align__(16) unsigned char tables[2 * NBT * 16 * (U8 ? 1 : 4)];
+    extern __shared__ __align__(16) unsigned char tables[];
+    const int NB = NBT ? NBT : p.NB;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
     const int q = blockIdx.y;
     const int j = blockIdx.x * n_waves + wave;
@@ -1138,14 +1185,14 @@ rescan_leaf_blocks_kernel(const ScanParams p, const FinishParams f, const LeafBl
     const int64_t blk = have ? list.blk[(size_t)q * list.stride + at] : 0;
     BlockRegs<NBT> regs;
     if (have) load_block<NBT>(regs, p.codes, blk, lane);
-    nibble_tables_fill<U8>(tables, p, q, NBT);
+    leaf_tables_fill<U8, WIDE>(tables, p, q, NB);
     __syncthreads();
     if (!have) return;
     const float ip = list.ip[(size_t)q * list.stride + at];
     const float scale = U8 ? p.scale[q] : 0.0f, bias = U8 ? p.bias[q] : 0.0f;
     float accf[4];
     uint32_t acci[4];
-    nibble_accumulate<U8, NBT>(tables, regs, p.codes + (size_t)blk * 256 * NBT, NBT, lane, accf, acci);
+    leaf_block_sums<U8, NBT, WIDE>(tables, regs, p, blk, NB, lane, accf, acci);
     const u64 t1 = f.meta[q].t1;
     u64 *cand = f.cand + (size_t)q * f.cand_stride;
 #pragma unroll
@@ -1815,26 +1862,8 @@ rescan_listed_blocks_kernel(const ScanParams p, const FinishParams f)
     BlockRegs<NBT> regs;
     int64_t blk = j < n_sel ? sel[j] : 0;
     if (j < n_sel) load_block<NBT>(regs, p.codes, blk, lane);
-    if constexpr (NIB) {
-        nibble_tables_fill<U8>(smem, p, q, NB);
-    } else { // 256 entries a byte position, four a thread and step, all loads on their way first
-        constexpr int kSteps = (NBT * 64 + 255) / 256;
-        uint4 four[kSteps];
-#pragma unroll
-        for (int i = 0; i < kSteps; ++i) {
-            const int e = threadIdx.x + i * 256;
-            if (e >= NBT * 64) continue;
-            if constexpr (U8) four[i].x = ((const uint32_t *)(p.lut8 + (size_t)q * NBT * 256))[e];
-            else four[i] = ((const uint4 *)(p.lut + (size_t)q * NBT * 256))[e];
-        }
-#pragma unroll
-        for (int i = 0; i < kSteps; ++i) {
-            const int e = threadIdx.x + i * 256;
-            if (e >= NBT * 64) continue;
-            if constexpr (U8) { const uint32_t w = four[i].x; four[i] = make_uint4(w & 255u, (w >> 8) & 255u, (w >> 16) & 255u, w >> 24); }
-            ((uint4 *)smem)[e] = four[i];
-        }
-    }
+    if constexpr (NIB) nibble_tables_fill<U8>(smem, p, q, NB);
+    else wide_tables_fill<U8>(smem, p, q, NB);
     __syncthreads();
     const u64 t1 = f.meta[q].t1;
     u64 *cand = f.cand + (size_t)q * f.cand_stride;
@@ -2630,24 +2659,39 @@ int launch_small_rescan(const ScanParams &p, const FinishParams &f, bool u8, hip
 
 bool leaf_small_supported(int NB, int bits)
 {
-    return bits == 4 && (NB == 8 || NB == 13 || NB == 25 || NB == 32);
+    return bits == 4 || NB <= 64; // (8-bit codes: two workgroups' tables in a compute unit's LDS)
 }
 
 template <bool U8>
 static int launch_leaf_small_u(const ScanParams &p, const FinishParams &f, const LeafBlockList &list, bool rescan, hipStream_t st)
 {
     const dim3 grid = rescan ? dim3((unsigned)((p.R + 3) / 4), p.B) : dim3((unsigned)p.Lp, p.B);
-#define AVQ_LEAF_SMALL(N)                                                                                          \
-    case N:                                                                                                        \
-        if (rescan) hipLaunchKernelGGL((rescan_leaf_blocks_kernel<U8, N>), grid, dim3(256), 0, st, p, f, list);    \
-        else hipLaunchKernelGGL((leaf_block_max_kernel<U8, N>), grid, dim3(256), 0, st, p, list);                  \
-        break;
-    switch (p.NB) {
-        AVQ_LEAF_SMALL(8)
-        AVQ_LEAF_SMALL(13)
-        AVQ_LEAF_SMALL(25)
-        AVQ_LEAF_SMALL(32)
-    default: set_error("leaf block maxima: unsupported code size %d", p.NB); return AVQ_EINVAL;
+    const bool wide = p.bits == 8;
+    const size_t lds = wide ? (size_t)p.NB * 1024 : (size_t)2 * p.NB * 16 * (U8 ? 1 : 4);
+#define AVQ_LEAF_SMALL(N, W)                                                                                              \
+    do {                                                                                                                  \
+        if (W) {                                                                                                          \
+            static LdsLimitOnce once[2];                                                                                  \
+            AVQ_TRY(set_lds_limit((const void *)rescan_leaf_blocks_kernel<U8, N, W>, 64 * 1024, &once[0]));               \
+            AVQ_TRY(set_lds_limit((const void *)leaf_block_max_kernel<U8, N, W>, 64 * 1024, &once[1]));                   \
+        }                                                                                                                 \
+        if (rescan) hipLaunchKernelGGL((rescan_leaf_blocks_kernel<U8, N, W>), grid, dim3(256), lds, st, p, f, list);      \
+        else hipLaunchKernelGGL((leaf_block_max_kernel<U8, N, W>), grid, dim3(256), lds, st, p, list);                    \
+    } while (0)
+    if (wide) {
+        switch (p.NB) {
+        case 25: AVQ_LEAF_SMALL(25, true); break;
+        case 32: AVQ_LEAF_SMALL(32, true); break;
+        default: AVQ_LEAF_SMALL(0, true); break;
+        }
+    } else {
+        switch (p.NB) {
+        case 8: AVQ_LEAF_SMALL(8, false); break;
+        case 13: AVQ_LEAF_SMALL(13, false); break;
+        case 25: AVQ_LEAF_SMALL(25, false); break;
+        case 32: AVQ_LEAF_SMALL(32, false); break;
+        default: AVQ_LEAF_SMALL(0, false); break;
+        }
     }
 #undef AVQ_LEAF_SMALL
     AVQ_HIP(hipGetLastError());

@@ -1,0 +1,76 @@
+"""A few queries on partitioned indexes of any code size against the oracle: leaf selection, and the scan of the probed
+leaves by block maxima and by lists."""
+import numpy as np
+import pytest
+
+import oracle
+from util import unit_rows
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+avq = pytest.importorskip("paper_1908_10396_amd")
+
+
+def pack(codes, bits):
+    if bits == 8:
+        return codes
+    n, M = codes.shape
+    wide = np.zeros((n, M + M % 2), np.uint8)
+    wide[:, :M] = codes
+    return wide[:, 0::2] | (wide[:, 1::2] << 4)
+
+
+# code bytes below, at and above four and eight of them, an odd number of subspaces, large codes, 8-bit codes with and without a
+# kernel of their own, and more than those kernels' tables have room for (65: the list scan); leaves of several blocks
+@pytest.mark.parametrize("d,M,bits", [(6, 3, 4), (32, 16, 4), (64, 32, 4), (105, 35, 4), (192, 96, 4), (36, 9, 8), (50, 25, 8), (64, 32, 8),
+                                      (65, 65, 8)])
+@pytest.mark.parametrize("nq,k,R,L", [(1, 10, 100, 7), (5, 1, 0, 3), (3, 10, 512, 13)])
+@pytest.mark.parametrize("mode", [avq.LUT_F32, avq.LUT_U8])
+def test_few_queries_on_any_code_size(d, M, bits, nq, k, R, L, mode):
+    rng = np.random.default_rng([d, M, nq])
+    n, leaves = 6000, 13
+    x, q, cen = unit_rows(rng, n, d), unit_rows(rng, nq, d), unit_rows(rng, leaves, d)
+    cb = (rng.standard_normal((M, 1 << bits, d // M)) / np.sqrt(d)).astype(np.float32)
+    codes = rng.integers(0, 1 << bits, (n, M), dtype=np.uint8)
+    assign = rng.integers(0, leaves - 1, n).astype(np.int32)  # the last leaf is empty
+    assign[: 2000] = 4                                         # and one has several blocks
+    idx = avq.Index(d, M, bits, n_leaves=leaves)
+    idx.set_codebooks(cb)
+    idx.set_leaf_centers(cen)
+    idx.set_database(torch.from_numpy(x).cuda(), torch.from_numpy(pack(codes, bits)).cuda(), assign)
+    oi, os_ = oracle.search(x, cb, codes, bits, q, k, R, mode, centers=cen, assign=assign, leaves_to_search=L)
+    qd = torch.from_numpy(q).cuda()
+    for impl in (0, 1):  # 1: the list scan
+        idx.set_tuning("small_batch_impl", impl)
+        ids, sc = idx.search(qd, k, R, mode, L)
+        np.testing.assert_array_equal(ids.cpu().numpy(), oi, err_msg="small_batch_impl %d" % impl)
+        np.testing.assert_array_equal(sc.cpu().numpy(), os_, err_msg="small_batch_impl %d" % impl)
+
+
+# one leaf, as many as threads and one more, as many as the histogram's registers hold and more; equal scores (one bin), all but one
+# equal (a bin with more than there is room for), infinite ones
+@pytest.mark.parametrize("leaves", [1, 2, 1024, 1025, 8192, 8193])
+@pytest.mark.parametrize("law", ["unit", "equal", "one", "infinite"])
+def test_leaf_selection_of_few_queries(leaves, law):
+    rng = np.random.default_rng(leaves)
+    d = 8
+    cen, q = unit_rows(rng, leaves, d), unit_rows(rng, 2, d)
+    if law == "equal":
+        cen[:] = cen[0]
+    elif law == "one":
+        cen[:] = cen[0]
+        cen[leaves // 2] = 100.0 * q[0]
+    elif law == "infinite":
+        cen[:: 3] = 0.0
+        cen[:: 3, 0] = 3e38
+        q *= np.float32(80.0)
+    idx = avq.Index(d, 1, 4, n_leaves=leaves)
+    idx.set_leaf_centers(cen)
+    idx.set_codebooks(np.zeros((1, 16, d), np.float32))
+    for L in (1, min(leaves, 100), min(leaves, 512)):
+        ids, ip = idx.debug_leaf_select(torch.from_numpy(q).cuda(), L)
+        for qi in range(len(q)):
+            oi, oip = oracle.leaf_select(cen, q[qi], L)
+            np.testing.assert_array_equal(ids[qi].cpu().numpy(), oi)
+            np.testing.assert_array_equal(ip[qi].cpu().numpy(), oip)
