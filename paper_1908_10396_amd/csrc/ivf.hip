@@ -245,14 +245,16 @@ leaf_scores_kernel(const float *__restrict__ centers_t, int n_leaves, int d, con
 // The L best of a query's leaves, in order; one workgroup a query, bound by its chain of exchanges and barriers. The scores
 // are counted in bins of equal width between the smallest and the largest; what reaches the bin of the L-th best - L leaves and
 // the few that share the bin - is ranked by counting, several threads a leaf. Up to 8,192 leaves whose scores are finite and
-// spread over the bins; the others by wg_select_threshold, which narrows the range pass by pass (2,000 leaves, L = 100: 11.2 us
-// that way, 6.0 this).
+// spread over the bins (2,000 leaves, L = 100: 6.0 us; 11.2 with wg_select_threshold, which narrows the range pass by pass);
+// as many that are not - most of them in one bin, or not finite - find the L-th score, and the last leaf of that score, two
+// bits a round; more than 8,192 by wg_select_threshold.
 constexpr int kLeafBins = 1024, kLeafTop = 1024;
 __global__ void __launch_bounds__(1024)
 leaf_top_kernel(const u64 *__restrict__ keys, int n_leaves, int L, int32_t *__restrict__ leaf_ids, float *__restrict__ leaf_ip)
 {
     __shared__ union { WgSelectScratch sel; uint32_t hist[kLeafBins]; } u;
     __shared__ __align__(16) u64 top[kLeafTop + 64];
+    __shared__ u64 wave_cnt[2][16];
     __shared__ float wave_hi[16], wave_lo[16];
     __shared__ uint32_t wave_sum[16], n_top, edge;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = blockIdx.x;
@@ -331,9 +333,49 @@ leaf_top_kernel(const u64 *__restrict__ keys, int n_leaves, int L, int32_t *__re
         }
         __syncthreads();
     }
-    if (!fast) {
-        if (tid == 0) n_top = 0u;
+    if (!fast && n_leaves <= kPer * 1024) {
+        uint32_t ord[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) ord[i] = tid + i * 1024 < n_leaves ? key_ord(row[tid + i * 1024]) : 0u;
+        // how many leaves hold(i, c), for c = 1, 2 and 3: 16 bits each (one barrier; the sums of two rounds lie apart)
+        auto counts = [&](int round, auto hold) {
+            u64 s = 0ull;
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                if (i * 1024 >= n_leaves) continue;
+                const bool there = tid + i * 1024 < n_leaves;
+#pragma unroll
+                for (int c = 1; c < 4; ++c) s += (u64)__popcll(__ballot(there && hold(i, (uint32_t)c))) << (16 * (c - 1));
+            }
+            if (lane == 0) wave_cnt[round & 1][wave] = s;
+            __syncthreads();
+            s = wave_cnt[round & 1][lane & 15];
+#pragma unroll
+            for (int m = 8; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
+            return s;
+        };
+        auto of = [](u64 s, int c) { return (int)((s >> (16 * (c - 1))) & 0xffffu); };
+        uint32_t t = 0u; // the largest that `want` scores reach, two bits a round
+        int round = 0;
+        for (int sh = 30; sh >= 0; sh -= 2, ++round) {
+            const u64 s = counts(round, [&](int i, uint32_t c) { return ord[i] >= t + (c << sh); });
+            t += (uint32_t)(of(s, 3) >= want ? 3 : of(s, 2) >= want ? 2 : of(s, 1) >= want ? 1 : 0) << sh;
+        }
+        const int need = want - of(counts(round++, [&](int i, uint32_t) { return ord[i] > t; }), 1); // of the score t: the first
+        int last = 0; // the leaf that is the last of them: fewer than `need` lie before it
+        for (int sh = 12; sh >= 0; sh -= 2, ++round) {
+            const u64 s = counts(round, [&](int i, uint32_t c) { return ord[i] == t && tid + i * 1024 < last + ((int)c << sh); });
+            last += (of(s, 3) < need ? 3 : of(s, 2) < need ? 2 : of(s, 1) < need ? 1 : 0) << sh;
+        }
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int l = tid + i * 1024;
+            if (l < n_leaves && (ord[i] > t || (ord[i] == t && l <= last))) top[atomicAdd(&n_top, 1u)] = make_key(ord[i], l); // `want` of them
+        }
+        __syncthreads();
+    } else if (!fast) {
         const u64 t = wg_select_threshold(row, n_leaves, L, &u.sel);
+        if (tid == 0) n_top = 0u;
         __syncthreads();
         for (int i = tid; i < n_leaves; i += 1024) {
             const u64 key = row[i];
