@@ -1474,7 +1474,7 @@ static bool use_search_one(const avq_index *idx, int nq, int R, bool fuse_tables
 }
 
 // Launches only: no allocation, no synchronisation. timers: per-stage event pairs while profiling is on.
-// tile: the batch form (8-bit codes): the full scan takes the queries sixteen at a time, with 6-bit byte tables.
+// tile: the batch form (8-bit codes): the full scan takes the queries sixteen at a time, with byte tables of 8 or 7 bits (own_bits below).
 static int search_small(avq_index *idx, const float *queries, int nq, int k, int reorder_k, bool u8, bool fuse_tables,
                         const SmallWs &w, bool timers, int32_t *ids_out, float *scores_out, hipStream_t st, bool tile = false)
 {
