@@ -829,10 +829,7 @@ encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, cons
             typedef const __attribute__((address_space(3))) float lds_float;
             lds_float *src = (lds_float *)(tab_lds + (m * KC + j) * (DS + 1));
 #pragma unroll
-            for (int l = 0; l < DS; ++l) {
-                if (l == 2) asm volatile("" : "+v"(src)); // three words are not read as one (see build.py)
-                c[l] = src[l];
-            }
+            for (int l = 0; l < DS; ++l) c[l] = src[l];
         };
         // this point's (and its center's) coordinates of subspaces m .. m + kAhead - 1; nothing beyond the row
         auto load_rows = [&](int m, float (&xs)[kAhead * DS], float (&ces)[RES ? kAhead * DS : 1]) {

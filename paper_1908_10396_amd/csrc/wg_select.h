@@ -23,25 +23,11 @@ struct WgSelectScratch {
     u64 red_max[16], red_min[16];
     uint32_t red_cnt[16];
     uint32_t wave_sum[16];
-    u64 found;       // published by the thread that owns the bin of the wanted key, in ONE word: population of the bin
-                     // << 32 | keys above the bin << 11 | bin. As three adjacent 32-bit words (which the compiler stores
-                     // and loads with one 96-bit LDS access) a 16-wave workgroup returned a wrong threshold about once
-                     // in ten calls on MI355X; a second barrier before the loads, or words placed apart, removed that (the second
-                     // barrier is there as well now: below).
+    u64 found;       // published by the thread that owns the bin of the wanted key, in one word: population of the bin
+                     // << 32 | keys above the bin << 11 | bin
     uint32_t list_cnt;
     u64 result;
 };
-
-// The barrier between a word that one thread has just written and its reads by all waves: twice. With one, some waves of a 16-wave
-// workgroup went on with another `found` than the rest where a pass counts many keys into one bin (1,024 of 1,025 keys of one score:
-// 22 of 48 selections wrong; 8,192 of 8,193: 35). With two, or with s_nops around the one, none of 96 was; doubling each of the
-// other barriers instead left them wrong. The generated code waits for the store and then for the barrier; why that is not enough
-// is not known.
-__device__ __forceinline__ void wg_publish()
-{
-    __syncthreads();
-    __syncthreads();
-}
 
 // All threads of the workgroup (a multiple of 64, at most 1024) must call this.
 // for_each_key(fn) calls fn once for each of the thread's keys, the same ones every time; no key is 0.
@@ -87,7 +73,7 @@ __device__ __forceinline__ u64 wg_select_threshold_of(ForEachKey for_each_key, i
             for_each_key([&](u64 kkey) {
                 if (kkey >= lo && kkey <= hi) s->list[atomicAdd(&s->list_cnt, 1u)] = kkey;
             });
-            wg_publish();
+            __syncthreads();
             const uint32_t c = s->list_cnt;
             for (uint32_t j = tid; j < c; j += nt) {
                 const u64 mine = s->list[j];
@@ -96,11 +82,14 @@ __device__ __forceinline__ u64 wg_select_threshold_of(ForEachKey for_each_key, i
                 for (uint32_t t = 0; t < c; ++t) rank += s->list[t] > mine;
                 if (rank == need - 1) s->result = mine;
             }
-            wg_publish();
+            __syncthreads();
             return s->result;
         }
         const u64 width = hi - lo;
-        const int shift = width < (u64)kSelBins ? 0 : (64 - __builtin_clzll(width)) - 11;
+        // A scalar, as a 64-bit vector shift must not take its amount from the last vector register that the kernel has
+        // (build.py has the reason and refuses such code): in one that did, a wave now and then went on with an `hi` of
+        // its own, keys were counted into bins too high, and the key returned ranked up to 50 places too high.
+        const int shift = __builtin_amdgcn_readfirstlane(width < (u64)kSelBins ? 0 : (64 - __builtin_clzll(width)) - 11);
         __syncthreads();
         for (int b = tid; b < kSelBins; b += nt) s->hist[b] = 0u;
         __syncthreads();
@@ -132,7 +121,7 @@ __device__ __forceinline__ u64 wg_select_threshold_of(ForEachKey for_each_key, i
             if (above < need && need <= above + h) s->found = ((u64)h << 32) | (above << 11) | (uint32_t)b; // above < R <= 2^21
             above += h;
         }
-        wg_publish();
+        __syncthreads();
         const u64 found = s->found;
         const uint32_t fb = (uint32_t)found & (uint32_t)(kSelBins - 1);
         need -= ((uint32_t)found >> 11);

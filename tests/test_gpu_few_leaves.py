@@ -55,9 +55,6 @@ def test_few_queries_on_any_code_size(d, M, bits, nq, k, R, L, mode):
 @pytest.mark.parametrize("leaves", [1, 2, 1024, 1025, 8192, 8193])
 @pytest.mark.parametrize("law", ["unit", "equal", "one", "infinite"])
 def test_leaf_selection_of_few_queries(leaves, law):
-    if leaves > 8192 and law in ("one", "infinite"):
-        pytest.skip("the selection by narrowing ranges, which serves more than 8,192 leaves, loses leaves now and then where "
-                    "thousands of them share a score; cause not known")
     rng = np.random.default_rng(leaves)
     d = 8
     cen, q = unit_rows(rng, leaves, d), unit_rows(rng, 2, d)
@@ -73,9 +70,11 @@ def test_leaf_selection_of_few_queries(leaves, law):
     idx = avq.Index(d, 1, 4, n_leaves=leaves)
     idx.set_leaf_centers(cen)
     idx.set_codebooks(np.zeros((1, 16, d), np.float32))
+    qd = torch.from_numpy(q).cuda()
     for L in (1, min(leaves, 100), min(leaves, 512)):
-        ids, ip = idx.debug_leaf_select(torch.from_numpy(q).cuda(), L)
-        for qi in range(len(q)):
-            oi, oip = oracle.leaf_select(cen, q[qi], L)
-            np.testing.assert_array_equal(ids[qi].cpu().numpy(), oi)
-            np.testing.assert_array_equal(ip[qi].cpu().numpy(), oip)
+        right = [oracle.leaf_select(cen, q[qi], L) for qi in range(len(q))]
+        for _ in range(8):  # (a selection that goes wrong does so now and then)
+            ids, ip = idx.debug_leaf_select(qd, L)
+            for qi, (oi, oip) in enumerate(right):
+                np.testing.assert_array_equal(ids[qi].cpu().numpy(), oi)
+                np.testing.assert_array_equal(ip[qi].cpu().numpy(), oip)
