@@ -1617,7 +1617,8 @@ constexpr int kLeafSmallMaxQueries = 80;
 static bool use_leaf_small(const avq_index *idx, int nq, int L, int R)
 {
     const int max_q = idx->tune_small_batch >= 0 ? std::min(idx->tune_small_batch, 4096) : kLeafSmallMaxQueries;
-    if (idx->cfg.n_leaves == 0 || idx->tune_small_impl == 1 || nq > max_q || L > 512 || !leaf_small_supported(idx->NB, idx->cfg.bits)) return false;
+    if (idx->cfg.n_leaves == 0 || idx->tune_small_impl == 1 || nq > max_q || L > 512 || !leaf_small_supported(idx->NB, idx->cfg.bits) ||
+        !leaf_select_few_supported(idx->cfg.d)) return false;
     if (idx->tune_small_batch >= 0) return true;
     const bool own = idx->cfg.bits == 4 && block_bound_supported(idx->NB, 4);
     const double listed = (double)L * (double)idx->n_blocks / idx->cfg.n_leaves; // blocks of a query's leaves

@@ -484,7 +484,8 @@ int group_by_leaf_prepare(int nq, int Lp, int n_leaves, uint32_t *ws, LeafGroups
 int group_by_leaf_lay_out(int nq, int Lp, int n_leaves, uint32_t *ws, LeafGroups *g);
 int launch_group_by_leaf(const int32_t *leaf_ids, int nq, int Lp, int n_leaves, const LeafGroups &g, hipStream_t st);
 // The same selection for a handful of queries (L <= 512): scores by many small workgroups into keys[nq][n_leaves]
-// (scratch), then the L best per query.
+// (scratch), then the L best per query. Up to 15,360 dimensions.
+bool leaf_select_few_supported(int d);
 int launch_leaf_select_few(const float *centers_t, int n_leaves, int d, const float *queries, int nq, int L, u64 *keys,
                            int32_t *leaf_ids, float *leaf_ip, hipStream_t st);
 // leaf_cnt (optional): leaf_cnt[leaf * cnt_stride] is incremented once per selected (query, leaf) pair; leaf_pos

@@ -407,10 +407,12 @@ leaf_top_kernel(const u64 *__restrict__ keys, int n_leaves, int L, int32_t *__re
     }
 }
 
+bool leaf_select_few_supported(int d) { return (size_t)d * 4 <= 60 * 1024; } // a query in LDS
+
 int launch_leaf_select_few(const float *centers_t, int n_leaves, int d, const float *queries, int nq, int L, u64 *keys,
                            int32_t *leaf_ids, float *leaf_ip, hipStream_t st)
 {
-    if (L < 1 || L > 512 || nq < 1 || n_leaves < 1 || (size_t)d * 4 > 60 * 1024 || !keys) {
+    if (L < 1 || L > 512 || nq < 1 || n_leaves < 1 || !leaf_select_few_supported(d) || !keys) {
         set_error("leaf select: bad arguments (L = %d)", L);
         return AVQ_EINVAL;
     }

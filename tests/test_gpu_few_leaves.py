@@ -78,3 +78,23 @@ def test_leaf_selection_of_few_queries(leaves, law):
             for qi, (oi, oip) in enumerate(right):
                 np.testing.assert_array_equal(ids[qi].cpu().numpy(), oi)
                 np.testing.assert_array_equal(ip[qi].cpu().numpy(), oip)
+
+
+# dimensions of which a query fits the LDS of the kernel that scores leaves for a few queries, and more: the list scan's selection
+@pytest.mark.parametrize("d", [15_360, 15_488])
+@pytest.mark.parametrize("M,bits", [(16, 4), (32, 4), (16, 8)])
+def test_few_queries_of_many_dimensions(d, M, bits):
+    rng = np.random.default_rng([d, M])
+    n, nq, k, R, leaves, L = 300, 2, 10, 40, 5, 3
+    x, q, cen = unit_rows(rng, n, d), unit_rows(rng, nq, d), unit_rows(rng, leaves, d)
+    cb = (rng.standard_normal((M, 1 << bits, d // M)) / np.sqrt(d)).astype(np.float32)
+    codes = rng.integers(0, 1 << bits, (n, M), dtype=np.uint8)
+    assign = rng.integers(0, leaves, n).astype(np.int32)
+    idx = avq.Index(d, M, bits, n_leaves=leaves)
+    idx.set_codebooks(cb)
+    idx.set_leaf_centers(cen)
+    idx.set_database(torch.from_numpy(x).cuda(), torch.from_numpy(pack(codes, bits)).cuda(), assign)
+    oi, os_ = oracle.search(x, cb, codes, bits, q, k, R, avq.LUT_F32, centers=cen, assign=assign, leaves_to_search=L)
+    ids, sc = idx.search(torch.from_numpy(q).cuda(), k, R, avq.LUT_F32, L)
+    np.testing.assert_array_equal(ids.cpu().numpy(), oi)
+    np.testing.assert_array_equal(sc.cpu().numpy(), os_)
