@@ -378,9 +378,10 @@ double avq_eta(int32_t d, double T, double norm, int32_t eta_mode);
  * one block of 256 points per wave; built in: 2 when the code array exceeds
  * 256 MB, the Infinity Cache, and the call has one or two queries, or up to
  * eight over more than 1 GiB of codes; else 1), "scratch_limit_kb" (the most
- * scratch avq_train, avq_encode, avq_brute_force and the matrix product of avq_search
- * may take for what speeds them up, in units of 1,024 bytes; 0 = built in: 256 MB kept
- * between calls, exact search as much as the points themselves, the product 4 GiB;
+ * scratch avq_train, avq_encode, avq_brute_force and the matrix product of avq_search, or
+ * its few queries on a partitioned index, may take for what speeds them up, in units of
+ * 1,024 bytes; 0 = built in: 256 MB kept between calls, exact search as much as the points
+ * themselves, the product 4 GiB, few queries what they need;
  * where more is asked for than the limit or the device has, they take the subspaces or
  * queries in smaller groups, or the kernels that need none or less).
  * Results never depend on these (dictionaries and centers to the rounding of the

@@ -1626,6 +1626,8 @@ static bool use_leaf_small(const avq_index *idx, int nq, int L, int R)
     return R <= 200 || nq * listed <= 20000.0 || (nq <= 64 && (own || idx->cfg.bits == 8 || idx->NB >= 24));
 }
 
+// AVQ_ENOMEM, with nothing launched, where there is no room for the scratch: 2 KB a result and query, for the points of the
+// listed blocks (64 queries, 512 results: 67 MB), and 16 bytes a block and query.
 static int search_leaves_small(avq_index *idx, const float *queries, int nq, int k, int reorder_k, int R, int L, bool u8,
                                int32_t *ids_out, float *scores_out, hipStream_t st)
 {
@@ -1644,6 +1646,7 @@ static int search_leaves_small(avq_index *idx, const float *queries, int nq, int
                  o_n = take(sizeof(uint32_t) * (size_t)nq), o_sel = take(sizeof(int32_t) * (size_t)nq * R),
                  o_meta = take(sizeof(SmallMeta) * (size_t)nq), o_cand = take(sizeof(u64) * (size_t)nq * 256 * R),
                  o_keys = take(sizeof(u64) * (size_t)nq * c.n_leaves);
+    if (idx->product.limit != 0 && off > idx->product.limit) { set_error("%zu bytes of scratch exceed the limit", off); return AVQ_ENOMEM; }
     AVQ_TRY(idx->tmp.reserve(off));
     unsigned char *base = (unsigned char *)idx->tmp.p;
     AVQ_TRY(idx->leaf_ids.reserve(sizeof(int32_t) * (size_t)nq * L));
@@ -1763,8 +1766,10 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
         if (rc != AVQ_ENOMEM) return rc;
     }
     const bool grouped = ivf && use_grouped_leaves(idx, nq, leaves_to_search, R);
-    if (ivf && use_leaf_small(idx, nq, leaves_to_search, R))
-        return search_leaves_small(idx, queries, nq, k, reorder_k, R, leaves_to_search, u8, ids_out, scores_out, st);
+    if (ivf && use_leaf_small(idx, nq, leaves_to_search, R)) {
+        const int rc = search_leaves_small(idx, queries, nq, k, reorder_k, R, leaves_to_search, u8, ids_out, scores_out, st);
+        if (rc != AVQ_ENOMEM) return rc; // the list scan needs less
+    }
     if (small && idx->tune_small_impl != 1) {
         SmallWs w;
         AVQ_TRY(small_ws_from_index(idx, nq, R, &w));

@@ -98,3 +98,30 @@ def test_few_queries_of_many_dimensions(d, M, bits):
     ids, sc = idx.search(torch.from_numpy(q).cuda(), k, R, avq.LUT_F32, L)
     np.testing.assert_array_equal(ids.cpu().numpy(), oi)
     np.testing.assert_array_equal(sc.cpu().numpy(), os_)
+
+
+# 67 MB of scratch are asked for; where they are not to be had, the list scan answers, for a tenth of that
+@pytest.mark.parametrize("bits", [4, 8])
+def test_few_queries_within_a_scratch_limit(bits):
+    rng = np.random.default_rng(bits)
+    n, d, M, nq, k, R, leaves, L = 6000, 50, 25, 64, 10, 512, 13, 5
+    x, q, cen = unit_rows(rng, n, d), unit_rows(rng, nq, d), unit_rows(rng, leaves, d)
+    cb = (rng.standard_normal((M, 1 << bits, d // M)) / np.sqrt(d)).astype(np.float32)
+    codes = rng.integers(0, 1 << bits, (n, M), dtype=np.uint8)
+    assign = rng.integers(0, leaves, n).astype(np.int32)
+    idx = avq.Index(d, M, bits, n_leaves=leaves)
+    idx.set_codebooks(cb)
+    idx.set_leaf_centers(cen)
+    idx.set_database(torch.from_numpy(x).cuda(), torch.from_numpy(pack(codes, bits)).cuda(), assign)
+    oi, os_ = oracle.search(x, cb, codes, bits, q, k, R, avq.LUT_F32, centers=cen, assign=assign, leaves_to_search=L)
+    qd = torch.from_numpy(q).cuda()
+    idx.set_tuning("scan_product", 1)  # not the path of batches, whatever it costs
+    taken = []
+    for limit_kb in (1024, 0, 1024):
+        idx.set_tuning("scratch_limit_kb", limit_kb)
+        free = torch.cuda.mem_get_info()[0]
+        ids, sc = idx.search(qd, k, R, avq.LUT_F32, L)
+        taken.append(free - torch.cuda.mem_get_info()[0])
+        np.testing.assert_array_equal(ids.cpu().numpy(), oi, err_msg="limit %d KB" % limit_kb)
+        np.testing.assert_array_equal(sc.cpu().numpy(), os_, err_msg="limit %d KB" % limit_kb)
+    assert taken[0] < 32 << 20 < 64 << 20 < taken[1], taken
