@@ -365,7 +365,7 @@ exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *
                     int32_t *__restrict__ ids_out, float *__restrict__ scores_out)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ uint32_t hist[kExactBins], wave_sum[kExactThreads / 64], found[2];
+    __shared__ __align__(16) uint32_t hist[kExactBins], wave_sum[kExactThreads / 64], found[2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = blockIdx.x;
     if ((need[0] | need[1 + q]) != 0u) return;
     constexpr int nw = kExactThreads / 64;
