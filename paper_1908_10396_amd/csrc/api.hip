@@ -795,22 +795,39 @@ static int search_through_candidates(avq_index *idx, const float *queries, int n
                            idx->scale.as<float>(), idx->bias.as<float>(), ids_out, scores_out, st);
 }
 
-// Queries on 8-bit codes one by one, or sixteen to a scan (us a call). Measured, one by one / sixteen to a scan, 25 bytes,
-// R = 100, fp32 tables: 200,000 points, 16 queries 59 / 63, 32 82 / 75; 500,000, 8 54 / 56, 16 72 / 63, 32 109 / 78; 1,183,514, 4
-// 55 / 60, 6 71 / 62, 16 110 / 71, 32 177 / 100; 5,000,000, 2 79 / 102, 4 110 / 110, 16 289 / 127, 64 1,016 / 341; 32 bytes,
-// 2,000,000, 4 80 / 85, 8 112 / 88, 64 580 / 256.
+// What a call on 8-bit codes takes (us): queries one by one, sixteen to a scan, or through the product of the queries with the
+// decoded points. Fitted to 3,132 calls: 2,000 to 10,000,000 points of 8, 13, 25 and 32 code bytes (32 to 256 dimensions), 1 to 1,000
+// queries, 1 to 500 results, tables of either kind; the forms chosen by these lines take 1.012 (up to 32 queries) and 1.008 times as
+// long as the best ones in the mean. Measured, one by one / sixteen to a scan, 25 bytes, R = 100, fp32 tables: 200,000 points, 16
+// queries 59 / 63, 32 82 / 75; 500,000, 8 54 / 56, 16 72 / 63, 32 109 / 78; 1,183,514, 4 55 / 60, 6 71 / 62, 16 110 / 71, 32 177 / 100;
+// 5,000,000, 2 79 / 102, 4 110 / 110, 16 289 / 127, 64 1,016 / 341; 256 dimensions in 32 bytes, 2,000,000, 4 80 / 85, 8 112 / 88, 64
+// 580 / 256; 250,000, 16 68 / 73. Sixteen to a scan / product: 2,000 points, 150 queries 66 / 113, 300 96 / 116, 1,000 170 / 126; 16,000,
+// 48 100 / 95, 150 147 / 95; 600,000, 80 137 / 123; R = 500: 4,000, 300 133 / 198; 16,000, 80 132 / 178, 150 162 / 185.
+static double listed_blocks(const avq_index *idx, int R) { return (double)std::min<int64_t>(R, 2 * idx->n_blocks); }
 static double per_query_us(const avq_index *idx, int R) // blocks listed, scored and ranked
 {
-    const double listed = (double)std::min<int64_t>(R, 2 * idx->n_blocks);
+    const double listed = listed_blocks(idx, R);
     return 0.25 + 0.005 * std::min(100.0, listed) + 0.009 * std::max(0.0, listed - 100.0);
 }
 static double single_us(const avq_index *idx, int nq, int R)
 {
     return 35.0 + nq * (0.1 + per_query_us(idx, R) + 3.3e-5 * idx->NB * (double)idx->n_blocks);
 }
-static double tile_us(const avq_index *idx, int nq, int R)
+static double tile_us(const avq_index *idx, int nq, int R, bool u8)
 {
-    return 45.0 + 1.28e-4 * idx->NB * (double)idx->n_blocks * ((nq + 15) / 16) + nq * (per_query_us(idx, R) + (idx->n_blocks < 4000 ? 0.1 : 0.0));
+    const double q = nq, d = idx->cfg.d, r = R, blocks = (double)idx->n_blocks, tiles = (nq + 15) / 16, codes = idx->NB * blocks;
+    if (nq <= 32) { // the launches' latencies, for the most part
+        const double rows = u8 || blocks <= 4000.0 ? 0.0 : 0.006 * std::max(0.0, listed_blocks(idx, R) - 100.0);
+        return 45.0 + 0.03 * std::max(0.0, d - 100.0) + 1.28e-4 * codes * tiles + q * (per_query_us(idx, R) + (blocks < 4000.0 ? 0.1 : 0.0) + rows);
+    }
+    const double listed = std::min(r, blocks), all = r >= 0.9 * blocks ? listed : 0.0; // all: every block of the index is listed
+    return 21.0 + 0.28 * d + 1.26e-4 * codes * tiles + 0.11 * listed + 0.57 * all + q * (0.126 + 0.0033 * listed + 0.0021 * all);
+}
+static double product8_us(const avq_index *idx, int nq, int R, bool u8)
+{
+    const double n = (double)idx->n, q = nq, d = idx->cfg.d, r = R;
+    return 44.0 + 0.32 * d + 0.133 * r + 0.108 * std::max(0.0, r - 200.0) + 5.1e-7 * std::max(0.0, n - 3e5) * d + q * (0.038 + 0.0002 * r) +
+           1.95e-9 * n * q * d + (u8 ? 17.0 + 0.11 * d : 0.0);
 }
 
 // Batches on a flat index through the product of the queries with the decoded points (product.hip), where it is expected to
@@ -823,8 +840,7 @@ static double tile_us(const avq_index *idx, int nq, int R)
 //  4-bit codes, 8-bit tables, whose rounding lets through several times R: 1,000,000 points 168 / 150 (64), 1,560 / 1,089;
 //    64,000 points 131 / 104 (256), 308 / 324 (4,096); R = 500: 200,000 points 790 / 1,078, 1,000,000 1,904 / 1,803.
 //  code sizes without matrix-core kernels (192 dimensions, 96 subspaces): 1,000,000 points 360 / 264 (32), 12,877 / 1,788.
-//  8-bit codes: 4,000 points 70 / 92 (64), 103 / 94 (256), 844 / 249; 1,000,000 points 155 / 126 (32), 203 / 129, 5,369 / 976;
-//    256 dimensions, R = 10: 1,000,000 points 210 / 399 (64, mostly the decoding), 398 / 410 (256), 1,406 / 679.
+//  8-bit codes: product8_us and the lines above it.
 //  and where the other batch path cannot guess its bounds (guessed false: 20,000 points, R = 100) 151 / 98 (256), 718 / 196.
 static bool use_product(const avq_index *idx, int nq, int R, bool u8, int few_max, bool guessed)
 {
@@ -836,14 +852,13 @@ static bool use_product(const avq_index *idx, int nq, int R, bool u8, int few_ma
         idx->tune_sample || idx->tune_small_impl || idx->tune_bound_bits || idx->tune_small_batch >= 0) return false;
     if (nq < 16) return false;
     const double n = (double)idx->n, q = (double)nq, d = (double)c.d, r = (double)R;
-    const double decode = std::max(0.0, n - 3e5) * d * (c.bits == 8 ? (d > 128 ? 5.0e-7 : 5.6e-7) : (d > 128 ? 6e-7 : 4.8e-7));
-    double product = 30.0 + 0.35 * d + 0.14 * r + decode + q * (0.02 + 0.00018 * r) + 1.6e-9 * n * q * d;
     const double few = 20.0 + q * (0.1 + 0.000037 * idx->NB * (double)idx->n_blocks + (guessed ? 0.001 : 0.002) * r);
     if (c.bits == 8) {
         if (!block_bound_supported(idx->NB, c.bits)) return true; // plain scans: 400 us and more
-        product += 0.12 * d + (u8 ? 4.0 + 0.12 * d + 0.1 * std::max(0.0, r - 100.0) : 0.0);
-        return product < (nq > few_max ? (u8 ? 0.93 : 1.0) * tile_us(idx, nq, R) : few);
+        return product8_us(idx, nq, R, u8) < (nq > few_max ? tile_us(idx, nq, R, u8) : few);
     }
+    const double decode = std::max(0.0, n - 3e5) * d * (d > 128 ? 6e-7 : 4.8e-7);
+    double product = 30.0 + 0.35 * d + 0.14 * r + decode + q * (0.02 + 0.00018 * r) + 1.6e-9 * n * q * d;
     const bool own = scan_mfma_supported(idx->NB, c.bits);
     if (u8) product += 12.0;
     if (idx->n <= 16384) {
@@ -1749,7 +1764,7 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
     if (c.bits == 8 && block_bound_supported(idx->NB, c.bits) && idx->tune_small_impl == 0)
         // (more than 200 results: as measured at first, 24 queries at 1.2 million points, two in any case)
         small_max = R > 200 ? (int)std::min<int64_t>(32, std::max<int64_t>(2, 120000 / std::max<int64_t>(1, idx->n_blocks)))
-                            : nq <= 2 || (nq <= 32 && single_us(idx, nq, R) <= tile_us(idx, nq, R)) ? nq : 0;
+                            : nq <= 2 || (nq <= 32 && single_us(idx, nq, R) <= tile_us(idx, nq, R, u8)) ? nq : 0;
     if (idx->tune_small_batch >= 0) small_max = idx->tune_small_batch;
     const bool product = use_product(idx, nq, R, u8, small_max, guessed);
     const bool small = !ivf && !product && nq <= small_max;
@@ -1785,7 +1800,7 @@ extern "C" int avq_search(avq_index *idx, const float *queries, int32_t nq, int3
         if (rc != AVQ_ENOMEM) return rc;
     }
     // Batches of 8-bit codes on a flat index: the same search through block bounds, the full scan taking the queries
-    // sixteen at a time (byte tables of six bits); "scan_prefilter" = 1 scores every point instead
+    // sixteen at a time (byte tables of eight or seven bits); "scan_prefilter" = 1 scores every point instead
     if (!ivf && !small && c.bits == 8 && idx->tune_prefilter != 1 && small_uses_bounds(idx)) {
         SmallWs w;
         AVQ_TRY(small_ws_from_index(idx, nq, R, &w));

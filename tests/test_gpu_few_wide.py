@@ -34,3 +34,17 @@ def test_queries_sixteen_to_a_scan(n, d, M, nq, k, R, mode):
         what = "small_batch_max %d, bound_bits %d" % (most_by_themselves, bits)
         np.testing.assert_array_equal(ids.cpu().numpy(), oi, err_msg=what)
         np.testing.assert_array_equal(sc.cpu().numpy(), os_, err_msg=what)
+
+
+# which of the two forms answers a batch, where one takes half as long again as the other: few blocks and not many queries sixteen
+# to a scan, else the product with the decoded points, the only one of them that takes a sample
+@pytest.mark.parametrize("n,d,M,nq,R,product", [(2000, 32, 8, 80, 200, False), (2000, 100, 25, 150, 100, False), (4000, 100, 25, 300, 500, False),
+                                                (16_000, 100, 25, 150, 100, True), (40_000, 100, 25, 80, 200, True)])
+def test_form_of_a_batch(n, d, M, nq, R, product):
+    rng = np.random.default_rng(n)
+    idx = avq.Index(d, M, 8)
+    idx.set_codebooks(rng.standard_normal((M, 256, d // M)).astype(np.float32))
+    idx.set_database(torch.from_numpy(unit_rows(rng, n, d)).cuda(), torch.from_numpy(rng.integers(0, 256, (n, M), dtype=np.uint8)).cuda())
+    idx.profile_enable()
+    idx.search(torch.from_numpy(unit_rows(rng, nq, d)).cuda(), 10, R, avq.LUT_F32)
+    assert (idx.profile_read()["sample"][1] > 0) == product
