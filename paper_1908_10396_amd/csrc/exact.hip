@@ -83,16 +83,16 @@ exact_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, v
 // column tiles than 8 steps would spill in the loop: one column tile. best[q][block of 64]: the workgroup's eight maxima of a
 // query leave as 32 adjacent bytes. xnorm[block] = largest norm and conversion error of its points, xnorm8 of the workgroup's.
 //
-// PAIR (97 to 112 dimensions): as many registers as let two workgroups share a compute unit, so that one's products go on
-// while the other reads its rows, and these come through LDS, sixteen a wave at a time, as one run of memory; an array
-// beyond the Infinity Cache is read past the caches, at 6 TB/s. Else a lane reads its points' coordinates itself, NS steps
-// ahead; past the caches that is slow, as it takes 32 bytes of a line at a time (1,183,514 x 100, one query: 211 us for the
-// product against 128).
+// A lane reads its points' coordinates itself, some steps ahead, four words a load whatever the row's alignment. PAIR (65 to 112
+// dimensions): as many registers as let two workgroups share a compute unit, so that one's products go on while the other
+// reads its rows, and these come through LDS, sixteen a wave at a time, as one run of memory, which reads each line once and
+// whole; an array beyond the Infinity Cache is read past the caches, at 6 TB/s (1,183,514 x 100, one query: 211 us for the
+// product with each lane its own rows and two workgroups, 129 with one, 111 this way).
 // Bound by the reading of x, then the tiles (5.6 us each, 4.1 of matrix instructions at the 2.0 GHz that they leave). Product
 // alone, 1,183,514 x 100, 1,024 queries: 310 us with a load waited for at a row's every step and the staged tile waited for
-// before each tile's first operand, 270 now; one query 137 / 111. One workgroup a compute unit, each lane its own rows:
-// 129 for one query. (32 to 48 dimensions, millions of points and a few queries: up to 6% more than before, 3,000,000 x 32,
-// one query 120 / 127 us a call; 300 queries 250 / 205.)
+// before each tile's first operand, 270 now. Rows that are no whole quads word by word / four words a load, us a call, one query:
+// 1,200,000 x 33 122 / 77, 400,000 x 97 139 / 89, 3,000,000 x 113 1,004 / 485, x 129 1,148 / 643. How many steps ahead makes
+// little difference: 3,000,000 x 48, one query, 1 / 2 / 4 / 6 / all twelve: 172 / 177 / 166 / 165 / 166.
 template <int NS, int CT, bool PAIR>
 __global__ void __launch_bounds__(512, PAIR ? 4 : 2)
 exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *__restrict__ packed, int n_tiles, int nq,
@@ -200,52 +200,89 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
             }
             end_of_points(c);
         }
-    } else if (quad) {
-        // a step's eight coordinates of a lane's point, those of kAsk steps asked for before they are used (without a branch
-        // between them: one for the row's end had each wait for the one before)
-        constexpr int kAsk = NS > 12 ? 12 : NS == 2 ? CT * NS : NS == 3 ? 2 : NS;
+    } else if (NS == 7 && quad) {
+        // as below, but a row's last words are left out by a choice rather than a branch (400,000 x 72, 64 queries: 79.5 us a call, 83
+        // as below; 96 dimensions 88.6 / 89.9; other numbers of steps gain from the latter: 3,000,000 x 128, one query 402 / 386)
         const float *row[CT];
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             const int64_t i = p0 + c * 32 + j;
             row[c] = x + (size_t)(i < n ? i : n - 1) * d; // padding points are copies of the last one
         }
-        float4 raw[kAsk][2];
+        float4 raw[NS][2];
         auto ask = [&](int e) __attribute__((always_inline)) {
             const int l = 16 * (e % NS) + 4 * h; // (beyond the row: its start, not used)
-            raw[e % kAsk][0] = *(const float4 *)(row[e / NS] + (l < d ? l : 0));
-            raw[e % kAsk][1] = *(const float4 *)(row[e / NS] + (l + 8 < d ? l + 8 : 0));
+            raw[e % NS][0] = *(const float4 *)(row[e / NS] + (l < d ? l : 0));
+            raw[e % NS][1] = *(const float4 *)(row[e / NS] + (l + 8 < d ? l + 8 : 0));
         };
 #pragma unroll
-        for (int e = 0; e < kAsk; ++e) ask(e);
+        for (int e = 0; e < NS; ++e) ask(e);
 #pragma unroll
         for (int e = 0; e < CT * NS; ++e) {
-            const float4 u = raw[e % kAsk][0], w = raw[e % kAsk][1];
+            const float4 u = raw[e % NS][0], w = raw[e % NS][1];
             const int l = 16 * (e % NS) + 4 * h;
             const bool in0 = l < d, in1 = l + 8 < d;
             const float v[8] = {in0 ? u.x : 0.0f, in0 ? u.y : 0.0f, in0 ? u.z : 0.0f, in0 ? u.w : 0.0f,
                                 in1 ? w.x : 0.0f, in1 ? w.y : 0.0f, in1 ? w.z : 0.0f, in1 ? w.w : 0.0f};
             operand(e / NS, e % NS, v);
+            if (e + NS < CT * NS) ask(e + NS);
+            __builtin_amdgcn_sched_barrier(0);
+            if (e % NS == NS - 1) end_of_points(e / NS);
+        }
+    } else if (d >= 4) {
+        // A step's eight coordinates of a lane's point, those of kAsk steps asked for before they are used (without a branch
+        // between them: one for the row's end had each wait for the one before). Four words are one load, at any word's
+        // alignment; where a row's end lies within them, the row's last four are read and moved down.
+        constexpr int kAsk = CT * NS < 6 ? CT * NS : 6;
+        const float *row[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const int64_t i = p0 + c * 32 + j;
+            row[c] = x + (size_t)(i < n ? i : n - 1) * d; // padding points are copies of the last one
+        }
+        float raw[kAsk][2][4];
+        auto ask = [&](int e) __attribute__((always_inline)) {
+            const int l = 16 * (e % NS) + 4 * h;
+            __builtin_memcpy(raw[e % kAsk][0], row[e / NS] + (l < d - 4 ? l : d - 4), 16);
+            __builtin_memcpy(raw[e % kAsk][1], row[e / NS] + (l + 8 < d - 4 ? l + 8 : d - 4), 16);
+        };
+#pragma unroll
+        for (int e = 0; e < kAsk; ++e) ask(e);
+#pragma unroll
+        for (int e = 0; e < CT * NS; ++e) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = raw[e % kAsk][u / 4][u % 4];
+            if (16 * (e % NS) + 16 > d) { // the row's end
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    const int l = 16 * (e % NS) + 4 * h + 8 * g, by = l + 4 - d; // by: words beyond the end
+                    const float w[4] = {v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+                    v[4 * g] = by <= 0 ? w[0] : by == 1 ? w[1] : by == 2 ? w[2] : by == 3 ? w[3] : 0.0f;
+                    v[4 * g + 1] = by <= 0 ? w[1] : by == 1 ? w[2] : by == 2 ? w[3] : 0.0f;
+                    v[4 * g + 2] = by <= 0 ? w[2] : by == 1 ? w[3] : 0.0f;
+                    v[4 * g + 3] = by <= 0 ? w[3] : 0.0f;
+                }
+            }
+            operand(e / NS, e % NS, v);
             if (e + kAsk < CT * NS) ask(e + kAsk);
             __builtin_amdgcn_sched_barrier(0);
             if (e % NS == NS - 1) end_of_points(e / NS);
         }
-    } else {
+    } else { // two or three dimensions
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             const int64_t i = p0 + c * 32 + j;
             const float *row = x + (size_t)(i < n ? i : n - 1) * d;
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                float v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int l = 16 * s + 4 * h + (u & 3) + 2 * (u & 4);
-                    v[u] = row[l < d ? l : 0];
-                    v[u] = l < d ? v[u] : 0.0f;
+                float v[8] = {};
+                if (s == 0 && h == 0) {
+                    v[0] = row[0];
+                    v[1] = row[1];
+                    v[2] = d == 3 ? row[2] : 0.0f;
                 }
                 operand(c, s, v);
-                __builtin_amdgcn_sched_barrier(0); // (all loads first would spill)
             }
             end_of_points(c);
         }

@@ -63,6 +63,13 @@ def test_exact_search_with_rows_through_lds(n, d, nq, shift):
     np.testing.assert_array_equal(sc.cpu().numpy(), os_)
 
 
+# the end of a row within a load of four words, before it and at it, in every number of steps; the last row is the array's end
+@pytest.mark.parametrize("d", [4, 5, 6, 7, 15, 17, 31, 34, 47, 49, 51, 63, 66, 99, 111, 114, 127, 130, 131, 191, 195, 253, 255])
+def test_exact_search_of_rows_that_are_no_whole_quads(d):
+    rng = np.random.default_rng(d)
+    check(unit_rows(rng, 3001, d), unit_rows(rng, 40, d), 10)
+
+
 # as many results as classes of blocks can tell apart, and more; values that many blocks share
 @pytest.mark.parametrize("n,nq,k", [(30_000, 20, 1), (30_000, 300, 15), (30_000, 20, 16), (30_000, 20, 17), (40_000, 20, 128),
                                     (40_000, 260, 128), (40_000, 260, 129), (80_000, 20, 257)])
