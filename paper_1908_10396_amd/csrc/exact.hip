@@ -383,15 +383,17 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
 
 // One workgroup per query. theta: the blocks are dealt to C classes, C a power of two from 8 k on, and theta is the k-th
 // largest of the classes' a - E, each that of the class's largest a: a few of the k best may share a class, which only lowers
-// theta a little, and a is read once, without the norms. (More results than a quarter of the threads: two histogram passes
-// over the ordering values of all a - E, 22 high bits, rounded down.) Then the blocks that reach theta as a list - against
-// the largest E of eight blocks first, so that few norms are read -, a wave per block and a lane per point, fp32 chain, wave
-// lists. There are at least 4 k blocks (exact_supported). More than max_listed (at most kExactBins) blocks: need[1 + q] is set
-// and the plain kernel answers.
+// theta a little, and a is read once, without the norms. Where that takes more than 256 classes, two histogram passes over the
+// ordering values (22 high bits, rounded down) of each thread's two largest blocks; for more results than a quarter of the
+// threads, of all blocks. Then the blocks that reach theta as a list - against the largest E of eight blocks first, so that few
+// norms are read -, a wave per block and a lane per point, fp32 chain, wave lists. There are at least 4 k blocks
+// (exact_supported). More than max_listed (at most kExactBins) blocks: need[1 + q] is set and the plain kernel answers.
 // Bound by what it reads: some fifteen blocks of 25 KB a query at the size above, and a twice (150 KB); 0.13 to 0.15 ms for 1,000
-// queries, 0.20 with the norms of all blocks read three times. Measured and dropped: the rows through LDS as one run of
-// memory (0.13 at k = 10, but 427 us instead of 286 for the search of 300,000 x 64, 600 queries, k = 100), sixteen loads of a
-// lane at once (more registers: 1.31 ms instead of 1.15 at k = 100).
+// queries, 0.20 with the norms of all blocks read three times. One query on 3,000,000 x 32 points: 47 us with the threads of a
+// class reading blocks C apart, 32 with adjacent threads at adjacent blocks and the classes' maxima exchanged. Measured and
+// dropped: the rows through LDS as one run of memory (0.13 at k = 10, but 427 us instead of 286 for the search of 300,000 x 64, 600
+// queries, k = 100), sixteen loads of a lane at once (more registers: 1.31 ms instead of 1.15 at k = 100), registers for eight
+// waves a SIMD (1,000 queries, k = 10 on 1,200,000 x 24: 169 us instead of 179, but k = 100 on x 100 1,218 instead of 1,009).
 constexpr int kExactBins = 2048;
 template <int kExactThreads>
 __global__ void __launch_bounds__(kExactThreads)
@@ -419,21 +421,28 @@ exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *
     int C = kExactThreads; // per = threads of a class, side by side
     while (C >= 16 * k && C > 64) C >>= 1;
     const int per_class = kExactThreads / C, cls = tid / per_class, sub = tid & (per_class - 1);
-    float low = -INFINITY, theta; // low: the class's
+    const bool ranked = classes && C <= 256;
+    float low = -INFINITY, low2 = -INFINITY, theta; // of the class, or the largest two of this thread's blocks
     if (classes) {
-        float top = -INFINITY;
-        int64_t at = 0;
+        float top = -INFINITY, top2 = -INFINITY;
+        uint32_t at = 0u, at2 = 0u;
 #pragma unroll 8
-        for (int64_t b = cls + (int64_t)C * sub; b < n_blocks; b += kExactThreads) {
+        for (uint32_t b = tid; b < (uint32_t)n_blocks; b += kExactThreads) {
             const float v = a[b];
+            at2 = v > top ? at : v > top2 ? b : at2;
+            top2 = v > top ? top : fmaxf(v, top2);
             at = v > top ? b : at;
             top = fmaxf(top, v);
         }
         if (top > -INFINITY) low = top - bound(at);
-        for (int m = 1; m < per_class; m <<= 1) low = fmaxf(low, __shfl_xor(low, m, 64));
+        if (!ranked && top2 > -INFINITY) low2 = top2 - bound(at2);
     }
-    if (classes && C <= 256) { // the value that fewer than k exceed and k reach; a class's threads each count a part
-        float *vals = (float *)hist;
+    if (ranked) { // the value that fewer than k exceed and k reach; a class's threads each count a part
+        float *vals = (float *)hist, *spread = vals + kExactBins / 2;
+        spread[tid] = low; // block b is of class b % C, so this thread's blocks are of class tid % C
+        __syncthreads();
+        low = spread[cls + C * sub]; // the threads of a class side by side
+        for (int m = 1; m < per_class; m <<= 1) low = fmaxf(low, __shfl_xor(low, m, 64));
         if (sub == 0) vals[cls] = low;
         __syncthreads();
         uint32_t more = 0u, same = 0u;
@@ -458,7 +467,7 @@ exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *
             };
             if (!classes)
                 for (int64_t b = tid; b < n_blocks; b += kExactThreads) count(a[b] - bound(b));
-            else if (sub == 0) count(low);
+            else { count(low); count(low2); } // (-infinity: none; there are k others)
             __syncthreads();
             uint32_t h[kExactBins / kExactThreads], sum = 0u;
 #pragma unroll

@@ -72,7 +72,8 @@ def test_exact_search_of_rows_that_are_no_whole_quads(d):
 
 # as many results as classes of blocks can tell apart, and more; values that many blocks share
 @pytest.mark.parametrize("n,nq,k", [(30_000, 20, 1), (30_000, 300, 15), (30_000, 20, 16), (30_000, 20, 17), (40_000, 20, 128),
-                                    (40_000, 260, 128), (40_000, 260, 129), (80_000, 20, 257)])
+                                    (40_000, 260, 128), (40_000, 260, 129), (80_000, 20, 257), (40_000, 20, 33), (70_000, 260, 17),
+                                    (140_000, 20, 64)])
 def test_exact_search_at_the_lines_of_the_selection(n, nq, k):
     rng = np.random.default_rng([n, nq, k])
     x = np.round(unit_rows(rng, n, 24) * 16).astype(np.float32)
