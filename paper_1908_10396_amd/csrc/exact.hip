@@ -85,15 +85,15 @@ exact_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, v
 //
 // A lane reads its points' coordinates itself, some steps ahead, four words a load whatever the row's alignment. PAIR (65 to 112
 // dimensions): as many registers as let two workgroups share a compute unit, so that one's products go on while the other
-// reads its rows, and these come through LDS, sixteen a wave at a time, as one run of memory, which reads each line once and
-// whole; an array beyond the Infinity Cache is read past the caches, at 6 TB/s (1,183,514 x 100, one query: 211 us for the
-// product with each lane its own rows and two workgroups, 129 with one, 111 this way).
+// reads its rows. RUNS: those rows come through LDS besides, sixteen a wave at a time, as one run of memory, which reads each
+// line once and whole; nt: past the caches, at 6 TB/s (1,183,514 x 100, one query: 211 us for the product with each lane its
+// own rows and two workgroups, 129 with one, 111 this way).
 // Bound by the reading of x, then the tiles (5.6 us each, 4.1 of matrix instructions at the 2.0 GHz that they leave). Product
 // alone, 1,183,514 x 100, 1,024 queries: 310 us with a load waited for at a row's every step and the staged tile waited for
 // before each tile's first operand, 270 now. Rows that are no whole quads word by word / four words a load, us a call, one query:
 // 1,200,000 x 33 122 / 77, 400,000 x 97 139 / 89, 3,000,000 x 113 1,004 / 485, x 129 1,148 / 643. How many steps ahead makes
 // little difference: 3,000,000 x 48, one query, 1 / 2 / 4 / 6 / all twelve: 172 / 177 / 166 / 165 / 166.
-template <int NS, int CT, bool PAIR>
+template <int NS, int CT, bool PAIR, bool RUNS>
 __global__ void __launch_bounds__(512, PAIR ? 4 : 2)
 exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *__restrict__ packed, int n_tiles, int nq,
                      float *__restrict__ best, int64_t best_stride, float2 *__restrict__ xnorm, uint32_t *__restrict__ need,
@@ -103,7 +103,7 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
     __shared__ __align__(16) float mx[2][32][8];
     __shared__ float2 norms[8];
     constexpr int kRows = 16; // (two workgroups of 7 steps share 160 KB)
-    __shared__ __align__(16) uint4 rows_lds[8][PAIR ? kRows * NS * 4 : 1];
+    __shared__ __align__(16) uint4 rows_lds[8][RUNS ? kRows * NS * 4 : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, h = lane >> 5;
     const int64_t p0 = (int64_t)blockIdx.x * (8 * CT * 32) + wave * (CT * 32);
     const bool quad = (d & 3) == 0 && ((uintptr_t)x & 15) == 0;
@@ -135,7 +135,7 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
         xe = fmaxf(xe, ce);
         n2 = e2 = 0.0f;
     };
-    if constexpr (PAIR) {
+    if constexpr (RUNS) {
         // The rows come through LDS, kRows of them at a time, which are one run of memory: each line is read once, whole, and no
         // register holds what is on its way. Rows of an even number of quads are turned by their number (quad c of row r is at
         // place c + r of it), so that the lanes of a read are spread over the banks; others are by themselves.
@@ -200,7 +200,7 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
             }
             end_of_points(c);
         }
-    } else if (NS == 7 && quad) {
+    } else if (NS == 7 && !PAIR && quad) {
         // as below, but a row's last words are left out by a choice rather than a branch (400,000 x 72, 64 queries: 79.5 us a call, 83
         // as below; 96 dimensions 88.6 / 89.9; other numbers of steps gain from the latter: 3,000,000 x 128, one query 402 / 386)
         const float *row[CT];
@@ -233,16 +233,17 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
         // A step's eight coordinates of a lane's point, those of kAsk steps asked for before they are used (without a branch
         // between them: one for the row's end had each wait for the one before). Four words are one load, at any word's
         // alignment; where a row's end lies within them, the row's last four are read and moved down.
-        constexpr int kAsk = CT * NS < 6 ? CT * NS : 6;
+        constexpr int kAsk = PAIR ? 2 : CT * NS < 6 ? CT * NS : 6; // (more spill in a pair)
         const float *row[CT];
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             const int64_t i = p0 + c * 32 + j;
             row[c] = x + (size_t)(i < n ? i : n - 1) * d; // padding points are copies of the last one
         }
-        float raw[kAsk][2][4];
+        float raw[kAsk][2][4] = {};
         auto ask = [&](int e) __attribute__((always_inline)) {
             const int l = 16 * (e % NS) + 4 * h;
+            if (PAIR && 16 * (e % NS) >= d) return; // (nothing of the row)
             __builtin_memcpy(raw[e % kAsk][0], row[e / NS] + (l < d - 4 ? l : d - 4), 16);
             __builtin_memcpy(raw[e % kAsk][1], row[e / NS] + (l + 8 < d - 4 ? l + 8 : d - 4), 16);
         };
@@ -652,26 +653,33 @@ int launch_exact(const float *x, int64_t n, int d, const float *queries, int nq,
     const int block_points = steps > 8 ? 32 : 64;
     *need_out = w.need;
     hipLaunchKernelGGL(exact_pack_kernel, dim3((unsigned)tiles), dim3(256), 0, st, queries, nq, d, steps, w.packed, w.qnorm, w.need);
-    // Two workgroups a compute unit and rows through LDS: where x does not fit the Infinity Cache, or from eight tiles of queries
-    // on. 100 dimensions, one / two, us a call: 140,000 points, 32 queries 60.2 / 67.2, 130 68.7 / 73.8, 1,000 165 / 159; 400,000, 1
-    // query 76 / 82, 130 98.4 / 99.0, 1,000 237 / 222; 1,183,514, 1 query 176 / 148, 64 200 / 179, 130 221 / 200, 1,000 509 / 431.
+    // One workgroup a compute unit, two that read their rows themselves (pair), two whose rows come through LDS (runs). us a call,
+    // k = 10, one / pair / runs: 400,000 x 72, 64 queries 79.5 / 78.7 / 84; 500,000 x 96, 64 queries 98 / 94 / 101, 128 106 / 100 / 107, 1
+    // 88 / 85 / 94; 140,000 x 100, 64 62 / 66 / 67, 300 91 / 90 / 94; 600,000 x 100, 64 101 / 112 / 102, 300 151 / 155 / 145, 1,000
+    // 285 / 273 / 262; 1,200,000 x 100, 1 184 / 212 / 150, 64 197 / 217 / 175, 300 276 / 275 / 236.
+    // The caches hold on to x up to somewhat more than their size, for the rows that the selection reads: x 275 MB of 112 dimensions, past
+    // the caches / not: one query 100 / 108, 64 125 / 117, 300 182 / 163; 400 MB 64 160 / 155, 300 224 / 213; 500 MB of 100, 64 191 / 192.
     const int64_t groups = w.stride / 8;
-    const int nt = sizeof(float) * (uint64_t)n * (uint64_t)d > ((uint64_t)256 << 20);
-    const bool pair = groups > 256 && (nt || tiles >= 8);
-#define AVQ_EXACT(NS, CT, PAIR)                                                                                          \
-    hipLaunchKernelGGL((exact_product_kernel<NS, CT, PAIR>), dim3((unsigned)(w.stride / 8)), dim3(512), 0, st, x, n, d, w.packed, \
+    const uint64_t mb = (sizeof(float) * (uint64_t)n * (uint64_t)d) >> 20;
+    const bool beyond = mb > 256; // the Infinity Cache
+    const int nt = beyond && (tiles == 1 || mb > 448);
+    const bool pair = groups > 256 && mb <= 200 && ((d <= 96 && tiles > 1) || tiles >= 8);
+    const bool runs = groups > 256 && (beyond || tiles >= 8);
+#define AVQ_EXACT(NS, CT, PAIR, RUNS)                                                                                    \
+    hipLaunchKernelGGL((exact_product_kernel<NS, CT, PAIR, RUNS>), dim3((unsigned)(w.stride / 8)), dim3(512), 0, st, x, n, d, w.packed, \
                        tiles, nq, w.best, w.stride, w.xnorm, w.need, w.xnorm8, nt)
     switch (steps) {
-    case 2: AVQ_EXACT(2, 2, false); break;
-    case 3: AVQ_EXACT(3, 2, false); break;
-    case 4: AVQ_EXACT(4, 2, false); break;
+    case 2: AVQ_EXACT(2, 2, false, false); break;
+    case 3: AVQ_EXACT(3, 2, false, false); break;
+    case 4: AVQ_EXACT(4, 2, false, false); break;
     case 7:
-        if (pair) AVQ_EXACT(7, 2, true);
-        else AVQ_EXACT(7, 2, false);
+        if (pair) AVQ_EXACT(7, 2, true, false);
+        else if (runs) AVQ_EXACT(7, 2, true, true);
+        else AVQ_EXACT(7, 2, false, false);
         break;
-    case 8: AVQ_EXACT(8, 2, false); break;
-    case 12: AVQ_EXACT(12, 1, false); break;
-    default: AVQ_EXACT(16, 1, false); break;
+    case 8: AVQ_EXACT(8, 2, false, false); break;
+    case 12: AVQ_EXACT(12, 1, false, false); break;
+    default: AVQ_EXACT(16, 1, false, false); break;
     }
 #undef AVQ_EXACT
     static LdsLimitOnce once[2];

@@ -70,6 +70,22 @@ def test_exact_search_of_rows_that_are_no_whole_quads(d):
     check(unit_rows(rng, 3001, d), unit_rows(rng, 40, d), 10)
 
 
+# 65 to 112 dimensions on more than 256 workgroups, by the size of the array (200, 256 and 448 MB) and tiles of queries (one, two, eight):
+# two workgroups a compute unit, whose lanes read their rows or have them through LDS, past the caches or not
+@pytest.mark.parametrize("n,d,nq", [(131_073, 66, 33), (131_100, 96, 40), (131_080, 97, 40), (545_001, 97, 225), (547_003, 96, 33), (671_203, 101, 33),
+                                    (1_200_007, 98, 34)])
+def test_exact_search_by_the_size_of_the_array(n, d, nq):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    xd = torch.nn.functional.normalize(torch.randn((n, d), generator=gen, device="cuda"))
+    q = unit_rows(np.random.default_rng(n), nq, d)
+    ids, sc = exact_index(xd).brute_force(torch.from_numpy(q).cuda(), 10)
+    some = [0, nq // 2, nq - 1]
+    oi, os_ = oracle.brute_force(xd.cpu().numpy(), np.ascontiguousarray(q[some]), 10)
+    np.testing.assert_array_equal(ids.cpu().numpy()[some], oi)
+    np.testing.assert_array_equal(sc.cpu().numpy()[some], os_)
+
+
 # as many results as classes of blocks can tell apart, and more; values that many blocks share
 @pytest.mark.parametrize("n,nq,k", [(30_000, 20, 1), (30_000, 300, 15), (30_000, 20, 16), (30_000, 20, 17), (40_000, 20, 128),
                                     (40_000, 260, 128), (40_000, 260, 129), (80_000, 20, 257), (40_000, 20, 33), (70_000, 260, 17),
