@@ -259,10 +259,15 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
                 for (int g = 0; g < 2; ++g) {
                     const int l = 16 * (e % NS) + 4 * h + 8 * g, by = l + 4 - d; // by: words beyond the end
                     const float w[4] = {v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
-                    v[4 * g] = by <= 0 ? w[0] : by == 1 ? w[1] : by == 2 ? w[2] : by == 3 ? w[3] : 0.0f;
-                    v[4 * g + 1] = by <= 0 ? w[1] : by == 1 ? w[2] : by == 2 ? w[3] : 0.0f;
-                    v[4 * g + 2] = by <= 0 ? w[2] : by == 1 ? w[3] : 0.0f;
-                    v[4 * g + 3] = by <= 0 ? w[3] : 0.0f;
+                    if (!PAIR && (d & 3) == 0) { // four or none (a pair: more registers, spilled)
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) v[4 * g + u] = by <= 0 ? w[u] : 0.0f;
+                    } else {
+                        v[4 * g] = by <= 0 ? w[0] : by == 1 ? w[1] : by == 2 ? w[2] : by == 3 ? w[3] : 0.0f;
+                        v[4 * g + 1] = by <= 0 ? w[1] : by == 1 ? w[2] : by == 2 ? w[3] : 0.0f;
+                        v[4 * g + 2] = by <= 0 ? w[2] : by == 1 ? w[3] : 0.0f;
+                        v[4 * g + 3] = by <= 0 ? w[3] : 0.0f;
+                    }
                 }
             }
             operand(e / NS, e % NS, v);
@@ -427,16 +432,25 @@ exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *
     if (classes) {
         float top = -INFINITY, top2 = -INFINITY;
         uint32_t at = 0u, at2 = 0u;
+        if (ranked) {
 #pragma unroll 8
-        for (uint32_t b = tid; b < (uint32_t)n_blocks; b += kExactThreads) {
-            const float v = a[b];
-            at2 = v > top ? at : v > top2 ? b : at2;
-            top2 = v > top ? top : fmaxf(v, top2);
-            at = v > top ? b : at;
-            top = fmaxf(top, v);
+            for (uint32_t b = tid; b < (uint32_t)n_blocks; b += kExactThreads) {
+                const float v = a[b];
+                at = v > top ? b : at;
+                top = fmaxf(top, v);
+            }
+        } else {
+#pragma unroll 4
+            for (uint32_t b = tid; b < (uint32_t)n_blocks; b += kExactThreads) {
+                const float v = a[b];
+                at2 = v > top ? at : v > top2 ? b : at2;
+                top2 = v > top ? top : fmaxf(v, top2);
+                at = v > top ? b : at;
+                top = fmaxf(top, v);
+            }
+            if (top2 > -INFINITY) low2 = top2 - bound(at2);
         }
         if (top > -INFINITY) low = top - bound(at);
-        if (!ranked && top2 > -INFINITY) low2 = top2 - bound(at2);
     }
     if (ranked) { // the value that fewer than k exceed and k reach; a class's threads each count a part
         float *vals = (float *)hist, *spread = vals + kExactBins / 2;
