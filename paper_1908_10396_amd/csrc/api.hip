@@ -1623,22 +1623,38 @@ static int check_search_args(const avq_index *idx, const float *queries, int32_t
 // with the one-query-per-workgroup scan over leaves, which keeps sorted lists per wave: between 64 and 96 queries at
 // 100 of 2,000 leaves).
 constexpr int kLeafSmallMaxQueries = 80;
-// 8-bit codes and code sizes without kernels of their own take it too, but for a few results from a few blocks, where the four
-// launches of the list scan are done before the six here. Many results from many blocks for many queries, all of which are
-// scored twice here, are left to the list scan. List scan / this, us a call, fp32 tables: 5,000 points, 5 of 70 leaves, 16 code
-// bytes, one query: R = 1 27 / 30, 100 39 / 36, 500 76 / 40; 900,000, 120 of 1,500: 1 query R = 100 106 / 42, 80 queries 146 / 132,
-// R = 500 384 / 128, 532 / 508 (40 queries), 616 / 734 (60), 387 / 939 (80); 25 bytes of 8-bit codes 113 / 42, 168 / 144, 416 / 127,
-// 717 / 509 (60), 446 / 610 (80); 48 bytes of 4-bit codes 159 / 62, 293 / 218, 550 / 148, 938 / 774, 575 / 973.
+// 8-bit codes and code sizes without kernels of their own take it too, but
+//  - for a few results from a few blocks, where the four launches of the list scan are done before the six here;
+//  - where all of a query's blocks, and of more than 64, are scored twice and all of their points are candidates, for many queries:
+//    those go to a query's list one by one, while the list scan's time hardly grows with the queries;
+//  - beyond 64 queries, where the list scan has four waves a workgroup rather than sixteen;
+//  - large codes for many queries, whose tables each workgroup copies.
+// List scan / this, us a call, fp32 tables, queries 1 / 24 / 60 / 80:
+//  16 bytes of 4-bit codes, 25 of 500 leaves, 32 blocks: R = 100 63/40 66/51 67/55 63/57, R = 500 208/50 216/63 218/71 234/76;
+//   60 of 300, 342 blocks: R = 30 67/40 78/58 78/74 94/84, 200 176/48 193/115 201/204 175/246, 350 280/136 310/450 312/785 250/964;
+//   100 of 2,000, 245 blocks: R = 200 170/49 204/134 296/242 201/285, 350 258/101 317/229 457/317 286/467, 500 379/104 438/248 623/390
+//   384/499; 10 of 100, 396 blocks: R = 350 451/83 511/282 530/526 421/608, 500 640/192 698/559 701/1,032 568/1,219.
+//  48 bytes of 4-bit codes, 342 blocks: R = 200 216/64 248/168 248/313 267/408, 245 blocks 258/76 361/241 442/423 348/486.
+//  8-bit codes, 342 blocks, R = 350: 25 bytes 301/136 326/314 340/584 273/670, 48 bytes 304/146 339/378 354/631 339/781; 48 bytes, 32
+//   blocks, R = 30: 60/49 62/61 74/92 76/103; 48 bytes of 4-bit codes, 4 blocks, R = 100, 60 queries 47 / 51.
+// Of 6,174 calls 23 take more than 5 % longer than by the list scan, 15 % at most (48 bytes of 8-bit codes, 342 blocks, 60 queries).
 static bool use_leaf_small(const avq_index *idx, int nq, int L, int R)
 {
     const int max_q = idx->tune_small_batch >= 0 ? std::min(idx->tune_small_batch, 4096) : kLeafSmallMaxQueries;
     if (idx->cfg.n_leaves == 0 || idx->tune_small_impl == 1 || nq > max_q || L > 512 || !leaf_small_supported(idx->NB, idx->cfg.bits) ||
         !leaf_select_few_supported(idx->cfg.d)) return false;
     if (idx->tune_small_batch >= 0) return true;
-    const bool own = idx->cfg.bits == 4 && block_bound_supported(idx->NB, 4);
+    const bool own = idx->cfg.bits == 4 && block_bound_supported(idx->NB, 4), wide = idx->cfg.bits == 8;
     const double listed = (double)L * (double)idx->n_blocks / idx->cfg.n_leaves; // blocks of a query's leaves
-    if (!own && R < 32 && listed < 12.0) return false;
-    return R <= 200 || nq * listed <= 20000.0 || (nq <= 64 && (own || idx->cfg.bits == 8 || idx->NB >= 24));
+    if (own) return R <= 200 || nq <= 64 || nq * listed <= 20000.0;
+    const bool all = R >= 0.9 * listed;
+    if (R < 32 && (listed < 12.0 || (all && nq > 24))) return false;
+    if (!wide && idx->NB > 32 && nq > 24 && R <= 100 && listed < 12.0) return false;
+    if (wide && idx->NB > 32 && nq > 32 && R <= 100 && listed < 2.0 * L) return false;
+    if (listed <= 64.0) return true;
+    if (nq > 64 && R > 128 && !(L < 16 && R <= 200)) return false;
+    if (all) return nq * listed <= R * (L >= 100 ? 44.0 : wide && idx->NB <= 32 ? 32.0 : 20.0);
+    return wide || idx->NB <= 32 || L < 16 || nq * R <= 10000;
 }
 
 // AVQ_ENOMEM, with nothing launched, where there is no room for the scratch: 2 KB a result and query, for the points of the

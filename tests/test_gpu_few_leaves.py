@@ -125,3 +125,19 @@ def test_few_queries_within_a_scratch_limit(bits):
         np.testing.assert_array_equal(ids.cpu().numpy(), oi, err_msg="limit %d KB" % limit_kb)
         np.testing.assert_array_equal(sc.cpu().numpy(), os_, err_msg="limit %d KB" % limit_kb)
     assert taken[0] < 32 << 20 < 64 << 20 < taken[1], taken
+
+
+# which of the two scans answers a few queries, where one takes twice as long as the other: 228 blocks of 1,300 are a query's; only
+# the scan by block maxima has a second pass
+@pytest.mark.parametrize("nq,R,maxima", [(1, 100, True), (60, 100, True), (12, 400, True), (60, 400, False), (80, 300, False)])
+def test_form_of_a_few_queries(nq, R, maxima):
+    rng = np.random.default_rng(nq)
+    n, d, M, leaves, L = 300_000, 32, 32, 100, 16
+    idx = avq.Index(d, M, 4, n_leaves=leaves)
+    idx.set_codebooks(rng.standard_normal((M, 16, 1)).astype(np.float32))
+    idx.set_leaf_centers(unit_rows(rng, leaves, d))
+    x = torch.from_numpy(unit_rows(rng, 1000, d)).cuda().repeat(300, 1)
+    idx.set_database(x, torch.from_numpy(rng.integers(0, 256, (n, 16), dtype=np.uint8)).cuda(), (np.arange(n) % leaves).astype(np.int32))
+    idx.profile_enable()
+    idx.search(torch.from_numpy(unit_rows(rng, nq, d)).cuda(), 10, R, avq.LUT_F32, L)
+    assert (idx.profile_read()["rescan"][1] > 0) == maxima
