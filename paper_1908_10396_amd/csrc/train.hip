@@ -634,7 +634,7 @@ int launch_assign_aniso(const float *x, int64_t n, int d, const float *centers, 
 // Windows of points handed out by a counter instead of split evenly: 2.63 -> 2.34 ms, as one SIMD of four held two waves.
 struct EncodeParams {
     const float *x;
-    int64_t n_slots;
+    int64_t n, n_slots;
     const int32_t *order; // slot -> point (-1: none), NULL: slot i is point i
     int32_t d, M, NB, passes;
     const float *codebooks;   // [M][codewords][dimensions]
@@ -645,6 +645,7 @@ struct EncodeParams {
     const double *w_in;       // NULL: w from eta_mode here
     uint8_t *packed;
     uint32_t *next_window;    // windows of slots, one a lane, are handed out: waves that share a SIMD get fewer
+    int32_t top_up;           // leaves, and more windows than waves: lanes without a point take the next window's while others are at work
     int32_t code_stride;      // bytes (odd dwords)
 };
 
@@ -769,7 +770,7 @@ encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, cons
         bool taken = false;
         while (need != 0ull) {
             if (win_left == 0) {
-                if (drained) break;
+                if (drained || (RES && !p.top_up && __builtin_amdgcn_ballot_w64(id >= 0) != 0ull)) break;
                 uint32_t w64 = 0u;
                 if (lane == 0) w64 = atomicAdd(p.next_window, 1u);
                 const int64_t s0 = (int64_t)__builtin_amdgcn_readfirstlane(w64) * 64, s = s0 + lane;
@@ -1061,7 +1062,7 @@ encode_wide_kernel(const EncodeParams p, const float *__restrict__ operands, con
         bool taken = false;
         while (need != 0u) {
             if (win_left == 0) {
-                if (drained) break;
+                if (drained || (RES && !p.top_up && __builtin_amdgcn_ballot_w64(id >= 0) != 0ull)) break;
                 uint32_t w32 = 0u;
                 if (lane == 0) w32 = atomicAdd(p.next_window, 1u);
                 const int64_t s0 = (int64_t)__builtin_amdgcn_readfirstlane(w32) * 32, s = s0 + j;
@@ -1394,7 +1395,8 @@ static int launch_encode_one(EncodeParams p, const float *tab, const float2 *lim
     // spread over the compute units first
     const int most = DS <= 2 && p.leaf_centers == nullptr ? 20 : 16;
     const size_t shared = (size_t)p.M * (16 * (DS + 1) + 2) * 4, per_wave = (size_t)64 * p.code_stride;
-    const int64_t groups = (p.n_slots + 63) / 64;
+    // windows that hold points: in order of the leaves, whose slots are whole blocks of 256, a leaf's last one may be short
+    const int64_t groups = p.order ? std::min<int64_t>((p.n_slots + 63) / 64, p.n / 64 + p.n_slots / 256) : (p.n_slots + 63) / 64;
     const int wanted = (int)std::min<int64_t>(8, std::max<int64_t>(1, (groups + 255) / 256));
     int waves = 0, resident = 0;
     for (int w = 1; w <= wanted; ++w) {
@@ -1404,9 +1406,14 @@ static int launch_encode_one(EncodeParams p, const float *tab, const float2 *lim
         if (r > resident) { resident = r; waves = w; }
     }
     if (waves == 0) return 1; // does not fit: the caller takes the plain kernel
-    const int64_t total = std::min<int64_t>(groups, (int64_t)256 * resident); // a resident set of waves
+    // a resident set of waves, one for each window with points, and one a compute unit for windows without
+    const int64_t total = std::max(std::min<int64_t>(groups, (int64_t)256 * resident), std::min<int64_t>((p.n_slots + 63) / 64, 256));
     const dim3 grid((unsigned)((total + waves - 1) / waves));
     const size_t lds = shared + waves * per_wave;
+    // As many waves as windows: a wave whose window has few points (a leaf's last ones) leaves the next window to another wave, rather
+    // than filling its lanes from it and having the rest of it wait for them. us a call, filling / leaving, 60 leaves: 9,000 x 192, 96
+    // subspaces 607 / 397; 30,000 x 100, 50 396 / 296.
+    p.top_up = groups > (int64_t)grid.x * waves;
     static LdsLimitOnce flat_done, res_done;
     AVQ_TRY(set_lds_limit((const void *)encode_aniso_kernel<DS, false>, kMaxDynLds, &flat_done));
     AVQ_TRY(set_lds_limit((const void *)encode_aniso_kernel<DS, true>, kMaxDynLds, &res_done));
@@ -1422,7 +1429,7 @@ static int launch_encode_wide(EncodeParams p, const float *operands, const float
     const size_t shared = (size_t)p.M * 1024, per_wave = (size_t)32 * p.code_stride;
     const bool cc_lds = shared + 4 * per_wave <= kMaxDynLds;
     const size_t fixed = cc_lds ? shared : 0;
-    const int64_t groups = (p.n_slots + 31) / 32;
+    const int64_t groups = p.order ? std::min<int64_t>((p.n_slots + 31) / 32, p.n / 32 + p.n_slots / 256) : (p.n_slots + 31) / 32;
     // waves per workgroup: few points are spread over the compute units first
     const int wanted = (int)std::min<int64_t>(8, std::max<int64_t>(1, (groups + 255) / 256));
     int waves = 0, resident = 0;
@@ -1433,8 +1440,9 @@ static int launch_encode_wide(EncodeParams p, const float *operands, const float
         if (r >= resident) { resident = r; waves = w; }
     }
     if (waves == 0) return 1;
-    const int64_t total = std::min<int64_t>(groups, (int64_t)256 * resident);
+    const int64_t total = std::max(std::min<int64_t>(groups, (int64_t)256 * resident), std::min<int64_t>((p.n_slots + 31) / 32, 256));
     const dim3 grid((unsigned)((total + waves - 1) / waves)), block(64 * waves);
+    p.top_up = groups > (int64_t)grid.x * waves;
     const size_t lds = fixed + waves * per_wave;
     static LdsLimitOnce done[4];
 #define AVQ_WIDE(RES, CC, I)                                                                                          \
@@ -1454,19 +1462,22 @@ static int launch_encode_wide(EncodeParams p, const float *operands, const float
     return AVQ_OK;
 }
 
-// Few subspaces: a thread per point in fp64 is done before the fp32 search's waves have handed out their points one by one
-// and staged their rows. One avq_encode of 300,000 points, fp64 / fp32 search (us): 16 codewords of 2 dimensions, ten
-// passes: 4 subspaces 75 / 127, 8 126 / 138, 10 153 / 142; no pass: 8 73 / 130, 16 139 / 139; of 1 dimension, ten passes: 4
-// 96 / 126, 6 135 / 134; of 3: 2 82 / 125, 3 133 / 126; of 4: 4 91 / 129, 6 131 / 137; 256 of 2, no pass, 16,000 points: 2
-// 64 / 81, 4 105 / 112, 6 145 / 145. (1,000,000 points, 2 subspaces of 2 dimensions, ten passes: 92 / 251.) At 500 to 16,000
-// points the lines lie one or two subspaces lower.
-static bool encode_few_steps(int ds, int kc, int M, int passes)
+// Few subspaces: a thread per point in fp64 is done before the fp32 search's waves have been handed their points, a window by one
+// counter (16 ns each). One avq_encode, fp64 / fp32 search (us): 16 codewords of 1 dimension, three passes: 4,000 points, 2 subspaces
+// 32 / 28; 100,000, 5 59 / 64, 6 69 / 64; 300,000, 5 111 / 137; 1,000,000, 4 236 / 262, 5 297 / 265; no pass: 4,000, 3 29 / 29, 4 31 /
+// 29; 1,000,000, 10 257 / 270, 12 328 / 272; of 2: 4,000, 2 28 / 29, 4 36 / 31; 100,000, 7 60 / 67, 8 68 / 67; no pass: 16,000, 6 32 / 33;
+// 100,000, 14 63 / 70; of 3: 16,000, 1 32 / 30; 100,000, 2 47 / 61, 3 63 / 64; no pass: 4 50 / 60, 5 64 / 62; of 4: 16,000, 3 36 / 37, 4
+// 41 / 36; 100,000, 5 57 / 69; 1,000,000, 6 298 / 277; no pass: 5 33 / 35, 100,000, 8 58 / 70. 256 of 2: 4,000, 1 63 / 44, 100,000, 1 81 /
+// 100, 2 140 / 114, no pass: 2 79 / 94, 3 107 / 101; of 4: 100,000, 1 96 / 105, no pass: 2 98 / 96, 300,000 158 / 170; of 8: 100,000, 1
+// 128 / 120, no pass: 75 / 100. (Three and ten passes alike.)
+static bool encode_few_steps(int64_t n, int ds, int kc, int M, int passes)
 {
+    const bool many = n >= 40000; // points
     if (kc == 16) {
-        const int most[5] = {0, 4, 7, 2, 5}, most_no_pass[5] = {0, 10, 14, 4, 8}; // by ds
-        return M <= (passes > 0 ? most : most_no_pass)[ds];
+        const int most[2][2][5] = {{{0, 3, 6, 1, 5}, {0, 1, 2, 0, 3}}, {{0, 10, 14, 4, 8}, {0, 4, 7, 2, 5}}}; // by many, passes, ds
+        return M <= most[many][passes > 0][ds];
     }
-    return M <= (ds == 2 ? (passes > 0 ? 2 : 4) : ds == 4 && passes == 0 ? 2 : 0);
+    return many && M <= (ds == 8 ? (passes > 0 ? 0 : 1) : passes > 0 ? 1 : 2);
 }
 
 int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, const float *codebooks, const float *leaf_centers,
@@ -1479,11 +1490,11 @@ int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, con
     int rc = AVQ_ENOMEM; // AVQ_ENOMEM or 1: the kernel below, which needs no scratch, takes the points
     const size_t b_tab = (sizeof(float) * (size_t)M * kc * (ds + 1) + 255) & ~(size_t)255, b_lim = sizeof(float2) * (size_t)kMaxM + 256;
     const bool weights = eta_mode == AVQ_ETA_EXACT;
-    if ((kc == 16 ? ds >= 1 && ds <= 4 : ds == 2 || ds == 4 || ds == 8) && !encode_few_steps(ds, kc, M, passes))
+    if ((kc == 16 ? ds >= 1 && ds <= 4 : ds == 2 || ds == 4 || ds == 8) && !encode_few_steps(n, ds, kc, M, passes))
         rc = ws->reserve(b_tab + b_lim + (weights ? sizeof(double) * (size_t)n : 0));
     if (rc == AVQ_OK) {
         EncodeParams p;
-        p.x = x; p.order = order; p.n_slots = order ? n_slots : n;
+        p.x = x; p.order = order; p.n = n; p.n_slots = order ? n_slots : n;
         p.d = d; p.M = M; p.NB = (M * bits + 7) / 8; p.passes = passes;
         p.codebooks = codebooks;
         float *tab = ws->as<float>();                                // [M][kc][ds + 1]: codeword, ||c||^2
