@@ -756,7 +756,7 @@ encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, cons
     for (int e = 0; e < p.code_stride; e += 4) *(uint32_t *)(my_codes + e) = 0u;
 
     int win_id = -1, win_left = 0;  // the window's points not yet taken: those of lanes 0 .. win_left - 1
-    bool drained = false;           // no windows left
+    bool first = true, drained = false; // drained: no windows left
     int id = -1, stage = 0;         // this lane's point (-1: none) and pass (-1: nearest codewords first)
     double P = 0.0, w = 0.0; // P = <x - center - codewords, x>, the codewords chosen so far
     const float *xi = p.x, *ce_row = RES ? p.leaf_centers : nullptr;
@@ -771,9 +771,13 @@ encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, cons
         while (need != 0ull) {
             if (win_left == 0) {
                 if (drained || (RES && !p.top_up && __builtin_amdgcn_ballot_w64(id >= 0) != 0ull)) break;
-                uint32_t w64 = 0u;
-                if (lane == 0) w64 = atomicAdd(p.next_window, 1u);
-                const int64_t s0 = (int64_t)__builtin_amdgcn_readfirstlane(w64) * 64, s = s0 + lane;
+                uint32_t w64 = blockIdx.x * (blockDim.x >> 6) + wave; // the first window; the others by the counter
+                if (!first) {
+                    if (lane == 0) w64 = gridDim.x * (blockDim.x >> 6) + atomicAdd(p.next_window, 1u);
+                    w64 = __builtin_amdgcn_readfirstlane(w64);
+                }
+                first = false;
+                const int64_t s0 = (int64_t)w64 * 64, s = s0 + lane;
                 if (s0 >= p.n_slots) { drained = true; break; }
                 const int slot = s < p.n_slots ? (p.order ? p.order[s] : (int)s) : -1;
                 const u64 there = __builtin_amdgcn_ballot_w64(slot >= 0);
@@ -1048,7 +1052,7 @@ encode_wide_kernel(const EncodeParams p, const float *__restrict__ operands, con
         for (int e = 0; e < p.code_stride; e += 4) *(uint32_t *)(my_codes + e) = 0u;
 
     int win_id = -1, win_left = 0;  // the window's points not yet taken: those of lanes 0 .. win_left - 1 of either half
-    bool drained = false;           // no windows left
+    bool first = true, drained = false; // drained: no windows left
     int id = -1, stage = 0;
     double P = 0.0, w = 0.0;
     const float *xi = p.x, *ce_row = RES ? p.leaf_centers : nullptr;
@@ -1063,9 +1067,13 @@ encode_wide_kernel(const EncodeParams p, const float *__restrict__ operands, con
         while (need != 0u) {
             if (win_left == 0) {
                 if (drained || (RES && !p.top_up && __builtin_amdgcn_ballot_w64(id >= 0) != 0ull)) break;
-                uint32_t w32 = 0u;
-                if (lane == 0) w32 = atomicAdd(p.next_window, 1u);
-                const int64_t s0 = (int64_t)__builtin_amdgcn_readfirstlane(w32) * 32, s = s0 + j;
+                uint32_t w32 = blockIdx.x * (blockDim.x >> 6) + wave; // the first window; the others by the counter
+                if (!first) {
+                    if (lane == 0) w32 = gridDim.x * (blockDim.x >> 6) + atomicAdd(p.next_window, 1u);
+                    w32 = __builtin_amdgcn_readfirstlane(w32);
+                }
+                first = false;
+                const int64_t s0 = (int64_t)w32 * 32, s = s0 + j;
                 if (s0 >= p.n_slots) { drained = true; break; }
                 const int slot = s < p.n_slots ? (p.order ? p.order[s] : (int)s) : -1;
                 const uint32_t there = (uint32_t)__builtin_amdgcn_ballot_w64(slot >= 0);
@@ -1462,22 +1470,22 @@ static int launch_encode_wide(EncodeParams p, const float *operands, const float
     return AVQ_OK;
 }
 
-// Few subspaces: a thread per point in fp64 is done before the fp32 search's waves have been handed their points, a window by one
-// counter (16 ns each). One avq_encode, fp64 / fp32 search (us): 16 codewords of 1 dimension, three passes: 4,000 points, 2 subspaces
-// 32 / 28; 100,000, 5 59 / 64, 6 69 / 64; 300,000, 5 111 / 137; 1,000,000, 4 236 / 262, 5 297 / 265; no pass: 4,000, 3 29 / 29, 4 31 /
-// 29; 1,000,000, 10 257 / 270, 12 328 / 272; of 2: 4,000, 2 28 / 29, 4 36 / 31; 100,000, 7 60 / 67, 8 68 / 67; no pass: 16,000, 6 32 / 33;
-// 100,000, 14 63 / 70; of 3: 16,000, 1 32 / 30; 100,000, 2 47 / 61, 3 63 / 64; no pass: 4 50 / 60, 5 64 / 62; of 4: 16,000, 3 36 / 37, 4
-// 41 / 36; 100,000, 5 57 / 69; 1,000,000, 6 298 / 277; no pass: 5 33 / 35, 100,000, 8 58 / 70. 256 of 2: 4,000, 1 63 / 44, 100,000, 1 81 /
-// 100, 2 140 / 114, no pass: 2 79 / 94, 3 107 / 101; of 4: 100,000, 1 96 / 105, no pass: 2 98 / 96, 300,000 158 / 170; of 8: 100,000, 1
-// 128 / 120, no pass: 75 / 100. (Three and ten passes alike.)
+// Few subspaces: a thread per point in fp64 is done before the fp32 search's waves, which share the windows by one counter and set up
+// their tables each. The lines lie where the two are level. One avq_encode, fp64 / fp32 search (us): 16 codewords of 1 dimension,
+// three passes: 4,000 points, 2 subspaces 32 / 27; 100,000, 3 43 / 46, 4 51 / 46; 1,000,000, 3 165 / 209, 4 237 / 210; no pass: 4,000,
+// 3 28 / 28, 4 31 / 28; 1,000,000, 7 171 / 215, 8 294 / 215; of 2: 4,000, 2 28 / 28, 3 36 / 30; 100,000, 5 48 / 49, 6 54 / 51; no pass:
+// 16,000, 6 31 / 32; 100,000, 12 54 / 53; of 3: 4,000, 1 31 / 28; 300,000, 2 77 / 81, 3 127 / 88; no pass: 3 71 / 82, 4 94 / 81; of 4:
+// 16,000, 2 31 / 31, 3 35 / 34; 100,000, 4 49 / 51, 5 56 / 56; no pass: 16,000, 4 30 / 31, 5 33 / 33; 300,000, 7 92 / 101, 8 107 / 95.
+// 256 of 2: 40,000, 1 76 / 63, 300,000, 1 132 / 148, 2 235 / 164, no pass: 2 123 / 146, 3 168 / 152; of 4: 100,000, 1 94 / 86, no pass:
+// 58 / 72, 2 97 / 81; of 8: 100,000, 1 124 / 102, no pass: 73 / 80. At 40,000 points the lines are those of fewer points.
 static bool encode_few_steps(int64_t n, int ds, int kc, int M, int passes)
 {
-    const bool many = n >= 40000; // points
+    const bool many = n >= 65536; // points: measured at 40,000 and 100,000
     if (kc == 16) {
-        const int most[2][2][5] = {{{0, 3, 6, 1, 5}, {0, 1, 2, 0, 3}}, {{0, 10, 14, 4, 8}, {0, 4, 7, 2, 5}}}; // by many, passes, ds
+        const int most[2][2][5] = {{{0, 3, 6, 1, 4}, {0, 0, 2, 0, 2}}, {{0, 7, 12, 3, 7}, {0, 3, 5, 2, 4}}}; // by many, passes, ds
         return M <= most[many][passes > 0][ds];
     }
-    return many && M <= (ds == 8 ? (passes > 0 ? 0 : 1) : passes > 0 ? 1 : 2);
+    return many && M <= (ds == 2) + (passes == 0);
 }
 
 int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, const float *codebooks, const float *leaf_centers,
