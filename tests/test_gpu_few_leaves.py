@@ -22,13 +22,13 @@ def pack(codes, bits):
 
 
 # code bytes below, at and above four and eight of them, an odd number of subspaces, large codes, 8-bit codes with and without a
-# kernel of their own, and more than those kernels' tables have room for (65: the list scan); leaves of several blocks
+# kernel of their own, the most that those kernels' tables have room for (64) and more (65: the list scan); leaves of several blocks
 @pytest.mark.parametrize("d,M,bits", [(6, 3, 4), (32, 16, 4), (64, 32, 4), (105, 35, 4), (192, 96, 4), (36, 9, 8), (50, 25, 8), (64, 32, 8),
-                                      (65, 65, 8)])
+                                      (33, 33, 8), (64, 64, 8), (65, 65, 8)])
 @pytest.mark.parametrize("nq,k,R,L", [(1, 10, 100, 7), (5, 1, 0, 3), (3, 10, 512, 13)])
 @pytest.mark.parametrize("mode", [avq.LUT_F32, avq.LUT_U8])
 def test_few_queries_on_any_code_size(d, M, bits, nq, k, R, L, mode):
-    if M == 65 and mode == avq.LUT_U8:
+    if M >= 64 and mode == avq.LUT_U8:
         pytest.skip("8-bit tables of more than 62 KB are refused")
     rng = np.random.default_rng([d, M, nq])
     n, leaves = 6000, 13
@@ -48,6 +48,35 @@ def test_few_queries_on_any_code_size(d, M, bits, nq, k, R, L, mode):
         ids, sc = idx.search(qd, k, R, mode, L)
         np.testing.assert_array_equal(ids.cpu().numpy(), oi, err_msg="small_batch_impl %d" % impl)
         np.testing.assert_array_equal(sc.cpu().numpy(), os_, err_msg="small_batch_impl %d" % impl)
+
+
+# more blocks listed than are ranked by counting (512), and more candidates; as many codes as points, some dozens (thousands of
+# points of each score, and every block's maximum the same but for a few), and one
+@pytest.mark.parametrize("M,bits", [(16, 4), (35, 4), (50, 4), (25, 8), (33, 8), (64, 8)])
+@pytest.mark.parametrize("distinct", [0, 40, 1])
+@pytest.mark.parametrize("nq,R", [(1, 100), (3, 512)])
+def test_few_queries_of_many_blocks(M, bits, distinct, nq, R):
+    rng = np.random.default_rng([M, bits, distinct, R])
+    n, d, k, leaves, L = 150_000, M, 10, 13, 12
+    x, q, cen = unit_rows(rng, n, d), unit_rows(rng, nq, d), unit_rows(rng, leaves, d)
+    cen[:] = cen[0] if distinct == 1 else cen  # (a leaf's own product is a part of its points' scores)
+    cb = (rng.standard_normal((M, 1 << bits, 1)) / np.sqrt(d)).astype(np.float32)
+    codes = rng.integers(0, 1 << bits, (distinct or n, M), dtype=np.uint8)
+    if distinct:
+        codes = codes[rng.integers(0, distinct, n)]
+    assign = rng.integers(0, leaves, n).astype(np.int32)
+    idx = avq.Index(d, M, bits, n_leaves=leaves)
+    idx.set_codebooks(cb)
+    idx.set_leaf_centers(cen)
+    idx.set_database(torch.from_numpy(x).cuda(), torch.from_numpy(pack(codes, bits)).cuda(), assign)
+    oi, os_ = oracle.search(x, cb, codes, bits, q, k, R, avq.LUT_F32, centers=cen, assign=assign, leaves_to_search=L)
+    idx.profile_enable()
+    for impl in (0, 1):  # 1: the list scan, which has no second pass
+        idx.set_tuning("small_batch_impl", impl)
+        ids, sc = idx.search(torch.from_numpy(q).cuda(), k, R, avq.LUT_F32, L)
+        np.testing.assert_array_equal(ids.cpu().numpy(), oi, err_msg="small_batch_impl %d" % impl)
+        np.testing.assert_array_equal(sc.cpu().numpy(), os_, err_msg="small_batch_impl %d" % impl)
+        assert (idx.profile_read()["rescan"][1] > 0) == (impl == 0)  # (reads and resets)
 
 
 # one leaf, as many as threads and one more, as many as the histogram's registers hold and more; equal scores (one bin), all but one
