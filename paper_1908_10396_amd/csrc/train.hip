@@ -644,32 +644,41 @@ struct EncodeParams {
     double T, eta_explicit;
     const double *w_in;       // NULL: w from eta_mode here
     uint8_t *packed;
+    uint32_t *distinct;       // 16 codewords: per dictionary a bit for each that equals none before it
     uint32_t *next_window;    // windows of slots, one a lane, are handed out: waves that share a SIMD get fewer
     int32_t top_up;           // leaves, and more windows than waves: lanes without a point take the next window's while others are at work
     int32_t code_stride;      // bytes (odd dwords)
 };
 
 __global__ void __launch_bounds__(64)
-encode_tables_kernel(const float *__restrict__ codebooks, int kc, int ds, float *__restrict__ tab, float2 *__restrict__ lim,
-                     uint32_t *__restrict__ next_window)
+encode_tables_kernel(const float *__restrict__ codebooks, int ds, float *__restrict__ tab, float2 *__restrict__ lim,
+                     uint32_t *__restrict__ distinct, uint32_t *__restrict__ next_window)
 {
     const int m = blockIdx.x, lane = threadIdx.x;
     if (m == 0 && lane == 0) *next_window = 0u;
     float cm = 0.0f, ccm = 0.0f;
-    for (int j = lane; j < kc; j += 64) {
-        const float *c = codebooks + ((size_t)m * kc + j) * ds;
-        float *o = tab + ((size_t)m * kc + j) * (ds + 1);
+    uint32_t alike = lane < 16 ? (1u << lane) - 1u : ~0u; // of the codewords before this lane's, those that equal it
+    if (lane < 16) {
+        const float *c = codebooks + ((size_t)m * 16 + lane) * ds;
+        float *o = tab + ((size_t)m * 16 + lane) * (ds + 1);
         double cc = 0.0;
         for (int l = 0; l < ds; ++l) {
             o[l] = c[l];
+            uint32_t same = 0u;
+            for (int j = 0; j < 16; ++j) same |= (c[l] == __shfl(c[l], j, 64) ? 1u : 0u) << j;
+            alike &= same;
             cc += (double)c[l] * (double)c[l];
             cm = fmaxf(cm, fabsf(c[l]));
         }
         o[ds] = (float)cc;
-        ccm = fmaxf(ccm, (float)cc);
+        ccm = (float)cc;
     }
+    const uint64_t first = __builtin_amdgcn_ballot_w64(alike == 0u);
     for (int s = 32; s > 0; s >>= 1) { cm = fmaxf(cm, __shfl_xor(cm, s, 64)); ccm = fmaxf(ccm, __shfl_xor(ccm, s, 64)); }
-    if (lane == 0) lim[m] = make_float2(cm * 1.0001f, ccm * 1.0001f);
+    if (lane == 0) {
+        lim[m] = make_float2(cm * 1.0001f, ccm * 1.0001f);
+        distinct[m] = (uint32_t)first;
+    }
 }
 
 // The same for 256 codewords (encode_wide_kernel): operands [m][(32 codewords g, two dimensions s) / 4][64][4], the lane's
@@ -870,7 +879,8 @@ encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, cons
             if constexpr (RES) F = fmaf(2.0f * lim.x, sr, F);
             const float lead = fmaf(F, 2.0f * kEps, 2.0e-37f);
 
-            // a half of the codewords at a time (more at once, or kept for the decisions in fp64, spill)
+            // a half of the codewords at a time: more need more than the 128 registers of four waves a SIMD (as it is, 30 and, with
+            // leaf centers, 40 are spilled at 4 dimensions, 7 and 4 with leaf centers at 3 and 2)
             constexpr int kPart = 8, kPart4 = kPart * (DS + 1) / 4;
             typedef float four_floats __attribute__((ext_vector_type(4)));
             typedef const __attribute__((address_space(3))) four_floats lds_float4;
@@ -915,10 +925,10 @@ encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, cons
             const bool open = active && !(second - best > lead);
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(open) != 0ull, 0)) {
                 if (open) {
-                    // Equal codewords leave this open at every step, mostly between two: those that f does not rule out are
-                    // found once more, and up to four taken one by one (200,000 x 100 points, 50 dictionaries of 8 pairs of
-                    // equal codewords: 1.06 ms with all sixteen,
-                    // 0.75 this way; 0.43 without the pairs).
+                    // Equal codewords leave this open at every step: those that f does not rule out are found once more, without
+                    // those that equal an earlier one, and up to four taken one by one. (200,000 x 100 points, 50 dictionaries, three
+                    // passes: 253 us; of 8 pairs of equal codewords 474 with both of a pair evaluated and 443 with one, five
+                    // alike 792 and 423, all sixteen alike 440 and 255.)
                     double bestv = INFINITY, xr[DS], xx = 0.0;
                     uint32_t left = 0u;
 #pragma unroll
@@ -926,6 +936,7 @@ encode_aniso_kernel(const EncodeParams p, const float *__restrict__ tables, cons
                         if (v % kPart == 0) load_part(v);
                         left |= value(v) - best > lead ? 0u : 1u << v;
                     }
+                    left &= p.distinct[m];
                     pick = 0;
 #pragma unroll
                     for (int l = 0; l < DS; ++l) {
@@ -1496,7 +1507,7 @@ int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, con
     if (M < 1 || d % M != 0) { set_error("encode: d = %d is not a multiple of M = %d", d, M); return AVQ_EINVAL; }
     const int ds = d / M;
     int rc = AVQ_ENOMEM; // AVQ_ENOMEM or 1: the kernel below, which needs no scratch, takes the points
-    const size_t b_tab = (sizeof(float) * (size_t)M * kc * (ds + 1) + 255) & ~(size_t)255, b_lim = sizeof(float2) * (size_t)kMaxM + 256;
+    const size_t b_tab = (sizeof(float) * (size_t)M * kc * (ds + 1) + 255) & ~(size_t)255, b_lim = sizeof(float2) * (size_t)kMaxM + 256 + 4 * (size_t)kMaxM;
     const bool weights = eta_mode == AVQ_ETA_EXACT;
     if ((kc == 16 ? ds >= 1 && ds <= 4 : ds == 2 || ds == 4 || ds == 8) && !encode_few_steps(n, ds, kc, M, passes))
         rc = ws->reserve(b_tab + b_lim + (weights ? sizeof(double) * (size_t)n : 0));
@@ -1512,10 +1523,11 @@ int launch_encode(const float *x, int64_t n, int d, int M, int kc, int bits, con
         p.w_in = weights ? (const double *)(ws->as<unsigned char>() + b_tab + b_lim) : nullptr;
         p.packed = packed;
         p.next_window = (uint32_t *)(lim + kMaxM);
+        p.distinct = p.next_window + 64;
         p.code_stride = 4 * (((M + 3) / 4) | 1);
         float *cc = tab + (size_t)M * kc * ds; // 256 codewords: after their operands
         if (kc == 16)
-            hipLaunchKernelGGL(encode_tables_kernel, dim3((unsigned)M), dim3(64), 0, st, codebooks, kc, ds, tab, lim, p.next_window);
+            hipLaunchKernelGGL(encode_tables_kernel, dim3((unsigned)M), dim3(64), 0, st, codebooks, ds, tab, lim, p.distinct, p.next_window);
         else
             hipLaunchKernelGGL(encode_operands_kernel, dim3((unsigned)M), dim3(256), 0, st, codebooks, ds, tab, cc, lim, p.next_window);
         if (weights)

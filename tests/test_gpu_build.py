@@ -351,6 +351,35 @@ def test_codes_with_equal_codewords(n, d, M, bits, leaves, passes):
     np.testing.assert_array_equal(idx.get_codes(), oracle.pack_codes(want, bits))
 
 
+# Runs of equal codewords: all of a dictionary, the first five, neighbours, a dictionary and coordinates of zeros of either sign
+@pytest.mark.parametrize("d,M,bits", [(12, 12, 4), (36, 18, 4), (45, 15, 4), (64, 16, 4), (24, 6, 8)])
+@pytest.mark.parametrize("law", ["all", "five", "neighbours", "zeros"])
+@pytest.mark.parametrize("leaves,passes", [(0, 6), (5, 6), (0, 0)])
+def test_codes_with_runs_of_equal_codewords(d, M, bits, law, leaves, passes):
+    rng = np.random.default_rng(d)
+    n, ds = 260, d // M
+    x, cb = unit_rows(rng, n, d), random_dictionaries(rng, M, 1 << bits, ds)
+    if law == "all":
+        cb[::2] = cb[::2, :1]
+    elif law == "five":
+        cb[:, 3:8] = cb[:, 3:4]
+    elif law == "neighbours":
+        cb[:, 1::2] = cb[:, ::2]
+    else:
+        cb[1::3] = 0.0
+        cb[1::3, 1::2] = -0.0
+        x.reshape(n, M, ds)[:, 1::3] = 0.0
+    idx = avq.Index(d, M, bits, T=0.2, encode_passes=passes, n_leaves=leaves)
+    okw = {}
+    if leaves:
+        okw["leaf_centers"] = unit_rows(rng, leaves, d)
+        okw["leaf_assign"] = oracle.assign_nearest(x, okw["leaf_centers"])
+        idx.set_leaf_centers(okw["leaf_centers"])
+    idx.set_codebooks(cb)
+    idx.encode(dev(x))
+    np.testing.assert_array_equal(idx.get_codes(), oracle.pack_codes(oracle.encode(x, cb, T=0.2, passes=passes, **okw), bits))
+
+
 # Every step open: 1.7 times as long as with codewords that differ (2.7 times with one codeword loaded at a time)
 def test_encode_time_with_equal_codewords():
     def twins(cb):
