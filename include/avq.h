@@ -373,7 +373,8 @@ double avq_eta(int32_t d, double T, double norm, int32_t eta_mode);
  * several, v candidates each; built in: 64 each for up to 16 queries whose
  * reorder_k rows do not fit one workgroup's LDS at once), "bound_bits" (batches
  * of 8-bit codes: 6, 7 or 8 bits per entry of the byte tables whose sums bound
- * a block's scores; built in: 7), "stream_loads" (the scan of the whole code
+ * a block's scores; built in: 7, or 8 for up to 64 queries and 200 results on
+ * up to 38 MB of codes), "stream_loads" (the scan of the whole code
  * array for one or a few queries: 1 = plain loads, 2 = nontemporal loads and
  * one block of 256 points per wave; built in: 2 when the code array exceeds
  * 256 MB, the Infinity Cache, and the call has one or two queries, or up to

@@ -323,7 +323,7 @@ leaf_top_kernel(const u64 *__restrict__ keys, int n_leaves, int L, int32_t *__re
             __syncthreads();
             const uint32_t from = edge >> 16;
             fast = (edge & 0xffffu) <= kLeafTop;
-            if (fast) {
+            if (fast) { // (the histogram holds every leaf, so as many as edge counts come, and top has room for them)
 #pragma unroll
                 for (int i = 0; i < kPer; ++i) {
                     const int l = tid + i * 1024;

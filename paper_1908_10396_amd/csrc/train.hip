@@ -626,8 +626,8 @@ int launch_assign_aniso(const float *x, int64_t n, int d, const float *centers, 
 // dictionaries are in LDS. On a partitioned index the points are taken leaf by leaf, and the lanes' leaf centers mostly
 // are one and the same.
 //
-// Bound by vector operations: some 160 a step, 0.27 a clock and SIMD at 1.98 GHz by the counters, more waves a compute unit
-// than twelve change nothing. A fifth of them are of waves that have no points left but their last ones. avq_encode of
+// Bound by vector operations: some 180 a step, idle lanes counted, 0.26 a clock and SIMD at 2.1 GHz by the counters; more waves a
+// compute unit than twelve change nothing. avq_encode of
 // 1,183,514 x 100 points, 50 subspaces, 2.18 ms with the rows of a wave's points in LDS, which left room for five waves a
 // compute unit, 1.43 this way (2,000 leaves: 3.96 / 2.83); 10^6 x 128, 64 subspaces 2.97 / 1.69; 500,000 x 192, 96 of them
 // 5.25 / 1.86; 200,000 x 384, 192: 12.6 / 2.5; a thread per point with every codeword in fp64: 9.3 (11.8) ms at the first.
