@@ -396,8 +396,9 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
 // (exact_supported). More than max_listed (at most kExactBins) blocks: need[1 + q] is set and the plain kernel answers.
 // Bound by what it reads: some fifteen blocks of 25 KB a query at the size above, and a twice (150 KB); 0.13 to 0.15 ms for 1,000
 // queries, 0.20 with the norms of all blocks read three times. One query on 3,000,000 x 32 points: 47 us with the threads of a
-// class reading blocks C apart, 32 with adjacent threads at adjacent blocks and the classes' maxima exchanged. Measured and
-// dropped: the rows through LDS as one run of memory (0.13 at k = 10, but 427 us instead of 286 for the search of 300,000 x 64, 600
+// class reading blocks C apart, 32 with adjacent threads at adjacent blocks and the classes' maxima exchanged. (Up to four threads a
+// class read whole lines as they are, and the exchange would cost 1,000 queries at the size above 2 us.) Measured and dropped:
+// the rows through LDS as one run of memory (0.13 at k = 10, but 427 us instead of 286 for the search of 300,000 x 64, 600
 // queries, k = 100), sixteen loads of a lane at once (more registers: 1.31 ms instead of 1.15 at k = 100), registers for eight
 // waves a SIMD (1,000 queries, k = 10 on 1,200,000 x 24: 169 us instead of 179, but k = 100 on x 100 1,218 instead of 1,009).
 constexpr int kExactBins = 2048;
@@ -428,13 +429,14 @@ exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *
     while (C >= 16 * k && C > 64) C >>= 1;
     const int per_class = kExactThreads / C, cls = tid / per_class, sub = tid & (per_class - 1);
     const bool ranked = classes && C <= 256;
+    const bool mixed = per_class > 4; // the threads of a class lie apart, and adjacent ones read adjacent blocks
     float low = -INFINITY, low2 = -INFINITY, theta; // of the class, or the largest two of this thread's blocks
     if (classes) {
         float top = -INFINITY, top2 = -INFINITY;
         uint32_t at = 0u, at2 = 0u;
         if (ranked) {
 #pragma unroll 8
-            for (uint32_t b = tid; b < (uint32_t)n_blocks; b += kExactThreads) {
+            for (uint32_t b = mixed ? tid : cls + C * sub; b < (uint32_t)n_blocks; b += kExactThreads) {
                 const float v = a[b];
                 at = v > top ? b : at;
                 top = fmaxf(top, v);
@@ -454,9 +456,11 @@ exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *
     }
     if (ranked) { // the value that fewer than k exceed and k reach; a class's threads each count a part
         float *vals = (float *)hist, *spread = vals + kExactBins / 2;
-        spread[tid] = low; // block b is of class b % C, so this thread's blocks are of class tid % C
-        __syncthreads();
-        low = spread[cls + C * sub]; // the threads of a class side by side
+        if (mixed) {
+            spread[tid] = low; // block b is of class b % C, so this thread's blocks are of class tid % C
+            __syncthreads();
+            low = spread[cls + C * sub]; // the threads of a class side by side
+        }
         for (int m = 1; m < per_class; m <<= 1) low = fmaxf(low, __shfl_xor(low, m, 64));
         if (sub == 0) vals[cls] = low;
         __syncthreads();
