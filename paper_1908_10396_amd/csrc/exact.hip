@@ -83,11 +83,11 @@ exact_pack_kernel(const float *__restrict__ queries, int nq, int d, int steps, v
 // column tiles than 8 steps would spill in the loop: one column tile. best[q][block of 64]: the workgroup's eight maxima of a
 // query leave as 32 adjacent bytes. xnorm[block] = largest norm and conversion error of its points, xnorm8 of the workgroup's.
 //
-// A lane reads its points' coordinates itself, some steps ahead, four words a load whatever the row's alignment. PAIR (65 to 112
+// A lane reads its points' coordinates itself, some steps ahead, four words a load whatever the row's alignment. PAIR (81 to 112
 // dimensions): as many registers as let two workgroups share a compute unit, so that one's products go on while the other
-// reads its rows. RUNS: those rows come through LDS besides, sixteen a wave at a time, as one run of memory, which reads each
-// line once and whole; nt: past the caches, at 6 TB/s (1,183,514 x 100, one query: 211 us for the product with each lane its
-// own rows and two workgroups, 129 with one, 111 this way).
+// reads its rows (fewer dimensions need no more anyway). RUNS: those rows come through LDS besides, sixteen a wave at a time, as
+// one run of memory, which reads each line once and whole; nt: past the caches, at 6 TB/s (1,183,514 x 100, one query: 211 us for
+// the product with each lane its own rows and two workgroups, 129 with one, 111 this way).
 // Bound by the reading of x, then the tiles (5.6 us each, 4.1 of matrix instructions at the 2.0 GHz that they leave). Product
 // alone, 1,183,514 x 100, 1,024 queries: 310 us with a load waited for at a row's every step and the staged tile waited for
 // before each tile's first operand, 270 now. Rows that are no whole quads word by word / four words a load, us a call, one query:
@@ -201,8 +201,8 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
             end_of_points(c);
         }
     } else if (NS == 7 && !PAIR && quad) {
-        // as below, but a row's last words are left out by a choice rather than a branch (400,000 x 72, 64 queries: 79.5 us a call, 83
-        // as below; 96 dimensions 88.6 / 89.9; other numbers of steps gain from the latter: 3,000,000 x 128, one query 402 / 386)
+        // as below, but a row's last words are left out by a choice rather than a branch (300,000 x 100, one query: 67.0 us a call,
+        // 68.2 as below; other numbers of steps gain from the latter: 3,000,000 x 128, one query 402 / 386)
         const float *row[CT];
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
@@ -243,7 +243,10 @@ exact_product_kernel(const float *__restrict__ x, int64_t n, int d, const v8bf *
         float raw[kAsk][2][4] = {};
         auto ask = [&](int e) __attribute__((always_inline)) {
             const int l = 16 * (e % NS) + 4 * h;
-            if (PAIR && 16 * (e % NS) >= d) return; // (nothing of the row)
+            // (Nothing of the row. A pair's rows end within the last step, but without the branch the compiler forms the addresses of
+            // all steps first and spills 8 registers rather than none at six steps, 32 rather than 13 at seven: 700,000 x 96, one
+            // query 102 us a call instead of 87.)
+            if (PAIR && 16 * (e % NS) >= d) return;
             __builtin_memcpy(raw[e % kAsk][0], row[e / NS] + (l < d - 4 ? l : d - 4), 16);
             __builtin_memcpy(raw[e % kAsk][1], row[e / NS] + (l + 8 < d - 4 ? l + 8 : d - 4), 16);
         };
@@ -576,7 +579,7 @@ exact_finish_kernel(const float *__restrict__ x, int64_t n, int d, const float *
 static int exact_steps(int d)
 {
     const int need = (d + 15) / 16;
-    for (int s : {2, 3, 4, 7, 8, 12, 16})
+    for (int s : {2, 3, 4, 5, 6, 7, 8, 12, 16})
         if (need <= s) return s;
     return 0;
 }
@@ -672,17 +675,22 @@ int launch_exact(const float *x, int64_t n, int d, const float *queries, int nq,
     *need_out = w.need;
     hipLaunchKernelGGL(exact_pack_kernel, dim3((unsigned)tiles), dim3(256), 0, st, queries, nq, d, steps, w.packed, w.qnorm, w.need);
     // One workgroup a compute unit, two that read their rows themselves (pair), two whose rows come through LDS (runs). us a call,
-    // k = 10, one / pair / runs: 400,000 x 72, 64 queries 79.5 / 78.7 / 84; 500,000 x 96, 64 queries 98 / 94 / 101, 128 106 / 100 / 107, 1
-    // 88 / 85 / 94; 140,000 x 100, 64 62 / 66 / 67, 300 91 / 90 / 94; 600,000 x 100, 64 101 / 112 / 102, 300 151 / 155 / 145, 1,000
-    // 285 / 273 / 262; 1,200,000 x 100, 1 184 / 212 / 150, 64 197 / 217 / 175, 300 276 / 275 / 236.
+    // k = 10. Seven steps, one / pair / runs: 140,000 x 100, 64 queries 62 / 66 / 67, 300 91 / 90 / 94; 600,000 x 100, 64 101 / 112 / 102,
+    // 300 151 / 155 / 145, 1,000 285 / 273 / 262; 1,200,000 x 100, 1 184 / 212 / 150, 64 197 / 217 / 175, 300 276 / 275 / 236.
+    // Six, pair / runs: 700,000 x 88, 1 84 / 94, 1,000 269 / 274; 1,000,000 x 88, 1 127 / 113, 64 138 / 139, 256 163 / 171, 640 274 / 276;
+    // 1,400,000 x 96, 1 151 / 151, 30 169 / 160, 256 203 / 216, 400 252 / 260, 1,000 438 / 416; 2,000,000 x 88, 400 356 / 344.
+    // Five, whose operands leave room for two workgroups anyway, one / runs: 700,000 x 72, 1 69 / 84, 1,000 214 / 220; 1,400,000 x 72, 1
+    // 122 / 129, 1,000 375 / 368; 2,000,000 x 72, 400 288 / 297, 640 396 / 379, 1,000 512 / 478.
+    // (65 to 96 dimensions by seven steps too: 400,000 x 72, 64 queries 77 us, by five 63; 400,000 x 96 83, by six 76.)
     // The caches hold on to x up to somewhat more than their size, for the rows that the selection reads: x 275 MB of 112 dimensions, past
     // the caches / not: one query 100 / 108, 64 125 / 117, 300 182 / 163; 400 MB 64 160 / 155, 300 224 / 213; 500 MB of 100, 64 191 / 192.
     const int64_t groups = w.stride / 8;
     const uint64_t mb = (sizeof(float) * (uint64_t)n * (uint64_t)d) >> 20;
     const bool beyond = mb > 256; // the Infinity Cache
     const int nt = beyond && (tiles == 1 || mb > 448);
-    const bool pair = groups > 256 && mb <= 200 && ((d <= 96 && tiles > 1) || tiles >= 8);
-    const bool runs = groups > 256 && (beyond || tiles >= 8);
+    const bool pair = groups > 256 && mb <= 200 && tiles >= 8;
+    const bool runs = steps == 5 ? mb > 448 && tiles > 16 : steps == 6 ? beyond && (tiles <= 2 || mb > (tiles > 16 ? 400 : 640))
+                                                          : groups > 256 && (beyond || tiles >= 8);
 #define AVQ_EXACT(NS, CT, PAIR, RUNS)                                                                                    \
     hipLaunchKernelGGL((exact_product_kernel<NS, CT, PAIR, RUNS>), dim3((unsigned)(w.stride / 8)), dim3(512), 0, st, x, n, d, w.packed, \
                        tiles, nq, w.best, w.stride, w.xnorm, w.need, w.xnorm8, nt)
@@ -690,6 +698,14 @@ int launch_exact(const float *x, int64_t n, int d, const float *queries, int nq,
     case 2: AVQ_EXACT(2, 2, false, false); break;
     case 3: AVQ_EXACT(3, 2, false, false); break;
     case 4: AVQ_EXACT(4, 2, false, false); break;
+    case 5:
+        if (runs) AVQ_EXACT(5, 2, true, true);
+        else AVQ_EXACT(5, 2, false, false);
+        break;
+    case 6:
+        if (runs) AVQ_EXACT(6, 2, true, true);
+        else AVQ_EXACT(6, 2, true, false);
+        break;
     case 7:
         if (pair) AVQ_EXACT(7, 2, true, false);
         else if (runs) AVQ_EXACT(7, 2, true, true);

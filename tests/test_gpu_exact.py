@@ -64,16 +64,17 @@ def test_exact_search_with_rows_through_lds(n, d, nq, shift):
 
 
 # the end of a row within a load of four words, before it and at it, in every number of steps; the last row is the array's end
-@pytest.mark.parametrize("d", [4, 5, 6, 7, 15, 17, 31, 34, 47, 49, 51, 63, 66, 99, 111, 114, 127, 130, 131, 191, 195, 253, 255])
+@pytest.mark.parametrize("d", [4, 5, 6, 7, 15, 17, 31, 34, 47, 49, 51, 63, 65, 66, 79, 81, 83, 95, 97, 99, 111, 114, 127, 130, 131, 191, 195, 253, 255])
 def test_exact_search_of_rows_that_are_no_whole_quads(d):
     rng = np.random.default_rng(d)
     check(unit_rows(rng, 3001, d), unit_rows(rng, 40, d), 10)
 
 
-# 65 to 112 dimensions on more than 256 workgroups, by the size of the array (200, 256 and 448 MB) and tiles of queries (one, two, eight):
-# two workgroups a compute unit, whose lanes read their rows or have them through LDS, past the caches or not
+# 65 to 112 dimensions on more than 256 workgroups, by the size of the array (200, 256, 400, 448 and 640 MB) and tiles of queries (one,
+# two, eight, sixteen): two workgroups a compute unit, whose lanes read their rows or have them through LDS, past the caches or not
 @pytest.mark.parametrize("n,d,nq", [(131_073, 66, 33), (131_100, 96, 40), (131_080, 97, 40), (545_001, 97, 225), (547_003, 96, 33), (671_203, 101, 33),
-                                    (1_200_007, 98, 34)])
+                                    (1_200_007, 98, 34), (1_800_003, 66, 513), (1_600_001, 80, 40), (800_003, 87, 40), (820_007, 84, 5),
+                                    (800_003, 87, 70), (1_300_009, 84, 513), (1_800_001, 96, 70)])
 def test_exact_search_by_the_size_of_the_array(n, d, nq):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(n)
@@ -96,9 +97,9 @@ def test_exact_search_at_the_lines_of_the_selection(n, nq, k):
     check(x, np.round(unit_rows(rng, nq, 24) * 16).astype(np.float32), k)
 
 
-# one to four query tiles through three buffers and two accumulators: two column tiles per wave of 14 (112 dimensions) and 16 (113)
-# operands, and one column tile (129, 256); points beyond the last full wave
-@pytest.mark.parametrize("d", [112, 113, 129, 256])
+# one to four query tiles through three buffers and two accumulators: two column tiles per wave of 10 (80 dimensions), 12 (96), 14
+# (112) and 16 (113) operands, and one column tile (129, 256); points beyond the last full wave
+@pytest.mark.parametrize("d", [80, 96, 112, 113, 129, 256])
 @pytest.mark.parametrize("nq", [32, 33, 96, 97])
 def test_exact_search_of_every_number_of_query_tiles(d, nq):
     rng = np.random.default_rng(d + nq)
